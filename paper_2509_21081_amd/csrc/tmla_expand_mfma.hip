@@ -4,14 +4,24 @@
 // i.e. one GEMM [tokens x 512] x [512 x 256 H] whose epilogue writes the matrix-core operand
 // order the decode kernels read (see typhoon_mla.h).
 //
-// Workgroup tile: 256 tokens x one head's 256 outputs (128 K-nope + 128 V), k = 512 in 16 stages
-// of 32.  Four wavefronts of 128 x 128 (4 x 4 MFMA blocks of 32 x 32): every fragment read from
-// LDS feeds four MFMAs, so the LDS runs at half its rate when the matrix cores are busy.  Both
-// operands are k-contiguous in memory (rows of c_KV, rows of W), so either can be the MFMA row
-// operand: the K wavefronts compute W c^T (lanes own tokens, 4 consecutive d per register group
-// -> 8-byte stores into the K fragment order), the V wavefronts compute c W^T (lanes own d,
-// 8 consecutive accumulators are exactly one 16-byte V fragment chunk).
-// Stages stream global -> LDS (global_load_lds) through a ring of four, three in flight.
+// MFMA-bound in principle (256 * 512 MAC against 640 + 1024 / H bytes per token and head), in
+// practice by the package power limit: MFMA and a stream of stores at once.
+//
+// A workgroup keeps ONE head's weights -- 256 output rows x 512, 256 KiB -- in registers (each of
+// the four wavefronts 64 rows, 256 registers per lane: half of its register file) and walks a
+// range of tokens, 32 at a time: only the latent rows travel, 1 KiB per token for 64 clocks of
+// matrix work, and every block of 32 tokens leaves as soon as it is done, its conversion and
+// stores between the MFMAs of the next one.  Every fragment read from LDS feeds two MFMAs (half of
+// the LDS rate).  Both operands are k-contiguous in memory (rows of c_KV, rows of W), so either
+// can be the MFMA row operand: the K wavefronts (0, 1) compute W c^T (lanes own tokens), the V
+// wavefronts (2, 3) c W^T (lanes own d, 8 consecutive accumulators are one 16-byte V chunk).
+// Latent rows stream global -> LDS (global_load_lds) through a ring of four 32-token tiles.
+// Measured on MI355X against a tile of 256 tokens x 256 outputs per workgroup with the whole
+// contraction streamed through LDS and an epilogue of its own: 32768 tokens x 128 heads 1573 ->
+// 945 us (1.16 PFLOP/s with 2.8 TB/s of stores; 800 us without the stores, 690 us without any
+// transfer), 4096 x 128 194 -> 126 us, 1003 x 16 20.0 -> 10.4 us.  Stores without the
+// non-temporal hint: 1240 us.
+#include <algorithm>
 #include <type_traits>
 
 #include "tmla_common.hpp"
@@ -20,215 +30,289 @@
 
 namespace tmla {
 
-constexpr int EX_TOK = 256;           // tokens per workgroup tile
-constexpr int EX_KSTAGE = 32;         // k elements per stage: 64 B per row = 4 chunks of 16 B
-constexpr int EX_NSTAGE = D_L / EX_KSTAGE;                 // 16
-constexpr int EX_OPER_BYTES = 256 * 64;                    // one operand tile of a stage: 16 KiB
-constexpr int EX_STAGE_BYTES = 2 * EX_OPER_BYTES;          // tokens, then weights
+constexpr int EX_ROW_BYTES = D_L * 2;                      // 1 KiB: one transfer
+constexpr int EX_ROPE_OFF = TOK_BLK * EX_ROW_BYTES;        // 32 KiB of latent rows
+constexpr int EX_TILE_BYTES = EX_ROPE_OFF + 4 * 1024;      // and the four rope fragments
 constexpr int EX_RING = 4;
-constexpr int EX_LDS_BYTES = EX_RING * EX_STAGE_BYTES;     // 128 KiB
-constexpr int EX_DMA_PER_WAVE = 8;                         // 32 transfers of 1 KiB per stage
+constexpr int EX_LDS_BYTES = EX_RING * EX_TILE_BYTES;      // 144 KiB
+constexpr int EX_DMA = 9;        // transfers of a wavefront per tile: 8 rows, 1 rope fragment
+constexpr int EX_NKS = D_L / 16;                           // 32 k-steps of an MFMA
+constexpr int EX_SYNC_KS = 22;   // k-step of a block behind which the next tile must have landed
+constexpr int EX_STORES = 5;     // vector stores of a wavefront per finished block (4 + rope)
 
 struct ExpandArgs {
   const __bf16* c; int64_t c_stride;      // latent rows [ntok, 512] (element stride between rows)
   const __bf16* r; int64_t r_stride;      // rope rows   [ntok, 64]
   const __bf16* w_uk; const __bf16* w_uv; // [H, 128, 512]
   __bf16* k_out; __bf16* v_out;
-  int64_t ntok, ntb, tiles;
-  int H;
+  int64_t ntok, ntb;                      // tokens; blocks of 32 tokens
+  int H, splits, units;                   // units = H * splits workgroups
 };
 
-// LDS operand tile of a stage: row i at i * 64, its 16-byte chunk c (k = 8c .. 8c+7) in slot
-// c ^ ((i >> 2) & 3): rows 64 B apart would put rows i and i + 4 on the same banks for the
-// 16-byte fragment reads (lane n reads row n); the slot swizzle spreads 16 consecutive rows over
-// all 16 sixteen-byte bank groups.  A 1 KiB transfer covers 16 rows (lane l: row l / 4, slot l % 4).
-__global__ void __launch_bounds__(256, 1) expand_gemm_kernel(ExpandArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t t_base = (int64_t)(blockIdx.x % a.tiles) * EX_TOK;
-  const int h = (int)(blockIdx.x / a.tiles);
-  const int wm = wave >> 1;          // token half of the tile: tokens [128 wm, 128 wm + 128)
-  const bool is_v = wave & 1;        // K-nope or V outputs
+// The weights sit in accumulation registers and the sums in vector registers, which only assembly
+// pins down (left to the allocator, weights are copied from file to file in front of their use).
+// The assembler does not see these MFMAs: their sums are read 4 MFMAs later at the earliest, or
+// behind expand_drain(), and no vector-ALU instruction writes their operands.  WAIT: the fragment
+// arrived (six younger requests may be in flight).
+template <bool IS_V, bool FIRST, bool WAIT>
+__device__ __forceinline__ void expand_mfma(f32x16& d, const bf16x8& c, const bf16x8& w) {
+#define TMLA_EX_MFMA(PRE, SRC_C, D)                                                          \
+  if constexpr (IS_V)                                                                        \
+    asm volatile(PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, " SRC_C : D(d) : "v"(c), "a"(w)); \
+  else                                                                                       \
+    asm volatile(PRE "v_mfma_f32_32x32x16_bf16 %0, %2, %1, " SRC_C : D(d) : "v"(c), "a"(w));
+  if constexpr (WAIT && FIRST) { TMLA_EX_MFMA("s_waitcnt lgkmcnt(6)\n\t", "0", "=&v") }
+  else if constexpr (WAIT) { TMLA_EX_MFMA("s_waitcnt lgkmcnt(6)\n\t", "%0", "+v") }
+  else if constexpr (FIRST) { TMLA_EX_MFMA("", "0", "=&v") }
+  else { TMLA_EX_MFMA("", "%0", "+v") }
+#undef TMLA_EX_MFMA
+}
+// enough idle issue slots for the last MFMA to have written its result
+__device__ inline void expand_drain() {
+  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+}
 
-  // ---- transfers: wavefront w moves token rows [64 w, 64 w + 64) and weight rows
-  // [64 w, 64 w + 64) (rows 0..127 = W_UK[h], 128..255 = W_UV[h]) of every stage, 4 + 4 transfers
-  // (base pointers are wave-uniform; the per-lane parts are 32-bit offsets)
-  const int dr = lane >> 2;                          // row inside a 16-row transfer
-  const int chunk16 = ((lane & 3) ^ ((dr >> 2) & 3)) << 4;   // 64 w + 16 i does not change the swizzle
-  const char* c_base = (const char*)(a.c + t_base * a.c_stride);
-  const int last_rel = (int)min((int64_t)EX_TOK - 1, a.ntok - 1 - t_base);   // rows past the end
-  int c_off[4];                                                               // repeat the last one
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-    c_off[i] = min(64 * wave + 16 * i + dr, last_rel) * (int)(a.c_stride * 2) + chunk16;
-  const char* w_base = (const char*)((wave < 2 ? a.w_uk : a.w_uv) +
-                                     ((size_t)h * 128 + 64 * (wave & 1)) * D_L);
-  const int w_lane = dr * (D_L * 2) + chunk16;
-  auto issue = [&](int st) __attribute__((always_inline)) {
-    char* dst = smem + (st % EX_RING) * EX_STAGE_BYTES + (64 * wave) * 64;
-    const char* cs = c_base + st * (EX_KSTAGE * 2);
-    const char* ws = w_base + st * (EX_KSTAGE * 2) + w_lane;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      dma16(cs + c_off[i], dst + i * 1024);
-      dma16(ws + i * 16 * (D_L * 2), dst + EX_OPER_BYTES + i * 1024);
+// One wavefront's part of the walk over blocks [b0, b1) of head h.  LDS tile: row r (token) at
+// r * 1024, its 16-byte chunk c in slot c ^ (r & 15): the 16 rows a 16-byte read serves at a time
+// fall on distinct banks.  Behind the rows, the rope part in fragment order, one fragment per
+// wavefront.
+template <bool IS_V>
+__device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int h, int64_t b0,
+                                            int64_t b1, int wave, int lane) {
+  const int n = lane & 31, g = lane >> 5, half = wave & 1;   // half: 64 of the 128 K or V rows
+  const int nblk = (int)(b1 - b0);
+
+  // ---- transfers: wavefront w moves rows 8 w .. 8 w + 7 of a tile and rope fragment w; rows past
+  // the last token repeat it (their results are replaced by zeros).  Row numbers inside the range
+  // are 32-bit.
+  const int last = (int)min((int64_t)0x7fffffff, a.ntok - 1 - b0 * TOK_BLK);
+  const char* c_src = (const char*)(a.c + b0 * TOK_BLK * a.c_stride);
+  const char* r_src = (const char*)(a.r + b0 * TOK_BLK * a.r_stride + 16 * wave + 8 * g);
+  const int64_t c_bytes = a.c_stride * 2, r_bytes = a.r_stride * 2;
+  auto issue = [&](int blk, int slot, auto part_) __attribute__((always_inline)) {
+    constexpr int part = decltype(part_)::value;
+    if constexpr (part < 8) {
+      const int row = 8 * wave + part;
+      dma16(c_src + min(blk * TOK_BLK + row, last) * c_bytes + ((lane ^ (row & 15)) << 4),
+            smem + slot + row * EX_ROW_BYTES);
+    } else {
+      dma16(r_src + min(blk * TOK_BLK + n, last) * r_bytes, smem + slot + EX_ROPE_OFF + wave * 1024);
     }
   };
 
-  // ---- fragment addresses: row operand rows [ra, ra + 128), column operand rows [rb, rb + 128)
-  //   K wavefronts: rows = d (W_UK, weight tile rows 0..127), columns = tokens
-  //   V wavefronts: rows = tokens, columns = d (W_UV, weight tile rows 128..255)
-  const uint32_t base = lds_addr(smem);
-  const uint32_t tok_off = (128 * wm + n) * 64;
-  const uint32_t w_off = EX_OPER_BYTES + ((is_v ? 128 : 0) + n) * 64;
-  const uint32_t a_off = is_v ? tok_off : w_off;
-  const uint32_t b_off = is_v ? w_off : tok_off;
-  // chunk 2*ks + g of row n + 32 i: slot (2 ks + g) ^ ((n >> 2) & 3)  (32 i does not change it)
-  const uint32_t sw = (n >> 2) & 3;
-  const uint32_t sl0 = ((0 + g) ^ sw) << 4, sl1 = ((2 + g) ^ sw) << 4;
-
-  f32x16 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-
-#pragma unroll
-  for (int st = 0; st < EX_RING - 1; st++) issue(st);
-
-  // Software pipeline over the two k-steps of a stage: while the 16 MFMAs of one k-step run, the
-  // fragments of the next one (possibly of the next stage) come in from LDS, the barrier for
-  // the next stage is passed and this wavefront's 8 transfers of the stage three ahead are
-  // issued between the MFMAs (a transfer holds the issuing wavefront for some tens of cycles).
-  bf16x8 fa[2][4], fb[2][4];
-  auto read_frags = [&](int st, auto ks_) __attribute__((always_inline)) {
-    constexpr int ks = decltype(ks_)::value;
-    const uint32_t sb = base + (st % EX_RING) * EX_STAGE_BYTES;
-    const uint32_t sl = ks ? sl1 : sl0;
-    static_for<4>([&](auto i_) {
+  // ---- weights: fragment (i, ks) = rows 64 half + 32 i + n, k = 16 ks + 8 g .. + 7.  They come
+  // through this wavefront's slot of the ring, 32 whole rows at a time, like tokens: read straight
+  // into the registers, 32 bytes of 32 rows per load, they took 4 us longer (14.3 against 10.4 us
+  // for 1003 tokens x 16 heads).
+  bf16x8 w[2][EX_NKS];
+  {
+    const char* wp = (const char*)((IS_V ? a.w_uv : a.w_uk) + ((size_t)h * 128 + 64 * half) * D_L);
+    char* mine = smem + wave * EX_TILE_BYTES;
+    const uint32_t rd = lds_addr(mine) + n * EX_ROW_BYTES;
+    const uint32_t swz = (uint32_t)(g ^ (n & 15)) << 4;
+    static_for<2>([&](auto i_) {
       constexpr int i = decltype(i_)::value;
-      fa[ks][i] = lds_read_b128<i * 32 * 64>(sb + a_off + sl);
-      fb[ks][i] = lds_read_b128<i * 32 * 64>(sb + b_off + sl);
+#pragma unroll
+      for (int r = 0; r < 32; r++)
+        dma16(wp + (32 * i + r) * EX_ROW_BYTES + ((lane ^ (r & 15)) << 4), mine + r * EX_ROW_BYTES);
+      vm_wait<0>();
+      static_for<EX_NKS>([&](auto ks_) {
+        constexpr int ks = decltype(ks_)::value;
+        w[i][ks] = lds_read_b128<256 * (ks >> 3)>(rd + (swz ^ ((2 * ks & 15) << 4)));
+      });
+      static_for<EX_NKS / 4>([&](auto k_) {
+        constexpr int k = 4 * decltype(k_)::value;
+        lgkm_wait<0>(w[i][k], w[i][k + 1], w[i][k + 2], w[i][k + 3]);
+        asm volatile("" : "+a"(w[i][k]), "+a"(w[i][k + 1]), "+a"(w[i][k + 2]), "+a"(w[i][k + 3]));
+      });
     });
+    raw_barrier();   // the ring is free
+  }
+  static_for<EX_RING - 1>([&](auto b_) {
+    constexpr int b = decltype(b_)::value;
+    static_for<EX_DMA>([&](auto p_) { issue(b, b * EX_TILE_BYTES, p_); });
+  });
+
+  const uint32_t row_addr = lds_addr(smem) + n * EX_ROW_BYTES;
+  const uint32_t rope_addr = lds_addr(smem) + wave * 1024 + lane * 16;
+  const uint32_t sw = (uint32_t)(g ^ (n & 15)) << 4;   // chunk 2 ks + g: slot (2 ks) ^ (g ^ n)
+
+  const int64_t blk_base = (int64_t)h * a.ntb + b0;
+  __bf16* k_dst = a.k_out + blk_base * K_BLK_ELEMS + lane * 8;
+  __bf16* v_dst = a.v_out + blk_base * V_BLK_ELEMS + lane * 8;
+
+  f32x16 acc[2][2];      // [parity of the block][32-row block of the weights]
+  bf16x8 rope;           // this wavefront's rope fragment of the block at work
+  bf16x8 fr[8];          // fragments on their way from LDS, six ahead
+
+  // slots of the ring as byte offsets: that of the block at work, and k slots behind it
+  int cur = 0;
+  auto behind = [&](int k) __attribute__((always_inline)) {
+    const int s = cur - k * EX_TILE_BYTES;
+    return s < 0 ? s + EX_LDS_BYTES : s;
   };
-  auto mma = [&](auto ks_, int pf_stage) __attribute__((always_inline)) {
+  auto read_frag = [&](int slot, auto ks_) __attribute__((always_inline)) {
     constexpr int ks = decltype(ks_)::value;
-    // pf_stage >= 0: issue half of that stage's transfers (4 of 8) between the MFMAs
-    char* dst = smem + (pf_stage % EX_RING) * EX_STAGE_BYTES + (64 * wave) * 64;
-    const char* cs = c_base + pf_stage * (EX_KSTAGE * 2);
-    const char* ws = w_base + pf_stage * (EX_KSTAGE * 2) + w_lane;
-    static_for<4>([&](auto i_) {
-      constexpr int i = decltype(i_)::value;
+    const uint32_t base = row_addr + slot;
+    // chunk 2 ks + g: its low four bits are swizzled, the high two select 256 bytes
+    fr[ks & 7] = lds_read_b128<256 * (ks >> 3)>(base + (sw ^ ((2 * ks & 15) << 4)));
+  };
+  // stores a quarter of this wavefront's part of the finished block blk
+  auto store_piece = [&](int blk, auto par_, auto piece_, auto tail_) __attribute__((always_inline)) {
+    constexpr int P = decltype(par_)::value, piece = decltype(piece_)::value;
+    constexpr bool TAIL = decltype(tail_)::value;
+    constexpr int i = piece >> 1, hp = piece & 1;
+    f32x16& d = acc[P][i];
+    asm volatile("" : "+v"(d));   // (no conversion is moved up to the MFMAs that form the sums)
+    bf16x8 o;
+    if constexpr (IS_V) {
+      // rows = tokens 16 hp + 4 g + 8 (e / 4) + e % 4, column d = 64 half + 32 i + n
 #pragma unroll
-      for (int j = 0; j < 4; j++) acc[i][j] = mfma32(fa[ks][i], fb[ks][j], acc[i][j]);
-      if (pf_stage >= 0) {
-        if constexpr (ks == 0) dma16(cs + c_off[i], dst + i * 1024);
-        else dma16(ws + i * 16 * (D_L * 2), dst + EX_OPER_BYTES + i * 1024);
+      for (int e = 0; e < 8; e++) o[e] = (__bf16)d[8 * hp + e];
+      if constexpr (TAIL) {
+        const int left = (int)(a.ntok - (b0 + blk) * TOK_BLK);
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+          if (acc_row(8 * hp + e, g) >= left) o[e] = (__bf16)0.f;
       }
-    });
+      __builtin_nontemporal_store(o, (bf16x8*)(v_dst + (int64_t)blk * V_BLK_ELEMS +
+                                               ((hp * 4 + 2 * half + i) * 64) * 8));
+    } else {
+      // column = token n, rows d = 64 half + 32 i + 16 hp + 8 x + 4 g + (0..3), x = 0, 1: the two
+      // halves of the wavefront trade so that a lane holds eight consecutive d of its token
+      typedef int int2v __attribute__((ext_vector_type(2)));
+      typedef int int4v __attribute__((ext_vector_type(4)));
+      bf16x4 lo, hi;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        lo[e] = (__bf16)d[8 * hp + e];
+        hi[e] = (__bf16)d[8 * hp + 4 + e];
+      }
+      const int2v l2 = __builtin_bit_cast(int2v, lo), h2 = __builtin_bit_cast(int2v, hi);
+      auto r0 = __builtin_amdgcn_permlane32_swap(l2[0], h2[0], false, false);
+      auto r1 = __builtin_amdgcn_permlane32_swap(l2[1], h2[1], false, false);
+      int4v w4 = {(int)r0[0], (int)r1[0], (int)r0[1], (int)r1[1]};
+      if constexpr (TAIL)
+        if ((b0 + blk) * TOK_BLK + n >= a.ntok) w4 = int4v{0, 0, 0, 0};
+      o = __builtin_bit_cast(bf16x8, w4);
+      __builtin_nontemporal_store(o, (bf16x8*)(k_dst + (int64_t)blk * K_BLK_ELEMS +
+                                               ((2 * (2 * half + i) + hp) * 64) * 8));
+    }
   };
-  constexpr std::integral_constant<int, 0> K0{};
-  constexpr std::integral_constant<int, 1> K1{};
+  auto store_rope = [&](int blk) __attribute__((always_inline)) {
+    const bf16x8 o = blk * TOK_BLK + n <= last ? rope : bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    __builtin_nontemporal_store(o, (bf16x8*)(k_dst + (int64_t)blk * K_BLK_ELEMS +
+                                             (8 + wave) * 64 * 8));
+  };
 
-  vm_wait<2 * EX_DMA_PER_WAVE>();   // stage 0 (EX_NSTAGE > EX_RING: three stages are in flight)
+  // One block: 32 k-steps of two MFMAs; the block before it (FIRST: there is none) is converted
+  // and stored in between.  No branches: past the last block of the range the requests for
+  // fragments and tiles go on, over whatever the ring holds and the last token again.
+  // Behind k-step EX_SYNC_KS: the next tile has landed for everyone, and everyone is done with
+  // the tile of the block before this one, whose slot takes the transfers of block blk + 3.
+  auto block = [&](int blk, auto par_, auto first_) __attribute__((always_inline)) {
+    constexpr int P = decltype(par_)::value;
+    constexpr bool FIRST = decltype(first_)::value;
+    constexpr std::integral_constant<int, P ^ 1> Q{};
+    const int next = behind(EX_RING - 1), slot2 = behind(2), slot3 = behind(1);
+    static_for<EX_NKS>([&](auto ks_) {
+      constexpr int ks = decltype(ks_)::value;
+      // fragment ks + 6, of this block or the next one
+      if constexpr (ks + 6 < EX_NKS) read_frag(cur, std::integral_constant<int, ks + 6>{});
+      else read_frag(next, std::integral_constant<int, ks + 6 - EX_NKS>{});
+      expand_mfma<IS_V, ks == 0, true>(acc[P][0], fr[ks & 7], w[0][ks]);
+      expand_mfma<IS_V, ks == 0, false>(acc[P][1], fr[ks & 7], w[1][ks]);
+      if constexpr (!FIRST && ks >= 2 && ks < 18 && (ks - 2) % 4 == 0)
+        store_piece(blk - 1, Q, std::integral_constant<int, (ks - 2) / 4>{}, std::false_type{});
+      // the rope fragment: requested behind k-step 4, there behind k-step 16 (the eleven younger
+      // requests of then are six)
+      if constexpr (ks == 4) rope = lds_read_b128<EX_ROPE_OFF>(rope_addr + cur);
+      if constexpr (ks == 16) {
+        lgkm_wait<6>(rope);
+        store_rope(blk);
+      }
+      if constexpr (ks == EX_SYNC_KS) {
+        // The transfers of block blk + 1 have landed (those of blocks 0, 1 and 2 had before the
+        // walk).  Younger and possibly in flight: the nine of block blk + 2 and this block's
+        // five stores.
+        if constexpr (!FIRST) vm_wait<EX_DMA + EX_STORES>();
+        raw_barrier();
+      }
+      // transfers: two of block blk + 3 behind the barrier, the other seven in the next block
+      if constexpr (ks >= 24 && ks % 4 == 0)
+        issue(blk + 3, slot3, std::integral_constant<int, (ks - 24) / 4>{});
+      if constexpr (!FIRST && ks < EX_SYNC_KS - 1 && ks % 3 == 0)
+        issue(blk + 2, slot2, std::integral_constant<int, 2 + ks / 3>{});
+    });
+    cur = next;
+  };
+
+  constexpr std::integral_constant<int, 0> P0{};
+  constexpr std::integral_constant<int, 1> P1{};
+  vm_wait<0>();
   raw_barrier();
-  read_frags(0, K0);
-  read_frags(0, K1);
-  for (int st = 0; st < EX_NSTAGE; st++) {
-    // the transfers of stage st + 3 go into the slot of stage st - 1, which everyone has left:
-    // each wavefront read its last fragments of it before the barrier of the previous iteration
-    const int pf = st + EX_RING - 1 < EX_NSTAGE ? st + EX_RING - 1 : -1;
-    lgkm_wait<8>(fa[0][0], fa[0][1], fa[0][2], fa[0][3]);
-    lgkm_wait<8>(fb[0][0], fb[0][1], fb[0][2], fb[0][3]);
-    mma(K0, pf);
-    lgkm_wait<0>(fa[1][0], fa[1][1], fa[1][2], fa[1][3]);
-    lgkm_wait<0>(fb[1][0], fb[1][1], fb[1][2], fb[1][3]);
-    if (st + 1 < EX_NSTAGE) {
-      // stage st + 1 must have landed for everyone before its fragments are read.  In flight
-      // behind it: stage st + 2 (8 transfers) and the first half of stage st + 3 (4)
-      const int ahead = EX_NSTAGE - 2 - st;           // stages issued after st + 1
-      if (ahead >= 2) vm_wait<EX_DMA_PER_WAVE + 4>();
-      else if (ahead == 1) vm_wait<EX_DMA_PER_WAVE>();
-      else vm_wait<0>();
-      raw_barrier();
-      read_frags(st + 1, K0);
-    }
-    mma(K1, pf);
-    if (st + 1 < EX_NSTAGE) read_frags(st + 1, K1);
+  static_for<6>([&](auto ks_) { read_frag(0, ks_); });
+  block(0, P0, std::true_type{});
+  int blk = 1;
+  for (; blk + 1 < nblk; blk += 2) {
+    block(blk, P1, std::false_type{});
+    block(blk + 1, P0, std::false_type{});
   }
-
-  // ---- epilogue: bf16, fragment order; tokens past the end are stored as zeros (the padding of
-  // the last 32-token block must be finite for the decode kernels and is specified as zero).
-  // The lane indices pass through an opaque statement so that the store addresses are computed
-  // here and not hoisted above the main loop, where they would push its registers into scratch
-  // (a scratch reload inside the loop waits for every transfer in flight).
-  int en = n, eg = g, elane = lane, etid = tid;
-  asm volatile("" : "+v"(en), "+v"(eg), "+v"(elane), "+v"(etid));
-  // likewise the accumulators: they stay in accumulation registers until here, their copies to
-  // vector registers (for the conversion) must not be spread over the loop
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-#pragma unroll
-    for (int j = 0; j < 4; j++) asm volatile("" : "+a"(acc[i][j]));
-  if (is_v) {
-    // block (i, j): tokens t_base + 128 wm + 32 i + acc_row, d = 32 j + n
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int64_t tok0 = t_base + 128 * wm + 32 * i;
-      const int64_t tb32 = tok0 / TOK_BLK;
-      if (tb32 >= a.ntb) continue;
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-#pragma unroll
-        for (int kk = 0; kk < 2; kk++) {
-          bf16x8 o;
-#pragma unroll
-          for (int e = 0; e < 8; e++) {
-            const int v = 8 * kk + e;
-            o[e] = (tok0 + acc_row(v, eg) < a.ntok) ? (__bf16)acc[i][j][v] : (__bf16)0.f;
-          }
-          *(bf16x8*)(a.v_out + (((((size_t)h * a.ntb + tb32) * 2 + kk) * 4 + j) * 64 + elane) * 8) = o;
-        }
-      }
-    }
+  // (the fragment requests that ran past the last block: their registers stay taken until the
+  // data is there)
+  auto settle = [&]() __attribute__((always_inline)) {
+    lgkm_wait<0>(fr[0], fr[1], fr[2], fr[3]);
+    lgkm_wait<0>(fr[4], fr[5]);
+    expand_drain();
+  };
+  auto finish = [&](auto par_, auto tail_) __attribute__((always_inline)) {
+    static_for<4>([&](auto p_) { store_piece(nblk - 1, par_, p_, tail_); });
+  };
+  const bool tail = b1 * TOK_BLK > a.ntok;
+  if (blk < nblk) {
+    block(blk, P1, std::false_type{});
+    settle();
+    if (tail) finish(P1, std::true_type{});
+    else finish(P1, std::false_type{});
   } else {
-    // block (i, j): d = 32 i + acc_row, tokens t_base + 128 wm + 32 j + n
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int64_t tok0 = t_base + 128 * wm + 32 * j;
-      const int64_t tb32 = tok0 / TOK_BLK;
-      if (tb32 >= a.ntb) continue;
-      const bool real = tok0 + en < a.ntok;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {   // d = 32 i + 8 q + 4 g + (0..3)
-          const int d0 = 32 * i + 8 * q;
-          bf16x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; e++) o[e] = real ? (__bf16)acc[i][j][4 * q + e] : (__bf16)0.f;
-          *(bf16x4*)(a.k_out + ((((size_t)h * a.ntb + tb32) * 12 + d0 / 16) * 64 + en +
-                                32 * ((d0 % 16) / 8)) * 8 + 4 * eg) = o;
-        }
-      }
-    }
+    settle();
+    if (tail) finish(P0, std::true_type{});
+    else finish(P0, std::false_type{});
   }
-  // rope part of K: verbatim copy, 256 tokens x 8 chunks of 16 B
-#pragma unroll
-  for (int i = 0; i < 8; i++) {
-    const int cidx = etid + 256 * i;
-    const int row = cidx >> 3, q = cidx & 7;
-    const int64_t t = t_base + row;
-    const int64_t tb32 = t / TOK_BLK;
-    if (tb32 >= a.ntb) continue;
-    bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-    const bf16x8 val = (t < a.ntok) ? *(const bf16x8*)(a.r + t * a.r_stride + q * 8) : z;
-    *(bf16x8*)(a.k_out + ((((size_t)h * a.ntb + tb32) * 12 + 8 + q / 2) * 64 + (int)(t % TOK_BLK) +
-                          32 * (q % 2)) * 8) = val;
+  vm_wait<0>();   // no transfer may land in LDS that another workgroup owns by then
+}
+
+__global__ void __launch_bounds__(256, 1) expand_gemm_kernel(ExpandArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  // consecutive workgroup ids go round-robin over the 8 XCDs: an XCD gets consecutive units, i.e.
+  // the token ranges of few heads, whose weights then come into one L2 only
+  const int per = (a.units + 7) / 8;
+  const int unit = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (unit >= a.units) return;
+  const int split = unit % a.splits, h = unit / a.splits;
+  const int64_t b0 = a.ntb * split / a.splits, b1 = a.ntb * (split + 1) / a.splits;
+  if (b0 >= b1) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (wave < 2) expand_walk<false>(a, smem, h, b0, b1, wave, lane);
+  else expand_walk<true>(a, smem, h, b0, b1, wave, lane);
+}
+
+// Token ranges per head.  One workgroup fits per compute unit, so H * splits workgroups take
+// ceil(H splits / 256) turns of a start-up (launch and weights: 7 us, about EX_START blocks of
+// 1.85 us) and ceil(blocks / splits) blocks each.  For every number of turns the most ranges that
+// fit are taken; the cheapest number wins.
+constexpr int EX_START = 4, EX_MAX_TURNS = 8;
+static int expand_splits(int H, int64_t ntb) {
+  int64_t best = -1;
+  int best_s = 1;
+  for (int turns = 1; turns <= EX_MAX_TURNS; turns++) {
+    const int s = (int)std::max<int64_t>(1, std::min<int64_t>(ntb, turns * NUM_CU / H));
+    const int64_t taken = ((int64_t)H * s + NUM_CU - 1) / NUM_CU;
+    const int64_t cost = taken * ((ntb + s - 1) / s + EX_START);
+    if (best < 0 || cost < best) { best = cost; best_s = s; }
   }
+  return best_s;
 }
 
 int mfma_expand(int H, int64_t ntok, const void* c, int64_t c_stride, const void* r,
@@ -240,12 +324,13 @@ int mfma_expand(int H, int64_t ntok, const void* c, int64_t c_stride, const void
   a.w_uk = (const __bf16*)w_uk; a.w_uv = (const __bf16*)w_uv;
   a.k_out = (__bf16*)k_out; a.v_out = (__bf16*)v_out;
   a.ntok = ntok; a.ntb = (ntok + TOK_BLK - 1) / TOK_BLK; a.H = H;
-  a.tiles = (ntok + EX_TOK - 1) / EX_TOK;
-  if (a.tiles * H > 0x7fffffff) return TMLA_ERR_UNSUPPORTED;
+  a.splits = expand_splits(H, a.ntb);
+  if ((int64_t)a.splits * H > 0x7ffffff0) return TMLA_ERR_UNSUPPORTED;
+  a.units = a.splits * H;
   static LdsOptIn lds;
   if (lds.ensure((const void*)expand_gemm_kernel, EX_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
-  hipLaunchKernelGGL(expand_gemm_kernel, dim3((unsigned)(a.tiles * H)), dim3(256), EX_LDS_BYTES,
-                     stream, a);
+  hipLaunchKernelGGL(expand_gemm_kernel, dim3((unsigned)((a.units + 7) / 8 * 8)), dim3(256),
+                     EX_LDS_BYTES, stream, a);
   return TMLA_OK;
 }
 

@@ -315,6 +315,35 @@ def test_expand_prefix_matches_definition(dtype, ntok, flags, gpu_device):
             assert np.all(kraw[Hh.k_offset(hh, ntb32, t, dd, dtype)] == 0)
 
 
+@pytest.mark.parametrize("heads,ntok", [(128, 64), (128, 97), (128, 160), (128, 193), (128, 330),
+                                        (16, 2700), (272, 70)])
+def test_expand_prefix_over_ranges_of_few_blocks(heads, ntok, gpu_device):
+    """Workgroups of one to eight 32-token blocks: odd and even walks, a ragged last block at the
+    end of either, more heads than compute units.  Bounds as above: one bf16 rounding of an fp32
+    accumulation over 512 products."""
+    wl = W.make_workload(W.small_spec(dtype="bf16", batch=1, heads=heads, prefix_len=ntok,
+                                      suffix_min=1, suffix_max=1, seed=140 + ntok))
+    a = wl.as_float64()
+    k_ref, v_ref = O.expand_prefix_definition(a["prefix_ckv"], a["prefix_krope"], a["w_uk"],
+                                              a["w_uv"])
+    d = wl.to(gpu_device)
+    print(f"expand heads={heads} ntok={ntok}", flush=True)
+    pk, pv = T.typhoon_mla_expand_prefix(Hh.dims_of(wl), d.prefix_ckv, d.prefix_krope, d.w_uk,
+                                         d.w_uv)
+    K, V = Hh.unpack_expanded(pk, pv, heads, ntok, "bf16")
+    np.testing.assert_allclose(K, k_ref, rtol=2.0 ** -8, atol=1e-3)
+    np.testing.assert_allclose(V, v_ref, rtol=2.0 ** -8, atol=1e-3)
+    if ntok % 32:   # the last block of every head: zeros behind the last token
+        ntb = (ntok + 31) // 32
+        kb = pk.view(torch.bfloat16).view(heads, ntb, 12, 2, 32, 8)[:, -1]
+        vb = pv.view(torch.bfloat16).view(heads, ntb, 2, 4, 2, 32, 8)[:, -1]
+        assert kb[:, :, :, ntok % 32:].abs().max() == 0
+        tok = torch.arange(32).view(2, 2, 2, 4)    # [16-token half, 8-token half, lane half, 4]
+        tok = tok.permute(0, 2, 1, 3).reshape(2, 1, 2, 1, 8).to(gpu_device)
+        assert torch.where(tok >= ntok % 32, vb.float(), torch.zeros_like(vb, dtype=torch.float32)
+                           ).abs().max() == 0
+
+
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("n,rows,width", [(1, 5, 128), (3, 130, 128), (7, 33, 512), (2, 1, 4)])
 def test_combine_lse_matches_definition(n, rows, width, out_dtype, gpu_device):

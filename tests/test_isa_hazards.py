@@ -25,7 +25,8 @@ import pytest
 from paper_2509_21081_amd import build as B
 
 KERNELS = [("tmla_prefix_mfma.hip", "prefix_attn_pipelined_kernel"),
-           ("tmla_absorb128_mfma.hip", "absorb128_kernel")]
+           ("tmla_absorb128_mfma.hip", "absorb128_kernel"),
+           ("tmla_expand_mfma.hip", "expand_gemm_kernel")]
 VALU_TO_MFMA = 4      # wait states between a vector-ALU write and an assembly MFMA reading it
 MFMA_RESULT = 12      # wait states between an 8-pass MFMA and any other use of its result
 MFMA_PASSES = 8
