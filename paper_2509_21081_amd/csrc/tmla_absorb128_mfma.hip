@@ -81,7 +81,7 @@ __device__ inline void a128_drain() {
 
 struct Absorb128Args {
   AbsorbArgs a;
-  int nqg, n_lat, B;
+  AbsorbGrid grid;
 };
 
 // HAS_PREFIX: the launch has work items over the shared latent prefix (absorb_only mode).  Those
@@ -93,18 +93,9 @@ __global__ void __launch_bounds__(256, 1) absorb128_kernel(Absorb128Args args) {
   const AbsorbArgs& a = args.a;
   // (the alignment makes the low address bits of every tile zero, which the XOR addressing needs)
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  // Workgroups that read the same tokens (the query groups of one request chunk) get ids 8 apart:
-  // hardware deals consecutive ids round-robin over the 8 XCDs, so they share an L2.
-  int item, qg, b;
-  {
-    const int id = blockIdx.x, x = id & 7, sl = id >> 3;
-    qg = sl % args.nqg;
-    const int j = (sl / args.nqg) * 8 + x;
-    if (j >= args.n_lat * args.B) return;
-    item = j % args.n_lat;
-    b = j / args.n_lat;
-    if (args.a.order) b = args.a.order[b];
-  }
+  const AbsorbUnit unit = absorb_unit<HAS_PREFIX>(a, args.grid, blockIdx.x);
+  if (unit.none) return;
+  const int item = unit.item, qg = unit.qg, b = unit.b, R = unit.R;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb = wave;                       // score product
@@ -112,35 +103,34 @@ __global__ void __launch_bounds__(256, 1) absorb128_kernel(Absorb128Args args) {
 
   // ---- which tokens
   int t0, t1;
-  const bool is_prefix = HAS_PREFIX && item < a.ap_chunks;
+  const bool is_prefix = HAS_PREFIX && unit.is_prefix;
   int len = 0;
   if (is_prefix) {
     t0 = item * a.ap_chunk;
     t1 = min(a.Ls, t0 + a.ap_chunk);
   } else {
-    len = a.lens[b];
+    len = scalar_load_i32(a.lens + b);
     t0 = (item - a.ap_chunks) * a.as_chunk;
     t1 = min(len, t0 + a.as_chunk);
   }
   const int r_own = (qg * 4 + qb) * 32 + n;   // the query row whose scores this lane holds
   int vis_q = t1;
   if (!is_prefix) {
-    const int s = r_own < a.R ? r_own / a.H : 0;
-    vis_q = max(0, min(len, len - a.Sq + s + 1));
+    vis_q = max(0, min(len, len - a.Sq + query_position(r_own, a.H, R) + 1));
   }
   if (t1 <= t0) {   // empty chunk (workgroup-uniform): only the LSEs are defined
-    if (g == 0 && r_own < a.R)
-      a.lat_lse[(size_t)item * a.rows + (int64_t)b * a.R + r_own] = -INFINITY;
+    if (g == 0 && r_own < R)
+      a.lat_lse[(size_t)item * a.rows + (int64_t)b * R + r_own] = -INFINITY;
     return;
   }
   const int nstep = (t1 - t0 + 63) / 64;
 
   // ---- tile streaming: global -> LDS
   const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
-  const int first_blk = is_prefix ? 0 : t0 / a.block_size;
+  const int first_blk = is_prefix ? 0 : t0 >> a.bs_shift;
   int bt_cache = 0;
   if (!is_prefix) {
-    const int nblk_chunk = (t1 - 1) / a.block_size - first_blk + 1;
+    const int nblk_chunk = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
     bt_cache = (lane < nblk_chunk) ? bt[first_blk + lane] : 0;
     asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
   }
@@ -181,7 +171,7 @@ __global__ void __launch_bounds__(256, 1) absorb128_kernel(Absorb128Args args) {
   // on a 64-token boundary and cache blocks hold a multiple of 64 tokens, so one block-table
   // entry serves a step.  A second tile past the end of the chunk is filled with the chunk's
   // last row: all its scores are masked.
-  const int bs_shift = __builtin_ctz((unsigned)a.block_size);
+  const int bs_shift = a.bs_shift;
   auto step_src = [&](int step, RowSrc& s0, RowSrc& s1) __attribute__((always_inline)) {
     const int tok0 = t0 + step * 64;
     s0.last = t1 - 1 - tok0;              // >= 0 for every step of the chunk
@@ -196,7 +186,7 @@ __global__ void __launch_bounds__(256, 1) absorb128_kernel(Absorb128Args args) {
       const int blk = bi < 64 ? __builtin_amdgcn_readlane(bt_cache, bi)
                               : scalar_load_i32(bt + first_blk + bi);
       s0.lat = (const char*)(a.pool +
-                             (((size_t)blk << bs_shift) + (tok0 & (a.block_size - 1))) * D_ROW);
+                             (((size_t)blk << bs_shift) + (tok0 & ((1 << bs_shift) - 1))) * D_ROW);
       s0.rope = s0.lat + D_L * 2;
       s0.lat_stride = s0.rope_stride = D_ROW * 2;
     }
@@ -236,7 +226,7 @@ __global__ void __launch_bounds__(256, 1) absorb128_kernel(Absorb128Args args) {
   issue_step(0);
   bf16x8 qf[36];
   {
-    const int64_t row = (int64_t)b * a.R + min(r_own, a.R - 1);
+    const int64_t row = (int64_t)b * R + min(r_own, R - 1);
     const __bf16* qrow = a.qabs + row * D_ROW + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < 36; ks++) qf[ks] = *(const bf16x8*)(qrow + 16 * ks);
@@ -497,32 +487,30 @@ __global__ void __launch_bounds__(256, 1) absorb128_kernel(Absorb128Args args) {
       for (int i = 0; i < 16; i++) {
         const int r = 2 * i + rr;
         const bf16x8 w = *(const bf16x8*)(mine + r * ST_ROW + ch * 16);
-        if (row0 + r < a.R)
-          *(bf16x8*)(a.lat_o + ((size_t)item * a.rows + (int64_t)b * a.R + row0 + r) * D_L +
+        if (row0 + r < R)
+          *(bf16x8*)(a.lat_o + ((size_t)item * a.rows + (int64_t)b * R + row0 + r) * D_L +
                      256 * lh + ch * 8) = w;
       }
     }
-    if (g == 0 && r_own < a.R) {
+    if (g == 0 && r_own < R) {
       const float lt = ll[qb];
-      a.lat_lse[(size_t)item * a.rows + (int64_t)b * a.R + r_own] =
+      a.lat_lse[(size_t)item * a.rows + (int64_t)b * R + r_own] =
           lt > 0.f ? (m + fast_log2(lt)) * LN2 : -INFINITY;
     }
   }
 }
 
-int mfma_absorb128_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a) {
-  static LdsOptIn lds[2];
-  auto kernel = a.ap_chunks > 0 ? absorb128_kernel<true> : absorb128_kernel<false>;
-  if (lds[a.ap_chunks > 0].ensure((const void*)kernel, A128_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
+int mfma_absorb128_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what) {
   Absorb128Args args;
   args.a = a;
-  args.nqg = (a.R + 127) / 128;
-  args.n_lat = p.n_lat;
-  args.B = p.B;
-  const long long units = (long long)p.n_lat * p.B;
-  const long long wgs = 8LL * args.nqg * ((units + 7) / 8);
-  if (wgs > 0x7fffffffLL) return TMLA_ERR_UNSUPPORTED;
-  args.a.order = suffix_request_order(p, d, wgs);
+  long long wgs;
+  if (!absorb_grid(p, what, 128, &args.grid, &wgs)) return TMLA_ERR_UNSUPPORTED;
+  if (wgs == 0) return TMLA_OK;
+  static LdsOptIn lds[2];
+  const bool prefix = what & WITH_PREFIX;
+  auto kernel = prefix ? absorb128_kernel<true> : absorb128_kernel<false>;
+  if (lds[prefix].ensure((const void*)kernel, A128_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
+  args.a.order = (what & WITH_SUFFIX) ? suffix_request_order(p, d, wgs) : nullptr;
   hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(256), A128_LDS_BYTES, d.stream, args);
   return TMLA_OK;
 }

@@ -17,26 +17,9 @@
 //   D (16 x 16): column n, rows 4*q + v, v in [0,4).
 #include <type_traits>
 
-#include "tmla_common.hpp"
-#include "tmla_lds_asm.hpp"
-#include "tmla_mfma.hpp"
+#include "tmla_absorb_tile.hpp"
 
 namespace tmla {
-
-struct Absorb16Args {
-  const __bf16* qabs;        // [rows, 576]
-  const __bf16* pc;          // prefix latent [Ls, 512]  (absorb_only)
-  const __bf16* pr;          // prefix rope   [Ls, 64]
-  const __bf16* pool;        // [num_blocks, block_size, 576]
-  const int32_t* block_table;
-  const int32_t* lens;
-  const int32_t* order;      // blockIdx.y -> request, or nullptr (identity)
-  __bf16* lat_o;             // [n_lat, rows, 512]
-  float* lat_lse;            // [n_lat, rows]
-  int Sq, H, R, Ls, ap_chunks, ap_chunk, as_chunks, as_chunk, ap_groups, max_blocks, block_size;
-  int64_t rows;
-  float c;                   // sm_scale * log2(e)
-};
 
 // private tile layout: latent rows at r * 1056 with the 16-byte chunk c in slot
 // c ^ ((r >> 3) & 1), then 32 x 128 B of rope with chunk c of row r in slot c ^ ((r >> 1) & 7).
@@ -68,30 +51,20 @@ __device__ inline float sum_quads(float x) {
   return sum_halves(x);
 }
 
-__global__ void __launch_bounds__(256, 1) absorb16_kernel(Absorb16Args a) {
+__global__ void __launch_bounds__(256, 1) absorb16_kernel(AbsorbArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int grp = blockIdx.x, b = a.order ? a.order[blockIdx.y] : blockIdx.y;
+  const int grp = blockIdx.x, b = a.order ? scalar_load_i32(a.order + blockIdx.y) : (int)blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool q_valid = n < a.R;
   const int64_t row = (int64_t)b * a.R + n;
 
   // ---- the span of this workgroup and this wavefront's share of it
-  const bool is_prefix = grp < a.ap_groups;
-  int first_item, nparts, span0, span1, len = 0;
-  if (is_prefix) {
-    first_item = 4 * grp;
-    nparts = min(4, a.ap_chunks - first_item);
-    span0 = first_item * a.ap_chunk;
-    span1 = min(a.Ls, span0 + nparts * a.ap_chunk);
-  } else {
-    const int sg = grp - a.ap_groups;
-    len = a.lens[b];
-    nparts = min(4, a.as_chunks - 4 * sg);
-    span0 = 4 * sg * a.as_chunk;
-    span1 = min(len, span0 + nparts * a.as_chunk);
-    first_item = a.ap_chunks + 4 * sg;
-  }
+  const int len = scalar_load_i32(a.lens + b);
+  const int nparts = min(4, a.as_chunks - 4 * grp);
+  const int span0 = 4 * grp * a.as_chunk;
+  const int span1 = min(len, span0 + nparts * a.as_chunk);
+  const int first_item = a.ap_chunks + 4 * grp;
   if (wave >= nparts) return;   // no barriers below: wavefronts are independent
   const int item = first_item + wave;
   __bf16* o_dst = a.lat_o + ((size_t)item * a.rows + row) * D_L + 4 * q4;
@@ -100,11 +73,7 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(Absorb16Args a) {
   const int part = ((span + nparts - 1) / nparts + 31) & ~31;   // tokens per wavefront, tile aligned
   const int t0 = __builtin_amdgcn_readfirstlane(span0 + wave * part);
   const int t1 = __builtin_amdgcn_readfirstlane(min(span1, t0 + part));
-  int vis_q = t1;
-  if (!is_prefix) {
-    const int s = q_valid ? n / a.H : 0;
-    vis_q = max(0, min(len, len - a.Sq + s + 1));
-  }
+  const int vis_q = max(0, min(len, len - a.Sq + query_position(n, a.H, a.R) + 1));
   if (t1 <= t0) {
     if (q_valid && q4 == 0) *l_dst = -INFINITY;
     return;
@@ -116,53 +85,35 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(Absorb16Args a) {
   // physical blocks of this wavefront's token range: one entry per lane, picked with v_readlane
   // (ranges longer than 64 blocks fall back to a scalar load per tile)
   const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
-  const int first_blk = is_prefix ? 0 : t0 / a.block_size;
-  int bt_cache = 0;
-  if (!is_prefix) {
-    const int nblk_mine = (t1 - 1) / a.block_size - first_blk + 1;
-    bt_cache = (lane < nblk_mine) ? bt[first_blk + lane] : 0;
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
-  }
+  const int first_blk = t0 >> a.bs_shift;
+  const int nblk_mine = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
+  int bt_cache = (lane < nblk_mine) ? bt[first_blk + lane] : 0;
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
+  const uint32_t tbase = lds_addr(slot);
   const int lane_off0 = lane << 4, lane_off1 = (lane ^ 1) << 4;
   const int rope_ch = ((lane & 7) ^ (lane >> 4)) << 4;   // rope group 0; odd groups: ^ 64
-  auto issue_tile = [&](int tile, auto prefix_tag) __attribute__((always_inline)) {
-    constexpr bool PREFIX = decltype(prefix_tag)::value;
+  auto issue = [&](int tile) __attribute__((always_inline)) {
     const int tok0 = t0 + tile * 32;
     const int last = t1 - 1 - tok0;      // last valid row of this tile (>= 0)
-    const char* base;
-    if constexpr (PREFIX) {
-      base = (const char*)a.pc + (size_t)tok0 * (D_L * 2);
-    } else {
-      const int bi = __builtin_amdgcn_readfirstlane(tok0 / a.block_size - first_blk);
-      const int blk = bi < 64 ? __builtin_amdgcn_readlane(bt_cache, bi)
-                              : scalar_load_i32(bt + first_blk + bi);
-      base = (const char*)(a.pool + ((size_t)blk * a.block_size + tok0 % a.block_size) * D_ROW);
-    }
-    constexpr int row_bytes = PREFIX ? D_L * 2 : D_ROW * 2;
+    const int bi = __builtin_amdgcn_readfirstlane((tok0 >> a.bs_shift) - first_blk);
+    const int blk = bi < 64 ? __builtin_amdgcn_readlane(bt_cache, bi)
+                            : scalar_load_i32(bt + first_blk + bi);
+    const char* base =
+        (const char*)(a.pool + ((size_t)blk << a.bs_shift) * D_ROW + (tok0 & ((1 << a.bs_shift) - 1)) * D_ROW);
+    constexpr int row_bytes = D_ROW * 2;
+    // (scalar base + lane offset: with a 64-bit vector address per transfer the 64 x 3000-token
+    // pass takes 39 us instead of 34.5)
 #pragma unroll
     for (int r = 0; r < 32; r++) {
       const int rr = min(r, last);
       const int loff = ((r >> 3) & 1) ? lane_off1 : lane_off0;
-      // (the shared latent prefix is read by every request: default policy; a request's own
-      // rows are streamed)
-      if constexpr (PREFIX) dma16(base + (size_t)rr * row_bytes + loff, slot + r * A16_ROW_BYTES);
-      else dma16_stream(base + (size_t)rr * row_bytes + loff, slot + r * A16_ROW_BYTES);
+      dma16_scalar_base<true>(loff, base + (size_t)rr * row_bytes, tbase, r * A16_ROW_BYTES);
     }
 #pragma unroll
     for (int j = 0; j < 4; j++) {
       const int rr = min(8 * j + (lane >> 3), last);
-      const char* src;
-      if constexpr (PREFIX)
-        src = (const char*)a.pr + (size_t)(tok0 + rr) * (D_R * 2) + (rope_ch ^ ((j & 1) << 6));
-      else
-        src = base + (size_t)rr * row_bytes + D_L * 2 + (rope_ch ^ ((j & 1) << 6));
-      if constexpr (PREFIX) dma16(src, slot + A16_MAIN_BYTES + j * 1024);
-      else dma16_stream(src, slot + A16_MAIN_BYTES + j * 1024);
+      dma16_scalar_base<true>(rr * row_bytes + (rope_ch ^ ((j & 1) << 6)), base + D_L * 2, tbase, A16_MAIN_BYTES + j * 1024);
     }
-  };
-  auto issue = [&](int tile) __attribute__((always_inline)) {
-    if (is_prefix) issue_tile(tile, std::true_type{});
-    else issue_tile(tile, std::false_type{});
   };
   issue(0);
 
@@ -185,7 +136,6 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(Absorb16Args a) {
   //       -> (16*mb + n)*1056 + ((q4 ^ sw) * 16) + 64*ks,  sw = (n >> 3) & 1 (16*mb does not change it)
   //   rope k-step k < 2: chunk c = 4*k + q4 in slot c ^ ((row >> 1) & 7), the same for row n
   //       and row 16 + n
-  const uint32_t tbase = lds_addr(slot);
   const uint32_t s_addr = tbase + n * A16_ROW_BYTES + ((q4 ^ ((n >> 3) & 1)) << 4);
   uint32_t r_addr[2];
 #pragma unroll
@@ -338,27 +288,10 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(Absorb16Args a) {
   }
 }
 
-int mfma_absorb16_attention(const Plan& p, const DecodeArgs& d) {
-  if (p.n_lat <= 0 || p.rows == 0) return TMLA_OK;
-  Absorb16Args a;
-  a.qabs = (const __bf16*)(d.ws + p.off_qabs);
-  a.pc = (const __bf16*)d.prefix_ckv;
-  a.pr = (const __bf16*)d.prefix_krope;
-  a.pool = (const __bf16*)d.suffix_pool;
-  a.block_table = d.block_table;
-  a.lens = d.suffix_lens;
-  a.lat_o = (__bf16*)(d.ws + p.off_lat_o);
-  a.lat_lse = (float*)(d.ws + p.off_lat_lse);
-  a.Sq = p.Sq; a.H = p.H; a.R = p.Sq * p.H; a.Ls = p.Ls;
-  a.ap_chunks = p.ap_chunks; a.ap_chunk = p.ap_chunk;
-  a.as_chunks = p.as_chunks; a.as_chunk = p.as_chunk;
-  a.ap_groups = (p.ap_chunks + 3) / 4;
-  a.max_blocks = d.max_blocks; a.block_size = d.block_size;
-  a.rows = p.rows;
-  a.c = d.sm_scale * LOG2E;
+int mfma_absorb16_attention(const Plan& p, const DecodeArgs& d, AbsorbArgs a) {
   static LdsOptIn lds;
   if (lds.ensure((const void*)absorb16_kernel, A16_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
-  dim3 grid(a.ap_groups + (p.as_chunks + 3) / 4, p.B);
+  dim3 grid((p.as_chunks + 3) / 4, p.B);
   a.order = suffix_request_order(p, d, (long long)grid.x * grid.y);
   hipLaunchKernelGGL(absorb16_kernel, grid, dim3(256), A16_LDS_BYTES, d.stream, a);
   return TMLA_OK;

@@ -47,7 +47,7 @@ static_assert(AB_ROW_BYTES >= A64_MAX_OFF + 16 && A64_LDS_BYTES <= 163840, "LDS 
 
 struct Absorb64Args {
   AbsorbArgs a;
-  int nqg, n_lat, B;
+  AbsorbGrid grid;
   int moving_only;   // debug: skip the walk with fixed references
 };
 
@@ -59,32 +59,22 @@ template <bool HAS_PREFIX>
 __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
   const AbsorbArgs& a = args.a;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  // Workgroups that read the same tokens (the query groups of one request chunk) get ids 8 apart:
-  // hardware deals consecutive ids round-robin over the 8 XCDs, so they share an L2 and run at
-  // the same time, and the second reader of a tile finds it there.
-  int item, qg, b;
-  {
-    const int id = blockIdx.x, x = id & 7, sl = id >> 3;
-    qg = sl % args.nqg;
-    const int j = (sl / args.nqg) * 8 + x;
-    if (j >= args.n_lat * args.B) return;
-    item = j % args.n_lat;
-    b = j / args.n_lat;
-    if (args.a.order) b = args.a.order[b];
-  }
+  const AbsorbUnit unit = absorb_unit<HAS_PREFIX>(a, args.grid, blockIdx.x);
+  if (unit.none) return;
+  const int item = unit.item, qg = unit.qg, b = unit.b, R = unit.R;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb = wave & 1, th = wave >> 1;
 
   // ---- which tokens
   int t0, t1;
-  const bool is_prefix = HAS_PREFIX && item < a.ap_chunks;
+  const bool is_prefix = HAS_PREFIX && unit.is_prefix;
   int len = 0;
   if (is_prefix) {
     t0 = item * a.ap_chunk;
     t1 = min(a.Ls, t0 + a.ap_chunk);
   } else {
-    len = a.lens[b];
+    len = scalar_load_i32(a.lens + b);
     t0 = (item - a.ap_chunks) * a.as_chunk;
     t1 = min(len, t0 + a.as_chunk);
   }
@@ -93,22 +83,21 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
   const int r_own = (qg * 2 + qb) * 32 + n;
   int vis_q = t1;
   if (!is_prefix) {
-    const int s = r_own < a.R ? r_own / a.H : 0;
-    vis_q = max(0, min(len, len - a.Sq + s + 1));
+    vis_q = max(0, min(len, len - a.Sq + query_position(r_own, a.H, R) + 1));
   }
   if (t1 <= t0) {   // empty chunk (workgroup-uniform): only the LSEs are defined
-    if (th == 0 && g == 0 && r_own < a.R)
-      a.lat_lse[(size_t)item * a.rows + (int64_t)b * a.R + r_own] = -INFINITY;
+    if (th == 0 && g == 0 && r_own < R)
+      a.lat_lse[(size_t)item * a.rows + (int64_t)b * R + r_own] = -INFINITY;
     return;
   }
   const int nstep = (t1 - t0 + 63) / 64;
 
   // ---- tile streaming: global -> LDS (see tmla_absorb_tile.hpp)
   const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
-  const int first_blk = is_prefix ? 0 : t0 / a.block_size;
+  const int first_blk = is_prefix ? 0 : t0 >> a.bs_shift;
   int bt_cache = 0;
   if (!is_prefix) {
-    const int nblk_chunk = (t1 - 1) / a.block_size - first_blk + 1;
+    const int nblk_chunk = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
     bt_cache = (lane < nblk_chunk) ? bt[first_blk + lane] : 0;
     asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
   }
@@ -117,7 +106,7 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
   // on a 64-token boundary and cache blocks hold a multiple of 64 tokens, so one block-table
   // entry serves a step.  A second tile past the end of the chunk is filled with the chunk's
   // last row: all its scores are masked.
-  const int bs_shift = __builtin_ctz((unsigned)a.block_size);
+  const int bs_shift = a.bs_shift;
   auto step_src = [&](int step, RowSrc& s0, RowSrc& s1) __attribute__((always_inline)) {
     const int tok0 = t0 + step * 64;
     s0.last = t1 - 1 - tok0;              // >= 0 for every step of the chunk
@@ -132,7 +121,7 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
       const int blk = bi < 64 ? __builtin_amdgcn_readlane(bt_cache, bi)
                               : scalar_load_i32(bt + first_blk + bi);
       s0.lat = (const char*)(a.pool +
-                             (((size_t)blk << bs_shift) + (tok0 & (a.block_size - 1))) * D_ROW);
+                             (((size_t)blk << bs_shift) + (tok0 & ((1 << bs_shift) - 1))) * D_ROW);
       s0.rope = s0.lat + D_L * 2;
       s0.lat_stride = s0.rope_stride = D_ROW * 2;
     }
@@ -155,17 +144,17 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
   // ---- absorbed query fragments of the own query block (B operand of the score product),
   // staged like cache tiles in slots 2 and 3 while step 0 streams into slots 0 and 1
   {
-    const int64_t req_row0 = (int64_t)b * a.R;
+    const int64_t req_row0 = (int64_t)b * R;
 #pragma unroll
     for (int j = 0; j < 2; j++) {
       const int blk_row0 = (qg * 2 + j) * 32;
       RowSrc qs;
       qs.stream = false;
-      qs.last = min(31, a.R - 1 - blk_row0);
+      qs.last = min(31, R - 1 - blk_row0);
       int64_t first = req_row0 + blk_row0;
       if (qs.last < 0) {   // block entirely past the request's rows: any valid row will do
         qs.last = 0;
-        first = req_row0 + a.R - 1;
+        first = req_row0 + R - 1;
       }
       qs.lat = (const char*)(a.qabs + first * D_ROW);
       qs.rope = qs.lat + D_L * 2;
@@ -441,8 +430,8 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
   #pragma unroll
     for (int q = 0; q < 2; q++) {
       const int r_local = (qg * 2 + q) * 32 + n;
-      if (r_local >= a.R) continue;
-      const int64_t row = (int64_t)b * a.R + r_local;
+      if (r_local >= R) continue;
+      const int64_t row = (int64_t)b * R + r_local;
       const float lt = ll[q] + ll[q + 2];
       float* l_dst = a.lat_lse + (size_t)item * a.rows + row;
       if (lt > 0.f) {
@@ -465,20 +454,18 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
   }
 }
 
-int mfma_absorb64_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a) {
-  static LdsOptIn lds[2];
-  auto kernel = a.ap_chunks > 0 ? absorb64_kernel<true> : absorb64_kernel<false>;
-  if (lds[a.ap_chunks > 0].ensure((const void*)kernel, A64_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
+int mfma_absorb64_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what) {
   Absorb64Args args;
   args.a = a;
-  args.nqg = (a.R + 63) / 64;
-  args.n_lat = p.n_lat;
-  args.B = p.B;
   args.moving_only = (debug_flags() & 0x800) != 0;
-  const long long units = (long long)p.n_lat * p.B;
-  const long long wgs = 8LL * args.nqg * ((units + 7) / 8);
-  if (wgs > 0x7fffffffLL) return TMLA_ERR_UNSUPPORTED;
-  args.a.order = suffix_request_order(p, d, wgs);
+  long long wgs;
+  if (!absorb_grid(p, what, 64, &args.grid, &wgs)) return TMLA_ERR_UNSUPPORTED;
+  if (wgs == 0) return TMLA_OK;
+  static LdsOptIn lds[2];
+  const bool prefix = what & WITH_PREFIX;
+  auto kernel = prefix ? absorb64_kernel<true> : absorb64_kernel<false>;
+  if (lds[prefix].ensure((const void*)kernel, A64_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
+  args.a.order = (what & WITH_SUFFIX) ? suffix_request_order(p, d, wgs) : nullptr;
   hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(256), A64_LDS_BYTES, d.stream, args);
   return TMLA_OK;
 }

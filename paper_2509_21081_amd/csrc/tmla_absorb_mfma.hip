@@ -17,6 +17,7 @@
 //   NQB = 2: 2 x 32 query rows, two wavefronts per block own 256 latent columns each
 //   NQB = 1: 32 query rows (H = 16 with S_q <= 2), four wavefronts own 128 latent columns each;
 //            the scores are recomputed per wavefront, which the HBM-bound small-H case affords.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -24,15 +25,12 @@
 
 namespace tmla {
 
-// HAS_PREFIX: the launch has work items over the shared latent prefix (absorb_only mode); then
-// every transfer is an ordinary one (see the 64-row kernel), else the suffix rows are streamed.
-template <int NQB, bool HAS_PREFIX>
 __global__ void __launch_bounds__(256, 1) absorb_attn_kernel(AbsorbArgs a) {
-  constexpr int NLP = 4 / NQB;
+  constexpr int NQB = 1, NLP = 4 / NQB;
   constexpr int MBW = 16 / NLP;  // 32-latent blocks owned by a wavefront
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int item = blockIdx.x, qg = blockIdx.y;
-  const int b = a.order ? a.order[blockIdx.z] : blockIdx.z;
+  const int item = a.ap_chunks + blockIdx.x, qg = 0;
+  const int b = a.order ? scalar_load_i32(a.order + blockIdx.y) : (int)blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: transfer bookkeeping is SALU
   const int qb = wave % NQB, lp = wave / NQB;
@@ -41,19 +39,10 @@ __global__ void __launch_bounds__(256, 1) absorb_attn_kernel(AbsorbArgs a) {
   const int64_t row = (int64_t)b * a.R + r_local; // global output row (b, s, h)
 
   // ---- which tokens
-  int t0, t1, vis_q;
-  const bool is_prefix = HAS_PREFIX && item < a.ap_chunks;
-  if (is_prefix) {
-    t0 = item * a.ap_chunk;
-    t1 = min(a.Ls, t0 + a.ap_chunk);
-    vis_q = t1;
-  } else {
-    const int len = a.lens[b];
-    t0 = (item - a.ap_chunks) * a.as_chunk;
-    t1 = min(len, t0 + a.as_chunk);
-    const int s = q_valid ? r_local / a.H : 0;
-    vis_q = max(0, min(len, len - a.Sq + s + 1));
-  }
+  const int len = scalar_load_i32(a.lens + b);
+  const int t0 = (item - a.ap_chunks) * a.as_chunk;
+  const int t1 = min(len, t0 + a.as_chunk);
+  const int vis_q = max(0, min(len, len - a.Sq + query_position(r_local, a.H, a.R) + 1));
   __bf16* o_dst = a.lat_o + ((size_t)item * a.rows + row) * D_L;
   float* l_dst = a.lat_lse + (size_t)item * a.rows + row;
   if (t1 <= t0) {   // empty chunk (workgroup-uniform)
@@ -67,32 +56,22 @@ __global__ void __launch_bounds__(256, 1) absorb_attn_kernel(AbsorbArgs a) {
   // 64 blocks here, longer ones fall back to a scalar load per tile), and picked with v_readlane:
   // no memory latency on the tile-issue path.
   const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
-  const int first_blk = is_prefix ? 0 : t0 / a.block_size;
-  int bt_cache = 0;
-  if (!is_prefix) {
-    const int nblk_chunk = (t1 - 1) / a.block_size - first_blk + 1;
-    bt_cache = (lane < nblk_chunk) ? bt[first_blk + lane] : 0;
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
-  }
+  const int first_blk = t0 >> a.bs_shift;
+  const int nblk_chunk = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
+  int bt_cache = (lane < nblk_chunk) ? bt[first_blk + lane] : 0;
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
   const DmaLane dl = dma_lane(wave, lane);
   auto tile_src = [&](int tile) __attribute__((always_inline)) {
     RowSrc s;
     const int tok0 = t0 + tile * 32;
     s.last = t1 - 1 - tok0;              // last valid row of this tile (>= 0)
-    s.stream = !HAS_PREFIX;
-    if (is_prefix) {
-      s.lat = (const char*)a.pc + (size_t)tok0 * (D_L * 2);
-      s.rope = (const char*)a.pr + (size_t)tok0 * (D_R * 2);
-      s.lat_stride = D_L * 2;
-      s.rope_stride = D_R * 2;
-    } else {
-      const int bi = __builtin_amdgcn_readfirstlane(tok0 / a.block_size - first_blk);
-      const int blk = bi < 64 ? __builtin_amdgcn_readlane(bt_cache, bi)
-                              : scalar_load_i32(bt + first_blk + bi);
-      s.lat = (const char*)(a.pool + ((size_t)blk * a.block_size + tok0 % a.block_size) * D_ROW);
-      s.rope = s.lat + D_L * 2;
-      s.lat_stride = s.rope_stride = D_ROW * 2;
-    }
+    s.stream = true;
+    const int bi = __builtin_amdgcn_readfirstlane((tok0 >> a.bs_shift) - first_blk);
+    const int blk = bi < 64 ? __builtin_amdgcn_readlane(bt_cache, bi)
+                            : scalar_load_i32(bt + first_blk + bi);
+    s.lat = (const char*)(a.pool + ((size_t)blk << a.bs_shift) * D_ROW + (tok0 & ((1 << a.bs_shift) - 1)) * D_ROW);
+    s.rope = s.lat + D_L * 2;
+    s.lat_stride = s.rope_stride = D_ROW * 2;
     return s;
   };
   auto slot_ptr = [&](int tile) __attribute__((always_inline)) {
@@ -330,9 +309,26 @@ const int32_t* suffix_request_order(const Plan& p, const DecodeArgs& d, long lon
   return order;
 }
 
+bool absorb_grid(const Plan& p, int what, int rows_per_wg, AbsorbGrid* g, long long* wgs) {
+  const int R = p.Sq * p.H;
+  g->pre_chunks = (what & WITH_PREFIX) ? p.ap_chunks : 0;
+  const long long groups = (p.rows + rows_per_wg - 1) / rows_per_wg;
+  const int suf_chunks = (what & WITH_SUFFIX) ? p.as_chunks : 0;
+  const int suf_groups = (R + rows_per_wg - 1) / rows_per_wg;
+  const long long pre = (g->pre_chunks * groups + 7) / 8 * 8;
+  const long long suf_units = (long long)suf_chunks * p.B;
+  *wgs = pre + (suf_units + 7) / 8 * 8 * suf_groups;
+  if (*wgs > 0x7fffffffLL) return false;
+  g->pre_ids = (int)pre;
+  g->suf_units = (int)suf_units;
+  g->pre_groups.set((uint32_t)groups);
+  g->suf_groups.set((uint32_t)suf_groups);
+  g->suf_chunks.set((uint32_t)suf_chunks);
+  return true;
+}
+
 int mfma_absorb_attention(const Plan& p, const DecodeArgs& d) {
   if (p.n_lat <= 0 || p.rows == 0) return TMLA_OK;
-  if (p.Sq * p.H <= 16) return mfma_absorb16_attention(p, d);
   AbsorbArgs a;
   a.qabs = (const __bf16*)(d.ws + p.off_qabs);
   a.pc = (const __bf16*)d.prefix_ckv;
@@ -344,23 +340,35 @@ int mfma_absorb_attention(const Plan& p, const DecodeArgs& d) {
   a.lat_o = (__bf16*)(d.ws + p.off_lat_o);
   a.lat_lse = (float*)(d.ws + p.off_lat_lse);
   a.Sq = p.Sq; a.H = p.H; a.R = p.Sq * p.H; a.Ls = p.Ls;
-  a.ap_chunks = p.ap_chunks; a.ap_chunk = p.ap_chunk; a.as_chunk = p.as_chunk;
-  a.max_blocks = d.max_blocks; a.block_size = d.block_size;
+  a.ap_chunks = p.ap_chunks; a.ap_chunk = p.ap_chunk;
+  a.as_chunks = p.as_chunks; a.as_chunk = p.as_chunk;
+  a.max_blocks = d.max_blocks; a.bs_shift = __builtin_ctz((unsigned)d.block_size);
   a.rows = p.rows;
   a.c = d.sm_scale * LOG2E;
-  // 128 rows per workgroup when the request has whole blocks of them and the grid still covers
-  // the chip (measured against the 64-row kernel at L_n = 256 ... 4096: 4 to 25 % less time).
   // Debug flags: bit 12 keeps the 64-row kernel, bit 13 takes the 128-row kernel whatever the
   // grid size.
-  if (a.R % 128 == 0 && !(debug_flags() & 0x1000) &&
-      ((debug_flags() & 0x2000) || (long long)p.n_lat * p.B * (a.R / 128) >= NUM_CU))
-    return mfma_absorb128_attention(p, d, a);
-  if (a.R > 32) return mfma_absorb64_attention(p, d, a);
-  static LdsOptIn lds[2];
-  auto kernel = a.ap_chunks > 0 ? absorb_attn_kernel<1, true> : absorb_attn_kernel<1, false>;
-  if (lds[a.ap_chunks > 0].ensure((const void*)kernel, AB_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
-  dim3 grid(p.n_lat, 1, p.B);
-  a.order = suffix_request_order(p, d, (long long)p.n_lat * p.B);
+  const bool keep64 = debug_flags() & 0x1000, force128 = debug_flags() & 0x2000;
+  if (p.abs_joint && !force128)
+    return p.ap_rows == 128 && !keep64 ? mfma_absorb128_attention(p, d, a, WITH_PREFIX | WITH_SUFFIX)
+                                       : mfma_absorb64_attention(p, d, a, WITH_PREFIX | WITH_SUFFIX);
+  if (p.ap_chunks > 0) {
+    const int rc = (p.ap_rows == 128 && !keep64) || force128
+                       ? mfma_absorb128_attention(p, d, a, WITH_PREFIX)
+                       : mfma_absorb64_attention(p, d, a, WITH_PREFIX);
+    if (rc != TMLA_OK || p.as_chunks == 0) return rc;
+  }
+  if (a.R <= 16) return mfma_absorb16_attention(p, d, a);
+  // 128 rows per workgroup when the request has whole blocks of them and the grid still covers
+  // the chip (measured against the 64-row kernel at L_n = 256 ... 4096: 4 to 25 % less time).
+  if (a.R % 128 == 0 && !keep64 &&
+      (force128 || (long long)p.as_chunks * p.B * (a.R / 128) >= NUM_CU))
+    return mfma_absorb128_attention(p, d, a, WITH_SUFFIX);
+  if (a.R > 32) return mfma_absorb64_attention(p, d, a, WITH_SUFFIX);
+  static LdsOptIn lds;
+  auto kernel = absorb_attn_kernel;
+  if (lds.ensure((const void*)kernel, AB_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
+  dim3 grid(p.as_chunks, p.B);
+  a.order = suffix_request_order(p, d, (long long)p.as_chunks * p.B);
   hipLaunchKernelGGL(kernel, grid, dim3(256), AB_LDS_BYTES, d.stream, a);
   return TMLA_OK;
 }

@@ -21,10 +21,82 @@ struct AbsorbArgs {
   const int32_t* order;      // workgroup's request slot -> request, or nullptr (identity)
   __bf16* lat_o;             // [n_lat, rows, 512]
   float* lat_lse;            // [n_lat, rows]
-  int Sq, H, R, Ls, ap_chunks, ap_chunk, as_chunk, max_blocks, block_size;
+  int Sq, H, R, Ls, ap_chunks, ap_chunk, as_chunks, as_chunk, max_blocks;
+  int bs_shift;              // log2 of the tokens per cache block
   int64_t rows;
   float c;                   // sm_scale * log2(e)
 };
+
+// Division of wave-uniform numbers by one the host knows: scalar multiplications instead of the
+// ~30 dependent vector instructions of an integer division (three of them in front of a
+// workgroup's first transfer cost 0.4 us).  recip = min(2^32 - 1, floor(2^32 / d)): the product's
+// high word is the quotient or one less, for every 32-bit numerator.
+struct UniformDiv {
+  uint32_t d, recip;
+  void set(uint32_t div) {
+    d = div > 0 ? div : 1;
+    recip = d == 1 ? 0xffffffffu : (uint32_t)(0x100000000ull / d);
+  }
+  __device__ __forceinline__ void divide(uint32_t x, int& q, int& r) const {
+    uint32_t qq = __umulhi(x, recip), rr = x - qq * d;
+    if (rr >= d) { rr -= d; qq++; }
+    q = (int)qq; r = (int)rr;
+  }
+};
+
+// query position s of a request's query row r = s * H + h (R = S_q * H rows, S_q <= 8)
+__device__ inline int query_position(int r, int H, int R) {
+  int s = 0;
+  for (int t = H; t < R; t += H) s += r >= t;
+  return s;
+}
+
+// Work of a launch of the 64- or 128-row kernel: `pre_chunks` chunks of the latent prefix for
+// `pre_groups` groups of query rows, then `suf_chunks` suffix chunks of B requests for `suf_groups`
+// groups of a request's rows.  Every request attends to the whole prefix, so its groups are cut
+// from the rows of all requests together (16 or 32 rows a request fill a group as well as 128),
+// while a suffix belongs to one request.
+struct AbsorbGrid {
+  int pre_chunks, pre_ids;   // pre_ids: workgroup ids of the prefix, a multiple of 8
+  int suf_units;             // suf_chunks * B
+  UniformDiv pre_groups, suf_groups, suf_chunks;
+};
+struct AbsorbUnit {
+  int item, qg, b, R;   // partial slot, row group, first row / R, rows that the groups are cut from
+  bool is_prefix, none;
+};
+// Hardware deals consecutive workgroup ids round-robin over the 8 XCDs.  A prefix launch gives
+// each XCD consecutive units, i.e. few chunks and many row groups: the chunk stays in its L2.
+// The row groups of one suffix chunk get ids 8 apart: same XCD, at the same time, so the second
+// reader of a tile finds it there.
+template <bool HAS_PREFIX>
+__device__ inline AbsorbUnit absorb_unit(const AbsorbArgs& a, const AbsorbGrid& gr, int id) {
+  // every argument that the way to the first transfer needs, fetched at once: left alone, the
+  // compiler fetches them in four dependent rounds behind the branches (+0.4 us a launch)
+  asm volatile("" ::"s"(a.lens), "s"(a.order), "s"(a.block_table), "s"(a.pool), "s"(a.qabs),
+               "s"(a.ap_chunks), "s"(a.as_chunk), "s"(a.max_blocks), "s"(a.bs_shift), "s"(a.R),
+               "s"(a.rows));
+  AbsorbUnit u;
+  if (HAS_PREFIX && id < gr.pre_ids) {
+    gr.pre_groups.divide((id & 7) * (gr.pre_ids >> 3) + (id >> 3), u.item, u.qg);
+    u.none = u.item >= gr.pre_chunks;
+    u.b = 0;
+    u.R = (int)a.rows;
+    u.is_prefix = true;
+    return u;
+  }
+  if (HAS_PREFIX) id -= gr.pre_ids;
+  int sl, chunk;
+  gr.suf_groups.divide(id >> 3, sl, u.qg);
+  const int j = sl * 8 + (id & 7);
+  u.none = j >= gr.suf_units;
+  gr.suf_chunks.divide(j, u.b, chunk);
+  u.item = a.ap_chunks + chunk;
+  if (a.order && !u.none) u.b = scalar_load_i32(a.order + u.b);
+  u.R = a.R;
+  u.is_prefix = false;
+  return u;
+}
 
 // LDS tile of 32 tokens (38912 B).  The LDS has 64 four-byte banks; a 16-byte read is served 16
 // consecutive lanes at a time, an 8-byte (transposing) read 32 lanes at a time, and a group is
@@ -124,7 +196,12 @@ __device__ __attribute__((always_inline)) inline void issue_all(const RowSrc& s,
   static_for<AB_DMA_PER_WAVE>([&](auto k) { issue_part<decltype(k)::value>(s, dst, d); });
 }
 
-int mfma_absorb64_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a);
-int mfma_absorb128_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a);
+// One launch over the latent prefix (WITH_PREFIX), the suffixes (WITH_SUFFIX) or both.
+enum { WITH_PREFIX = 1, WITH_SUFFIX = 2 };
+// its grid for `rows_per_wg` (64 or 128) rows a workgroup; false: too many workgroups
+bool absorb_grid(const Plan& p, int what, int rows_per_wg, AbsorbGrid* grid, long long* wgs);
+int mfma_absorb64_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what);
+int mfma_absorb128_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what);
+int mfma_absorb16_attention(const Plan& p, const DecodeArgs& d, AbsorbArgs a);   // S_q * H <= 16, suffixes
 
 }  // namespace tmla

@@ -71,37 +71,146 @@ static void plan_prefix_splits(int H, int M, int Ls, int* p_chunk, int* np_split
 
 void layout_workspace(Plan* p);
 
-// Token chunk of the absorb pass for a grid with fewer (request, row group) pairs than compute
-// units, where the chunk count alone decides how the pass fills the chip: 264 workgroups take two
-// rounds on 256 units, 240 take one.  Every chunk length (in 64-token steps) is priced with a
-// small model of the 64- and 128-row kernels -- rounds x (start-up + steps x step time) plus the
-// merge of the partials -- and the cheapest is taken.  The constants are measured on MI355X
-// (start-up 15 us, 3.3 / 4.1 us per step, partials merged at 3 TB/s); they only have to rank the
-// candidates.  Ls = latent prefix tokens walked in absorb form (0 in mixed mode).
-static int plan_small_grid_chunk(int B, int R, int Ls, int Ln, int block_size) {
-  const int g64 = ceil_div(R, 64);
-  const int longest = std::max(Ls, Ln);
-  double best = 1e300;
-  int best_T = 0;
-  // candidates: the longer part cut into n = 1 ... MAX_CHUNKS equal chunks of whole 64-token steps
-  // (chunks under 256 tokens are not worth a partial)
-  for (int n = 1; n <= MAX_CHUNKS; n++) {
-    const int T = (int)((((int64_t)longest + n - 1) / n + 63) / 64 * 64);
-    if (n > 1 && T < 256) break;
-    const int Ts = round_up(T, block_size);
-    const int ap = Ls > 0 ? ceil_div(Ls, T) : 0, as = Ln > 0 ? ceil_div(Ln, Ts) : 0;
-    if (ap > MAX_CHUNKS || as > MAX_CHUNKS) continue;
-    const int n_lat = ap + as;
-    const bool rows128 = R % 128 == 0 && (long long)n_lat * B * (R / 128) >= NUM_CU;
-    const long long wgs = (long long)n_lat * B * (rows128 ? R / 128 : g64);
-    const int steps = ceil_div(std::max(std::min(T, Ls), std::min(Ts, Ln)), 64);
-    const double rounds = (double)((wgs + NUM_CU - 1) / NUM_CU);
-    double t = rounds * (15.0 + steps * (rows128 ? 4.1 : 3.3));
-    if (n_lat > 4) t += 3.0 + (double)n_lat * B * R * 1024.0 / 3e6;
-    else t += 1.5 * (n_lat - 1);
-    if (t < best) { best = t; best_T = T; }   // ties: the longer chunk
+// ---- absorb passes (bf16): which kernels, how many chunks
+// Times below are microseconds, fitted to the kernels on MI355X (absorb stage alone, 300 ... 16384
+// prefix tokens, 16 ... 32768 query rows, 2 ... 512 requests, 100 ... 1100 workgroups); they only
+// have to rank the candidates.
+static double merge_us(int n_lat, double rows) {   // partials of a row -> one
+  return n_lat > 4 ? 3.0 + rows * (0.0008 + n_lat * 1028.0 / 6e6)
+                   : (n_lat - 1) * (0.9 + rows * 1.8e-4);
+}
+static double rounds_of(double wgs) { return std::ceil(wgs / NUM_CU); }
+// One workgroup of the 64- or 128-row kernel over `steps` 64-token steps, `wgs` of them in flight:
+// beyond about 200 the chip's power, not the kernel, sets the pace.
+static double wg_us(int per_wg, double steps, double wgs) {
+  const double n = std::min<double>(wgs, NUM_CU);
+  return per_wg == 64 ? 11.5 + steps * 1.9 * std::max(1.0, n / 220)
+                      : 17.0 + steps * 2.75 * std::max(1.0, n / 205);
+}
+// A step over suffix rows takes a quarter longer than one over the prefix, which comes from L2.
+constexpr double OWN_STEP = 1.25;
+// `n_pre` workgroups of t_pre each, then `n_own` of at most t_own (suffixes are ragged: 0.85 of
+// that on average), dealt out to the compute units as they become free
+static double dealt_us(double n_pre, double t_pre, double n_own, double t_own) {
+  const double longest = std::max(n_pre > 0 ? t_pre : 0.0, n_own > 0 ? t_own : 0.0);
+  if (n_pre + n_own <= NUM_CU) return longest;
+  return std::max(rounds_of(n_pre) * t_pre,
+                  (n_pre * t_pre + 0.85 * n_own * t_own) / NUM_CU + 0.5 * longest);
+}
+// The suffixes in the kernel of their own rows per request, `as` chunks of Ts tokens.
+static double suffix_us(int B, int R, int Ln, int as, int Ts) {
+  const double T = std::min(Ts, Ln);
+  if (R <= 16) {   // four chunks a workgroup, a 32-token tile a wavefront; HBM at 5.2 TB/s
+    const double bytes = (double)B * Ln * 1152 + (double)as * B * R * 2180;
+    const int waves = std::min(as, 4);   // that share what the workgroup's chunks hold
+    const double tiles = ceil_div(ceil_div(std::min(Ln, waves * Ts), waves), 32);
+    const double lat = rounds_of((double)B * ceil_div(as, 4)) * (10.5 + tiles * (1.3 + 0.22 * waves));
+    return std::max(lat, 8.0 + bytes / 5.2e6) + 0.2 * lat;   // (they overlap, but not quite)
   }
-  return best_T ? best_T : round_up(std::max(longest, 64), 64);
+  if (R <= 32) return dealt_us(0, 0, (double)B * as, 7.0 + T / 32 * 1.8);
+  const bool rows128 = R % 128 == 0 && (long long)as * B * (R / 128) >= NUM_CU;
+  const int per_wg = rows128 ? 128 : 64;
+  const double wgs = (double)as * B * ceil_div(R, per_wg);
+  return dealt_us(0, 0, wgs, wg_us(per_wg, OWN_STEP * std::ceil(T / 64), wgs));
+}
+
+// Chunk counts that are tried.
+static const int CHUNK_COUNTS[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16,
+                                   20, 24, 28, 32, 40, 48, 56, 64};
+static_assert(MAX_CHUNKS == 64, "chunk counts that are tried");
+
+// Fixes the chunks of the suffixes (Ln tokens at most) and of the latent prefix (Ls, 0: none).
+//   * Up to 32 rows per request a pass over short chunks is latency and little else, so the
+//     chunks are cut until the chip is covered once: 8 requests x 1024 tokens x 16 heads
+//     28 -> 15 us (256 -> 64 tokens a chunk), 64 requests 41 -> 28 us.
+//   * The latent prefix is walked by the 64- or 128-row kernel over groups cut from the rows of
+//     ALL requests -- a pass of its own behind which the suffixes run in their usual kernel, or,
+//     where that is cheaper, one launch for both (a second launch of short work costs 10 us and
+//     more): 8 requests x 16 heads, 4096 + 1200 tokens: 25 us in two
+//     launches, 13 us in one.
+// More partials than before must not push a call over the static scratch that it fitted in:
+// candidates beyond that size are dropped unless a plan of no more partials needed it anyway.
+// (`general`: chunks of 256 tokens or more, as long as the grid covers the chip about twice.)
+static void plan_absorb_bf16(Plan* p, int Ls, int Ln, int block_size) {
+  const int B = p->B, R = p->Sq * p->H;
+  const double rows = (double)p->rows;
+  const int g64 = ceil_div(R, 64);
+  const int wgs = std::max(1, B * g64);
+  const int want = std::max(1, ceil_div(2 * NUM_CU, wgs)) * (R <= 16 ? 4 : 1);
+  auto general = [&](int L, int unit) {
+    const int T = std::max(std::max(256, ceil_div(L, want)), ceil_div(L, MAX_CHUNKS));
+    return round_up(std::min(T, round_up(L, unit)), unit);
+  };
+  const bool small = R > 32 && wgs < NUM_CU;
+  const int n_general = small ? 2 : (Ls > 0 ? ceil_div(Ls, general(Ls, TOK_BLK)) : 0) +
+                                        (Ln > 0 ? ceil_div(Ln, general(Ln, block_size)) : 0);
+  const double other = rows * (D_ROW * 2.0 + (p->np_split + p->ns_chunks) * (D_V * 4.0 + 4)) + 4096 +
+                       4.0 * B;
+  auto allowed = [&](int n_lat) {
+    return n_lat <= n_general || other + n_lat * rows * (D_L * 2.0 + 4) <= TMLA_STATIC_SCRATCH_BYTES;
+  };
+
+  // the suffixes by themselves
+  double t_suf = 0.0;
+  if (Ln > 0) {
+    p->as_chunk = general(Ln, block_size);
+    p->as_chunks = ceil_div(Ln, p->as_chunk);
+    if (R <= 32 || small) {
+      // (shorter chunks than the general rule's, or than 256 tokens, have to win by more than the
+      // model's error)
+      const int usual = R <= 32 ? p->as_chunk : 256;
+      double best = R <= 32 ? suffix_us(B, R, Ln, p->as_chunks, p->as_chunk) +
+                                  merge_us(p->as_chunks + (Ls > 0), rows) : 1e300;
+      for (int n : CHUNK_COUNTS) {
+        const int T = round_up(ceil_div(Ln, n), block_size), as = ceil_div(Ln, T);
+        if (n > 1 && !allowed(as + (Ls > 0))) break;
+        double t = suffix_us(B, R, Ln, as, T) + merge_us(as + (Ls > 0), rows);
+        if (T < usual) t = R <= 16 ? 1.08 * t + 2.0 : 1.12 * t;
+        if (t < best && (R > 32 || T < usual)) { best = t; p->as_chunk = T; p->as_chunks = as; }
+        if (T == block_size) break;
+      }
+    }
+    t_suf = suffix_us(B, R, Ln, p->as_chunks, p->as_chunk);
+  }
+  if (Ls <= 0) return;
+
+  double best = 1e300;
+  const int as_own = p->as_chunks, as_own_chunk = p->as_chunk;
+  for (int per_wg = 64; per_wg <= 128; per_wg += 64) {
+    const long long groups = ((long long)p->rows + per_wg - 1) / per_wg;
+    for (int n : CHUNK_COUNTS) {
+      const int T = round_up(ceil_div(Ls, n), 64), ap = ceil_div(Ls, T);
+      if (!allowed(ap + as_own) && (n > 1 || Ln > 0)) break;   // (one launch, one chunk each: allowed)
+      const double wgs = (double)ap * groups;
+      const double t = dealt_us(wgs, wg_us(per_wg, ceil_div(std::min(T, Ls), 64), wgs), 0, 0) +
+                       t_suf + merge_us(ap + as_own, rows);
+      if (t < best) {
+        best = t; p->ap_chunk = T; p->ap_chunks = ap; p->ap_rows = per_wg; p->abs_joint = false;
+      }
+      if (T == 64) break;
+    }
+  }
+  if (Ln <= 0) return;
+  for (int per_wg = 64; per_wg <= (R % 128 == 0 ? 128 : 64); per_wg += 64) {
+    for (int n : CHUNK_COUNTS) {
+      const int T = round_up(ceil_div(std::max(Ls, Ln), n), 64), Ts = round_up(T, block_size);
+      const int ap = ceil_div(Ls, T), as = ceil_div(Ln, Ts);
+      if (n > 1 && !allowed(ap + as)) break;
+      const double n_pre = (double)(ap * ((p->rows + per_wg - 1) / per_wg));
+      const double n_suf = (double)as * B * ceil_div(R, per_wg);
+      const double n_all = n_pre + n_suf;
+      const double t =
+          dealt_us(n_pre, wg_us(per_wg, ceil_div(std::min(T, Ls), 64), n_all), n_suf,
+                   wg_us(per_wg, OWN_STEP * ceil_div(std::min(Ts, Ln), 64), n_all)) +
+          merge_us(ap + as, rows);
+      if (t < best) {
+        best = t; p->ap_chunk = T; p->ap_chunks = ap; p->ap_rows = per_wg; p->abs_joint = true;
+        p->as_chunk = Ts; p->as_chunks = as;
+      }
+      if (T == 64) break;
+    }
+  }
+  if (!p->abs_joint) { p->as_chunks = as_own; p->as_chunk = as_own_chunk; }
 }
 
 // Cuts the call into work items (token chunks) and lays the intermediates out in the workspace.
@@ -115,7 +224,6 @@ int make_plan(const tmla_dims* dims, int mode, int B, int Sq, int Ls, int max_su
   p->rows = (int64_t)B * Sq * dims->num_heads;
   const int H = dims->num_heads;
   const int M = B * Sq;
-  const int target = 2 * NUM_CU;
 
   if (Ls > 0 && mode != TMLA_MODE_ABSORB_ONLY) {
     // naive prefix pass: one workgroup owns a head and a block of up to 256 queries
@@ -130,28 +238,21 @@ int make_plan(const tmla_dims* dims, int mode, int B, int Sq, int Ls, int max_su
     p->ns_chunks = ceil_div(max_suffix, p->ns_chunk);
   }
   if (mode != TMLA_MODE_NAIVE_ONLY) {
-    // absorb pass: one workgroup owns a request, one token chunk and up to 64 of its S_q*H query
-    // rows (with at most 16 rows: four consecutive chunks, one per wavefront).  Chunks are kept
-    // as long as the grid still covers the chip about twice: every extra chunk costs a
-    // 512-wide partial per row and a workgroup start-up.
-    const int R = Sq * H;
-    const int per_wg = R <= 16 ? 4 : 1;
-    const int wgs = std::max(1, B * ceil_div(R, 64));
-    const int want = std::max(1, ceil_div(2 * NUM_CU, wgs)) * per_wg;   // chunks per request
     const int Ls_abs = mode == TMLA_MODE_ABSORB_ONLY ? Ls : 0;
-    // small grids of the 64- / 128-row kernels: chunk from the model above
-    const int modelled = (R > 32 && wgs < NUM_CU && (Ls_abs > 0 || max_suffix > 0))
-                             ? plan_small_grid_chunk(B, R, Ls_abs, max_suffix, block_size) : 0;
-    if (mode == TMLA_MODE_ABSORB_ONLY && Ls > 0) {
-      int chunk = tune(TMLA_TUNE_ABSORB_PREFIX_CHUNK);
-      if (chunk <= 0) chunk = modelled ? modelled : std::max(256, ceil_div(Ls, want));
-      chunk = std::max(chunk, ceil_div(Ls, MAX_CHUNKS));
-      p->ap_chunk = round_up(std::min(chunk, round_up(Ls, TOK_BLK)), TOK_BLK);
-      p->ap_chunks = ceil_div(Ls, p->ap_chunk);
+    if (p->dtype == TMLA_BF16) plan_absorb_bf16(p, Ls_abs, max_suffix, block_size);
+    // fp32 (a workgroup per row and chunk): chunks until there are some workgroups per compute
+    // unit; the tuning overrides: as they say
+    const int want32 = std::max<int>(1, (int)((8 * NUM_CU + p->rows - 1) / std::max<int64_t>(1, p->rows)));
+    int chunk = tune(TMLA_TUNE_ABSORB_PREFIX_CHUNK);
+    if (Ls_abs > 0 && (chunk > 0 || p->ap_chunks == 0)) {
+      if (chunk <= 0) chunk = std::max(64, ceil_div(Ls_abs, want32));
+      chunk = std::max(chunk, ceil_div(Ls_abs, MAX_CHUNKS));
+      p->ap_chunk = round_up(std::min(chunk, round_up(Ls_abs, TOK_BLK)), TOK_BLK);
+      p->ap_chunks = ceil_div(Ls_abs, p->ap_chunk);
     }
-    if (max_suffix > 0) {
-      int chunk = tune(TMLA_TUNE_SUFFIX_CHUNK);
-      if (chunk <= 0) chunk = modelled ? modelled : std::max(256, ceil_div(max_suffix, want));
+    chunk = tune(TMLA_TUNE_SUFFIX_CHUNK);
+    if (max_suffix > 0 && (chunk > 0 || p->as_chunks == 0)) {
+      if (chunk <= 0) chunk = std::max(64, ceil_div(max_suffix, want32));
       chunk = std::max(chunk, ceil_div(max_suffix, MAX_CHUNKS));
       p->as_chunk = round_up(std::min(chunk, round_up(max_suffix, block_size)), block_size);
       p->as_chunks = ceil_div(max_suffix, p->as_chunk);

@@ -81,6 +81,8 @@ struct Plan {
   int ns_chunk;        //   tokens per chunk (multiple of block_size)
   int ap_chunks;       // absorb over the latent prefix (absorb_only): chunks per request
   int ap_chunk;        //   tokens per chunk (multiple of 32)
+  int ap_rows;         //   query rows a workgroup takes (64 or 128), cut from all requests' rows
+  bool abs_joint;      //   prefix and suffix in one launch, of ap_rows rows a workgroup
   int as_chunks;       // absorb over the paged suffix: chunks per request
   int as_chunk;        //   tokens per chunk (multiple of block_size)
   int n_naive;         // = np_split + ns_chunks   (128-wide partials per row)

@@ -280,6 +280,25 @@ def test_suffix_scores_far_from_the_first_step_128_rows(gain, gpu_device, tune):
                          peaked=True)
 
 
+@pytest.mark.parametrize("flags", [0, 0x1000, 0x2000], ids=["planned", "rows64", "rows128"])
+@pytest.mark.parametrize("heads,batch,q_len,prefix,suffix,block",
+                         [(16, 9, 1, 700, (0, 90), 64), (48, 5, 2, 129, (2, 300), 128),
+                          (80, 3, 1, 64, (1, 65), 64), (32, 17, 3, 1000, (0, 0), 64),
+                          (128, 2, 1, 63, (700, 700), 64)])
+def test_absorb_prefix_over_the_rows_of_all_requests(heads, batch, q_len, prefix, suffix, block,
+                                                     flags, gpu_device):
+    """The latent prefix is walked for groups of 64 or 128 rows cut across requests: groups that
+    end inside a request, a last group that is nearly empty, chunks that end inside a step, one
+    launch for prefix and suffix or two (the flags), no suffix at all."""
+    wl = W.make_workload(W.small_spec(dtype="bf16", batch=batch, heads=heads, q_len=q_len,
+                                      prefix_len=prefix, suffix_min=suffix[0],
+                                      suffix_max=suffix[1], block_size=block, seed=300 + batch))
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64())
+    print(f"absorb prefix rows={batch * q_len * heads} prefix={prefix} flags={flags:#x}", flush=True)
+    got, got_lse = Hh.run_library(wl, "absorb_only", gpu_device, flags=flags)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"absorb_prefix_{heads}x{batch}")
+
+
 @pytest.mark.parametrize("flags", [0, 1], ids=["mfma", "scalar"])
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("ntok", [1, 31, 64, 100, 300])
