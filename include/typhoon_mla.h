@@ -272,12 +272,16 @@ int typhoon_mla_combine_lse(int32_t num_partials, int64_t rows, int32_t width,
  *   bit 11 (0x800): the absorb attention kernel for more than 32 query rows per request walks
  *     every chunk with moving exponent references (otherwise only chunks in which its first walk,
  *     with references fixed at the chunk's first tokens, overflowed).
- *   bit 12 (0x1000): requests with a multiple of 128 query rows keep the absorb kernel that
- *     gives a workgroup 64 rows; bit 13 (0x2000): they take the 128-row kernel even when its
- *     grid does not cover the chip (by default it is chosen only when it does).
+ *   bit 12 (0x1000): the absorb passes keep the kernel that gives a workgroup 64 query rows;
+ *     bit 13 (0x2000): the latent prefix, and the suffixes of requests with a multiple of 128
+ *     rows, take the 128-row kernel whatever the grid size (by default a cost model decides for
+ *     the prefix, and the suffixes take it when its grid covers the chip).
  *   bit 14 (0x4000): the absorb attention kernels start the requests with the longest suffix
  *     first whatever the grid size (by default only when a pass has more workgroups than the
  *     chip has compute units, and the batch has at most 4096 requests); bit 15 (0x8000): never.
+ *   bit 17 (0x20000): naive prefix attention with 65 to 128 queries per head runs on the
+ *     software-pipelined kernel with paired wavefronts whatever the prefix length (by default
+ *     only long prefixes do).  Set it before the workspace query: it changes the plan.
  * Returns the previous value.
  */
 int typhoon_mla_set_debug_flags(int flags);

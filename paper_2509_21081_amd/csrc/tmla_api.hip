@@ -61,7 +61,8 @@ static inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p % 
 
 // Token splits of a naive pass over Ls shared tokens for M queries per head.
 static void plan_prefix_splits(int H, int M, int Ls, int* p_chunk, int* np_split) {
-  const int wgs = std::max(1, H * (M > PIPELINED_MIN_M ? ceil_div(M, 256) : ceil_div(M, 64)));
+  const int wgs = std::max(1, H * (M > PIPELINED_MIN_M ? ceil_div(M, 256)
+                                   : prefix_paired(H, M, Ls) ? 1 : ceil_div(M, 64)));
   int splits = tune(TMLA_TUNE_PREFIX_SPLITS);
   if (splits <= 0) splits = std::max(1, NUM_CU / wgs);
   splits = std::max(1, std::min(splits, ceil_div(Ls, 128)));
@@ -262,6 +263,14 @@ int make_plan(const tmla_dims* dims, int mode, int B, int Sq, int Ls, int max_su
   p->n_lat = p->ap_chunks + p->as_chunks;
 
   layout_workspace(p);
+  if (p->total > (size_t)TMLA_STATIC_SCRATCH_BYTES && p->np_split > 1 &&
+      tune(TMLA_TUNE_PREFIX_SPLITS) <= 0 && prefix_paired(H, M, Ls)) {
+    // (twice the splits of the token-split kernel must not be what a call no longer fits for)
+    p->p_chunk = round_up(ceil_div(Ls, std::max(1, NUM_CU / (2 * H))), TOK_BLK);
+    p->np_split = ceil_div(Ls, p->p_chunk);
+    p->n_naive = p->np_split + p->ns_chunks;
+    layout_workspace(p);
+  }
   return TMLA_OK;
 }
 

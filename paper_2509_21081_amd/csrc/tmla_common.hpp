@@ -164,6 +164,19 @@ int mfma_finalize(const Plan& p, const DecodeArgs& a);
 // of a head sharing its cache through L2).  Measured with the bound at 64: equal at 4096-token
 // prefixes, 7 % less kernel time at 32768 tokens but a longer step (more partials to combine).
 constexpr int PIPELINED_MIN_M = 128;
+// 65 to 128 queries per head: the pipelined kernel with its wavefronts in pairs where a workgroup
+// gets enough of the prefix -- it reads every byte once, but has twice the splits of the
+// token-split kernel (whose two query groups share a head) and more start-up.  Prefix pass and
+// step against the token-split kernel: 128 heads x 128 queries, 2048 tokens per workgroup (4096 in
+// all) 77.5 -> 65.5 and 116.6 -> 108.1 us, 8192 per workgroup 270 -> 198 and 314 -> 239; 1250 per
+// workgroup (64 heads) 48.4 -> 46.5 but 78.9 -> 82.9, 512 per workgroup 26.6 -> 27.7.
+// Debug flag bit 17: the pairs whatever the length.
+constexpr int PAIRED_MIN_M = 64;
+constexpr int PAIRED_MIN_TOKENS = 1600;
+inline bool prefix_paired(int H, int M, int Ls) {
+  return M > PAIRED_MIN_M && M <= PIPELINED_MIN_M && !(debug_flags() & 0x400) &&
+         ((debug_flags() & 0x20000) || (int64_t)Ls * H >= (int64_t)PAIRED_MIN_TOKENS * NUM_CU);
+}
 constexpr int MAX_CHUNKS = 64;  // per-request chunk bound for each of the latent prefix / suffix
 void launch_combine_lse(int num_partials, int64_t rows, int width, const float* po,
                         const float* pl, void* out, int out_dtype, float* lse_out,

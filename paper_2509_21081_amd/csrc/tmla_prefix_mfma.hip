@@ -13,7 +13,8 @@
 //     through LDS rings (K and V separately, all 160 KiB); one hand-laid instruction stream per
 //     wavefront overlaps the scores of block t+1, the softmax of block t and P V of block t-1.
 //     Used when a head has more than 128 queries: the MFMA-bound regime (intensity = number of
-//     queries per fetched byte).
+//     queries per fetched byte).  For 65 to 128 queries the wavefronts work in two pairs, each on
+//     half of the blocks (long prefixes).
 //   * query-split : the same split of the queries over eight wavefronts (two per SIMD) with
 //     moving exponent references, scheduled by the compiler; kept as the debug alternative.
 //   * token-split : all four wavefronts own the same <= 64 queries and stream disjoint token
@@ -431,21 +432,52 @@ __device__ inline void pl_mfma_o_dma(f32x16& d, const bf16x8& a, const bf16x8& b
 __device__ inline void pl_mfma_drain() {
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
 }
+// PAIRED (65 to 128 queries per head): the wavefronts work in two pairs, each on all 128 queries and
+// one half of the split's blocks, with rings of its own in one half of the LDS (four slots, one
+// group in flight: 40 to 80 KiB on their way per compute unit, enough for the HBM-bound regime
+// this is); the two halves are merged through LDS at the end.  Both pairs take as many blocks: of
+// an odd number, the middle one is the last of the first pair (all of it masked) and the first of
+// the second.
+// Measured against the token-split kernel, 128 queries x 128 heads: 16384 tokens 270 -> 198 us
+// (5.4 TB/s), 4096 tokens 77.5 -> 65.5 us; where the line lies: prefix_paired().
+template <bool PAIRED>
+struct PlRing {
+  static constexpr int AHEAD = PAIRED ? 4 : PL_AHEAD;
+  static constexpr int NK = PAIRED ? 4 : PL_NK, NV = PAIRED ? 4 : PL_NV;
+  static constexpr int V_BASE = NK * PL_K_BYTES;
+  static constexpr int BYTES = V_BASE + NV * PL_V_BYTES;      // per ring: half or all of LDS
+  static constexpr int WAVES = PAIRED ? 2 : 4;                // that share a ring
+  static constexpr int KT = 12 / WAVES, VT = 8 / WAVES;       // a wavefront's transfers per block
+  static constexpr int QUERIES = 64 * WAVES;                  // per workgroup
+};
+template <bool PAIRED>
 __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArgs a) {
+  using RG = PlRing<PAIRED>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int h = blockIdx.x, mb = blockIdx.y, sp = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int q0 = mb * PL_QUERIES + wave * 64;   // first query of this wavefront
+  const int pair = PAIRED ? wave >> 1 : 0, wq = PAIRED ? wave & 1 : wave;
+  const int q0 = mb * RG::QUERIES + wq * 64;   // first query of this wavefront
 
-  const int tb0 = sp * a.blocks_per_split;
+  int tb0 = sp * a.blocks_per_split;
   const int tb1 = min(a.ntb, tb0 + a.blocks_per_split);
-  const int nblk = tb1 - tb0;
+  int nblk = tb1 - tb0;
   // the very last block of the prefix may be partial; it gets a masked pass after the loop
-  const bool has_tail = (tb1 == a.ntb) && (a.Ls % TOK_BLK != 0) && nblk > 0;
+  bool has_tail = (tb1 == a.ntb) && (a.Ls % TOK_BLK != 0) && nblk > 0;
+  int tail_limit = a.Ls - (tb1 - 1) * TOK_BLK;   // valid tokens of a partial tail
+  if constexpr (PAIRED) {
+    // (a masked pass for both pairs or for neither: they meet at the same barriers)
+    const bool odd = nblk > 0 && (nblk & 1);
+    if (pair == 0) tail_limit = odd ? 0 : 32;
+    else if (!has_tail) tail_limit = 32;
+    has_tail = has_tail || odd;
+    const int half = (nblk + 1) / 2;
+    if (pair == 1) tb0 += nblk - half;
+    nblk = half;
+  }
   const int nfull = has_tail ? nblk - 1 : nblk;
-  const int tail_limit = a.Ls - (tb0 + nblk - 1) * TOK_BLK;   // valid tokens of a partial tail
-  const uint32_t lane_addr = lds_addr(smem) + lane * 16;
+  const uint32_t lane_addr = lds_addr(smem) + pair * RG::BYTES + lane * 16;
 
   bf16x8 qf[2][12];
 #pragma unroll
@@ -466,33 +498,42 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
                    : "+a"(qf[nb][ks]), "+a"(qf[nb][ks + 1]), "+a"(qf[nb][ks + 2]),
                      "+a"(qf[nb][ks + 3])::"memory");
 
-  // transfers: fragment f of a block is moved by wavefront f % 4 (K: 12 fragments, V: 8)
+  // transfers: fragment f of a block is moved by wavefront f % WAVES (K: 12 fragments, V: 8)
   const char* kbase = (const char*)(a.pk + ((size_t)h * a.ntb + tb0) * K_BLK_ELEMS);
   const char* vbase = (const char*)(a.pv + ((size_t)h * a.ntb + tb0) * V_BLK_ELEMS);
   // The RoPE part of a key (fragments 8 .. 11 of a block) is the same for every head: all heads
   // take it from head 0's blocks, so that it is fetched from HBM once and served from cache to
   // the other heads (a fifth of the expanded cache's bytes), with the ordinary cache policy.
   const char* rbase = (const char*)(a.pk + (size_t)tb0 * K_BLK_ELEMS);
-  const uint32_t lds_base = lds_addr(smem) + wave * 1024;
-  uint32_t lane_off[3];   // fragment w, w + 4, w + 8 of a block
+  const uint32_t lds_base = lds_addr(smem) + pair * RG::BYTES + wq * 1024;
+  constexpr int F_STEP = RG::WAVES * 1024;   // from one fragment of this wavefront to its next
+  uint32_t lane_off[RG::KT];   // fragment w, w + WAVES, ... of a block
 #pragma unroll
-  for (int f = 0; f < 3; f++) lane_off[f] = f * 4096 + wave * 1024 + lane * 16;
+  for (int f = 0; f < RG::KT; f++) lane_off[f] = f * F_STEP + wq * 1024 + lane * 16;
+  constexpr int ROPE_F = 8 / RG::WAVES;      // from this transfer on: the RoPE part
   using GUARD = std::true_type;
   using NOGUARD = std::false_type;
   auto dma_k = [&](int k, int f, auto guard_tag) __attribute__((always_inline)) {
     if (!decltype(guard_tag)::value || k < nblk) {
-      if (f == 2)
+      if (f >= ROPE_F)
         dma16_scalar_base<false>(lane_off[f], rbase + (size_t)k * PL_K_BYTES,
-                                 lds_base + (k & (PL_NK - 1)) * PL_K_BYTES + f * 4096);
+                                 lds_base + (k & (RG::NK - 1)) * PL_K_BYTES + f * F_STEP);
       else
         dma16_scalar_base<true>(lane_off[f], kbase + (size_t)k * PL_K_BYTES,
-                                lds_base + (k & (PL_NK - 1)) * PL_K_BYTES + f * 4096);
+                                lds_base + (k & (RG::NK - 1)) * PL_K_BYTES + f * F_STEP);
     }
   };
   auto dma_v = [&](int kv, int f, auto guard_tag) __attribute__((always_inline)) {
     if (!decltype(guard_tag)::value || (kv >= 0 && kv < nblk))
       dma16_scalar_base(lane_off[f], vbase + (size_t)kv * PL_V_BYTES,
-               lds_base + PL_V_BASE + (kv & (PL_NV - 1)) * PL_V_BYTES + f * 4096);
+               lds_base + RG::V_BASE + (kv & (RG::NV - 1)) * PL_V_BYTES + f * F_STEP);
+  };
+  // group k, in the guarded variant: K(k) and V(k - 3) where they exist
+  auto dma_group = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < RG::KT; f++) dma_k(k, f, GUARD{});
+#pragma unroll
+    for (int f = 0; f < RG::VT; f++) dma_v(k - 3, f, GUARD{});
   };
   f32x16 o[4][2];
   // Softmax bookkeeping.  The exponent reference m of a query is fixed before the walk over the
@@ -506,23 +547,25 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
   float m_exact[2] = {0.f, 0.f};
   const float c = a.c;
 
-  // top of period t: groups t+3 .. t+PL_AHEAD-1 may still be in flight, group t+2 must have
-  // landed.  Group k holds three transfers of K(k) if k < nblk and two of V(k-3) if
-  // 0 <= k-3 < nblk.
+  // top of period t: groups t+3 .. t+AHEAD-1 may still be in flight, group t+2 must have
+  // landed.  Group k holds KT transfers of K(k) if k < nblk and VT of V(k-3) if 0 <= k-3 < nblk.
   auto sync = [&](int t, auto steady_tag) __attribute__((always_inline)) {
-    static_assert(PL_AHEAD == 8, "the waits below assume five groups in flight");
+    constexpr int GT = RG::KT + RG::VT, FLY = (RG::AHEAD - 3) * GT;
+    static_assert(FLY == 25 || FLY == 10, "the waits below assume five groups of 5 or one of 10");
     if constexpr (decltype(steady_tag)::value) {
-      vm_wait<25>();
+      vm_wait<FLY>();
     } else {
-      const int lo = t + 3, hi = t + PL_AHEAD - 1;
+      const int lo = t + 3, hi = t + RG::AHEAD - 1;
       const int nk = max(0, min(hi, nblk - 1) - max(lo, 0) + 1);
       const int nv = max(0, min(hi, nblk + 2) - max(lo, 3) + 1);
-      const int pend = 3 * nk + 2 * nv;
+      const int pend = RG::KT * nk + RG::VT * nv;
       if (pend >= 25) vm_wait<25>();
       else if (pend >= 20) vm_wait<20>();
       else if (pend >= 15) vm_wait<15>();
       else if (pend >= 10) vm_wait<10>();
-      else if (pend >= 5) vm_wait<5>();
+      else if (PAIRED && pend >= 6) vm_wait<6>();
+      else if (!PAIRED && pend >= 5) vm_wait<5>();
+      else if (PAIRED && pend >= 4) vm_wait<4>();
       else vm_wait<0>();
     }
     raw_barrier();
@@ -539,7 +582,7 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
   //     probabilities nobody reads, and their sum is dropped;
   //   * P V of block -1 (period 0) multiplies the all-zero initial probabilities with the K
   //     fragments of block 0 standing in for V, which adds exact zeros.
-  // STEADY: 2 <= t and t + PL_AHEAD < nblk -- every block and transfer the period touches exists,
+  // STEADY: 2 <= t and t + AHEAD < nblk -- every block and transfer the period touches exists,
   // so the guards and the count of transfers in flight are compile-time facts.
   auto period = [&](int t, auto par_tag, auto steady_tag) __attribute__((always_inline)) {
     constexpr int PAR = decltype(par_tag)::value;
@@ -550,11 +593,11 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
     bf16x8 (&p_in)[2][2] = pb[PAR ^ 1];
 
     sync(t, steady_tag);
-    const uint32_t ka1 = lane_addr + ((t + 1) & (PL_NK - 1)) * PL_K_BYTES;   // K(t+1)
-    const uint32_t ka2 = lane_addr + ((t + 2) & (PL_NK - 1)) * PL_K_BYTES;   // K(t+2)
+    const uint32_t ka1 = lane_addr + ((t + 1) & (RG::NK - 1)) * PL_K_BYTES;   // K(t+1)
+    const uint32_t ka2 = lane_addr + ((t + 2) & (RG::NK - 1)) * PL_K_BYTES;   // K(t+2)
     const uint32_t va =                                                // V(t-1), or K(0)
-        lane_addr + (STEADY || t >= 1 ? PL_V_BASE + ((t - 1) & (PL_NV - 1)) * PL_V_BYTES : 0);
-    const int kg = t + PL_AHEAD;      // group issued in this period
+        lane_addr + (STEADY || t >= 1 ? RG::V_BASE + ((t - 1) & (RG::NV - 1)) * PL_V_BYTES : 0);
+    const int kg = t + RG::AHEAD;      // group issued in this period
 
     float xa = 0.f, xb = 0.f, ea = 0.f, eb = 0.f;
     // denominators of block t, per column block; the two probabilities of a packed pair go to
@@ -608,8 +651,8 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
     };
     auto dma = [&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value;
-      if constexpr (i < 3) dma_k(kg, i, std::integral_constant<bool, !STEADY>{});
-      else dma_v(kg - 3, i - 3, std::integral_constant<bool, !STEADY>{});
+      if constexpr (i < RG::KT) dma_k(kg, i, std::integral_constant<bool, !STEADY>{});
+      else dma_v(kg - 3, i - RG::KT, std::integral_constant<bool, !STEADY>{});
     };
 
     // Quantum j: two MFMAs on fragment j (one per column block of queries).  A wavefront issues
@@ -625,10 +668,10 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
         constexpr int nb = decltype(nb_tag)::value;
         // (the first MFMA of a group of PL_WG quanta waits for the group's fragments)
         constexpr bool wait_here = nb == 0 && j % PL_WG == 0;
-        // the period's five transfers ride behind the MFMAs of quanta 16 .. 18; in the steady
-        // state (no guards) each is fused with its MFMA
-        constexpr int d = 2 * (j - 16) + nb;
-        constexpr bool has_dma = d >= 0 && d < 5;
+        // the period's five transfers ride behind the MFMAs of quanta 16 .. 18 (PAIRED: ten, 15 ..
+        // 19); in the steady state (no guards) each is fused with its MFMA
+        constexpr int d = 2 * (j - (PAIRED ? 15 : 16)) + nb;
+        constexpr bool has_dma = d >= 0 && d < RG::KT + RG::VT;
         constexpr bool fused_dma = STEADY && has_dma;
         if constexpr (j == 0) {
           if constexpr (wait_here) pl_mfma_s_first_w(s_out[nb], fr[cur], qf[nb][j]);
@@ -639,21 +682,19 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
         } else {
           constexpr int kk = (j - 12) / 4, db = (j - 12) % 4;
           if constexpr (fused_dma) {
-            // transfer d of the group: K fragments w, w + 4, w + 8 of block kg, then V fragments
-            // w, w + 4 of block kg - 3
-            if constexpr (d < 2)
-              pl_mfma_o_dma<wait_here, true>(o[db][nb], fr[cur], p_in[nb][kk], lane_off[d],
-                                             kbase + (size_t)kg * PL_K_BYTES,
-                                             lds_base + (kg & (PL_NK - 1)) * PL_K_BYTES + d * 4096);
-            else if constexpr (d == 2)
-              pl_mfma_o_dma<wait_here, false>(o[db][nb], fr[cur], p_in[nb][kk], lane_off[d],
-                                              rbase + (size_t)kg * PL_K_BYTES,
-                                              lds_base + (kg & (PL_NK - 1)) * PL_K_BYTES + d * 4096);
+            // transfer d of the group: this wavefront's K fragments of block kg, then its V
+            // fragments of block kg - 3
+            if constexpr (d < RG::KT)
+              pl_mfma_o_dma<wait_here, (d < ROPE_F)>(
+                  o[db][nb], fr[cur], p_in[nb][kk], lane_off[d],
+                  (d < ROPE_F ? kbase : rbase) + (size_t)kg * PL_K_BYTES,
+                  lds_base + (kg & (RG::NK - 1)) * PL_K_BYTES + d * F_STEP);
             else
-              pl_mfma_o_dma<wait_here, true>(o[db][nb], fr[cur], p_in[nb][kk], lane_off[d - 3],
-                                       vbase + (size_t)(kg - 3) * PL_V_BYTES,
-                                       lds_base + PL_V_BASE + ((kg - 3) & (PL_NV - 1)) * PL_V_BYTES +
-                                           (d - 3) * 4096);
+              pl_mfma_o_dma<wait_here, true>(o[db][nb], fr[cur], p_in[nb][kk], lane_off[d - RG::KT],
+                                             vbase + (size_t)(kg - 3) * PL_V_BYTES,
+                                             lds_base + RG::V_BASE +
+                                                 ((kg - 3) & (RG::NV - 1)) * PL_V_BYTES +
+                                                 (d - RG::KT) * F_STEP);
           } else if constexpr (wait_here) {
             pl_mfma_o_w(o[db][nb], fr[cur], p_in[nb][kk]);
           } else {
@@ -706,16 +747,20 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
   // double buffering of K through the ring, one barrier per block).
   auto exact_maxima = [&]() __attribute__((always_inline)) {
     float mx[2] = {-INFINITY, -INFINITY};
-    dma_k(0, 0, GUARD{}); dma_k(0, 1, GUARD{}); dma_k(0, 2, GUARD{});
+    auto dma_all_k = [&](int bk) __attribute__((always_inline)) {
+#pragma unroll
+      for (int f = 0; f < RG::KT; f++) dma_k(bk, f, GUARD{});
+    };
+    dma_all_k(0);
     for (int bk = 0; bk < nblk; bk++) {
       if (bk + 1 < nblk) {
-        dma_k(bk + 1, 0, GUARD{}); dma_k(bk + 1, 1, GUARD{}); dma_k(bk + 1, 2, GUARD{});
-        vm_wait<3>();
+        dma_all_k(bk + 1);
+        vm_wait<RG::KT>();
       } else {
         vm_wait<0>();
       }
       raw_barrier();
-      const uint32_t ka = lane_addr + (bk & (PL_NK - 1)) * PL_K_BYTES;
+      const uint32_t ka = lane_addr + (bk & (RG::NK - 1)) * PL_K_BYTES;
       static_for<12>([&](auto j_tag) {
         constexpr int j = decltype(j_tag)::value;
         fr[j % 8] = lds_read_b128<1024 * j>(ka);
@@ -759,14 +804,11 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
     asm volatile("" : "+v"(pb[0][0][0]), "+v"(pb[0][0][1]), "+v"(pb[0][1][0]), "+v"(pb[0][1][1]),
                       "+v"(pb[1][0][0]), "+v"(pb[1][0][1]), "+v"(pb[1][1][0]), "+v"(pb[1][1][1]));
     l[0] = l[1] = 0.f;
-    for (int k = 0; k < PL_AHEAD - 1; k++) {
-      dma_k(k, 0, GUARD{}); dma_k(k, 1, GUARD{}); dma_k(k, 2, GUARD{});
-      dma_v(k - 3, 0, GUARD{}); dma_v(k - 3, 1, GUARD{});
-    }
+    for (int k = 0; k < RG::AHEAD - 1; k++) dma_group(k);
 
     if (nblk > 0) {
       // before period 0: the scores of block 0 and from them the exponent references, the first
-      // fragments of K(1), group PL_AHEAD - 1
+      // fragments of K(1), group AHEAD - 1
       sync(-1, NOGUARD{});
       {
         const uint32_t ka0 = lane_addr, ka1 = lane_addr + PL_K_BYTES;
@@ -784,9 +826,7 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
           constexpr int j = decltype(j_tag)::value;
           fr[j] = lds_read_b128<1024 * j>(ka1);
         });
-        const int k = PL_AHEAD - 1;
-        dma_k(k, 0, GUARD{}); dma_k(k, 1, GUARD{}); dma_k(k, 2, GUARD{});
-        dma_v(k - 3, 0, GUARD{}); dma_v(k - 3, 1, GUARD{});
+        dma_group(RG::AHEAD - 1);
         pl_mfma_drain();
         if (attempt == 0) {
           const int limit0 = nfull > 0 ? 32 : tail_limit;
@@ -802,7 +842,7 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
       period(0, P0{}, GN{});
       if (1 <= nfull) period(1, P1{}, GN{});
       int t = 2;
-      for (; t + 1 + PL_AHEAD < nblk; t += 2) {
+      for (; t + 1 + RG::AHEAD < nblk; t += 2) {
         period(t, P0{}, ST{});
         period(t + 1, P1{}, ST{});
       }
@@ -832,7 +872,7 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
           }
         // packed before the fragment reads, i.e. well in front of the MFMAs that read them
         asm volatile("s_nop 3" : "+v"(pt[0][0]), "+v"(pt[0][1]), "+v"(pt[1][0]), "+v"(pt[1][1]));
-        const uint32_t va = lane_addr + PL_V_BASE + ((nblk - 1) & (PL_NV - 1)) * PL_V_BYTES;
+        const uint32_t va = lane_addr + RG::V_BASE + ((nblk - 1) & (RG::NV - 1)) * PL_V_BYTES;
         bf16x8 vf[8];
         static_for<8>([&](auto j) { vf[j] = lds_read_b128<1024 * decltype(j)::value>(va); });
         lgkm_wait<0>(vf[0], vf[1], vf[2], vf[3]);
@@ -879,12 +919,36 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
     lgkm_wait<0>();
     raw_barrier();
     float* tile = (float*)smem + wave * (64 * PL_OUT_ROW);
+    // PAIRED: the pairs' partials of a query against their common reference; wavefront w and
+    // w ^ 2 hold the same queries
+    float mm[2] = {m[0], m[1]}, den[2] = {lt[0], lt[1]}, scale[2];
+    if constexpr (PAIRED) {
+      float* const st = (float*)(smem + 4 * 64 * PL_OUT_ROW * 4);   // [wavefront][m, l][64]
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++)
+        if (g == 0) {
+          st[wave * 128 + nb * 32 + n] = m[nb];
+          st[wave * 128 + 64 + nb * 32 + n] = lt[nb];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++) {
+        const float mo = st[(wave ^ 2) * 128 + nb * 32 + n], lo = st[(wave ^ 2) * 128 + 64 + nb * 32 + n];
+        // (a half that saw nothing has l = 0 and no reference)
+        mm[nb] = fmaxf(lt[nb] > 0.f ? m[nb] : -INFINITY, lo > 0.f ? mo : -INFINITY);
+        const float w = lt[nb] > 0.f ? fast_exp2(m[nb] - mm[nb]) : 0.f;
+        den[nb] = lt[nb] * w + (lo > 0.f ? lo * fast_exp2(mo - mm[nb]) : 0.f);
+        scale[nb] = w;
+      }
+    } else {
+      scale[0] = scale[1] = 1.f;
+    }
     bool row_ok[2];
 #pragma unroll
     for (int nb = 0; nb < 2; nb++) {
       const int qi = q0 + nb * 32 + n;
-      row_ok[nb] = qi < a.M && lt[nb] > 0.f;
-      const float inv = row_ok[nb] ? 1.f / lt[nb] : 0.f;
+      row_ok[nb] = qi < a.M && den[nb] > 0.f;
+      const float inv = row_ok[nb] ? scale[nb] / den[nb] : 0.f;
 #pragma unroll
       for (int db = 0; db < 4; db++)
 #pragma unroll
@@ -893,15 +957,32 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArg
                                        o[db][nb][4 * v4 + 2] * inv, o[db][nb][4 * v4 + 3] * inv);
           *(float4*)(tile + (nb * 32 + n) * PL_OUT_ROW + 32 * db + 8 * v4 + 4 * g) = w;
         }
-      if (qi < a.M && g == 0) {
+      if (qi < a.M && g == 0 && pair == 0) {
         const size_t row = (size_t)sp * a.rows + (size_t)qi * a.H + h;
-        a.lse[row] = row_ok[nb] ? (m[nb] + fast_log2(lt[nb])) * LN2 : -INFINITY;
+        a.lse[row] = row_ok[nb] ? (mm[nb] + fast_log2(den[nb])) * LN2 : -INFINITY;
       }
     }
     // which of this wavefront's 64 rows are written: one bit per row, from the lanes that own them
     const uint64_t ok0 = __builtin_amdgcn_ballot_w64(row_ok[0] && g == 0);
     const uint64_t ok1 = __builtin_amdgcn_ballot_w64(row_ok[1] && g == 0);
     const uint64_t ok = (ok0 & 0xffffffffull) | (ok1 << 32);
+    if constexpr (PAIRED) {
+      __syncthreads();
+      // pair p stores rows 32 p ... 32 p + 31 of its queries, the sums of both tiles
+      const float* other = (const float*)smem + (wave ^ 2) * (64 * PL_OUT_ROW);
+#pragma unroll 4
+      for (int i = 0; i < 16; i++) {
+        const int r = 32 * pair + 2 * i + g;
+        const float4 x = *(const float4*)(tile + r * PL_OUT_ROW + 4 * n);
+        const float4 y = *(const float4*)(other + r * PL_OUT_ROW + 4 * n);
+        if ((ok >> r) & 1) {
+          const size_t row = (size_t)sp * a.rows + (size_t)(q0 + r) * a.H + h;
+          *(float4*)(a.o + row * D_V + 4 * n) =
+              make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+        }
+      }
+      return;
+    }
     // (each wavefront reads back only what it wrote itself: no barrier)
 #pragma unroll 4
     for (int i = 0; i < 32; i++) {
@@ -1171,12 +1252,17 @@ int mfma_prefix_attention(const Plan& p, const DecodeArgs& d) {
   a.blocks_per_split = p.p_chunk / TOK_BLK;
   a.rows = p.rows;
   a.c = d.sm_scale * LOG2E;
-  static LdsOptIn lds_pl, lds_qs, lds_ts;
+  static LdsOptIn lds_pl, lds_pp, lds_qs, lds_ts;
   if (a.M > PIPELINED_MIN_M && !(debug_flags() & 0x400)) {
-    if (lds_pl.ensure((const void*)prefix_attn_pipelined_kernel, PL_LDS_BYTES) != hipSuccess)
+    if (lds_pl.ensure((const void*)prefix_attn_pipelined_kernel<false>, PL_LDS_BYTES) != hipSuccess)
       return TMLA_ERR_HIP;
     dim3 grid(p.H, (a.M + PL_QUERIES - 1) / PL_QUERIES, p.np_split);
-    hipLaunchKernelGGL(prefix_attn_pipelined_kernel, grid, dim3(256), PL_LDS_BYTES, d.stream, a);
+    hipLaunchKernelGGL(prefix_attn_pipelined_kernel<false>, grid, dim3(256), PL_LDS_BYTES, d.stream, a);
+  } else if (prefix_paired(a.H, a.M, a.Ls)) {
+    if (lds_pp.ensure((const void*)prefix_attn_pipelined_kernel<true>, PL_LDS_BYTES) != hipSuccess)
+      return TMLA_ERR_HIP;
+    hipLaunchKernelGGL(prefix_attn_pipelined_kernel<true>, dim3(p.H, 1, p.np_split), dim3(256),
+                       PL_LDS_BYTES, d.stream, a);
   } else if (a.M > PIPELINED_MIN_M) {
     if (lds_qs.ensure((const void*)prefix_attn_query_split_kernel<1>, QS_LDS_BYTES) != hipSuccess)
       return TMLA_ERR_HIP;

@@ -166,6 +166,28 @@ def test_prefix_scores_far_from_the_first_block(gain, first, gpu_device, tune):
                      peaked=True)
 
 
+@pytest.mark.parametrize("batch", [65, 96, 128])
+@pytest.mark.parametrize("prefix_len,splits,gain",
+                         [(1, 1, 1.0), (32, 1, 1.0), (33, 1, 1.0), (64, 1, 1.0), (95, 1, 1.0),
+                          (96, 1, 1.0), (288, 1, 1.0), (600, 1, 1.0), (1100, 2, 1.0),
+                          (1000, 0, 1.0), (1100, 1, 256.0)])
+def test_prefix_kernel_with_wavefront_pairs(prefix_len, splits, gain, batch, gpu_device, tune):
+    """65 to 128 queries per head: the two pairs of wavefronts take half of a split's blocks each.
+    One block (one pair sees nothing), odd and even numbers of blocks with and without a partial
+    last one, shorter and longer than the ring, several splits, and (gain) denominators that
+    overflow in one pair alone, which makes the whole workgroup walk again."""
+    tune(T.TUNE_PREFIX_SPLITS, splits)
+    spec = W.small_spec(name="pairs", dtype="bf16", batch=batch, heads=16, q_len=1,
+                        prefix_len=prefix_len, suffix_min=0, suffix_max=30, seed=500 + prefix_len)
+    wl = W.make_workload(spec)
+    wl.prefix_krope[700:] *= gain
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64())
+    print(f"paired prefix, batch={batch} prefix_len={prefix_len} splits={splits}", flush=True)
+    got, got_lse = Hh.run_library(wl, "mixed", gpu_device, flags=0x20000)   # whatever the length
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"pairs_{batch}_{prefix_len}",
+                     peaked=gain != 1.0)
+
+
 @pytest.mark.parametrize("gain", [256.0, 16.0, 1.0 / 64.0])
 def test_suffix_scores_far_from_the_first_step(gain, gpu_device, tune):
     """The same for the absorb pass over the suffix with more than 32 query rows per request: the
