@@ -223,20 +223,28 @@ __device__ inline void finalize_tail_prefetched(const FinalizeArgs& a, size_t ro
 // they get ids 8 apart and consecutive in that stride, so they run at the same time on one XCD
 // (hardware deals consecutive ids round-robin over the 8 XCDs) and the weights come from HBM
 // once.
-__device__ inline bool finalize_item(const FinalizeArgs& a, int& h, int& qb) {
-  const int nqb = (a.M + 31) / 32;
+template <bool SPLIT>
+__device__ inline bool finalize_item(const FinalizeArgs& a, int& h, int& qb, int& vb) {
+  const int nqb = (a.M + 31) / 32 * (SPLIT ? 4 : 1);
   const int id = blockIdx.x, x = id & 7, sl = id >> 3;
   qb = sl % nqb;
   h = (sl / nqb) * 8 + x;
+  if constexpr (SPLIT) {
+    vb = qb & 3;
+    qb >>= 2;
+  }
   return h < a.H;
 }
 
+constexpr int TAIL_UNROLL = 4;
 // Steps shared by both finalize kernels: merge O_A (LSE l_a, this wavefront's 32 value columns
 // in oa) with the naive partials, normalise, store.
 __device__ inline void finalize_tail(const FinalizeArgs& a, size_t row, int wave, int g, float l_a,
                                      float (&oa)[16]) {
   // merge O_A (LSE l_a) with the naive partials; this wavefront owns value block `wave`
+  // (unrolled, and without a branch around the loads, so that several are in flight)
   float m2 = l_a;
+#pragma unroll 8
   for (int i = 0; i < a.n_naive; i++) m2 = fmaxf(m2, a.naive_lse[(size_t)i * a.rows + row]);
   __bf16* dst = a.out + row * D_V + 32 * wave + 4 * g;
   if (m2 == -INFINITY) {
@@ -252,17 +260,18 @@ __device__ inline void finalize_tail(const FinalizeArgs& a, size_t row, int wave
   float z2 = w_a;
 #pragma unroll
   for (int v = 0; v < 16; v++) oa[v] *= w_a;
+#pragma unroll TAIL_UNROLL
   for (int i = 0; i < a.n_naive; i++) {
     const float li = a.naive_lse[(size_t)i * a.rows + row];
-    if (li == -INFINITY) continue;
-    const float w = __expf(li - m2);
+    const bool use = li > -INFINITY;   // (else the partial was never written)
+    const float w = use ? __expf(li - m2) : 0.f;
     z2 += w;
     const float* src = a.naive_o + ((size_t)i * a.rows + row) * D_V + 32 * wave + 4 * g;
 #pragma unroll
     for (int v4 = 0; v4 < 4; v4++) {
-      const float4 x = *(const float4*)(src + 8 * v4);
-      oa[4 * v4] += w * x.x; oa[4 * v4 + 1] += w * x.y;
-      oa[4 * v4 + 2] += w * x.z; oa[4 * v4 + 3] += w * x.w;
+      const f32x4 x = *(const f32x4*)(src + 8 * v4);
+#pragma unroll
+      for (int e = 0; e < 4; e++) oa[4 * v4 + e] += use ? w * x[e] : 0.f;
     }
   }
   const float inv2 = 1.f / z2;
@@ -279,8 +288,8 @@ __device__ inline void finalize_tail(const FinalizeArgs& a, size_t row, int wave
 __global__ void __launch_bounds__(256) finalize_kernel(FinalizeArgs a) {
   __shared__ float wtab[FIN_MAX_LAT][32];    // normalised merge weight of each latent partial
   __shared__ float red[4][4][16][64];        // [wavefront][value block][acc register][lane]
-  int h, qb;
-  if (!finalize_item(a, h, qb)) return;
+  int h, qb, vb;
+  if (!finalize_item<false>(a, h, qb, vb)) return;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int qi = qb * 32 + n;
   const bool valid = qi < a.M;
@@ -350,11 +359,14 @@ __global__ void __launch_bounds__(256) finalize_kernel(FinalizeArgs a) {
 // one memory round trip instead of one per k-step; the merge weights live in registers.
 // NN > 0: the number of naive partials is NN and they are loaded up front with everything else
 // (0: any number, loaded in the epilogue).
-template <int NL, int NN>
+// SPLIT: a workgroup takes one of the four value blocks -- small batches, where a workgroup per head
+// and query block leaves compute units idle while each of the others fetches 128 KiB of weights.
+template <int NL, int NN, bool SPLIT>
 __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
-  __shared__ float red[4][4][16][64];        // [wavefront][value block][acc register][lane]
-  int h, qb;
-  if (!finalize_item(a, h, qb)) return;
+  constexpr int MB = SPLIT ? 1 : 4;          // value blocks of 32 columns of this workgroup
+  __shared__ float red[4][MB][16][64];       // [wavefront][value block][acc register][lane]
+  int h, qb, vb = 0;
+  if (!finalize_item<SPLIT>(a, h, qb, vb)) return;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int qi = qb * 32 + n;
   const bool valid = qi < a.M;
@@ -363,13 +375,13 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
   float ll[NL];
 #pragma unroll
   for (int i = 0; i < NL; i++) ll[i] = a.lat_lse[(size_t)i * a.rows + row];
-  const __bf16* wp = a.w_uv + ((size_t)h * D_V + n) * D_L + 8 * g + 128 * wave;
+  const __bf16* wp = a.w_uv + ((size_t)h * D_V + 32 * vb + n) * D_L + 8 * g + 128 * wave;
   const __bf16* lp = a.lat_o + row * D_L + 8 * g + 128 * wave;
-  bf16x8 wf[8][4];
+  bf16x8 wf[8][MB];
 #pragma unroll
   for (int ks = 0; ks < 8; ks++)
 #pragma unroll
-    for (int mb = 0; mb < 4; mb++)
+    for (int mb = 0; mb < MB; mb++)
       wf[ks][mb] = *(const bf16x8*)(wp + (size_t)(32 * mb) * D_L + 16 * ks);
   bf16x8 x[NL][8];
 #pragma unroll
@@ -378,8 +390,10 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
     for (int ks = 0; ks < 8; ks++)
       x[i][ks] = *(const bf16x8*)(lp + (size_t)i * a.rows * D_L + 16 * ks);
   NaivePrefetch<(NN > 0 ? NN : 1)> pre;
+  // the value block that this wavefront finishes (SPLIT: wavefront 0 the workgroup's only one)
+  const int own = SPLIT ? vb : wave;
   if constexpr (NN > 0) {
-    prefetch_naive(a, row, wave, g, pre);
+    prefetch_naive(a, row, own, g, pre);
 #pragma unroll
     for (int i = 0; i < NN; i++)
       asm volatile("" : "+v"(pre.lse[i]), "+v"(pre.o[i][0]), "+v"(pre.o[i][1]), "+v"(pre.o[i][2]),
@@ -390,7 +404,8 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
   // uses to save registers, and each k-step waits for its own round trip
 #pragma unroll
   for (int ks = 0; ks < 8; ks++) {
-    asm volatile("" : "+v"(wf[ks][0]), "+v"(wf[ks][1]), "+v"(wf[ks][2]), "+v"(wf[ks][3]));
+#pragma unroll
+    for (int mb = 0; mb < MB; mb++) asm volatile("" : "+v"(wf[ks][mb]));
 #pragma unroll
     for (int i = 0; i < NL; i++) asm volatile("" : "+v"(x[i][ks]));
   }
@@ -411,9 +426,9 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
 #pragma unroll
   for (int i = 0; i < NL; i++) w[i] *= inv;
 
-  f32x16 acc[4];
+  f32x16 acc[MB];
 #pragma unroll
-  for (int mb = 0; mb < 4; mb++)
+  for (int mb = 0; mb < MB; mb++)
 #pragma unroll
     for (int v = 0; v < 16; v++) acc[mb][v] = 0.f;
 #pragma unroll
@@ -435,21 +450,22 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
       for (int e = 0; e < 8; e++) bfrag[e] = (__bf16)m8[e];
     }
 #pragma unroll
-    for (int mb = 0; mb < 4; mb++) acc[mb] = mfma32(wf[ks][mb], bfrag, acc[mb]);
+    for (int mb = 0; mb < MB; mb++) acc[mb] = mfma32(wf[ks][mb], bfrag, acc[mb]);
   }
 #pragma unroll
-  for (int mb = 0; mb < 4; mb++)
+  for (int mb = 0; mb < MB; mb++)
 #pragma unroll
     for (int v = 0; v < 16; v++) red[wave][mb][v][lane] = acc[mb][v];
   __syncthreads();
+  if (SPLIT && wave > 0) return;
+  const int rb = SPLIT ? 0 : wave;
   float oa[16];
 #pragma unroll
   for (int v = 0; v < 16; v++)
-    oa[v] = red[0][wave][v][lane] + red[1][wave][v][lane] + red[2][wave][v][lane] +
-            red[3][wave][v][lane];
+    oa[v] = red[0][rb][v][lane] + red[1][rb][v][lane] + red[2][rb][v][lane] + red[3][rb][v][lane];
   if (!valid) return;
-  if constexpr (NN > 0) finalize_tail_prefetched(a, row, wave, g, l_a, oa, pre);
-  else finalize_tail(a, row, wave, g, l_a, oa);
+  if constexpr (NN > 0) finalize_tail_prefetched(a, row, own, g, l_a, oa, pre);
+  else finalize_tail(a, row, own, g, l_a, oa);
 }
 
 // One latent partial (the suffix is in one chunk -- every large batch) and many queries per head:
@@ -617,15 +633,15 @@ static int launch_finalize_stream(const FinalizeArgs& a, int heads8, int nqb, in
   return TMLA_OK;
 }
 
-template <int NL>
+template <int NL, bool SPLIT>
 static void launch_finalize_few(const FinalizeArgs& a, dim3 grid, hipStream_t stream) {
   // The prefetch costs 34 registers, which halves the wavefronts per SIMD: it pays only where a
   // compute unit gets so few workgroups that latency, not occupancy, sets the time.
-  const bool few_wgs = grid.x <= 2 * NUM_CU;
+  const bool few_wgs = SPLIT || grid.x <= 2 * NUM_CU;
   switch (few_wgs ? a.n_naive : 0) {
-    case 1: hipLaunchKernelGGL((finalize_few_kernel<NL, 1>), grid, dim3(256), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((finalize_few_kernel<NL, 2>), grid, dim3(256), 0, stream, a); break;
-    default: hipLaunchKernelGGL((finalize_few_kernel<NL, 0>), grid, dim3(256), 0, stream, a);
+    case 1: hipLaunchKernelGGL((finalize_few_kernel<NL, 1, SPLIT>), grid, dim3(256), 0, stream, a); break;
+    case 2: hipLaunchKernelGGL((finalize_few_kernel<NL, 2, SPLIT>), grid, dim3(256), 0, stream, a); break;
+    default: hipLaunchKernelGGL((finalize_few_kernel<NL, 0, SPLIT>), grid, dim3(256), 0, stream, a);
   }
 }
 
@@ -638,16 +654,26 @@ static void launch_finalize_few(const FinalizeArgs& a, dim3 grid, hipStream_t st
 // a wavefront reads a partial row as one contiguous KiB (lane = 16-byte chunk) eight at a time,
 // the four sums meet in LDS.  Lane i holds the LSEs and the weights of partials i and i + 64 (at
 // most MERGE_MAX_LAT = 128 partials).  A partial with LSE = -inf was never written and is skipped.
+template <int N>
 __global__ void __launch_bounds__(256) merge_latent_kernel(__bf16* lat_o, float* lat_lse,
                                                            int n_lat, int64_t rows) {
   __shared__ float part[4][64][8];
   const int64_t row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const __bf16* src = lat_o + (size_t)row * D_L + lane * 8;
+  // everything that this wavefront may need is requested at once, before its weights are known
+  // (N loads: 4 N partials at most), so the pass pays one memory round trip
+  bf16x8 x[N];
+#pragma unroll
+  for (int j = 0; j < N; j++)
+    if (wave + 4 * j < n_lat) x[j] = *(const bf16x8*)(src + (size_t)(wave + 4 * j) * rows * D_L);
   float li[2], e[2], wgt[2];
 #pragma unroll
   for (int k = 0; k < 2; k++)
     li[k] = lane + 64 * k < n_lat ? lat_lse[(size_t)(lane + 64 * k) * rows + row] : -INFINITY;
+#pragma unroll
+  for (int j = 0; j < N; j++) asm volatile("" : "+v"(x[j]));
   float mx = fmaxf(li[0], li[1]);
 #pragma unroll
   for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s));
@@ -659,22 +685,14 @@ __global__ void __launch_bounds__(256) merge_latent_kernel(__bf16* lat_o, float*
 #pragma unroll
   for (int k = 0; k < 2; k++) wgt[k] = z > 0.f ? e[k] / z : 0.f;   // normalised weights
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const __bf16* src = lat_o + (size_t)row * D_L + lane * 8;
-  for (int i0 = wave; i0 < n_lat; i0 += 32) {
-    bf16x8 x[8];
-    float w[8];
 #pragma unroll
-    for (int j = 0; j < 8; j++) {
-      const int i = i0 + 4 * j;
-      w[j] = i < n_lat ? __shfl(i < 64 ? wgt[0] : wgt[1], i & 63) : 0.f;   // wave-uniform
-      if (w[j] > 0.f) x[j] = *(const bf16x8*)(src + (size_t)i * rows * D_L);
+  for (int j = 0; j < N; j++) {
+    const int i = wave + 4 * j;
+    const float w = i < n_lat ? __shfl(i < 64 ? wgt[0] : wgt[1], i & 63) : 0.f;   // wave-uniform
+    if (w > 0.f) {
+#pragma unroll
+      for (int k = 0; k < 8; k++) acc[k] += w * (float)x[j][k];
     }
-#pragma unroll
-    for (int j = 0; j < 8; j++)
-      if (w[j] > 0.f) {
-#pragma unroll
-        for (int k = 0; k < 8; k++) acc[k] += w[j] * (float)x[j][k];
-      }
   }
 #pragma unroll
   for (int k = 0; k < 8; k++) part[wave][lane][k] = acc[k];
@@ -703,7 +721,9 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
   a.lse_out = d.lse_out;
   a.M = p.B * p.Sq; a.H = p.H; a.n_naive = p.n_naive; a.n_lat = p.n_lat; a.rows = p.rows;
   if (a.n_lat > 4 && !merge_inside) {
-    hipLaunchKernelGGL(merge_latent_kernel, dim3((unsigned)p.rows), dim3(256), 0, d.stream,
+    auto merge = a.n_lat <= 16 ? merge_latent_kernel<4> : a.n_lat <= 32 ? merge_latent_kernel<8>
+                 : a.n_lat <= 64 ? merge_latent_kernel<16> : merge_latent_kernel<32>;
+    hipLaunchKernelGGL(merge, dim3((unsigned)p.rows), dim3(256), 0, d.stream,
                        (__bf16*)(d.ws + p.off_lat_o), (float*)(d.ws + p.off_lat_lse), a.n_lat,
                        (int64_t)p.rows);
     a.n_lat = 1;
@@ -720,11 +740,20 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
                             : launch_finalize_stream<2>(a, heads8, nqb, qbk, d.stream);
   }
   dim3 grid(8 * ((a.M + 31) / 32) * ((p.H + 7) / 8));
+  // up to half a workgroup per compute unit the value blocks are dealt out (one request x 128
+  // heads 40.1 -> 37.2 us a step, 8 x 16 heads 31.3 -> 27.8); from 256 workgroups on that costs 7 us,
+  // since every workgroup reads all latent partials
+  const bool split = grid.x <= NUM_CU / 2;
+  if (split && a.n_lat >= 1 && a.n_lat <= 4) grid.x *= 4;
   switch (a.n_lat) {
-    case 1: launch_finalize_few<1>(a, grid, d.stream); break;
-    case 2: launch_finalize_few<2>(a, grid, d.stream); break;
-    case 3: launch_finalize_few<3>(a, grid, d.stream); break;
-    case 4: launch_finalize_few<4>(a, grid, d.stream); break;
+#define TMLA_FEW(NL) \
+  if (split) launch_finalize_few<NL, true>(a, grid, d.stream); \
+  else launch_finalize_few<NL, false>(a, grid, d.stream)
+    case 1: TMLA_FEW(1); break;
+    case 2: TMLA_FEW(2); break;
+    case 3: TMLA_FEW(3); break;
+    case 4: TMLA_FEW(4); break;
+#undef TMLA_FEW
     default: hipLaunchKernelGGL(finalize_kernel, grid, dim3(256), 0, d.stream, a);
   }
   return TMLA_OK;

@@ -124,6 +124,26 @@ def test_many_latent_partials_small_batch(mode, flags, gpu_device):
         Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"many_partials/{mode}/definition")
 
 
+@pytest.mark.parametrize("batch", [1, 33])
+@pytest.mark.parametrize("chunks", [4, 5, 16, 17, 32, 33, 64, 70])
+def test_latent_partials_of_every_merge_size(chunks, batch, gpu_device, tune):
+    """4 to 70 latent partials per row (64-token chunks, forced): the merge inside the projection
+    kernel and every size of the merge pass, with an empty suffix chunk among them for some
+    requests; one query block per head and two."""
+    tune(T.TUNE_ABSORB_PREFIX_CHUNK, 64)
+    tune(T.TUNE_SUFFIX_CHUNK, 64)
+    n_suffix = max(1, chunks - 64)
+    spec = W.small_spec(name="merge", dtype="bf16", batch=batch, heads=16, q_len=1,
+                        prefix_len=64 * (chunks - n_suffix) - 5, suffix_min=0,
+                        suffix_max=64 * n_suffix, seed=700 + chunks)
+    wl = W.make_workload(spec)
+    pairs = [(b, h) for b in range(0, batch, 8) for h in (0, 7, 15)]
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64(), pairs=pairs)
+    print(f"merge of {chunks} latent partials, batch={batch}", flush=True)
+    got, got_lse = Hh.run_library(wl, "absorb_only", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"merge_{chunks}_{batch}")
+
+
 @pytest.mark.parametrize("flags", [0, 0x400], ids=["pipelined", "8-wave"])
 @pytest.mark.parametrize("prefix_len", [31, 32, 40, 288, 1024, 1100])
 def test_pipelined_prefix_kernel_long_runs(prefix_len, flags, gpu_device, tune):
