@@ -1,6 +1,7 @@
-// Scalar (non matrix-core) HIP kernels for every step of the decode path.  They are the fp32
-// implementation and a second, independent GPU implementation of the bf16 path used to bring up
-// and cross-check the matrix-core kernels.  fp32 accumulation everywhere.
+// Vector-ALU (non matrix-core) HIP kernels for every step of the decode path, fp32 accumulation
+// everywhere: the fp32 implementation (fp32_* kernels, and simple_expand), and a second,
+// independent GPU implementation of the bf16 path (simple_* kernels) used to bring up and
+// cross-check the matrix-core kernels.
 //
 // Steps (paper Algorithm 1): prefix expansion (Section 3.1 "Prefill"), naive attention over
 // expanded K/V (step 4), query absorption q_nope W_UK (step 5), absorb attention over latent
@@ -302,6 +303,286 @@ simple_finalize_kernel(Plan p, const float* __restrict__ naive_o,
   if (lse_out && tid == 0) lse_out[row] = m + logf(z);
 }
 
+// ---------------------------------------------------------------- fp32 decode path
+// One workgroup of 256 threads per output row and chunk, as above, but with every global access a
+// 16-byte piece of a row that neighbouring lanes continue, and many of them in flight: a thread per
+// token (or per value column of W_UV) walking its own row one element at a time spends the time on
+// the latency of scattered 4-byte loads.  4 requests x 16 heads over 256 + 64 tokens: absorb pass
+// 42.6 -> 8.0 us, combine 10.2 -> 7.0 us, naive pass 9.4 -> 6.8 us, absorption 5.7 -> 4.2 us.
+constexpr int FP = 256;         // threads
+constexpr int FP_TILE = 64;     // tokens per tile: 16 per wavefront, four at a time
+
+// sum over the 16 lanes that share a row
+__device__ inline float sum16(float v) {
+#pragma unroll
+  for (int s = 8; s >= 1; s >>= 1) v += __shfl_xor(v, s);
+  return v;
+}
+
+// Softmax attention of one query vector (q_lds, DK1 + 64 elements) over tokens [t0, t1): key of
+// token t = DK1 elements at k1(t) and 64 at k2(t), value = DV elements at vv(t).
+template <int DK1, int DV, typename K1, typename K2, typename VV>
+__device__ void fp32_attend(const float* q_lds, int t0, int t1, float scale, K1 k1, K2 k2, VV vv,
+                            float* o_out, float* lse_out) {
+  constexpr int NK = DK1 / 64, COLS = DV / 4, NG = FP / COLS;
+  __shared__ float s_lds[FP_TILE];
+  __shared__ float4 part[FP];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, tq = lane >> 4;
+  if (t1 <= t0) {
+    if (tid == 0) *lse_out = -INFINITY;
+    return;
+  }
+  float4 q[NK + 1];
+#pragma unroll
+  for (int k = 0; k <= NK; k++) q[k] = *(const float4*)(q_lds + 64 * k + 4 * l16);
+  auto dot4 = [](const float4& a, const float4& b) {
+    return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
+  };
+  const int col = tid % COLS, grp = tid / COLS;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  float m_run = -INFINITY, l_run = 0.f;
+  for (int base = t0; base < t1; base += FP_TILE) {
+    const int n = min(FP_TILE, t1 - base);
+    // scores: tokens 16 wave + 4 i + tq of the tile (past the end: the last token again, unused)
+    float4 x[4][NK + 1];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int t = base + min(16 * wave + 4 * i + tq, n - 1);
+      const float* a = k1(t);
+#pragma unroll
+      for (int k = 0; k < NK; k++) x[i][k] = *(const float4*)(a + 64 * k + 4 * l16);
+      x[i][NK] = *(const float4*)(k2(t) + 4 * l16);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      float d = 0.f;
+#pragma unroll
+      for (int k = 0; k <= NK; k++) d += dot4(q[k], x[i][k]);
+      d = sum16(d);
+      if (l16 == 0) s_lds[16 * wave + 4 * i + tq] = d * scale;
+    }
+    __syncthreads();
+    // every wavefront: lane = token
+    const float s = lane < n ? s_lds[lane] : -INFINITY;
+    float mx = s;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    const float m_new = fmaxf(m_run, mx);
+    const float p = lane < n ? expf(s - m_new) : 0.f;
+    const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - m_new);
+    float sum = p;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+    l_run = l_run * alpha + sum;
+    m_run = m_new;
+    acc.x *= alpha; acc.y *= alpha; acc.z *= alpha; acc.w *= alpha;
+    // values: thread = (column quarter, tokens grp, grp + NG, ...)
+#pragma unroll 8
+    for (int j = 0; j < FP_TILE / NG; j++) {
+      const int jj = grp + NG * j;
+      const float w = __shfl(p, jj);            // 0 past the end
+      const float4 v = *(const float4*)(vv(base + min(jj, n - 1)) + 4 * col);
+      acc.x += w * v.x; acc.y += w * v.y; acc.z += w * v.z; acc.w += w * v.w;
+    }
+    __syncthreads();   // the scores are read before the next tile's are written
+  }
+  part[tid] = acc;
+  __syncthreads();
+  if (tid < COLS) {
+    float4 o = part[tid];
+#pragma unroll
+    for (int i = 1; i < NG; i++) {
+      const float4 x = part[tid + i * COLS];
+      o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
+    }
+    const float inv = 1.f / l_run;
+    *(float4*)(o_out + 4 * tid) = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+    if (tid == 0) *lse_out = m_run + logf(l_run);
+  }
+}
+
+// grid (rows, chunks), chunks as in simple_naive_kernel
+__global__ void __launch_bounds__(FP)
+fp32_naive_kernel(Plan p, const float* __restrict__ q, const float* __restrict__ pk,
+                  const float* __restrict__ pv, const float* __restrict__ sk,
+                  const float* __restrict__ sv, const int32_t* __restrict__ block_table,
+                  const int32_t* __restrict__ lens, int max_blocks, int bs_shift,
+                  int64_t pool_tokens, float scale, float* __restrict__ naive_o,
+                  float* __restrict__ naive_lse, int first_chunk) {
+  __shared__ __align__(16) float q_lds[D_QK];
+  const int64_t row = blockIdx.x;
+  const int chunk = first_chunk + blockIdx.y;
+  const int h = (int)(row % p.H);
+  const int s = (int)((row / p.H) % p.Sq);
+  const int b = (int)(row / ((int64_t)p.H * p.Sq));
+  for (int i = threadIdx.x; i < D_QK; i += FP) q_lds[i] = q[row * D_QK + i];
+  __syncthreads();
+  float* o_out = naive_o + ((size_t)chunk * p.rows + row) * D_V;
+  float* l_out = naive_lse + (size_t)chunk * p.rows + row;
+  if (chunk < p.np_split) {
+    const int t0 = chunk * p.p_chunk, t1 = min(p.Ls, t0 + p.p_chunk);
+    const float* kh = pk + (size_t)h * p.Ls * D_QK;
+    const float* vh = pv + (size_t)h * p.Ls * D_V;
+    fp32_attend<D_N, D_V>(
+        q_lds, t0, t1, scale, [=](int t) { return kh + (size_t)t * D_QK; },
+        [=](int t) { return kh + (size_t)t * D_QK + D_N; },
+        [=](int t) { return vh + (size_t)t * D_V; }, o_out, l_out);
+  } else {
+    const int c = chunk - p.np_split;
+    const int vis = visible_suffix(lens[b], p.Sq, s);
+    const int t0 = min(vis, c * p.ns_chunk), t1 = min(vis, t0 + p.ns_chunk);
+    const int32_t* bt = block_table + (size_t)b * max_blocks;
+    const float* kh = sk + (size_t)h * pool_tokens * D_QK;
+    const float* vh = sv + (size_t)h * pool_tokens * D_V;
+    auto phys = [=](int j) {
+      return ((size_t)bt[j >> bs_shift] << bs_shift) + (j & ((1 << bs_shift) - 1));
+    };
+    fp32_attend<D_N, D_V>(
+        q_lds, t0, t1, scale, [=](int j) { return kh + phys(j) * D_QK; },
+        [=](int j) { return kh + phys(j) * D_QK + D_N; },
+        [=](int j) { return vh + phys(j) * D_V; }, o_out, l_out);
+  }
+}
+
+// grid (rows, n_lat), items as in simple_absorb_kernel
+__global__ void __launch_bounds__(FP)
+fp32_absorb_kernel(Plan p, const float* __restrict__ qabs, const float* __restrict__ pc,
+                   const float* __restrict__ pr, const float* __restrict__ pool,
+                   const int32_t* __restrict__ block_table, const int32_t* __restrict__ lens,
+                   int max_blocks, int bs_shift, float scale, float* __restrict__ lat_o,
+                   float* __restrict__ lat_lse) {
+  __shared__ __align__(16) float q_lds[D_ROW];
+  const int64_t row = blockIdx.x;
+  const int item = blockIdx.y;
+  const int s = (int)((row / p.H) % p.Sq);
+  const int b = (int)(row / ((int64_t)p.H * p.Sq));
+  for (int i = threadIdx.x; i < D_ROW; i += FP) q_lds[i] = qabs[row * D_ROW + i];
+  __syncthreads();
+  float* o_out = lat_o + ((size_t)item * p.rows + row) * D_L;
+  float* l_out = lat_lse + (size_t)item * p.rows + row;
+  if (item < p.ap_chunks) {
+    const int t0 = min(p.Ls, item * p.ap_chunk), t1 = min(p.Ls, t0 + p.ap_chunk);
+    auto lat = [=](int t) { return pc + (size_t)t * D_L; };
+    fp32_attend<D_L, D_L>(q_lds, t0, t1, scale, lat, [=](int t) { return pr + (size_t)t * D_R; },
+                          lat, o_out, l_out);
+  } else {
+    const int c = item - p.ap_chunks;
+    const int vis = visible_suffix(lens[b], p.Sq, s);
+    const int t0 = min(vis, c * p.as_chunk), t1 = min(vis, t0 + p.as_chunk);
+    const int32_t* bt = block_table + (size_t)b * max_blocks;
+    auto lat = [=](int j) {
+      return pool + (((size_t)bt[j >> bs_shift] << bs_shift) + (j & ((1 << bs_shift) - 1))) * D_ROW;
+    };
+    fp32_attend<D_L, D_L>(q_lds, t0, t1, scale, lat, [=](int j) { return lat(j) + D_L; }, lat,
+                          o_out, l_out);
+  }
+}
+
+// q_abs = q_nope W_UK: thread = (four latent columns, half of the 128 noPE dims)
+__global__ void __launch_bounds__(FP)
+fp32_qabs_kernel(int H, const float* __restrict__ q, const float* __restrict__ w_uk,
+                 float* __restrict__ qabs) {
+  __shared__ float qn[D_N];
+  __shared__ float4 part[D_L / 4];
+  const int64_t row = blockIdx.x;
+  const int h = (int)(row % H);
+  const int tid = threadIdx.x, c = tid & 127, half = tid >> 7;
+  if (tid < D_N) qn[tid] = q[row * D_QK + tid];
+  __syncthreads();
+  const float* w = w_uk + ((size_t)h * D_N + 64 * half) * D_L + 4 * c;
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 16
+  for (int i = 0; i < 64; i++) {
+    const float4 x = *(const float4*)(w + (size_t)i * D_L);
+    const float y = qn[64 * half + i];
+    a.x += y * x.x; a.y += y * x.y; a.z += y * x.z; a.w += y * x.w;
+  }
+  if (half) part[c] = a;
+  __syncthreads();
+  if (!half) {
+    const float4 b = part[c];
+    *(float4*)(qabs + row * D_ROW + 4 * c) = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+    if (c < D_R / 4)
+      *(float4*)(qabs + row * D_ROW + D_L + 4 * c) = *(const float4*)(q + row * D_QK + D_N + 4 * c);
+  }
+}
+
+// steps 7 + 8 as in simple_finalize_kernel; 16 lanes share a row of W_UV[h]
+__global__ void __launch_bounds__(FP)
+fp32_finalize_kernel(Plan p, const float* __restrict__ naive_o, const float* __restrict__ naive_lse,
+                     const float* __restrict__ lat_o, const float* __restrict__ lat_lse,
+                     const float* __restrict__ w_uv, float* __restrict__ out,
+                     float* __restrict__ lse_out) {
+  __shared__ __align__(16) float lat[D_L];
+  __shared__ float oa[D_V];
+  const int64_t row = blockIdx.x;
+  const int h = (int)(row % p.H);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, tq = lane >> 4;
+  float l_a = -INFINITY;
+  if (p.n_lat > 0) {
+    float m = -INFINITY;
+#pragma unroll 8
+    for (int i = 0; i < p.n_lat; i++) m = fmaxf(m, lat_lse[(size_t)i * p.rows + row]);
+    if (m > -INFINITY) {
+      float z = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll 4
+      for (int i = 0; i < p.n_lat; i++) {
+        const float li = lat_lse[(size_t)i * p.rows + row];
+        const bool use = li > -INFINITY;   // (else the partial was never written)
+        const float w = use ? expf(li - m) : 0.f;
+        z += w;
+        const float2 x = *(const float2*)(lat_o + ((size_t)i * p.rows + row) * D_L + 2 * tid);
+        a0 += use ? w * x.x : 0.f;
+        a1 += use ? w * x.y : 0.f;
+      }
+      const float inv = 1.f / z;
+      lat[2 * tid] = a0 * inv;
+      lat[2 * tid + 1] = a1 * inv;
+      l_a = m + logf(z);
+      __syncthreads();
+      float4 y[8];
+#pragma unroll
+      for (int k = 0; k < 8; k++) y[k] = *(const float4*)(lat + 64 * k + 4 * l16);
+#pragma unroll 4
+      for (int it = 0; it < 8; it++) {   // rows 16 it + 4 wave + tq
+        const int d = 16 * it + 4 * wave + tq;
+        const float* w = w_uv + ((size_t)h * D_V + d) * D_L + 4 * l16;
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+          const float4 x = *(const float4*)(w + 64 * k);
+          s += x.x * y[k].x + x.y * y[k].y + x.z * y[k].z + x.w * y[k].w;
+        }
+        s = sum16(s);
+        if (l16 == 0) oa[d] = s;
+      }
+      __syncthreads();
+    }
+  }
+  if (tid >= D_V) return;
+  float m = l_a;
+#pragma unroll 8
+  for (int i = 0; i < p.n_naive; i++) m = fmaxf(m, naive_lse[(size_t)i * p.rows + row]);
+  if (m == -INFINITY) {
+    out[row * D_V + tid] = 0.f;
+    if (lse_out && tid == 0) lse_out[row] = -INFINITY;
+    return;
+  }
+  float z = 0.f, num = 0.f;
+  if (l_a > -INFINITY) { const float w = expf(l_a - m); z += w; num += w * oa[tid]; }
+#pragma unroll 4
+  for (int i = 0; i < p.n_naive; i++) {
+    const float li = naive_lse[(size_t)i * p.rows + row];
+    const bool use = li > -INFINITY;
+    const float w = use ? expf(li - m) : 0.f;
+    z += w;
+    const float x = naive_o[((size_t)i * p.rows + row) * D_V + tid];
+    num += use ? w * x : 0.f;
+  }
+  out[row * D_V + tid] = num / z;
+  if (lse_out && tid == 0) lse_out[row] = m + logf(z);
+}
+
 __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -319,22 +600,42 @@ void simple_stage_naive(const Plan& p, const DecodeArgs& a, int first_chunk, int
   if (grid_rows < 0) grid_rows = p.rows;
   if (grid_rows == 0 || n_chunks <= 0) return;
   const int64_t pool_tokens = (int64_t)a.num_blocks * a.block_size;
-  hipLaunchKernelGGL(simple_naive_kernel<T>, dim3((unsigned)grid_rows, n_chunks), dim3(NT), 0,
+  if constexpr (sizeof(T) == 4) {
+    hipLaunchKernelGGL(fp32_naive_kernel, dim3((unsigned)grid_rows, n_chunks), dim3(FP), 0, a.stream,
+                       p, (const float*)a.q, (const float*)a.prefix_k, (const float*)a.prefix_v,
+                       (const float*)a.suffix_k_pool, (const float*)a.suffix_v_pool, a.block_table,
+                       a.suffix_lens, a.max_blocks, __builtin_ctz((unsigned)a.block_size),
+                       pool_tokens, a.sm_scale, (float*)(a.ws + p.off_naive_o),
+                       (float*)(a.ws + p.off_naive_lse), first_chunk);
+  } else {
+    hipLaunchKernelGGL(simple_naive_kernel<T>, dim3((unsigned)grid_rows, n_chunks), dim3(NT), 0,
                      a.stream, p, (const T*)a.q, (const T*)a.prefix_k, (const T*)a.prefix_v,
                      (const T*)a.suffix_k_pool, (const T*)a.suffix_v_pool, a.block_table,
                      a.suffix_lens, a.max_blocks, a.block_size, pool_tokens, a.sm_scale,
                      (float*)(a.ws + p.off_naive_o), (float*)(a.ws + p.off_naive_lse), first_chunk);
+  }
 }
 template <typename T>
 void simple_stage_qabs(const Plan& p, const DecodeArgs& a) {
   if (p.rows == 0 || p.n_lat <= 0) return;
-  hipLaunchKernelGGL(simple_qabs_kernel<T>, dim3((unsigned)p.rows), dim3(256), 0, a.stream, p.H,
+  if constexpr (sizeof(T) == 4)
+    hipLaunchKernelGGL(fp32_qabs_kernel, dim3((unsigned)p.rows), dim3(FP), 0, a.stream, p.H,
+                       (const float*)a.q, (const float*)a.w_uk, (float*)(a.ws + p.off_qabs));
+  else
+    hipLaunchKernelGGL(simple_qabs_kernel<T>, dim3((unsigned)p.rows), dim3(256), 0, a.stream, p.H,
                      (const T*)a.q, (const T*)a.w_uk, (T*)(a.ws + p.off_qabs));
 }
 template <typename T>
 void simple_stage_absorb(const Plan& p, const DecodeArgs& a) {
   if (p.rows == 0 || p.n_lat <= 0) return;
-  hipLaunchKernelGGL(simple_absorb_kernel<T>, dim3((unsigned)p.rows, p.n_lat), dim3(NT), 0,
+  if constexpr (sizeof(T) == 4)
+    hipLaunchKernelGGL(fp32_absorb_kernel, dim3((unsigned)p.rows, p.n_lat), dim3(FP), 0, a.stream, p,
+                       (const float*)(a.ws + p.off_qabs), (const float*)a.prefix_ckv,
+                       (const float*)a.prefix_krope, (const float*)a.suffix_pool, a.block_table,
+                       a.suffix_lens, a.max_blocks, __builtin_ctz((unsigned)a.block_size), a.sm_scale,
+                       (float*)(a.ws + p.off_lat_o), (float*)(a.ws + p.off_lat_lse));
+  else
+    hipLaunchKernelGGL(simple_absorb_kernel<T>, dim3((unsigned)p.rows, p.n_lat), dim3(NT), 0,
                      a.stream, p, (const T*)(a.ws + p.off_qabs), (const T*)a.prefix_ckv,
                      (const T*)a.prefix_krope, (const T*)a.suffix_pool, a.block_table,
                      a.suffix_lens, a.max_blocks, a.block_size, a.sm_scale,
@@ -343,7 +644,13 @@ void simple_stage_absorb(const Plan& p, const DecodeArgs& a) {
 template <typename T>
 void simple_stage_finalize(const Plan& p, const DecodeArgs& a) {
   if (p.rows == 0) return;
-  hipLaunchKernelGGL(simple_finalize_kernel<T>, dim3((unsigned)p.rows), dim3(NT), 0, a.stream, p,
+  if constexpr (sizeof(T) == 4)
+    hipLaunchKernelGGL(fp32_finalize_kernel, dim3((unsigned)p.rows), dim3(FP), 0, a.stream, p,
+                       (const float*)(a.ws + p.off_naive_o), (const float*)(a.ws + p.off_naive_lse),
+                       (const float*)(a.ws + p.off_lat_o), (const float*)(a.ws + p.off_lat_lse),
+                       (const float*)a.w_uv, (float*)a.out, a.lse_out);
+  else
+    hipLaunchKernelGGL(simple_finalize_kernel<T>, dim3((unsigned)p.rows), dim3(NT), 0, a.stream, p,
                      (const float*)(a.ws + p.off_naive_o), (const float*)(a.ws + p.off_naive_lse),
                      (const T*)(a.ws + p.off_lat_o), (const float*)(a.ws + p.off_lat_lse),
                      (const T*)a.w_uv, (T*)a.out, a.lse_out);

@@ -144,6 +144,22 @@ def test_latent_partials_of_every_merge_size(chunks, batch, gpu_device, tune):
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"merge_{chunks}_{batch}")
 
 
+@pytest.mark.parametrize("mode", ["mixed", "naive_only", "absorb_only"])
+@pytest.mark.parametrize("prefix,suffix,q_len", [(1, 64, 1), (63, 65, 2), (64, 1, 1), (65, 129, 3),
+                                                 (200, 0, 1), (0, 130, 1)])
+def test_fp32_kernels_at_the_edges_of_their_tiles(prefix, suffix, q_len, mode, gpu_device):
+    """fp32: token counts one below, at and above the 64-token tiles, an empty part, the causal
+    edge inside a tile; 40 requests so that one chunk holds several tiles."""
+    wl = W.make_workload(W.small_spec(dtype="fp32", batch=40, heads=16, q_len=q_len,
+                                      prefix_len=prefix, suffix_min=min(q_len, suffix),
+                                      suffix_max=suffix, seed=900 + prefix))
+    pairs = [(b, h) for b in range(0, 40, 5) for h in (0, 9, 15)]
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64(), pairs=pairs)
+    print(f"fp32 tiles {mode} prefix={prefix} suffix={suffix} q_len={q_len}", flush=True)
+    got, got_lse = Hh.run_library(wl, mode, gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "fp32", f"fp32_tiles/{mode}")
+
+
 @pytest.mark.parametrize("flags", [0, 0x400], ids=["pipelined", "8-wave"])
 @pytest.mark.parametrize("prefix_len", [31, 32, 40, 288, 1024, 1100])
 def test_pipelined_prefix_kernel_long_runs(prefix_len, flags, gpu_device, tune):
