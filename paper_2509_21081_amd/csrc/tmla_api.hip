@@ -59,12 +59,13 @@ static int check_dims(const tmla_dims* d) {
 static inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p % a) != 0; }
 
 
-// Token splits of a naive pass over Ls shared tokens for M queries per head.
-static void plan_prefix_splits(int H, int M, int Ls, int* p_chunk, int* np_split) {
+// Token splits of a naive pass over Ls shared tokens for M queries per head; `share`: the part of
+// the chip the pass has to itself (nodes of a tree that run in one launch share it).
+static void plan_prefix_splits(int H, int M, int Ls, double share, int* p_chunk, int* np_split) {
   const int wgs = std::max(1, H * (M > PIPELINED_MIN_M ? ceil_div(M, 256)
                                    : prefix_paired(H, M, Ls) ? 1 : ceil_div(M, 64)));
   int splits = tune(TMLA_TUNE_PREFIX_SPLITS);
-  if (splits <= 0) splits = std::max(1, NUM_CU / wgs);
+  if (splits <= 0) splits = std::max(1, (int)(NUM_CU * share / wgs + 1e-6));
   splits = std::max(1, std::min(splits, ceil_div(Ls, 128)));
   *p_chunk = round_up(ceil_div(Ls, splits), TOK_BLK);
   *np_split = ceil_div(Ls, *p_chunk);
@@ -230,7 +231,7 @@ int make_plan(const tmla_dims* dims, int mode, int B, int Sq, int Ls, int max_su
     // naive prefix pass: one workgroup owns a head and a block of up to 256 queries
     // (64 when the batch is small and the token-split kernel runs); one workgroup fits per
     // compute unit, so the prefix is split until the grid covers the chip once
-    plan_prefix_splits(H, M, Ls, &p->p_chunk, &p->np_split);
+    plan_prefix_splits(H, M, Ls, 1.0, &p->p_chunk, &p->np_split);
   }
   if (mode == TMLA_MODE_NAIVE_ONLY && max_suffix > 0) {
     int chunk = tune(TMLA_TUNE_NAIVE_SUFFIX_CHUNK);
@@ -609,6 +610,8 @@ struct TreePlan {
   Plan p;                            // suffix plan + workspace layout; n_naive = all level slots
   int level_slot0[TREE_MAX_LEVELS];  // first partial slot of a level
   std::vector<int> chunk, splits;    // per node
+  std::vector<PrefixKind> kind;
+  double work[4];                    // per kind
 };
 
 // Validates the nodes and fixes the partial slots: a level owns as many slots as its most split
@@ -622,6 +625,8 @@ static int make_tree_plan(const tmla_dims* dims, int batch, int q_len, const tml
   int level_slots[TREE_MAX_LEVELS] = {0};
   tp->chunk.assign(num_nodes, 0);
   tp->splits.assign(num_nodes, 0);
+  tp->kind.assign(num_nodes, PREFIX_PIPELINED);
+  for (double& w : tp->work) w = 0.0;
   for (int i = 0; i < num_nodes; i++) {
     const tmla_prefix_node& nd = nodes[i];
     if (nd.len < 0 || nd.level < 0 || nd.level >= TREE_MAX_LEVELS || nd.batch_begin < 0 ||
@@ -634,7 +639,16 @@ static int make_tree_plan(const tmla_dims* dims, int batch, int q_len, const tml
       if (nd.batch_begin < o.batch_begin + o.batch_count && o.batch_begin < nd.batch_begin + nd.batch_count)
         return TMLA_ERR_INVALID_ARG;
     }
-    plan_prefix_splits(dims->num_heads, nd.batch_count * q_len, nd.len, &tp->chunk[i],
+    tp->kind[i] = prefix_kind(dims->num_heads, nd.batch_count * q_len, nd.len);
+    // work of the kinds of kernel: the nodes of one kind share a launch and hence the chip
+    tp->work[tp->kind[i]] += (double)ceil_div(nd.batch_count * q_len, 64) * nd.len;
+  }
+  for (int i = 0; i < num_nodes; i++) {
+    const tmla_prefix_node& nd = nodes[i];
+    if (nd.len == 0 || nd.batch_count == 0) continue;
+    const double own = (double)ceil_div(nd.batch_count * q_len, 64) * nd.len;
+    const double share = dims->dtype == TMLA_BF16 ? own / tp->work[tp->kind[i]] : 1.0;
+    plan_prefix_splits(dims->num_heads, nd.batch_count * q_len, nd.len, share, &tp->chunk[i],
                        &tp->splits[i]);
     level_slots[nd.level] = std::max(level_slots[nd.level], tp->splits[i]);
   }
@@ -704,8 +718,17 @@ int typhoon_mla_decode_tree(const tmla_dims* dims, int32_t batch, int32_t q_len,
   const size_t esz = bf16 ? 2 : 4;
 
   const LaunchCheck launches;
-  // every level slot starts empty; a node's pass fills the rows of its own requests
-  launch_fill_f32((float*)(a.ws + p.off_naive_lse), (int64_t)p.n_naive * p.rows, -INFINITY, a.stream);
+  // A slot's rows that no node writes must read as empty.  Where the nodes of a level cover every
+  // request with as many splits as the level has slots, there are none.
+  int64_t covered = 0, slots_all = 0;
+  for (int i = 0; i < num_nodes; i++)
+    covered += (int64_t)tp.splits[i] * (tp.splits[i] ? nodes[i].batch_count : 0);
+  slots_all = (int64_t)p.n_naive * batch;
+  if (covered < slots_all)
+    launch_fill_f32((float*)(a.ws + p.off_naive_lse), (int64_t)p.n_naive * p.rows, -INFINITY, a.stream);
+  std::vector<Plan> kind_plans[4];
+  std::vector<DecodeArgs> kind_args[4];
+  const bool matrix = bf16 && !(debug_flags() & 1);
   for (int i = 0; i < num_nodes; i++) {
     if (tp.splits[i] == 0) continue;
     const tmla_prefix_node& nd = nodes[i];
@@ -718,13 +741,21 @@ int typhoon_mla_decode_tree(const tmla_dims* dims, int32_t batch, int32_t q_len,
     DecodeArgs an = a;
     an.q = (const char*)q + (size_t)row0 * D_QK * esz;
     an.prefix_k = nd.k; an.prefix_v = nd.v;
-    if (bf16 && !(debug_flags() & 1)) {
-      if ((st = mfma_prefix_attention(pn, an)) != TMLA_OK) return st;
+    if (matrix) {
+      kind_plans[tp.kind[i]].push_back(pn);
+      kind_args[tp.kind[i]].push_back(an);
     } else if (bf16) {
       simple_stage_naive<bf16_t>(pn, an, 0, pn.np_split, (int64_t)nd.batch_count * q_len * dims->num_heads);
     } else {
       simple_stage_naive<float>(pn, an, 0, pn.np_split, (int64_t)nd.batch_count * q_len * dims->num_heads);
     }
+  }
+  for (int k = 0; k < 4; k++) {
+    const int n = (int)kind_plans[k].size(), most = k == PREFIX_QUERY_SPLIT ? 1 : PREFIX_NODES_MAX;
+    for (int i = 0; i < n; i += most)
+      if ((st = mfma_prefix_nodes((PrefixKind)k, &kind_plans[k][i], &kind_args[k][i],
+                                  std::min(most, n - i))) != TMLA_OK)
+        return st;
   }
   if (!bf16) {
     simple_stage_qabs<float>(p, a);

@@ -150,6 +150,12 @@ int mfma_expand(int H, int64_t ntok, const void* c, int64_t c_stride, const void
                 int64_t r_stride, const void* w_uk, const void* w_uv, void* k_out, void* v_out,
                 hipStream_t stream);
 int mfma_prefix_attention(const Plan& p, const DecodeArgs& a);
+// the kernel that the naive prefix pass of M queries per head over Ls tokens runs on
+enum PrefixKind { PREFIX_PIPELINED, PREFIX_PAIRED, PREFIX_TOKEN_SPLIT, PREFIX_QUERY_SPLIT };
+PrefixKind prefix_kind(int H, int M, int Ls);
+// n <= PREFIX_NODES_MAX tree nodes of one kind (not PREFIX_QUERY_SPLIT for n > 1) in one launch
+constexpr int PREFIX_NODES_MAX = 8;
+int mfma_prefix_nodes(PrefixKind kind, const Plan* plans, const DecodeArgs* args, int n);
 int mfma_naive_suffix_attention(const Plan& p, const DecodeArgs& a);
 int mfma_query_absorb(const Plan& p, const DecodeArgs& a);
 int mfma_absorb_attention(const Plan& p, const DecodeArgs& a);

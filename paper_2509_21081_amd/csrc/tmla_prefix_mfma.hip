@@ -47,6 +47,33 @@ struct PrefixArgs {
   int Sq, first_slot;           // partial slot of chunk 0
 };
 
+// Prefix nodes of a tree that run in one launch (nodes of one kernel, which write different
+// partial slots or rows): grid.z counts the splits of all of them, node i from z0[i] on.  A node's
+// own launch ends with compute units idle and begins with a fill of its own, about 15 us together.
+struct PrefixNodes {
+  int n;                        // 0: the arguments themselves are the only prefix
+  int z0[PREFIX_NODES_MAX];
+  struct Node {
+    const __bf16 *q, *pk, *pv;
+    float *o, *lse;
+    int M, Ls, ntb, blocks_per_split;
+  } node[PREFIX_NODES_MAX];
+};
+// the arguments of this workgroup's node; `sp`: its split
+__device__ __forceinline__ PrefixArgs prefix_node_args(const PrefixArgs& common,
+                                                       const PrefixNodes& nodes, int& sp) {
+  PrefixArgs a = common;
+  if (nodes.n > 0) {
+    int i = 0;
+    while (i + 1 < nodes.n && sp >= nodes.z0[i + 1]) i++;
+    const PrefixNodes::Node& nd = nodes.node[i];
+    a.q = nd.q; a.pk = nd.pk; a.pv = nd.pv; a.o = nd.o; a.lse = nd.lse;
+    a.M = nd.M; a.Ls = nd.Ls; a.ntb = nd.ntb; a.blocks_per_split = nd.blocks_per_split;
+    sp -= nodes.z0[i];
+  }
+  return a;
+}
+
 __device__ inline void load_q_frags(const PrefixArgs& a, int h, int q0, int n, int g,
                                     bf16x8 (&qf)[2][12], int q_end = 0x7fffffff) {
 #pragma unroll
@@ -451,10 +478,14 @@ struct PlRing {
   static constexpr int QUERIES = 64 * WAVES;                  // per workgroup
 };
 template <bool PAIRED>
-__global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArgs a) {
+__global__ void __launch_bounds__(256, 1) prefix_attn_pipelined_kernel(PrefixArgs common,
+                                                                       PrefixNodes nodes) {
   using RG = PlRing<PAIRED>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int h = blockIdx.x, mb = blockIdx.y, sp = blockIdx.z;
+  const int h = blockIdx.x, mb = blockIdx.y;
+  int sp = blockIdx.z;
+  const PrefixArgs a = prefix_node_args(common, nodes, sp);
+  if (mb * RG::QUERIES >= a.M) return;   // (the grid is as wide as the largest node)
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pair = PAIRED ? wave >> 1 : 0, wq = PAIRED ? wave & 1 : wave;
@@ -1088,9 +1119,13 @@ __device__ inline void ts_block(uint32_t blk, int lane, const bf16x8 (&qf)[2][12
 // token chunk sp of its own suffix, 32-token blocks located through the block table, causal mask
 // inside the suffix.  Same streaming and merge; grid.y = request.
 template <bool PAGED>
-__global__ void __launch_bounds__(256, 1) prefix_attn_token_split_kernel(PrefixArgs a) {
+__global__ void __launch_bounds__(256, 1) prefix_attn_token_split_kernel(PrefixArgs common,
+                                                                         PrefixNodes nodes) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int h = blockIdx.x, mb = blockIdx.y, sp = blockIdx.z;
+  const int h = blockIdx.x, mb = blockIdx.y;
+  int sp = blockIdx.z;
+  const PrefixArgs a = prefix_node_args(common, nodes, sp);
+  if (!PAGED && mb * 64 >= a.M) return;   // (the grid is as wide as the largest node)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int q0 = PAGED ? mb * a.Sq : mb * 64;
   const int q_end = PAGED ? q0 + a.Sq : a.M;
@@ -1239,8 +1274,44 @@ __global__ void __launch_bounds__(256, 1) prefix_attn_token_split_kernel(PrefixA
   }
 }
 
-int mfma_prefix_attention(const Plan& p, const DecodeArgs& d) {
-  if (p.np_split <= 0) return TMLA_OK;
+PrefixKind prefix_kind(int H, int M, int Ls) {
+  if (M > PIPELINED_MIN_M) return debug_flags() & 0x400 ? PREFIX_QUERY_SPLIT : PREFIX_PIPELINED;
+  return prefix_paired(H, M, Ls) ? PREFIX_PAIRED : PREFIX_TOKEN_SPLIT;
+}
+
+static int launch_prefix(PrefixKind kind, const PrefixArgs& a, const PrefixNodes& nodes, int max_m,
+                         int splits, hipStream_t stream) {
+  static LdsOptIn lds_pl, lds_pp, lds_qs, lds_ts;
+  if (kind == PREFIX_PIPELINED) {
+    if (lds_pl.ensure((const void*)prefix_attn_pipelined_kernel<false>, PL_LDS_BYTES) != hipSuccess)
+      return TMLA_ERR_HIP;
+    dim3 grid(a.H, (max_m + PL_QUERIES - 1) / PL_QUERIES, splits);
+    hipLaunchKernelGGL(prefix_attn_pipelined_kernel<false>, grid, dim3(256), PL_LDS_BYTES, stream, a,
+                       nodes);
+  } else if (kind == PREFIX_PAIRED) {
+    if (lds_pp.ensure((const void*)prefix_attn_pipelined_kernel<true>, PL_LDS_BYTES) != hipSuccess)
+      return TMLA_ERR_HIP;
+    hipLaunchKernelGGL(prefix_attn_pipelined_kernel<true>, dim3(a.H, 1, splits), dim3(256),
+                       PL_LDS_BYTES, stream, a, nodes);
+  } else if (kind == PREFIX_QUERY_SPLIT) {
+    if (lds_qs.ensure((const void*)prefix_attn_query_split_kernel<1>, QS_LDS_BYTES) != hipSuccess)
+      return TMLA_ERR_HIP;
+    dim3 grid(a.H, (max_m + QS_QUERIES - 1) / QS_QUERIES, splits);
+    // NB = 1 measured faster than NB = 2 on every configuration: vector-ALU and matrix-core
+    // instructions of a SIMD issue serially, so hiding LDS and barrier latency with a second
+    // wavefront pays more than halving the LDS traffic
+    hipLaunchKernelGGL(prefix_attn_query_split_kernel<1>, grid, dim3(512), QS_LDS_BYTES, stream, a);
+  } else {
+    if (lds_ts.ensure((const void*)prefix_attn_token_split_kernel<false>, TS_LDS_BYTES) != hipSuccess)
+      return TMLA_ERR_HIP;
+    dim3 grid(a.H, (max_m + 63) / 64, splits);
+    hipLaunchKernelGGL(prefix_attn_token_split_kernel<false>, grid, dim3(256), TS_LDS_BYTES, stream, a,
+                       nodes);
+  }
+  return TMLA_OK;
+}
+
+static PrefixArgs prefix_args(const Plan& p, const DecodeArgs& d) {
   PrefixArgs a = {};
   a.q = (const __bf16*)d.q;
   a.pk = (const __bf16*)d.prefix_k;
@@ -1252,33 +1323,31 @@ int mfma_prefix_attention(const Plan& p, const DecodeArgs& d) {
   a.blocks_per_split = p.p_chunk / TOK_BLK;
   a.rows = p.rows;
   a.c = d.sm_scale * LOG2E;
-  static LdsOptIn lds_pl, lds_pp, lds_qs, lds_ts;
-  if (a.M > PIPELINED_MIN_M && !(debug_flags() & 0x400)) {
-    if (lds_pl.ensure((const void*)prefix_attn_pipelined_kernel<false>, PL_LDS_BYTES) != hipSuccess)
-      return TMLA_ERR_HIP;
-    dim3 grid(p.H, (a.M + PL_QUERIES - 1) / PL_QUERIES, p.np_split);
-    hipLaunchKernelGGL(prefix_attn_pipelined_kernel<false>, grid, dim3(256), PL_LDS_BYTES, d.stream, a);
-  } else if (prefix_paired(a.H, a.M, a.Ls)) {
-    if (lds_pp.ensure((const void*)prefix_attn_pipelined_kernel<true>, PL_LDS_BYTES) != hipSuccess)
-      return TMLA_ERR_HIP;
-    hipLaunchKernelGGL(prefix_attn_pipelined_kernel<true>, dim3(p.H, 1, p.np_split), dim3(256),
-                       PL_LDS_BYTES, d.stream, a);
-  } else if (a.M > PIPELINED_MIN_M) {
-    if (lds_qs.ensure((const void*)prefix_attn_query_split_kernel<1>, QS_LDS_BYTES) != hipSuccess)
-      return TMLA_ERR_HIP;
-    dim3 grid(p.H, (a.M + QS_QUERIES - 1) / QS_QUERIES, p.np_split);
-    // NB = 1 measured faster than NB = 2 on every configuration: vector-ALU and matrix-core
-    // instructions of a SIMD issue serially, so hiding LDS and barrier latency with a second
-    // wavefront pays more than halving the LDS traffic
-    hipLaunchKernelGGL(prefix_attn_query_split_kernel<1>, grid, dim3(512), QS_LDS_BYTES, d.stream,
-                       a);
-  } else {
-    if (lds_ts.ensure((const void*)prefix_attn_token_split_kernel<false>, TS_LDS_BYTES) != hipSuccess)
-      return TMLA_ERR_HIP;
-    dim3 grid(p.H, (a.M + 63) / 64, p.np_split);
-    hipLaunchKernelGGL(prefix_attn_token_split_kernel<false>, grid, dim3(256), TS_LDS_BYTES, d.stream, a);
+  return a;
+}
+
+int mfma_prefix_attention(const Plan& p, const DecodeArgs& d) {
+  if (p.np_split <= 0) return TMLA_OK;
+  PrefixNodes nodes;
+  nodes.n = 0;
+  const PrefixArgs a = prefix_args(p, d);
+  return launch_prefix(prefix_kind(p.H, a.M, p.Ls), a, nodes, a.M, p.np_split, d.stream);
+}
+
+int mfma_prefix_nodes(PrefixKind kind, const Plan* plans, const DecodeArgs* args, int n) {
+  if (n == 1) return mfma_prefix_attention(plans[0], args[0]);
+  PrefixNodes nodes;
+  nodes.n = n;
+  int splits = 0, max_m = 0;
+  PrefixArgs a = {};
+  for (int i = 0; i < n; i++) {
+    a = prefix_args(plans[i], args[i]);
+    nodes.z0[i] = splits;
+    nodes.node[i] = {a.q, a.pk, a.pv, a.o, a.lse, a.M, a.Ls, a.ntb, a.blocks_per_split};
+    splits += plans[i].np_split;
+    max_m = max_m > a.M ? max_m : a.M;
   }
-  return TMLA_OK;
+  return launch_prefix(kind, a, nodes, max_m, splits, args[0].stream);
 }
 
 // Naive attention over each request's own expanded paged suffix (naive_only mode): chunks of
@@ -1304,7 +1373,10 @@ int mfma_naive_suffix_attention(const Plan& p, const DecodeArgs& d) {
   if (lds.ensure((const void*)prefix_attn_token_split_kernel<true>, TS_LDS_BYTES) != hipSuccess)
     return TMLA_ERR_HIP;
   dim3 grid(p.H, p.B, p.ns_chunks);
-  hipLaunchKernelGGL(prefix_attn_token_split_kernel<true>, grid, dim3(256), TS_LDS_BYTES, d.stream, a);
+  PrefixNodes nodes;
+  nodes.n = 0;
+  hipLaunchKernelGGL(prefix_attn_token_split_kernel<true>, grid, dim3(256), TS_LDS_BYTES, d.stream, a,
+                     nodes);
   return TMLA_OK;
 }
 

@@ -111,3 +111,62 @@ def test_tree_with_one_root_equals_plain_decode(gpu_device):
                                        max_suffix_len=wl.max_suffix_len, w_uk=d.w_uk, w_uv=d.w_uv)
     torch.cuda.synchronize(gpu_device)
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
+
+
+# nodes on top of the root: more of one kernel than one launch takes, of different lengths (slots
+# that not every node fills); two that cover every request between them (no slot starts out empty),
+# on the token-split kernel and (flag) the pipelined one with wavefront pairs
+SHARED_LAUNCHES = {
+    "ten_nodes": ([(1, 16 * i, 16, 40 + 97 * i) for i in range(10)], 0),
+    "two_halves": ([(1, 0, 80, 700), (1, 80, 80, 300)], 0),
+    "two_halves_paired": ([(1, 0, 80, 700), (1, 80, 80, 300)], 0x20000),
+    "two_kinds": ([(1, 0, 20, 200), (1, 20, 140, 330), (2, 0, 70, 65), (2, 90, 70, 257)], 0x20000),
+}
+
+
+@pytest.mark.parametrize("tree", list(SHARED_LAUNCHES))
+def test_nodes_of_one_kernel_share_a_launch(tree, gpu_device):
+    extra, flags = SHARED_LAUNCHES[tree]
+    B, H = 160, 16
+    wl = W.make_workload(W.small_spec(name=f"tree_{tree}", dtype="bf16", batch=B, heads=H, q_len=1,
+                                      prefix_len=150, suffix_min=0, suffix_max=40, seed=91))
+    extra = [(lv, b0, bc, ln) + _latents(ln, "bf16", 800 + i)
+             for i, (lv, b0, bc, ln) in enumerate(extra)]
+    a = wl.as_float64()
+    sample = list(range(0, B, 7)) + [15, 16, 19, 20, 79, 80, 159]
+    ref = np.full((B, 1, H, 128), np.nan)
+    ref_lse = np.full((B, 1, H), np.nan)
+    for b in sample:
+        ckv, kr = [a["prefix_ckv"]], [a["prefix_krope"]]
+        for lv, b0, bc, ln, c, r in sorted(extra, key=lambda e: e[0]):
+            if b0 <= b < b0 + bc:
+                ckv.append(c.double().numpy())
+                kr.append(r.double().numpy())
+        o, l = O.mla_decode_definition(
+            q=a["q"][b:b + 1], prefix_ckv=np.concatenate(ckv), prefix_krope=np.concatenate(kr),
+            pool=a["pool"], block_table=a["block_table"][b:b + 1],
+            suffix_lens=a["suffix_lens"][b:b + 1], w_uk=a["w_uk"], w_uv=a["w_uv"],
+            sm_scale=a["sm_scale"])
+        ref[b], ref_lse[b] = o[0], l[0]
+    d = wl.to(gpu_device)
+    dims = Hh.dims_of(wl)
+    print(f"tree launches {tree}", flush=True)
+    nodes = [T.typhoon_mla_expand_prefix(dims, d.prefix_ckv, d.prefix_krope, d.w_uk, d.w_uv)
+             + (wl.spec.prefix_len, 0, 0, B)]
+    for lv, b0, bc, ln, c, r in extra:
+        nodes.append(T.typhoon_mla_expand_prefix(dims, c.to(gpu_device), r.to(gpu_device), d.w_uk,
+                                                 d.w_uv) + (ln, lv, b0, bc))
+    old = T.typhoon_mla_set_debug_flags(flags)
+    try:
+        need = T.typhoon_mla_decode_tree_workspace_bytes(dims, B, 1, nodes, wl.max_suffix_len)
+        # (every float of it is a NaN: a slot that neither a node nor the fill writes would show)
+        ws = torch.full((need,), 255, dtype=torch.uint8, device=gpu_device)
+        out, lse = T.typhoon_mla_decode_tree(
+            dims, d.q, nodes, suffix_pool=d.pool, block_table=d.block_table,
+            suffix_lens=d.suffix_lens, max_suffix_len=wl.max_suffix_len, w_uk=d.w_uk, w_uv=d.w_uv,
+            workspace=ws)
+        torch.cuda.synchronize(gpu_device)
+    finally:
+        T.typhoon_mla_set_debug_flags(old)
+    Hh.assert_parity(out.double().cpu().numpy(), lse.double().cpu().numpy(), ref, ref_lse, "bf16",
+                     f"tree_{tree}")
