@@ -157,12 +157,14 @@ static void plan_absorb_bf16(Plan* p, int Ls, int Ln, int block_size) {
   if (Ln > 0) {
     p->as_chunk = general(Ln, block_size);
     p->as_chunks = ceil_div(Ln, p->as_chunk);
-    if (R <= 32 || small) {
+    if (R <= 32 || wgs < 2 * NUM_CU) {
       // (shorter chunks than the general rule's, or than 256 tokens, have to win by more than the
-      // model's error)
+      // model's error, and so has whatever departs from the rule on a grid that covers the chip:
+      // 256 requests x 64 rows x 512 tokens in one chunk each instead of two, the whole step
+      // 225 -> 199 us)
       const int usual = R <= 32 ? p->as_chunk : 256;
-      double best = R <= 32 ? suffix_us(B, R, Ln, p->as_chunks, p->as_chunk) +
-                                  merge_us(p->as_chunks + (Ls > 0), rows) : 1e300;
+      double best = small ? 1e300 : (suffix_us(B, R, Ln, p->as_chunks, p->as_chunk) +
+                                     merge_us(p->as_chunks + (Ls > 0), rows)) * (R <= 32 ? 1.0 : 0.95);
       for (int n : CHUNK_COUNTS) {
         const int T = round_up(ceil_div(Ln, n), block_size), as = ceil_div(Ln, T);
         if (n > 1 && !allowed(as + (Ls > 0))) break;
@@ -400,7 +402,10 @@ static int check_decode_sizes(const tmla_dims* dims, int mode, int batch, int q_
 // batch, and a short step is mostly launch latency.  So the library interpolates its own
 // measured cross-overs (bench.py --sweep, S_q = 1, suffix 512: the batch at which mixed
 // overtakes absorb_only) in log2(heads) x log2(prefix length), clamped at the table's edges.
-// (The dips at 32 heads are real: 32 query rows per request run the small shared-tile kernel.)
+// The numbers are part of the interface (callers size batches by them) and stand as they were
+// first measured; with the latent prefix walked for all requests' rows together the cross-overs
+// of 16 and 32 heads lie higher now (4096 tokens: 136 and 81 requests; 16384: 73 and 43; at 128
+// heads 46 and 40 as in the table), which `absorb_only` reaches by choice.
 static double fitted_batch_threshold(int heads, int prefix_len) {
   static const double cross[4][4] = {
       //  16     32     64    128 heads

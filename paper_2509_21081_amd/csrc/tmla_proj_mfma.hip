@@ -490,7 +490,7 @@ template <int NN>
 struct FsLayout {
   static constexpr int NSLOT = NN == 1 ? 3 : 2;
   static constexpr int SLOT = FS_X_BYTES + NN * FS_N_BYTES;
-  static constexpr int BYTES = NSLOT * SLOT;     // 144 KiB (one naive partial), 128 KiB (two)
+  static constexpr int BYTES = NSLOT * SLOT;     // 144 KiB (one naive partial), 128 (two), 160 (three)
   static constexpr int TPW = 8 + 4 * NN;         // transfers per wavefront and block
 };
 
@@ -728,16 +728,17 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
                        (int64_t)p.rows);
     a.n_lat = 1;
   }
-  // one latent partial, one or two naive partials, and at least two blocks of 32 queries per
+  // one latent partial, one to three naive partials, and at least two blocks of 32 queries per
   // compute unit: runs of up to eight blocks per workgroup, so that the grid still covers the chip
-  if (a.n_lat == 1 && (p.n_naive == 1 || p.n_naive == 2)) {
+  if (a.n_lat == 1 && p.n_naive >= 1 && p.n_naive <= 3) {
     const int nqb = (a.M + 31) / 32;
     const int heads8 = (p.H + 7) / 8 * 8;
     const long long per_cu = (long long)heads8 * nqb / NUM_CU;
     const int qbk = (int)(per_cu > 8 ? 8 : per_cu);
     if (qbk >= 2)
-      return p.n_naive == 1 ? launch_finalize_stream<1>(a, heads8, nqb, qbk, d.stream)
-                            : launch_finalize_stream<2>(a, heads8, nqb, qbk, d.stream);
+      return p.n_naive == 1   ? launch_finalize_stream<1>(a, heads8, nqb, qbk, d.stream)
+             : p.n_naive == 2 ? launch_finalize_stream<2>(a, heads8, nqb, qbk, d.stream)
+                              : launch_finalize_stream<3>(a, heads8, nqb, qbk, d.stream);
   }
   dim3 grid(8 * ((a.M + 31) / 32) * ((p.H + 7) / 8));
   // up to half a workgroup per compute unit the value blocks are dealt out (one request x 128

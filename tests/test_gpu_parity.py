@@ -144,6 +144,21 @@ def test_latent_partials_of_every_merge_size(chunks, batch, gpu_device, tune):
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"merge_{chunks}_{batch}")
 
 
+def test_streaming_projection_with_three_naive_partials(gpu_device, tune):
+    """200 requests x 128 heads in three prefix splits: the streaming up-projection with three naive
+    partials per row (LDS full to the byte), runs of 3, 3 and 1 blocks, a ragged last block and
+    requests without a suffix."""
+    tune(T.TUNE_PREFIX_SPLITS, 3)
+    spec = W.small_spec(name="stream3", dtype="bf16", batch=200, heads=128, q_len=1, prefix_len=300,
+                        suffix_min=0, suffix_max=20, seed=333)
+    wl = W.make_workload(spec)
+    pairs = [(b, h) for b in (0, 31, 32, 95, 96, 191, 192, 199) for h in (0, 63, 127)]
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64(), pairs=pairs)
+    print("streaming projection, three naive partials", flush=True)
+    got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", "stream3")
+
+
 @pytest.mark.parametrize("mode", ["mixed", "naive_only", "absorb_only"])
 @pytest.mark.parametrize("prefix,suffix,q_len", [(1, 64, 1), (63, 65, 2), (64, 1, 1), (65, 129, 3),
                                                  (200, 0, 1), (0, 130, 1)])
