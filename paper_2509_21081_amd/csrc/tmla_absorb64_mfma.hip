@@ -1,5 +1,7 @@
-// Absorb-formulation flash-decode over latent cache rows for requests with more than 32 query
-// rows (S_q * H > 32; paper Algorithm 1 step 6): 64 query rows per workgroup, 64 tokens per step.
+// Absorb-formulation flash-decode over latent cache rows (paper Algorithm 1 step 6), 64 query rows
+// per workgroup, 64 tokens per step: the suffixes of requests with more than 32 query rows
+// (S_q * H > 32), the latent prefix for groups of 64 rows cut from all requests, and on small
+// grids both in one launch, whatever the rows per request.
 //
 // The two matrix products of a step want different work splits, so the four wavefronts change
 // roles inside a step and hand the probabilities over through LDS:

@@ -2,21 +2,17 @@
 // (paper Algorithm 1 step 6; the absorbed queries of step 5 arrive precomputed, the W_UV
 // up-projection of step 7 is applied after the split partials are merged because it is linear).
 //
-// One workgroup = one request x one token chunk x up to 128 of its S_q*H query rows.  Each
-// 576-wide cache row is read from HBM once per workgroup (fully coalesced 1152-byte rows) into
-// an LDS tile of 32 tokens, and serves both products:
+// The kernel here takes the suffixes of requests with 17 to 32 query rows (H = 16 with S_q = 2, or
+// H = 32): one workgroup = one request x one token chunk.  Each 576-wide cache row is read from HBM
+// once per workgroup (fully coalesced 1152-byte rows) into an LDS tile of 32 tokens, and serves both
+// products:
 //   S^T  = C   Q_abs^T   (tokens x queries, k = 576): A operand = token-major rows (ds_read_b128)
 //   O^T += C_N^T P^T     (latent x queries, k = tokens): A operand = the same tile read through
 //                         the transposing LDS load (ds_read_b64_tr_b16), no second copy.
 // Queries sit on the MFMA column axis, so softmax statistics are per-lane and P^T feeds the second
-// product straight from the accumulator registers.
-//
-// Wavefront roles (template NQB = query blocks of 32 rows per workgroup, NQB * NLP = 4):
-//   NQB = 4: four wavefronts own 4 x 32 query rows and all 512 latent columns each (not built:
-//            it needs more registers than a wavefront has)
-//   NQB = 2: 2 x 32 query rows, two wavefronts per block own 256 latent columns each
-//   NQB = 1: 32 query rows (H = 16 with S_q <= 2), four wavefronts own 128 latent columns each;
-//            the scores are recomputed per wavefront, which the HBM-bound small-H case affords.
+// product straight from the accumulator registers.  The four wavefronts own 128 latent columns
+// each; the scores are recomputed per wavefront, which this HBM-bound case affords.
+// Behind it, the dispatch over the absorb kernels.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
