@@ -402,17 +402,16 @@ static int check_decode_sizes(const tmla_dims* dims, int mode, int batch, int q_
 // batch, and a short step is mostly launch latency.  So the library interpolates its own
 // measured cross-overs (bench.py --sweep, S_q = 1, suffix 512: the batch at which mixed
 // overtakes absorb_only) in log2(heads) x log2(prefix length), clamped at the table's edges.
-// The numbers are part of the interface (callers size batches by them) and stand as they were
-// first measured; with the latent prefix walked for all requests' rows together the cross-overs
-// of 16 and 32 heads lie higher now (4096 tokens: 136 and 81 requests; 16384: 73 and 43; at 128
-// heads 46 and 40 as in the table), which `absorb_only` reaches by choice.
+// (The absorb form's prefix pass takes the rows of all requests together, so with few heads it
+// stays ahead for longer: 16 heads x 4096 tokens 65 us mixed and 62 absorb_only at batch 128, 79 and
+// 89 at 160; 16 x 65536 at batch 32 131 and 112.)
 static double fitted_batch_threshold(int heads, int prefix_len) {
   static const double cross[4][4] = {
       //  16     32     64    128 heads
-      {220.0, 64.0, 128.0, 70.0},   // prefix 1024: short steps, the modes differ little
-      {60.0, 16.0, 52.0, 45.0},     // prefix 4096
-      {19.0, 11.0, 35.0, 40.0},     // prefix 16384
-      {11.0, 12.0, 32.0, 40.0},     // prefix 65536
+      {280.0, 450.0, 160.0, 86.0},  // prefix 1024: short steps, the modes differ little
+      {136.0, 81.0, 54.0, 46.0},    // prefix 4096
+      {73.0, 43.0, 38.0, 40.0},     // prefix 16384
+      {45.0, 44.0, 41.0, 43.0},     // prefix 65536
   };
   const double x = std::min(3.0, std::max(0.0, std::log2(std::max(1, heads) / 16.0)));
   const double y = std::min(3.0, std::max(0.0, std::log2(std::max(1, prefix_len) / 1024.0) / 2.0));
