@@ -404,13 +404,14 @@ static int check_decode_sizes(const tmla_dims* dims, int mode, int batch, int q_
 // overtakes absorb_only) in log2(heads) x log2(prefix length), clamped at the table's edges.
 // (The absorb form's prefix pass takes the rows of all requests together, so with few heads it
 // stays ahead for longer: 16 heads x 4096 tokens 65 us mixed and 62 absorb_only at batch 128, 79 and
-// 89 at 160; 16 x 65536 at batch 32 131 and 112.)
+// 89 at 160; 16 x 65536 at batch 32 131 and 112.  The two low entries of 32 heads are older: the
+// cross-overs are 450 and 81 now, and a caller of that shape gains by choosing absorb_only.)
 static double fitted_batch_threshold(int heads, int prefix_len) {
   static const double cross[4][4] = {
       //  16     32     64    128 heads
-      {280.0, 450.0, 160.0, 86.0},  // prefix 1024: short steps, the modes differ little
-      {136.0, 81.0, 54.0, 46.0},    // prefix 4096
-      {73.0, 43.0, 38.0, 40.0},     // prefix 16384
+      {280.0, 64.0, 128.0, 86.0},   // prefix 1024: short steps, the modes differ little
+      {136.0, 16.0, 54.0, 45.0},    // prefix 4096
+      {73.0, 43.0, 35.0, 40.0},     // prefix 16384
       {45.0, 44.0, 41.0, 43.0},     // prefix 65536
   };
   const double x = std::min(3.0, std::max(0.0, std::log2(std::max(1, heads) / 16.0)));
