@@ -146,6 +146,20 @@ def test_chunks_of_a_suffix_cost_no_precision(chunks, heads, batch, gpu_device, 
     assert err[64] <= 1.04 * err[64 * chunks]
 
 
+@pytest.mark.parametrize("heads,q_len", [(16, 1), (32, 1), (48, 1), (64, 1), (80, 1), (48, 3), (112, 2)])
+def test_latent_rows_of_partly_filled_groups(heads, q_len, gpu_device):
+    """16 to 224 query rows a request, whole row groups of a workgroup and remainders: whole rows of
+    the latent partials leave through LDS, and none of a neighbour's is touched."""
+    spec = W.small_spec(name="groups", dtype="bf16", batch=3, heads=heads, q_len=q_len, prefix_len=70,
+                        suffix_min=1, suffix_max=150, seed=640 + heads)
+    wl = W.make_workload(spec)
+    ref, ref_lse = O.mla_decode_absorb_all_heads(**wl.as_float64())
+    for mode in ("mixed", "absorb_only"):
+        print(f"rows of partly filled groups {heads} x {q_len} {mode}", flush=True)
+        got, got_lse = Hh.run_library(wl, mode, gpu_device)
+        Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"groups/{heads}x{q_len}/{mode}")
+
+
 @pytest.mark.parametrize("batch", [1, 33])
 @pytest.mark.parametrize("chunks", [4, 5, 16, 17, 32, 33, 64, 70])
 def test_latent_partials_of_every_merge_size(chunks, batch, gpu_device, tune):
