@@ -3,14 +3,17 @@
 // (about 30 FLOP per cache byte), so the design minimises everything except the cache stream:
 //
 //   * v_mfma_f32_16x16x32_bf16 with the 16 queries on the column axis: no padding to 32 columns;
-//   * every wavefront is an independent worker with a private 32-token LDS tile: it streams its
-//     own contiguous share of the request's tokens (global -> LDS), reads the tile once for the
-//     scores and once (transposed) for P V, and never synchronises with the other wavefronts.
+//   * every wavefront walks a contiguous quarter of the workgroup's chunk with a private 32-token
+//     LDS tile: it streams its own tokens (global -> LDS), reads the tile once for the scores and
+//     once (transposed) for P V, and does not synchronise with the other wavefronts meanwhile.
 //     Each cache row is therefore read from LDS exactly twice per workgroup, and the latency of
-//     a wavefront's tile load is hidden by the other three wavefronts of the compute unit;
-//   * the wavefronts of a workgroup cover up to four consecutive plan items (token chunks) of
-//     one request; the span is divided evenly among them at run time so that requests shorter
-//     than the planned span still use all four.  Each writes its own latent partial + LSE.
+//     a wavefront's tile load is hidden by the other three wavefronts of the compute unit.  The
+//     chunk is divided at run time, so that a request shorter than the planned chunk still uses
+//     all four;
+//   * the four partial softmaxes are merged in fp32 through LDS at the end: one latent partial per
+//     chunk, whole rows of 1 KiB.  Written out one by one, in 8-byte pieces, they were four bf16
+//     partials a row that the projection had to fetch and to merge: 512 requests x 16 heads mixed,
+//     16384 + 512 to 4096 tokens, 67 -> 42 MB for it to read, step 348 -> 327 us.
 //
 // MFMA 16x16x32 operand layout (lane = n + 16*q, n in [0,16), q in [0,4)):
 //   A (16 x 32): row n, k = 8*q + e;   B (32 x 16): column n, k = 8*q + e;
@@ -32,7 +35,11 @@ namespace tmla {
 constexpr int A16_ROW_BYTES = 1056;
 constexpr int A16_MAIN_BYTES = 32 * A16_ROW_BYTES;
 constexpr int A16_TILE_BYTES = A16_MAIN_BYTES + 32 * 128;   // 37888
-constexpr int A16_LDS_BYTES = 4 * A16_TILE_BYTES;
+constexpr int A16_ML_OFF = 4 * A16_TILE_BYTES;              // [wavefront][reference, denominator][row]
+constexpr int A16_LDS_BYTES = A16_ML_OFF + 4 * 2 * 16 * 4;
+// a wavefront's outputs in its tile at the end: 512 floats a row, conflict-free for 16 rows x 16 B
+constexpr int A16_OUT_ROW = D_L * 4 + 16;
+static_assert(16 * A16_OUT_ROW <= A16_TILE_BYTES && A16_LDS_BYTES <= 163840, "LDS layout");
 
 __device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -53,41 +60,41 @@ __device__ inline float sum_quads(float x) {
 
 __global__ void __launch_bounds__(256, 1) absorb16_kernel(AbsorbArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int grp = blockIdx.x, b = a.order ? scalar_load_i32(a.order + blockIdx.y) : (int)blockIdx.y;
+  const int chunk = blockIdx.x, b = a.order ? scalar_load_i32(a.order + blockIdx.y) : (int)blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool q_valid = n < a.R;
   const int64_t row = (int64_t)b * a.R + n;
 
-  // ---- the span of this workgroup and this wavefront's share of it
+  // ---- the chunk of this workgroup and this wavefront's share of it
+  const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
+  // a table of up to 64 blocks per request is fetched whole, next to the request's length
+  const bool whole_table = a.max_blocks <= 64;
+  int bt_cache = whole_table && lane < a.max_blocks ? bt[lane] : 0;
   const int len = scalar_load_i32(a.lens + b);
-  const int nparts = min(4, a.as_chunks - 4 * grp);
-  const int span0 = 4 * grp * a.as_chunk;
-  const int span1 = min(len, span0 + nparts * a.as_chunk);
-  const int first_item = a.ap_chunks + 4 * grp;
-  if (wave >= nparts) return;   // no barriers below: wavefronts are independent
-  const int item = first_item + wave;
-  __bf16* o_dst = a.lat_o + ((size_t)item * a.rows + row) * D_L + 4 * q4;
+  const int span0 = chunk * a.as_chunk;
+  const int span1 = min(len, span0 + a.as_chunk);
+  const int item = a.ap_chunks + chunk;
   float* l_dst = a.lat_lse + (size_t)item * a.rows + row;
-  const int span = max(0, span1 - span0);
-  const int part = ((span + nparts - 1) / nparts + 31) & ~31;   // tokens per wavefront, tile aligned
+  if (span1 <= span0) {   // empty chunk (workgroup-uniform): only the LSEs are defined
+    if (wave == 0 && q_valid && q4 == 0) *l_dst = -INFINITY;
+    return;
+  }
+  const int part = ((span1 - span0 + 3) / 4 + 31) & ~31;   // tokens per wavefront, tile aligned
   const int t0 = __builtin_amdgcn_readfirstlane(span0 + wave * part);
   const int t1 = __builtin_amdgcn_readfirstlane(min(span1, t0 + part));
   const int vis_q = max(0, min(len, len - a.Sq + query_position(n, a.H, a.R) + 1));
-  if (t1 <= t0) {
-    if (q_valid && q4 == 0) *l_dst = -INFINITY;
-    return;
-  }
-  const int ntile = (t1 - t0 + 31) / 32;
+  const int ntile = t1 > t0 ? (t1 - t0 + 31) / 32 : 0;
 
   // ---- tile streaming into this wavefront's private slot: 32 latent rows + 4 rope groups
   char* slot = smem + wave * A16_TILE_BYTES;
   // physical blocks of this wavefront's token range: one entry per lane, picked with v_readlane
   // (ranges longer than 64 blocks fall back to a scalar load per tile)
-  const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
-  const int first_blk = t0 >> a.bs_shift;
-  const int nblk_mine = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
-  int bt_cache = (lane < nblk_mine) ? bt[first_blk + lane] : 0;
+  const int first_blk = whole_table ? 0 : t0 >> a.bs_shift;
+  if (!whole_table) {
+    const int nblk_mine = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
+    if (lane < nblk_mine) bt_cache = bt[first_blk + lane];
+  }
   asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
   const uint32_t tbase = lds_addr(slot);
   const int lane_off0 = lane << 4, lane_off1 = (lane ^ 1) << 4;
@@ -115,7 +122,7 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(AbsorbArgs a) {
       dma16_scalar_base<true>(rr * row_bytes + (rope_ch ^ ((j & 1) << 6)), base + D_L * 2, tbase, A16_MAIN_BYTES + j * 1024);
     }
   };
-  issue(0);
+  if (ntile > 0) issue(0);
 
   // ---- absorbed query fragments (B operand): 18 k-steps of 32
   bf16x8 qf[18];
@@ -271,27 +278,63 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(AbsorbArgs a) {
     if (tile + 1 < ntile) issue(tile + 1);
   }
 
+  // ---- merge of the four wavefronts: weights from their references and denominators, weighted
+  // outputs into the own tile (free by now), whole rows out
+  float* ml = (float*)(smem + A16_ML_OFF);
   const float lt = sum_quads(l);
-  if (!q_valid) return;
-  if (lt > 0.f) {
-    const float inv = 1.f / lt;
+  if (q4 == 0) {
+    ml[(wave * 2 + 0) * 16 + n] = m;
+    ml[(wave * 2 + 1) * 16 + n] = lt;
+  }
+  lgkm_wait<0>();
+  raw_barrier();
+  float mw[4], lw[4], ms = -INFINITY, ls = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; w++) {
+    mw[w] = ml[(w * 2 + 0) * 16 + n];
+    lw[w] = ml[(w * 2 + 1) * 16 + n];
+    if (lw[w] > 0.f) ms = fmaxf(ms, mw[w]);   // (else: no token of that share is visible)
+  }
+#pragma unroll
+  for (int w = 0; w < 4; w++) ls += lw[w] > 0.f ? lw[w] * fast_exp2(mw[w] - ms) : 0.f;
+  const bool use = lt > 0.f;
+  const float f = use ? fast_exp2(m - ms) / ls : 0.f;
+  {
+    char* dst = slot + n * A16_OUT_ROW + 16 * q4;
 #pragma unroll
     for (int mb = 0; mb < 32; mb++) {
-      bf16x4 w;
+      f32x4 w;
 #pragma unroll
-      for (int e = 0; e < 4; e++) w[e] = (__bf16)(o[mb][e] * inv);
-      *(bf16x4*)(o_dst + 16 * mb) = w;
+      for (int e = 0; e < 4; e++) w[e] = use ? o[mb][e] * f : 0.f;
+      *(f32x4*)(dst + 64 * mb) = w;
     }
-    if (q4 == 0) *l_dst = (m + fast_log2(lt)) * LN2;
-  } else if (q4 == 0) {
-    *l_dst = -INFINITY;
+  }
+  if (wave == 0 && q4 == 0 && q_valid) *l_dst = ls > 0.f ? (ms + fast_log2(ls)) * LN2 : -INFINITY;
+  lgkm_wait<0>();
+  raw_barrier();
+  __bf16* o_dst = a.lat_o + ((size_t)item * a.rows + (int64_t)b * a.R) * D_L + lane * 8;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int r = 4 * i + wave;
+    if (r >= a.R) continue;
+    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+      const f32x4* src = (const f32x4*)(smem + w * A16_TILE_BYTES + r * A16_OUT_ROW + lane * 32);
+#pragma unroll
+      for (int e = 0; e < 8; e++) x[e] += src[e >> 2][e & 3];
+    }
+    bf16x8 w8;
+#pragma unroll
+    for (int e = 0; e < 8; e++) w8[e] = (__bf16)x[e];
+    *(bf16x8*)(o_dst + (size_t)r * D_L) = w8;
   }
 }
 
 int mfma_absorb16_attention(const Plan& p, const DecodeArgs& d, AbsorbArgs a) {
   static LdsOptIn lds;
   if (lds.ensure((const void*)absorb16_kernel, A16_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
-  dim3 grid((p.as_chunks + 3) / 4, p.B);
+  dim3 grid(p.as_chunks, p.B);
   a.order = suffix_request_order(p, d, (long long)grid.x * grid.y);
   hipLaunchKernelGGL(absorb16_kernel, grid, dim3(256), A16_LDS_BYTES, d.stream, a);
   return TMLA_OK;
