@@ -67,10 +67,6 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(AbsorbArgs a) {
   const int64_t row = (int64_t)b * a.R + n;
 
   // ---- the chunk of this workgroup and this wavefront's share of it
-  const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
-  // a table of up to 64 blocks per request is fetched whole, next to the request's length
-  const bool whole_table = a.max_blocks <= 64;
-  int bt_cache = whole_table && lane < a.max_blocks ? bt[lane] : 0;
   const int len = scalar_load_i32(a.lens + b);
   const int span0 = chunk * a.as_chunk;
   const int span1 = min(len, span0 + a.as_chunk);
@@ -90,11 +86,10 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(AbsorbArgs a) {
   char* slot = smem + wave * A16_TILE_BYTES;
   // physical blocks of this wavefront's token range: one entry per lane, picked with v_readlane
   // (ranges longer than 64 blocks fall back to a scalar load per tile)
-  const int first_blk = whole_table ? 0 : t0 >> a.bs_shift;
-  if (!whole_table) {
-    const int nblk_mine = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
-    if (lane < nblk_mine) bt_cache = bt[first_blk + lane];
-  }
+  const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
+  const int first_blk = t0 >> a.bs_shift;
+  const int nblk_mine = ((t1 - 1) >> a.bs_shift) - first_blk + 1;
+  int bt_cache = (lane < nblk_mine) ? bt[first_blk + lane] : 0;
   asm volatile("s_waitcnt vmcnt(0)" : "+v"(bt_cache)::"memory");
   const uint32_t tbase = lds_addr(slot);
   const int lane_off0 = lane << 4, lane_off1 = (lane ^ 1) << 4;

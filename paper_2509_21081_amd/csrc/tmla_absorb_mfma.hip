@@ -36,7 +36,6 @@ __global__ void __launch_bounds__(256, 1) absorb_attn_kernel(AbsorbArgs a) {
   const int t0 = (item - a.ap_chunks) * a.as_chunk;
   const int t1 = min(len, t0 + a.as_chunk);
   const int vis_q = max(0, min(len, len - a.Sq + query_position(n, a.H, a.R) + 1));
-  __bf16* o_dst = a.lat_o + ((size_t)item * a.rows + row) * D_L;
   float* l_dst = a.lat_lse + (size_t)item * a.rows + row;
   if (t1 <= t0) {   // empty chunk (workgroup-uniform)
     if (q_valid && wave == 0 && g == 0) *l_dst = -INFINITY;
@@ -231,22 +230,32 @@ __global__ void __launch_bounds__(256, 1) absorb_attn_kernel(AbsorbArgs a) {
     }
   }
 
+  // ---- outputs, turned around in the slot that the last barrier left idle: whole rows of 1 KiB
+  // instead of 8-byte pieces of 32 rows per instruction (steps of 1 to 40 requests x 32 heads, 64 to
+  // 2500 tokens, 0.8 to 1.2 us shorter: 12 x 64 16.4 -> 15.4)
+  constexpr int ST_ROW = D_L * 2 + 16;
+  static_assert(32 * ST_ROW <= AB_TILE_BYTES, "the outputs fit a slot");
   const float lt = sum_halves(l);
-  if (!q_valid) return;
-  if (lt > 0.f) {
-    const float inv = 1.f / lt;
+  // (0: the causal mask hid every token of this chunk from this query; the row is not read)
+  const float inv = lt > 0.f ? 1.f / lt : 0.f;
+  char* st = slot_ptr(ntile);
 #pragma unroll
-    for (int mb = 0; mb < MBW; mb++)
+  for (int mb = 0; mb < MBW; mb++)
 #pragma unroll
-      for (int v4 = 0; v4 < 4; v4++) {
-        bf16x4 w;
+    for (int v4 = 0; v4 < 4; v4++) {
+      bf16x4 w;
 #pragma unroll
-        for (int e = 0; e < 4; e++) w[e] = (__bf16)(o[mb][4 * v4 + e] * inv);
-        *(bf16x4*)(o_dst + 32 * (wave * MBW + mb) + 8 * v4 + 4 * g) = w;
-      }
-    if (wave == 0 && g == 0) *l_dst = (m + fast_log2(lt)) * LN2;
-  } else if (wave == 0 && g == 0) {
-    *l_dst = -INFINITY;   // causal mask hid every token of this chunk from this query
+      for (int e = 0; e < 4; e++) w[e] = (__bf16)(o[mb][4 * v4 + e] * inv);
+      *(bf16x4*)(st + n * ST_ROW + (32 * (wave * MBW + mb) + 8 * v4 + 4 * g) * 2) = w;
+    }
+  if (wave == 0 && g == 0 && q_valid) *l_dst = lt > 0.f ? (m + fast_log2(lt)) * LN2 : -INFINITY;
+  lgkm_wait<0>();
+  raw_barrier();
+  __bf16* o_dst = a.lat_o + ((size_t)item * a.rows + (int64_t)b * a.R) * D_L + lane * 8;
+#pragma unroll
+  for (int i = 0; i < 8; i++) {
+    const int r = 4 * i + wave;
+    if (r < a.R) *(bf16x8*)(o_dst + (size_t)r * D_L) = *(const bf16x8*)(st + r * ST_ROW + lane * 16);
   }
 }
 
