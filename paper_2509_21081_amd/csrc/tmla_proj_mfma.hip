@@ -674,6 +674,12 @@ static void launch_finalize_few(const FinalizeArgs& a, dim3 grid, hipStream_t st
   }
 }
 
+// Value of a lane whose number is wave-uniform, as a scalar.  (Fetched with __shfl, i.e. through LDS,
+// the weights of one request's 66 partials took 3 us of the merge pass.)
+__device__ inline float lane_value(float x, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+
 // More than four latent partials per row -- a small batch whose long prefix (absorb_only) or
 // suffix is cut into many chunks so that the pass fills the chip -- are merged by a pass of its
 // own into partial 0, after which the up-projection sees a single partial.  Merging inside the
@@ -717,7 +723,7 @@ __global__ void __launch_bounds__(256) merge_latent_kernel(__bf16* lat_o, float*
 #pragma unroll
   for (int j = 0; j < N; j++) {
     const int i = wave + 4 * j;
-    const float w = i < n_lat ? __shfl(i < 64 ? wgt[0] : wgt[1], i & 63) : 0.f;   // wave-uniform
+    const float w = i < n_lat ? lane_value(i < 64 ? wgt[0] : wgt[1], i & 63) : 0.f;
     if (w > 0.f) {
 #pragma unroll
       for (int k = 0; k < 8; k++) acc[k] += w * (float)x[j][k];
@@ -736,6 +742,128 @@ __global__ void __launch_bounds__(256) merge_latent_kernel(__bf16* lat_o, float*
   }
 }
 
+// The same merge and the projection in one launch, for so few rows that every one can have two
+// workgroups, each for half of its value columns: a workgroup merges the row (both halves do) and
+// multiplies it with 64 rows of W_UV[h], which it requests together with the partials.  Latency is
+// all there is to it, so the row stays in fp32 and the products are vector arithmetic: thread 4 c + k
+// takes column c and the k-th 8 of every 32 latent columns.  A head's workgroups have ids of one
+// residue mod 8: same XCD.
+template <int N>
+__global__ void __launch_bounds__(256) merge_project_kernel(FinalizeArgs a) {
+  __shared__ __attribute__((aligned(16))) float part[4][D_L];
+  __shared__ __attribute__((aligned(16))) float merged[D_L];
+  const int id = blockIdx.x, sl = id >> 3, groups = a.H >> 3;
+  const int h = (sl % groups) * 8 + (id & 7), half = (sl / groups) & 1, qi = sl / groups >> 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = 64 * half + (tid >> 2), k4 = tid & 3;
+  const size_t row = (size_t)qi * a.H + h;
+
+  bf16x8 x[N];
+  const __bf16* src = a.lat_o + row * D_L + lane * 8;
+#pragma unroll
+  for (int j = 0; j < N; j++)
+    if (wave + 4 * j < a.n_lat) x[j] = *(const bf16x8*)(src + (size_t)(wave + 4 * j) * a.rows * D_L);
+  float li[2], e[2], wgt[2];
+#pragma unroll
+  for (int k = 0; k < 2; k++)
+    li[k] = lane + 64 * k < a.n_lat ? a.lat_lse[(size_t)(lane + 64 * k) * a.rows + row] : -INFINITY;
+  bf16x8 wf[16];
+  const __bf16* wp = a.w_uv + ((size_t)h * D_V + c) * D_L + 8 * k4;
+#pragma unroll
+  for (int j = 0; j < 16; j++) wf[j] = *(const bf16x8*)(wp + 32 * j);
+  // naive partials k4, k4 + 4, ... of this thread's column (the first sixteen of a row; any others below)
+  float nl[4], no[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    const int i = k4 + 4 * j;
+    nl[j] = -INFINITY;
+    no[j] = 0.f;
+    if (i < a.n_naive) {
+      nl[j] = a.naive_lse[(size_t)i * a.rows + row];
+      no[j] = a.naive_o[((size_t)i * a.rows + row) * D_V + c];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < N; j++) asm volatile("" : "+v"(x[j]));
+  float mx = fmaxf(li[0], li[1]);
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s));
+#pragma unroll
+  for (int k = 0; k < 2; k++) e[k] = mx > -INFINITY && li[k] > -INFINITY ? __expf(li[k] - mx) : 0.f;
+  float z = e[0] + e[1];
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) z += __shfl_xor(z, s);
+#pragma unroll
+  for (int k = 0; k < 2; k++) wgt[k] = z > 0.f ? e[k] / z : 0.f;   // normalised weights
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int j = 0; j < N; j++) {
+    const int i = wave + 4 * j;
+    const float w = i < a.n_lat ? lane_value(i < 64 ? wgt[0] : wgt[1], i & 63) : 0.f;
+    if (w > 0.f) {   // (a partial with LSE = -inf was never written)
+#pragma unroll
+      for (int k = 0; k < 8; k++) acc[k >> 2][k & 3] += w * (float)x[j][k];
+    }
+  }
+  *(f32x4*)&part[wave][lane * 8] = acc[0];
+  *(f32x4*)&part[wave][lane * 8 + 4] = acc[1];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    const int col = tid + 256 * k;
+    merged[col] = part[0][col] + part[1][col] + part[2][col] + part[3][col];
+  }
+  __syncthreads();
+  float oa = 0.f;
+#pragma unroll
+  for (int j = 0; j < 16; j++) {
+    const f32x4 m0 = *(const f32x4*)&merged[32 * j + 8 * k4], m1 = *(const f32x4*)&merged[32 * j + 8 * k4 + 4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) oa += (float)wf[j][k] * m0[k] + (float)wf[j][4 + k] * m1[k];
+  }
+  auto sum4 = [](float v) {
+    v += __shfl_xor(v, 1);
+    return v + __shfl_xor(v, 2);
+  };
+  oa = sum4(oa);
+
+  // ---- combine with the naive partials (a NaN among their LSEs stays one)
+  const float l_a = z > 0.f ? mx + __logf(z) : -INFINITY;
+  float m2 = l_a;
+#pragma unroll
+  for (int j = 0; j < 4; j++) m2 = fmaxf(m2, nl[j]);
+  for (int i = 16 + k4; i < a.n_naive; i += 4) m2 = fmaxf(m2, a.naive_lse[(size_t)i * a.rows + row]);
+  m2 = fmaxf(m2, __shfl_xor(m2, 1));
+  m2 = fmaxf(m2, __shfl_xor(m2, 2));
+  float o2 = 0.f, z2 = 0.f;
+  auto add = [&](float l, float v) {
+    if (l == -INFINITY) return;
+    const float w = __expf(l - m2);
+    z2 += w;
+    o2 += w * v;
+  };
+#pragma unroll
+  for (int j = 0; j < 4; j++) add(nl[j], no[j]);
+  for (int i = 16 + k4; i < a.n_naive; i += 4)
+    add(a.naive_lse[(size_t)i * a.rows + row], a.naive_o[((size_t)i * a.rows + row) * D_V + c]);
+  const float w_a = l_a > -INFINITY ? __expf(l_a - m2) : 0.f;
+  z2 = sum4(z2) + w_a;
+  o2 = sum4(o2) + w_a * oa;
+  if (k4 == 0) {
+    const bool any = m2 > -INFINITY;
+    a.out[row * D_V + c] = (__bf16)(any ? o2 / z2 : 0.f);
+    if (a.lse_out && half == 0 && tid == 0) a.lse_out[row] = any ? m2 + __logf(z2) : -INFINITY;
+  }
+}
+// Steps with the merge pass and the projection / with this kernel, absorb form, 4096 + 300 tokens: 16
+// rows 20.6 / 18.8 us, 128 rows 27.4 / 24.8, 384 30.0 / 28.8, 512 30.6 / 30.3, 768 36.4 / 36.7, 1024
+// 37.8 / 39.8.  Fewer partials, which the projection by itself would merge: four latent and two naive
+// ones, 128 rows 74.5 / 70.9, 512 rows 75.7 / 73.7; two and two, 128 rows 43.2 / 42.7, 512 44.4 / 45.0.
+static bool merge_project_pays(int64_t rows, int n_lat) {
+  return n_lat >= 1 && rows <= (n_lat >= 3 ? 512 : 256);
+}
+
 int mfma_finalize(const Plan& p, const DecodeArgs& d) {
   if (p.rows == 0) return TMLA_OK;
   const bool merge_inside = (debug_flags() & 0x10000) != 0;   // debug: no separate merge pass
@@ -749,6 +877,12 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
   a.out = (__bf16*)d.out;
   a.lse_out = d.lse_out;
   a.M = p.B * p.Sq; a.H = p.H; a.n_naive = p.n_naive; a.n_lat = p.n_lat; a.rows = p.rows;
+  if (!merge_inside && merge_project_pays(p.rows, a.n_lat)) {
+    auto merge = a.n_lat <= 4 ? merge_project_kernel<1> : a.n_lat <= 16 ? merge_project_kernel<4> : a.n_lat <= 32 ? merge_project_kernel<8>
+                 : a.n_lat <= 64 ? merge_project_kernel<16> : merge_project_kernel<32>;
+    hipLaunchKernelGGL(merge, dim3((unsigned)(2 * p.rows)), dim3(256), 0, d.stream, a);
+    return TMLA_OK;
+  }
   if (a.n_lat > 4 && !merge_inside) {
     auto merge = a.n_lat <= 16 ? merge_latent_kernel<4> : a.n_lat <= 32 ? merge_latent_kernel<8>
                  : a.n_lat <= 64 ? merge_latent_kernel<16> : merge_latent_kernel<32>;
@@ -770,9 +904,8 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
                               : launch_finalize_stream<3>(a, heads8, nqb, qbk, d.stream);
   }
   dim3 grid(8 * ((a.M + 31) / 32) * ((p.H + 7) / 8));
-  // up to half a workgroup per compute unit the value blocks are dealt out (one request x 128
-  // heads 40.1 -> 37.2 us a step, 8 x 16 heads 31.3 -> 27.8); from 256 workgroups on that costs 7 us,
-  // since every workgroup reads all latent partials
+  // up to half a workgroup per compute unit the value blocks are dealt out; from 256 workgroups on that
+  // costs 7 us, since every workgroup reads all latent partials
   const bool split = grid.x <= NUM_CU / 2;
   if (split && a.n_lat >= 1 && a.n_lat <= 4) grid.x *= 4;
   switch (a.n_lat) {

@@ -180,6 +180,23 @@ def test_latent_partials_of_every_merge_size(chunks, batch, gpu_device, tune):
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"merge_{chunks}_{batch}")
 
 
+@pytest.mark.parametrize("heads,batch,chunks", [(16, 1, 1), (16, 3, 4), (128, 2, 2), (48, 5, 4), (16, 16, 5),
+                                                (16, 32, 3), (16, 33, 3), (128, 4, 6)])
+@pytest.mark.parametrize("splits", [0, 1, 4, 19])
+def test_merge_and_projection_in_one_launch(splits, heads, batch, chunks, gpu_device, tune):
+    """16 to 528 rows, 1 to 6 latent partials beside none to 19 naive ones (16 are requested up front),
+    some requests without a suffix and, without a prefix, with nothing to see at all."""
+    tune(T.TUNE_PREFIX_SPLITS, splits)
+    tune(T.TUNE_SUFFIX_CHUNK, 64)
+    spec = W.small_spec(name="one_launch", dtype="bf16", batch=batch, heads=heads, q_len=1,
+                        prefix_len=128 * splits, suffix_min=0, suffix_max=64 * chunks, seed=660 + splits)
+    wl = W.make_workload(spec)
+    ref, ref_lse = O.mla_decode_absorb_all_heads(**wl.as_float64())
+    print(f"merge and projection {heads} x {batch}, {chunks} + {splits} partials", flush=True)
+    got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"one_launch/{heads}x{batch}/{chunks}+{splits}")
+
+
 def test_streaming_projection_with_three_naive_partials(gpu_device, tune):
     """200 requests x 128 heads in three prefix splits: the streaming up-projection with three naive
     partials per row (LDS full to the byte), runs of 3, 3 and 1 blocks, a ragged last block and
