@@ -35,6 +35,8 @@ constexpr int EX_ROPE_OFF = TOK_BLK * EX_ROW_BYTES;        // 32 KiB of latent r
 constexpr int EX_TILE_BYTES = EX_ROPE_OFF + 4 * 1024;      // and the four rope fragments
 constexpr int EX_RING = 4;
 constexpr int EX_LDS_BYTES = EX_RING * EX_TILE_BYTES;      // 144 KiB
+constexpr int EX_W_PIECE = 32 * 256;   // of the weights on their way to the registers
+static_assert(4 * 3 * EX_W_PIECE <= 3 * EX_TILE_BYTES, "three pieces per wavefront beside the first tile");
 constexpr int EX_DMA = 9;        // transfers of a wavefront per tile: 8 rows, 1 rope fragment
 constexpr int EX_NKS = D_L / 16;                           // 32 k-steps of an MFMA
 constexpr int EX_SYNC_KS = 22;   // k-step of a block behind which the next tile must have landed
@@ -100,36 +102,52 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
     }
   };
 
+  // The first tile is requested in front of the weights.
+  static_for<EX_DMA>([&](auto p_) { issue(0, 0, p_); });
+
   // ---- weights: fragment (i, ks) = rows 64 half + 32 i + n, k = 16 ks + 8 g .. + 7.  They come
-  // through this wavefront's slot of the ring, 32 whole rows at a time, like tokens: read straight
-  // into the registers, 32 bytes of 32 rows per load, they took 4 us longer (14.3 against 10.4 us
-  // for 1003 tokens x 16 heads).
+  // through LDS in pieces of 32 rows x 128 columns, three of a wavefront's eight under way at a time
+  // in the ring's other slots: row r of a piece at r * 256, its 16-byte chunk c in place c ^ (r & 15).
+  // (32 whole rows at a time, each half waited for by itself and the first tiles behind them, they
+  // held up 1003 tokens x 16 heads by 1.3 us, 10.3 against 9.0; read straight into the registers, 32 bytes of 32 rows
+  // per load, by another 4 us.)
   bf16x8 w[2][EX_NKS];
   {
+    constexpr int PIECES = 8, AHEAD = 3, DMAS = EX_W_PIECE / 1024;
     const char* wp = (const char*)((IS_V ? a.w_uv : a.w_uk) + ((size_t)h * 128 + 64 * half) * D_L);
-    char* mine = smem + wave * EX_TILE_BYTES;
-    const uint32_t rd = lds_addr(mine) + n * EX_ROW_BYTES;
-    const uint32_t swz = (uint32_t)(g ^ (n & 15)) << 4;
-    static_for<2>([&](auto i_) {
-      constexpr int i = decltype(i_)::value;
+    char* mine = smem + EX_TILE_BYTES + wave * (AHEAD * EX_W_PIECE);
+    const uint32_t rd = lds_addr(mine) + n * 256, swz = (uint32_t)(g ^ (n & 15)) << 4;
+    uint32_t off[4];   // rows 4 t .. 4 t + 3, 16 lanes each
 #pragma unroll
-      for (int r = 0; r < 32; r++)
-        dma16(wp + (32 * i + r) * EX_ROW_BYTES + ((lane ^ (r & 15)) << 4), mine + r * EX_ROW_BYTES);
-      vm_wait<0>();
-      static_for<EX_NKS>([&](auto ks_) {
+    for (int t = 0; t < 4; t++)
+      off[t] = (lane >> 4) * EX_ROW_BYTES + (((lane & 15) ^ (4 * t + (lane >> 4))) << 4);
+    auto request = [&](auto p_) __attribute__((always_inline)) {
+      constexpr int p = decltype(p_)::value, i = p >> 2, kq = p & 3;
+#pragma unroll
+      for (int t = 0; t < DMAS; t++)
+        dma16(wp + (32 * i + 4 * t) * EX_ROW_BYTES + 256 * kq + off[t & 3],
+              mine + (p % AHEAD) * EX_W_PIECE + t * 1024);
+    };
+    static_for<AHEAD>([&](auto p_) { request(p_); });
+    static_for<PIECES>([&](auto p_) {
+      constexpr int p = decltype(p_)::value, i = p >> 2, kq = p & 3;
+      constexpr int behind = PIECES - 1 - p < AHEAD - 1 ? PIECES - 1 - p : AHEAD - 1;
+      vm_wait<behind * DMAS>();
+      static_for<8>([&](auto ks_) {
         constexpr int ks = decltype(ks_)::value;
-        w[i][ks] = lds_read_b128<256 * (ks >> 3)>(rd + (swz ^ ((2 * ks & 15) << 4)));
+        w[i][8 * kq + ks] = lds_read_b128<(p % AHEAD) * EX_W_PIECE>(rd + (swz ^ (ks << 5)));
       });
-      static_for<EX_NKS / 4>([&](auto k_) {
-        constexpr int k = 4 * decltype(k_)::value;
+      static_for<2>([&](auto k_) {
+        constexpr int k = 8 * kq + 4 * decltype(k_)::value;
         lgkm_wait<0>(w[i][k], w[i][k + 1], w[i][k + 2], w[i][k + 3]);
         asm volatile("" : "+a"(w[i][k]), "+a"(w[i][k + 1]), "+a"(w[i][k + 2]), "+a"(w[i][k + 3]));
       });
+      if constexpr (p + AHEAD < PIECES) request(std::integral_constant<int, p + AHEAD>{});
     });
-    raw_barrier();   // the ring is free
+    raw_barrier();   // slots 1 to 3 are free, and the first tile is there
   }
-  static_for<EX_RING - 1>([&](auto b_) {
-    constexpr int b = decltype(b_)::value;
+  static_for<EX_RING - 2>([&](auto b_) {
+    constexpr int b = decltype(b_)::value + 1;
     static_for<EX_DMA>([&](auto p_) { issue(b, b * EX_TILE_BYTES, p_); });
   });
 
@@ -232,10 +250,9 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
         store_rope(blk);
       }
       if constexpr (ks == EX_SYNC_KS) {
-        // The transfers of block blk + 1 have landed (those of blocks 0, 1 and 2 had before the
-        // walk).  Younger and possibly in flight: the nine of block blk + 2 and this block's
-        // five stores.
-        if constexpr (!FIRST) vm_wait<EX_DMA + EX_STORES>();
+        // The transfers of block blk + 1 have landed.  Younger and possibly in flight: the nine of
+        // block blk + 2 and this block's five stores (of the first block: the rope fragment's).
+        vm_wait<EX_DMA + (FIRST ? 1 : EX_STORES)>();
         raw_barrier();
       }
       // transfers: two of block blk + 3 behind the barrier, the other seven in the next block
@@ -249,8 +266,6 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
 
   constexpr std::integral_constant<int, 0> P0{};
   constexpr std::integral_constant<int, 1> P1{};
-  vm_wait<0>();
-  raw_barrier();
   static_for<6>([&](auto ks_) { read_frag(0, ks_); });
   block(0, P0, std::true_type{});
   int blk = 1;
@@ -299,7 +314,7 @@ __global__ void __launch_bounds__(256, 1) expand_gemm_kernel(ExpandArgs a) {
 }
 
 // Token ranges per head.  One workgroup fits per compute unit, so H * splits workgroups take
-// ceil(H splits / 256) turns of a start-up (launch and weights: 7 us, about EX_START blocks of
+// ceil(H splits / 256) turns of a start-up (launch and weights: 6 us; EX_START blocks of
 // 1.85 us) and ceil(blocks / splits) blocks each.  For every number of turns the most ranges that
 // fit are taken; the cheapest number wins.
 constexpr int EX_START = 4, EX_MAX_TURNS = 8;
