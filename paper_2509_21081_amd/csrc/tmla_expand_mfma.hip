@@ -19,7 +19,7 @@
 // Measured on MI355X against a tile of 256 tokens x 256 outputs per workgroup with the whole
 // contraction streamed through LDS and an epilogue of its own: 32768 tokens x 128 heads 1573 ->
 // 930 to 975 us (1.13 to 1.18 PFLOP/s with 2.8 TB/s of stores; 800 us without the stores, 690 us
-// without any transfer), 4096 x 128 194 -> 126 us, 1003 x 16 20.0 -> 10.4 us.  Stores without the
+// without any transfer), 4096 x 128 194 -> 126 us, 1003 x 16 20.0 -> 9.4 us.  Stores without the
 // non-temporal hint: 1240 us.
 #include <algorithm>
 #include <type_traits>
@@ -40,7 +40,6 @@ static_assert(4 * 3 * EX_W_PIECE <= 3 * EX_TILE_BYTES, "three pieces per wavefro
 constexpr int EX_DMA = 9;        // transfers of a wavefront per tile: 8 rows, 1 rope fragment
 constexpr int EX_NKS = D_L / 16;                           // 32 k-steps of an MFMA
 constexpr int EX_SYNC_KS = 22;   // k-step of a block behind which the next tile must have landed
-constexpr int EX_STORES = 5;     // vector stores of a wavefront per finished block (4 + rope)
 
 struct ExpandArgs {
   const __bf16* c; int64_t c_stride;      // latent rows [ntok, 512] (element stride between rows)
@@ -48,7 +47,7 @@ struct ExpandArgs {
   const __bf16* w_uk; const __bf16* w_uv; // [H, 128, 512]
   __bf16* k_out; __bf16* v_out;
   int64_t ntok, ntb;                      // tokens; blocks of 32 tokens
-  int H, splits, units;                   // units = H * splits workgroups
+  int H, splits, units;                   // units = H * splits workgroups (twice that in halves)
 };
 
 // The weights sit in accumulation registers and the sums in vector registers, which only assembly
@@ -78,10 +77,14 @@ __device__ inline void expand_drain() {
 // r * 1024, its 16-byte chunk c in slot c ^ (r & 15): the 16 rows a 16-byte read serves at a time
 // fall on distinct banks.  Behind the rows, the rope part in fragment order, one fragment per
 // wavefront.
-template <bool IS_V>
+// NI: 32-row blocks of the weights per wavefront -- two, or one where the workgroup has half of the
+// head's rows (K or V) to itself.  ROPE: the workgroup writes the rope part as well.
+template <bool IS_V, int NI, bool ROPE>
 __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int h, int64_t b0,
                                             int64_t b1, int wave, int lane) {
-  const int n = lane & 31, g = lane >> 5, half = wave & 1;   // half: 64 of the 128 K or V rows
+  const int n = lane & 31, g = lane >> 5;
+  const int rb0 = NI == 2 ? 2 * (wave & 1) : wave;   // first of the 32-row blocks of the 128 K or V rows
+  constexpr int STORES = 2 * NI + ROPE;              // vector stores of a wavefront per finished block
   const int nblk = (int)(b1 - b0);
 
   // ---- transfers: wavefront w moves rows 8 w .. 8 w + 7 of a tile and rope fragment w; rows past
@@ -105,16 +108,16 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
   // The first tile is requested in front of the weights.
   static_for<EX_DMA>([&](auto p_) { issue(0, 0, p_); });
 
-  // ---- weights: fragment (i, ks) = rows 64 half + 32 i + n, k = 16 ks + 8 g .. + 7.  They come
+  // ---- weights: fragment (i, ks) = rows 32 (rb0 + i) + n, k = 16 ks + 8 g .. + 7.  They come
   // through LDS in pieces of 32 rows x 128 columns, three of a wavefront's eight under way at a time
   // in the ring's other slots: row r of a piece at r * 256, its 16-byte chunk c in place c ^ (r & 15).
   // (32 whole rows at a time, each half waited for by itself and the first tiles behind them, they
-  // held up 1003 tokens x 16 heads by 1.3 us, 10.3 against 9.0; read straight into the registers, 32 bytes of 32 rows
-  // per load, by another 4 us.)
-  bf16x8 w[2][EX_NKS];
+  // held up 1003 tokens x 16 heads by 1.3 us, 10.3 against 9.0; read straight into the registers, 32
+  // bytes of 32 rows per load, by another 4 us.)
+  bf16x8 w[NI][EX_NKS];
   {
-    constexpr int PIECES = 8, AHEAD = 3, DMAS = EX_W_PIECE / 1024;
-    const char* wp = (const char*)((IS_V ? a.w_uv : a.w_uk) + ((size_t)h * 128 + 64 * half) * D_L);
+    constexpr int PIECES = 4 * NI, AHEAD = 3, DMAS = EX_W_PIECE / 1024;
+    const char* wp = (const char*)((IS_V ? a.w_uv : a.w_uk) + ((size_t)h * 128 + 32 * rb0) * D_L);
     char* mine = smem + EX_TILE_BYTES + wave * (AHEAD * EX_W_PIECE);
     const uint32_t rd = lds_addr(mine) + n * 256, swz = (uint32_t)(g ^ (n & 15)) << 4;
     uint32_t off[4];   // rows 4 t .. 4 t + 3, 16 lanes each
@@ -159,7 +162,7 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
   __bf16* k_dst = a.k_out + blk_base * K_BLK_ELEMS + lane * 8;
   __bf16* v_dst = a.v_out + blk_base * V_BLK_ELEMS + lane * 8;
 
-  f32x16 acc[2][2];      // [parity of the block][32-row block of the weights]
+  f32x16 acc[2][NI];     // [parity of the block][32-row block of the weights]
   bf16x8 rope;           // this wavefront's rope fragment of the block at work
   bf16x8 fr[8];          // fragments on their way from LDS, six ahead
 
@@ -175,7 +178,7 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
     // chunk 2 ks + g: its low four bits are swizzled, the high two select 256 bytes
     fr[ks & 7] = lds_read_b128<256 * (ks >> 3)>(base + (sw ^ ((2 * ks & 15) << 4)));
   };
-  // stores a quarter of this wavefront's part of the finished block blk
+  // stores one of 2 NI pieces of this wavefront's part of the finished block blk
   auto store_piece = [&](int blk, auto par_, auto piece_, auto tail_) __attribute__((always_inline)) {
     constexpr int P = decltype(par_)::value, piece = decltype(piece_)::value;
     constexpr bool TAIL = decltype(tail_)::value;
@@ -184,7 +187,7 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
     asm volatile("" : "+v"(d));   // (no conversion is moved up to the MFMAs that form the sums)
     bf16x8 o;
     if constexpr (IS_V) {
-      // rows = tokens 16 hp + 4 g + 8 (e / 4) + e % 4, column d = 64 half + 32 i + n
+      // rows = tokens 16 hp + 4 g + 8 (e / 4) + e % 4, column d = 32 (rb0 + i) + n
 #pragma unroll
       for (int e = 0; e < 8; e++) o[e] = (__bf16)d[8 * hp + e];
       if constexpr (TAIL) {
@@ -194,9 +197,9 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
           if (acc_row(8 * hp + e, g) >= left) o[e] = (__bf16)0.f;
       }
       __builtin_nontemporal_store(o, (bf16x8*)(v_dst + (int64_t)blk * V_BLK_ELEMS +
-                                               ((hp * 4 + 2 * half + i) * 64) * 8));
+                                               ((hp * 4 + rb0 + i) * 64) * 8));
     } else {
-      // column = token n, rows d = 64 half + 32 i + 16 hp + 8 x + 4 g + (0..3), x = 0, 1: the two
+      // column = token n, rows d = 32 (rb0 + i) + 16 hp + 8 x + 4 g + (0..3), x = 0, 1: the two
       // halves of the wavefront trade so that a lane holds eight consecutive d of its token
       typedef int int2v __attribute__((ext_vector_type(2)));
       typedef int int4v __attribute__((ext_vector_type(4)));
@@ -214,7 +217,7 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
         if ((b0 + blk) * TOK_BLK + n >= a.ntok) w4 = int4v{0, 0, 0, 0};
       o = __builtin_bit_cast(bf16x8, w4);
       __builtin_nontemporal_store(o, (bf16x8*)(k_dst + (int64_t)blk * K_BLK_ELEMS +
-                                               ((2 * (2 * half + i) + hp) * 64) * 8));
+                                               ((2 * (rb0 + i) + hp) * 64) * 8));
     }
   };
   auto store_rope = [&](int blk) __attribute__((always_inline)) {
@@ -239,20 +242,22 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
       if constexpr (ks + 6 < EX_NKS) read_frag(cur, std::integral_constant<int, ks + 6>{});
       else read_frag(next, std::integral_constant<int, ks + 6 - EX_NKS>{});
       expand_mfma<IS_V, ks == 0, true>(acc[P][0], fr[ks & 7], w[0][ks]);
-      expand_mfma<IS_V, ks == 0, false>(acc[P][1], fr[ks & 7], w[1][ks]);
-      if constexpr (!FIRST && ks >= 2 && ks < 18 && (ks - 2) % 4 == 0)
+      if constexpr (NI == 2) expand_mfma<IS_V, ks == 0, false>(acc[P][1], fr[ks & 7], w[1][ks]);
+      if constexpr (!FIRST && NI == 2 && ks >= 2 && ks < 18 && (ks - 2) % 4 == 0)
         store_piece(blk - 1, Q, std::integral_constant<int, (ks - 2) / 4>{}, std::false_type{});
+      if constexpr (!FIRST && NI == 1 && (ks == 6 || ks == 12))
+        store_piece(blk - 1, Q, std::integral_constant<int, ks / 6 - 1>{}, std::false_type{});
       // the rope fragment: requested behind k-step 4, there behind k-step 16 (the eleven younger
       // requests of then are six)
-      if constexpr (ks == 4) rope = lds_read_b128<EX_ROPE_OFF>(rope_addr + cur);
-      if constexpr (ks == 16) {
+      if constexpr (ROPE && ks == 4) rope = lds_read_b128<EX_ROPE_OFF>(rope_addr + cur);
+      if constexpr (ROPE && ks == 16) {
         lgkm_wait<6>(rope);
         store_rope(blk);
       }
       if constexpr (ks == EX_SYNC_KS) {
         // The transfers of block blk + 1 have landed.  Younger and possibly in flight: the nine of
-        // block blk + 2 and this block's five stores (of the first block: the rope fragment's).
-        vm_wait<EX_DMA + (FIRST ? 1 : EX_STORES)>();
+        // block blk + 2 and this block's stores (of the first block: the rope fragment's).
+        vm_wait<EX_DMA + (FIRST ? (int)ROPE : STORES)>();
         raw_barrier();
       }
       // transfers: two of block blk + 3 behind the barrier, the other seven in the next block
@@ -281,7 +286,7 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
     expand_drain();
   };
   auto finish = [&](auto par_, auto tail_) __attribute__((always_inline)) {
-    static_for<4>([&](auto p_) { store_piece(nblk - 1, par_, p_, tail_); });
+    static_for<2 * NI>([&](auto p_) { store_piece(nblk - 1, par_, p_, tail_); });
   };
   const bool tail = b1 * TOK_BLK > a.ntok;
   if (blk < nblk) {
@@ -297,6 +302,7 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
   vm_wait<0>();   // no transfer may land in LDS that another workgroup owns by then
 }
 
+template <bool HALVES>
 __global__ void __launch_bounds__(256, 1) expand_gemm_kernel(ExpandArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // consecutive workgroup ids go round-robin over the 8 XCDs: an XCD gets consecutive units, i.e.
@@ -304,13 +310,19 @@ __global__ void __launch_bounds__(256, 1) expand_gemm_kernel(ExpandArgs a) {
   const int per = (a.units + 7) / 8;
   const int unit = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   if (unit >= a.units) return;
-  const int split = unit % a.splits, h = unit / a.splits;
+  const int item = HALVES ? unit >> 1 : unit;
+  const int split = item % a.splits, h = item / a.splits;
   const int64_t b0 = a.ntb * split / a.splits, b1 = a.ntb * (split + 1) / a.splits;
   if (b0 >= b1) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  if (wave < 2) expand_walk<false>(a, smem, h, b0, b1, wave, lane);
-  else expand_walk<true>(a, smem, h, b0, b1, wave, lane);
+  if constexpr (HALVES) {
+    if (unit & 1) expand_walk<true, 1, false>(a, smem, h, b0, b1, wave, lane);
+    else expand_walk<false, 1, true>(a, smem, h, b0, b1, wave, lane);
+  } else {
+    if (wave < 2) expand_walk<false, 2, true>(a, smem, h, b0, b1, wave, lane);
+    else expand_walk<true, 2, true>(a, smem, h, b0, b1, wave, lane);
+  }
 }
 
 // Token ranges per head.  One workgroup fits per compute unit, so H * splits workgroups take
@@ -329,6 +341,16 @@ static int expand_splits(int H, int64_t ntb) {
   }
   return best_s;
 }
+// K and V of a head by workgroups of their own: half of the weights to fetch, twice the blocks, and each
+// of them bound by LDS (a fragment feeds one MFMA) rather than by the matrix cores.  Where all ranges run at
+// once, a workgroup takes 6.0 us + 1.75 per block with both and 5.2 + 1.0 with one of them (16 to
+// 64 heads, one to eight blocks, within 4 %): 200 tokens x 16 heads 7.4 / 6.3 us, 600 x 32 11.1 / 10.2,
+// 1003 x 16 9.9 / 9.4, 1003 x 32 13.0 / 13.2, 434 x 128 20.1 / 22.4.
+static bool expand_in_halves(int H, int64_t ntb, int splits) {
+  if (2 * H > NUM_CU || H * splits > NUM_CU) return false;
+  const int64_t s = std::min<int64_t>(ntb, NUM_CU / (2 * H));
+  return 5.2 + 1.0 * ((ntb + s - 1) / s) < 6.0 + 1.75 * ((ntb + splits - 1) / splits);
+}
 
 int mfma_expand(int H, int64_t ntok, const void* c, int64_t c_stride, const void* r,
                 int64_t r_stride, const void* w_uk, const void* w_uv, void* k_out, void* v_out,
@@ -340,12 +362,14 @@ int mfma_expand(int H, int64_t ntok, const void* c, int64_t c_stride, const void
   a.k_out = (__bf16*)k_out; a.v_out = (__bf16*)v_out;
   a.ntok = ntok; a.ntb = (ntok + TOK_BLK - 1) / TOK_BLK; a.H = H;
   a.splits = expand_splits(H, a.ntb);
+  const bool halves = expand_in_halves(H, a.ntb, a.splits);
+  if (halves) a.splits = (int)std::min<int64_t>(a.ntb, NUM_CU / (2 * H));
   if ((int64_t)a.splits * H > 0x7ffffff0) return TMLA_ERR_UNSUPPORTED;
-  a.units = a.splits * H;
-  static LdsOptIn lds;
-  if (lds.ensure((const void*)expand_gemm_kernel, EX_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
-  hipLaunchKernelGGL(expand_gemm_kernel, dim3((unsigned)((a.units + 7) / 8 * 8)), dim3(256),
-                     EX_LDS_BYTES, stream, a);
+  a.units = a.splits * H * (halves ? 2 : 1);
+  static LdsOptIn lds[2];
+  auto kernel = halves ? expand_gemm_kernel<true> : expand_gemm_kernel<false>;
+  if (lds[halves].ensure((const void*)kernel, EX_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((a.units + 7) / 8 * 8)), dim3(256), EX_LDS_BYTES, stream, a);
   return TMLA_OK;
 }
 

@@ -662,6 +662,13 @@ def test_expand_prefix_over_ranges_of_few_blocks(heads, ntok, gpu_device):
                            ).abs().max() == 0
 
 
+@pytest.mark.parametrize("heads,ntok", [(16, 32), (16, 255), (16, 600), (16, 1003), (16, 1790), (32, 620),
+                                        (48, 200), (64, 300), (64, 437)])
+def test_expand_prefix_with_k_and_v_apart(heads, ntok, gpu_device):
+    """Workgroups that expand a head's K or its V only: 1 to 7 blocks, the same bounds."""
+    test_expand_prefix_over_ranges_of_few_blocks(heads, ntok, gpu_device)
+
+
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("n,rows,width", [(1, 5, 128), (3, 130, 128), (7, 33, 512), (2, 1, 4)])
 def test_combine_lse_matches_definition(n, rows, width, out_dtype, gpu_device):

@@ -12,7 +12,8 @@ from tests import test_isa_hazards as hz
 
 
 @pytest.mark.parametrize("source,kernel,count", [("tmla_prefix_mfma.hip", "prefix_attn_pipelined_kernel", 2),
-                                                 ("tmla_absorb128_mfma.hip", "absorb128_kernel", 2)])
+                                                 ("tmla_absorb128_mfma.hip", "absorb128_kernel", 2),
+                                                 ("tmla_expand_mfma.hip", "expand_gemm_kernel", 2)])
 @pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="hipcc not available")
 def test_every_instance_keeps_the_wait_states(source, kernel, count):
     with tempfile.TemporaryDirectory() as tmp:
