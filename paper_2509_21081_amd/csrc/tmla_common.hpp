@@ -146,6 +146,8 @@ void launch_fill_f32(float* p, int64_t n, float v, hipStream_t stream);
 template <typename T> void simple_stage_qabs(const Plan& p, const DecodeArgs& a);
 template <typename T> void simple_stage_absorb(const Plan& p, const DecodeArgs& a);
 template <typename T> void simple_stage_finalize(const Plan& p, const DecodeArgs& a);
+// fp32: the naive and the absorb pass of a call in one launch (behind the query absorption)
+void fp32_stage_attention(const Plan& p, const DecodeArgs& a);
 
 // Matrix-core kernels (bf16).  Each returns a tmla_status.
 int mfma_expand(int H, int64_t ntok, const void* c, int64_t c_stride, const void* r,

@@ -304,13 +304,15 @@ simple_finalize_kernel(Plan p, const float* __restrict__ naive_o,
 }
 
 // ---------------------------------------------------------------- fp32 decode path
-// One workgroup of 256 threads per output row and chunk, as above, but with every global access a
-// 16-byte piece of a row that neighbouring lanes continue, and many of them in flight: a thread per
-// token (or per value column of W_UV) walking its own row one element at a time spends the time on
-// the latency of scattered 4-byte loads.  4 requests x 16 heads over 256 + 64 tokens: absorb pass
-// 42.6 -> 8.0 us, combine 10.2 -> 7.0 us, naive pass 9.4 -> 6.8 us, absorption 5.7 -> 4.2 us.
+// Small calls: what counts is how few memory round trips follow each other, how many bytes a compute
+// unit has to fetch in each, and the launches.  Every global access is a 16-byte piece of a row that
+// neighbouring lanes continue; a tile's keys and values are requested at once and read once; chunks go
+// down to 16 tokens; weights are dealt out by columns; the naive and the absorb pass, which do not
+// depend on each other, share a launch.  4 requests x 16 heads over 256 + 64 tokens, the step: 81.5 us
+// with a thread per token, 30.0 with coalesced accesses and a launch per stage, 16.8 now.
 constexpr int FP = 256;         // threads
-constexpr int FP_TILE = 64;     // tokens per tile: 16 per wavefront, four at a time
+constexpr int FP_GROUPS = FP / 16;
+constexpr int FP_TILE = 4 * FP_GROUPS;   // tokens per tile, four per group of 16 lanes
 
 // sum over the 16 lanes that share a row
 __device__ inline float sum16(float v) {
@@ -318,210 +320,247 @@ __device__ inline float sum16(float v) {
   for (int s = 8; s >= 1; s >>= 1) v += __shfl_xor(v, s);
   return v;
 }
+__device__ inline float dot4(const float4& a, const float4& b) {
+  return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
+}
+__device__ inline void fma4(float4& a, float w, const float4& x) {
+  a.x += w * x.x; a.y += w * x.y; a.z += w * x.z; a.w += w * x.w;
+}
 
-// Softmax attention of one query vector (q_lds, DK1 + 64 elements) over tokens [t0, t1): key of
-// token t = DK1 elements at k1(t) and 64 at k2(t), value = DV elements at vv(t).
-template <int DK1, int DV, typename K1, typename K2, typename VV>
-__device__ void fp32_attend(const float* q_lds, int t0, int t1, float scale, K1 k1, K2 k2, VV vv,
-                            float* o_out, float* lse_out) {
-  constexpr int NK = DK1 / 64, COLS = DV / 4, NG = FP / COLS;
-  __shared__ float s_lds[FP_TILE];
-  __shared__ float4 part[FP];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, tq = lane >> 4;
+// Softmax attention of one query vector (64 NK + 64 elements) over tokens [t0, t1): key of token t = 64
+// NK elements at k1(t) and 64 at k2(t); value = 128 elements at vv(t) (APART), or the first part of
+// the key.  A group of 16 lanes has tokens of its own and its own running maximum and sums; the groups
+// meet in LDS (part: FP_GROUPS * 64 NV floats) at the end only.
+template <int NK, bool APART, typename K1, typename K2, typename VV>
+__device__ void fp32_attend(const float* q_row, int t0, int t1, float scale, K1 k1, K2 k2, VV vv,
+                            float* part, float* o_out, float* lse_out) {
+  constexpr int NV = APART ? 2 : NK, NX = NK + 1 + (APART ? NV : 0), V0 = APART ? NK + 1 : 0;
+  __shared__ float m_lds[FP_GROUPS], l_lds[FP_GROUPS];
+  const int tid = threadIdx.x, l16 = tid & 15, grp = tid >> 4;
   if (t1 <= t0) {
     if (tid == 0) *lse_out = -INFINITY;
     return;
   }
   float4 q[NK + 1];
 #pragma unroll
-  for (int k = 0; k <= NK; k++) q[k] = *(const float4*)(q_lds + 64 * k + 4 * l16);
-  auto dot4 = [](const float4& a, const float4& b) {
-    return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
-  };
-  const int col = tid % COLS, grp = tid / COLS;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  float m_run = -INFINITY, l_run = 0.f;
+  for (int k = 0; k <= NK; k++) q[k] = *(const float4*)(q_row + 64 * k + 4 * l16);
+  float4 acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; k++) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+  float m = -INFINITY, l = 0.f;
   for (int base = t0; base < t1; base += FP_TILE) {
     const int n = min(FP_TILE, t1 - base);
-    // scores: tokens 16 wave + 4 i + tq of the tile (past the end: the last token again, unused)
-    float4 x[4][NK + 1];
+    float4 x[4][NX];
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      const int t = base + min(16 * wave + 4 * i + tq, n - 1);
+      if (FP_GROUPS * i >= n) break;   // (uniform)
+      const int t = base + min(FP_GROUPS * i + grp, n - 1);
       const float* a = k1(t);
 #pragma unroll
       for (int k = 0; k < NK; k++) x[i][k] = *(const float4*)(a + 64 * k + 4 * l16);
       x[i][NK] = *(const float4*)(k2(t) + 4 * l16);
+      if constexpr (APART) {
+        const float* v = vv(t);
+#pragma unroll
+        for (int k = 0; k < NV; k++) x[i][V0 + k] = *(const float4*)(v + 64 * k + 4 * l16);
+      }
     }
+    float s[4], m_new = m;
+    bool valid[4];
 #pragma unroll
     for (int i = 0; i < 4; i++) {
+      valid[i] = FP_GROUPS * i + grp < n;
+      s[i] = -INFINITY;
+      if (FP_GROUPS * i >= n) continue;
       float d = 0.f;
 #pragma unroll
       for (int k = 0; k <= NK; k++) d += dot4(q[k], x[i][k]);
-      d = sum16(d);
-      if (l16 == 0) s_lds[16 * wave + 4 * i + tq] = d * scale;
+      d = sum16(d) * scale;
+      if (valid[i]) s[i] = d;
+      m_new = fmaxf(m_new, s[i]);
     }
-    __syncthreads();
-    // every wavefront: lane = token
-    const float s = lane < n ? s_lds[lane] : -INFINITY;
-    float mx = s;
+    const float alpha = m == -INFINITY ? 0.f : expf(m - m_new);
+    l *= alpha;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    const float m_new = fmaxf(m_run, mx);
-    const float p = lane < n ? expf(s - m_new) : 0.f;
-    const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - m_new);
-    float sum = p;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
-    l_run = l_run * alpha + sum;
-    m_run = m_new;
-    acc.x *= alpha; acc.y *= alpha; acc.z *= alpha; acc.w *= alpha;
-    // values: thread = (column quarter, tokens grp, grp + NG, ...)
-#pragma unroll 8
-    for (int j = 0; j < FP_TILE / NG; j++) {
-      const int jj = grp + NG * j;
-      const float w = __shfl(p, jj);            // 0 past the end
-      const float4 v = *(const float4*)(vv(base + min(jj, n - 1)) + 4 * col);
-      acc.x += w * v.x; acc.y += w * v.y; acc.z += w * v.z; acc.w += w * v.w;
+    for (int k = 0; k < NV; k++) {
+      acc[k].x *= alpha; acc[k].y *= alpha; acc[k].z *= alpha; acc[k].w *= alpha;
     }
-    __syncthreads();   // the scores are read before the next tile's are written
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      if (!valid[i]) continue;
+      const float p = expf(s[i] - m_new);
+      l += p;
+#pragma unroll
+      for (int k = 0; k < NV; k++) fma4(acc[k], p, x[i][V0 + k]);
+    }
+    m = m_new;
   }
-  part[tid] = acc;
+#pragma unroll
+  for (int k = 0; k < NV; k++) *(float4*)(part + grp * (64 * NV) + 64 * k + 4 * l16) = acc[k];
+  if (l16 == 0) {
+    m_lds[grp] = m;
+    l_lds[grp] = l;
+  }
   __syncthreads();
-  if (tid < COLS) {
-    float4 o = part[tid];
+  float mx = -INFINITY, lt = 0.f, w[FP_GROUPS];
 #pragma unroll
-    for (int i = 1; i < NG; i++) {
-      const float4 x = part[tid + i * COLS];
-      o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
-    }
-    const float inv = 1.f / l_run;
-    *(float4*)(o_out + 4 * tid) = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
-    if (tid == 0) *lse_out = m_run + logf(l_run);
+  for (int i = 0; i < FP_GROUPS; i++) mx = fmaxf(mx, m_lds[i]);
+#pragma unroll
+  for (int i = 0; i < FP_GROUPS; i++) {
+    const float li = l_lds[i];
+    w[i] = li == 0.f ? 0.f : expf(m_lds[i] - mx);   // (0: a group without tokens; a NaN stays one)
+    lt += li * w[i];
   }
+  const float inv = 1.f / lt;
+  for (int c = tid; c < 64 * NV; c += FP) {
+    float o = 0.f;
+#pragma unroll
+    for (int i = 0; i < FP_GROUPS; i++) o += w[i] * part[i * (64 * NV) + c];
+    o_out[c] = o * inv;
+  }
+  if (tid == 0) *lse_out = mx + logf(lt);
 }
 
-// grid (rows, chunks), chunks as in simple_naive_kernel
-__global__ void __launch_bounds__(FP)
-fp32_naive_kernel(Plan p, const float* __restrict__ q, const float* __restrict__ pk,
-                  const float* __restrict__ pv, const float* __restrict__ sk,
-                  const float* __restrict__ sv, const int32_t* __restrict__ block_table,
-                  const int32_t* __restrict__ lens, int max_blocks, int bs_shift,
-                  int64_t pool_tokens, float scale, float* __restrict__ naive_o,
-                  float* __restrict__ naive_lse, int first_chunk) {
-  __shared__ __align__(16) float q_lds[D_QK];
+struct Fp32Attention {
+  Plan p;
+  const float *q, *pk, *pv, *sk, *sv;      // naive
+  const float *qabs, *pc, *pr, *pool;      // absorb
+  const int32_t *block_table, *lens;
+  int max_blocks, bs_shift;
+  int64_t pool_tokens;
+  float scale;
+  float *naive_o, *naive_lse, *lat_o, *lat_lse;
+  int n_lat, first_chunk;   // grid.y: n_lat absorb items, then naive chunks from first_chunk on
+};
+// grid (rows, items and chunks), as in simple_absorb_kernel and simple_naive_kernel
+__global__ void __launch_bounds__(FP) fp32_attention_kernel(Fp32Attention a) {
+  __shared__ __align__(16) float part[FP_GROUPS * D_L];
+  const Plan& p = a.p;
   const int64_t row = blockIdx.x;
-  const int chunk = first_chunk + blockIdx.y;
   const int h = (int)(row % p.H);
   const int s = (int)((row / p.H) % p.Sq);
   const int b = (int)(row / ((int64_t)p.H * p.Sq));
-  for (int i = threadIdx.x; i < D_QK; i += FP) q_lds[i] = q[row * D_QK + i];
-  __syncthreads();
-  float* o_out = naive_o + ((size_t)chunk * p.rows + row) * D_V;
-  float* l_out = naive_lse + (size_t)chunk * p.rows + row;
+  const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
+  auto phys = [=](int j) {
+    return ((size_t)bt[j >> a.bs_shift] << a.bs_shift) + (j & ((1 << a.bs_shift) - 1));
+  };
+  if ((int)blockIdx.y < a.n_lat) {
+    const int item = blockIdx.y;
+    const float* q = a.qabs + row * D_ROW;
+    float* o_out = a.lat_o + ((size_t)item * p.rows + row) * D_L;
+    float* l_out = a.lat_lse + (size_t)item * p.rows + row;
+    if (item < p.ap_chunks) {
+      const int t0 = min(p.Ls, item * p.ap_chunk), t1 = min(p.Ls, t0 + p.ap_chunk);
+      auto lat = [=](int t) { return a.pc + (size_t)t * D_L; };
+      fp32_attend<D_L / 64, false>(q, t0, t1, a.scale, lat,
+                                   [=](int t) { return a.pr + (size_t)t * D_R; }, lat, part, o_out, l_out);
+    } else {
+      const int c = item - p.ap_chunks;
+      const int vis = visible_suffix(a.lens[b], p.Sq, s);
+      const int t0 = min(vis, c * p.as_chunk), t1 = min(vis, t0 + p.as_chunk);
+      auto lat = [=](int j) { return a.pool + phys(j) * D_ROW; };
+      fp32_attend<D_L / 64, false>(q, t0, t1, a.scale, lat, [=](int j) { return lat(j) + D_L; }, lat, part,
+                                   o_out, l_out);
+    }
+    return;
+  }
+  const int chunk = a.first_chunk + blockIdx.y - a.n_lat;
+  const float* q = a.q + row * D_QK;
+  float* o_out = a.naive_o + ((size_t)chunk * p.rows + row) * D_V;
+  float* l_out = a.naive_lse + (size_t)chunk * p.rows + row;
   if (chunk < p.np_split) {
     const int t0 = chunk * p.p_chunk, t1 = min(p.Ls, t0 + p.p_chunk);
-    const float* kh = pk + (size_t)h * p.Ls * D_QK;
-    const float* vh = pv + (size_t)h * p.Ls * D_V;
-    fp32_attend<D_N, D_V>(
-        q_lds, t0, t1, scale, [=](int t) { return kh + (size_t)t * D_QK; },
+    const float* kh = a.pk + (size_t)h * p.Ls * D_QK;
+    const float* vh = a.pv + (size_t)h * p.Ls * D_V;
+    fp32_attend<D_N / 64, true>(
+        q, t0, t1, a.scale, [=](int t) { return kh + (size_t)t * D_QK; },
         [=](int t) { return kh + (size_t)t * D_QK + D_N; },
-        [=](int t) { return vh + (size_t)t * D_V; }, o_out, l_out);
+        [=](int t) { return vh + (size_t)t * D_V; }, part, o_out, l_out);
   } else {
     const int c = chunk - p.np_split;
-    const int vis = visible_suffix(lens[b], p.Sq, s);
+    const int vis = visible_suffix(a.lens[b], p.Sq, s);
     const int t0 = min(vis, c * p.ns_chunk), t1 = min(vis, t0 + p.ns_chunk);
-    const int32_t* bt = block_table + (size_t)b * max_blocks;
-    const float* kh = sk + (size_t)h * pool_tokens * D_QK;
-    const float* vh = sv + (size_t)h * pool_tokens * D_V;
-    auto phys = [=](int j) {
-      return ((size_t)bt[j >> bs_shift] << bs_shift) + (j & ((1 << bs_shift) - 1));
-    };
-    fp32_attend<D_N, D_V>(
-        q_lds, t0, t1, scale, [=](int j) { return kh + phys(j) * D_QK; },
+    const float* kh = a.sk + (size_t)h * a.pool_tokens * D_QK;
+    const float* vh = a.sv + (size_t)h * a.pool_tokens * D_V;
+    fp32_attend<D_N / 64, true>(
+        q, t0, t1, a.scale, [=](int j) { return kh + phys(j) * D_QK; },
         [=](int j) { return kh + phys(j) * D_QK + D_N; },
-        [=](int j) { return vh + phys(j) * D_V; }, o_out, l_out);
+        [=](int j) { return vh + phys(j) * D_V; }, part, o_out, l_out);
   }
 }
 
-// grid (rows, n_lat), items as in simple_absorb_kernel
+// q_abs = q_nope W_UK for up to four queries of a head and 32 latent columns: thread = (four columns,
+// every 32nd noPE dim).  grid (ceil(M / 4) * H, 16)
+constexpr int FP_QUERIES = 4;
 __global__ void __launch_bounds__(FP)
-fp32_absorb_kernel(Plan p, const float* __restrict__ qabs, const float* __restrict__ pc,
-                   const float* __restrict__ pr, const float* __restrict__ pool,
-                   const int32_t* __restrict__ block_table, const int32_t* __restrict__ lens,
-                   int max_blocks, int bs_shift, float scale, float* __restrict__ lat_o,
-                   float* __restrict__ lat_lse) {
-  __shared__ __align__(16) float q_lds[D_ROW];
-  const int64_t row = blockIdx.x;
-  const int item = blockIdx.y;
-  const int s = (int)((row / p.H) % p.Sq);
-  const int b = (int)(row / ((int64_t)p.H * p.Sq));
-  for (int i = threadIdx.x; i < D_ROW; i += FP) q_lds[i] = qabs[row * D_ROW + i];
-  __syncthreads();
-  float* o_out = lat_o + ((size_t)item * p.rows + row) * D_L;
-  float* l_out = lat_lse + (size_t)item * p.rows + row;
-  if (item < p.ap_chunks) {
-    const int t0 = min(p.Ls, item * p.ap_chunk), t1 = min(p.Ls, t0 + p.ap_chunk);
-    auto lat = [=](int t) { return pc + (size_t)t * D_L; };
-    fp32_attend<D_L, D_L>(q_lds, t0, t1, scale, lat, [=](int t) { return pr + (size_t)t * D_R; },
-                          lat, o_out, l_out);
-  } else {
-    const int c = item - p.ap_chunks;
-    const int vis = visible_suffix(lens[b], p.Sq, s);
-    const int t0 = min(vis, c * p.as_chunk), t1 = min(vis, t0 + p.as_chunk);
-    const int32_t* bt = block_table + (size_t)b * max_blocks;
-    auto lat = [=](int j) {
-      return pool + (((size_t)bt[j >> bs_shift] << bs_shift) + (j & ((1 << bs_shift) - 1))) * D_ROW;
-    };
-    fp32_attend<D_L, D_L>(q_lds, t0, t1, scale, lat, [=](int j) { return lat(j) + D_L; }, lat,
-                          o_out, l_out);
-  }
-}
-
-// q_abs = q_nope W_UK: thread = (four latent columns, half of the 128 noPE dims)
-__global__ void __launch_bounds__(FP)
-fp32_qabs_kernel(int H, const float* __restrict__ q, const float* __restrict__ w_uk,
+fp32_qabs_kernel(int H, int M, const float* __restrict__ q, const float* __restrict__ w_uk,
                  float* __restrict__ qabs) {
-  __shared__ float qn[D_N];
-  __shared__ float4 part[D_L / 4];
-  const int64_t row = blockIdx.x;
-  const int h = (int)(row % H);
-  const int tid = threadIdx.x, c = tid & 127, half = tid >> 7;
-  if (tid < D_N) qn[tid] = q[row * D_QK + tid];
+  __shared__ float qn[FP_QUERIES][D_N];
+  __shared__ float4 part[4][FP_QUERIES][8];
+  const int h = blockIdx.x % H, q0 = blockIdx.x / H * FP_QUERIES, col0 = blockIdx.y * 32;
+  const int tid = threadIdx.x, c4 = tid & 7, ks = tid >> 3, lane = tid & 63, wave = tid >> 6;
+  const float* w = w_uk + ((size_t)h * D_N + ks) * D_L + col0 + 4 * c4;
+  float4 x[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++) x[j] = *(const float4*)(w + (size_t)(32 * j) * D_L);
+  const int nq = min(FP_QUERIES, M - q0);
+  for (int i = tid; i < nq * D_N; i += FP)
+    qn[i / D_N][i % D_N] = q[((size_t)(q0 + i / D_N) * H + h) * D_QK + i % D_N];
   __syncthreads();
-  const float* w = w_uk + ((size_t)h * D_N + 64 * half) * D_L + 4 * c;
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 16
-  for (int i = 0; i < 64; i++) {
-    const float4 x = *(const float4*)(w + (size_t)i * D_L);
-    const float y = qn[64 * half + i];
-    a.x += y * x.x; a.y += y * x.y; a.z += y * x.z; a.w += y * x.w;
+#pragma unroll
+  for (int u = 0; u < FP_QUERIES; u++) {
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (u < nq) {
+#pragma unroll
+      for (int j = 0; j < 4; j++) fma4(a, qn[u][ks + 32 * j], x[j]);
+    }
+#pragma unroll
+    for (int s = 8; s <= 32; s <<= 1) {
+      a.x += __shfl_xor(a.x, s); a.y += __shfl_xor(a.y, s);
+      a.z += __shfl_xor(a.z, s); a.w += __shfl_xor(a.w, s);
+    }
+    if (lane < 8) part[wave][u][c4] = a;
   }
-  if (half) part[c] = a;
   __syncthreads();
-  if (!half) {
-    const float4 b = part[c];
-    *(float4*)(qabs + row * D_ROW + 4 * c) = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
-    if (c < D_R / 4)
-      *(float4*)(qabs + row * D_ROW + D_L + 4 * c) = *(const float4*)(q + row * D_QK + D_N + 4 * c);
+  if (tid < 8 * nq) {
+    const int u = tid >> 3;
+    float4 a = part[0][u][c4];
+#pragma unroll
+    for (int i = 1; i < 4; i++) fma4(a, 1.f, part[i][u][c4]);
+    *(float4*)(qabs + ((size_t)(q0 + u) * H + h) * D_ROW + col0 + 4 * c4) = a;
   }
+  if (col0 == 0)   // RoPE part: verbatim copy
+    for (int i = tid; i < nq * (D_R / 4); i += FP) {
+      const size_t row = (size_t)(q0 + i / (D_R / 4)) * H + h;
+      const int c = 4 * (i % (D_R / 4));
+      *(float4*)(qabs + row * D_ROW + D_L + c) = *(const float4*)(q + row * D_QK + D_N + c);
+    }
 }
 
-// steps 7 + 8 as in simple_finalize_kernel; 16 lanes share a row of W_UV[h].  A partial with LSE =
-// -inf was never written and is left out.  One with LSE = NaN (a NaN among its scores) is not: it
-// makes the row NaN, however many finite partials there are beside it.
+// steps 7 + 8 as in simple_finalize_kernel, 32 value columns of a row per workgroup; 16 lanes share a row
+// of W_UV[h].  A partial with LSE = -inf was never written and is left out.  One with LSE = NaN (a NaN
+// among its scores) is not: it makes the row NaN, however many finite partials there are beside it.
+// grid (rows, 4)
 __global__ void __launch_bounds__(FP)
 fp32_finalize_kernel(Plan p, const float* __restrict__ naive_o, const float* __restrict__ naive_lse,
                      const float* __restrict__ lat_o, const float* __restrict__ lat_lse,
                      const float* __restrict__ w_uv, float* __restrict__ out,
                      float* __restrict__ lse_out) {
   __shared__ __align__(16) float lat[D_L];
-  __shared__ float oa[D_V];
+  __shared__ float oa[32];
   const int64_t row = blockIdx.x;
+  const int d0 = blockIdx.y * 32;
   const int h = (int)(row % p.H);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, tq = lane >> 4;
+  const int tid = threadIdx.x, l16 = tid & 15, grp = tid >> 4;
   float l_a = -INFINITY;
   if (p.n_lat > 0) {
+    // (rows d0 + grp and d0 + 16 + grp of W_UV[h], requested in front of everything else)
+    float4 w[2][8];
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int k = 0; k < 8; k++)
+        w[i][k] = *(const float4*)(w_uv + ((size_t)h * D_V + d0 + 16 * i + grp) * D_L + 64 * k + 4 * l16);
     float m = -INFINITY;
     bool written = false;
 #pragma unroll 8
@@ -532,41 +571,34 @@ fp32_finalize_kernel(Plan p, const float* __restrict__ naive_o, const float* __r
     }
     if (written) {
       float z = 0.f, a0 = 0.f, a1 = 0.f;
-#pragma unroll 4
+#pragma unroll 8
       for (int i = 0; i < p.n_lat; i++) {
         const float li = lat_lse[(size_t)i * p.rows + row];
         const bool use = li != -INFINITY;
-        const float w = use ? expf(li - m) : 0.f;
-        z += w;
+        const float e = use ? expf(li - m) : 0.f;
+        z += e;
         const float2 x = *(const float2*)(lat_o + ((size_t)i * p.rows + row) * D_L + 2 * tid);
-        a0 += use ? w * x.x : 0.f;
-        a1 += use ? w * x.y : 0.f;
+        a0 += use ? e * x.x : 0.f;
+        a1 += use ? e * x.y : 0.f;
       }
       const float inv = 1.f / z;
       lat[2 * tid] = a0 * inv;
       lat[2 * tid + 1] = a1 * inv;
       l_a = m + logf(z);
       __syncthreads();
-      float4 y[8];
 #pragma unroll
-      for (int k = 0; k < 8; k++) y[k] = *(const float4*)(lat + 64 * k + 4 * l16);
-#pragma unroll 4
-      for (int it = 0; it < 8; it++) {   // rows 16 it + 4 wave + tq
-        const int d = 16 * it + 4 * wave + tq;
-        const float* w = w_uv + ((size_t)h * D_V + d) * D_L + 4 * l16;
+      for (int i = 0; i < 2; i++) {
         float s = 0.f;
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-          const float4 x = *(const float4*)(w + 64 * k);
-          s += x.x * y[k].x + x.y * y[k].y + x.z * y[k].z + x.w * y[k].w;
-        }
+        for (int k = 0; k < 8; k++) s += dot4(w[i][k], *(const float4*)(lat + 64 * k + 4 * l16));
         s = sum16(s);
-        if (l16 == 0) oa[d] = s;
+        if (l16 == 0) oa[16 * i + grp] = s;
       }
       __syncthreads();
     }
   }
-  if (tid >= D_V) return;
+  if (tid >= 32) return;
+  const size_t at = row * D_V + d0 + tid;
   float m = l_a;
   bool written = l_a != -INFINITY;
 #pragma unroll 8
@@ -575,24 +607,48 @@ fp32_finalize_kernel(Plan p, const float* __restrict__ naive_o, const float* __r
     m = fmaxf(m, li);
     written |= li != -INFINITY;
   }
+  const bool first = d0 == 0 && tid == 0;
   if (!written) {
-    out[row * D_V + tid] = 0.f;
-    if (lse_out && tid == 0) lse_out[row] = -INFINITY;
+    out[at] = 0.f;
+    if (lse_out && first) lse_out[row] = -INFINITY;
     return;
   }
   float z = 0.f, num = 0.f;
-  if (l_a != -INFINITY) { const float w = expf(l_a - m); z += w; num += w * oa[tid]; }
-#pragma unroll 4
+  if (l_a != -INFINITY) { const float e = expf(l_a - m); z += e; num += e * oa[tid]; }
+#pragma unroll 8
   for (int i = 0; i < p.n_naive; i++) {
     const float li = naive_lse[(size_t)i * p.rows + row];
     const bool use = li != -INFINITY;
-    const float w = use ? expf(li - m) : 0.f;
-    z += w;
-    const float x = naive_o[((size_t)i * p.rows + row) * D_V + tid];
-    num += use ? w * x : 0.f;
+    const float e = use ? expf(li - m) : 0.f;
+    z += e;
+    const float x = naive_o[(size_t)i * p.rows * D_V + at];
+    num += use ? e * x : 0.f;
   }
-  out[row * D_V + tid] = num / z;
-  if (lse_out && tid == 0) lse_out[row] = m + logf(z);
+  out[at] = num / z;
+  if (lse_out && first) lse_out[row] = m + logf(z);
+}
+
+static void launch_fp32_attention(const Plan& p, const DecodeArgs& a, int n_lat, int first_chunk,
+                                  int n_chunks, int64_t grid_rows) {
+  if (grid_rows == 0 || n_lat + n_chunks <= 0) return;
+  Fp32Attention f;
+  f.p = p;
+  f.q = (const float*)a.q; f.pk = (const float*)a.prefix_k; f.pv = (const float*)a.prefix_v;
+  f.sk = (const float*)a.suffix_k_pool; f.sv = (const float*)a.suffix_v_pool;
+  f.qabs = (const float*)(a.ws + p.off_qabs); f.pc = (const float*)a.prefix_ckv;
+  f.pr = (const float*)a.prefix_krope; f.pool = (const float*)a.suffix_pool;
+  f.block_table = a.block_table; f.lens = a.suffix_lens; f.max_blocks = a.max_blocks;
+  f.bs_shift = __builtin_ctz((unsigned)a.block_size);
+  f.pool_tokens = (int64_t)a.num_blocks * a.block_size;
+  f.scale = a.sm_scale;
+  f.naive_o = (float*)(a.ws + p.off_naive_o); f.naive_lse = (float*)(a.ws + p.off_naive_lse);
+  f.lat_o = (float*)(a.ws + p.off_lat_o); f.lat_lse = (float*)(a.ws + p.off_lat_lse);
+  f.n_lat = n_lat; f.first_chunk = first_chunk;
+  hipLaunchKernelGGL(fp32_attention_kernel, dim3((unsigned)grid_rows, n_lat + n_chunks), dim3(FP), 0,
+                     a.stream, f);
+}
+void fp32_stage_attention(const Plan& p, const DecodeArgs& a) {
+  launch_fp32_attention(p, a, p.n_lat, 0, p.n_naive, p.rows);
 }
 
 __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
@@ -613,12 +669,7 @@ void simple_stage_naive(const Plan& p, const DecodeArgs& a, int first_chunk, int
   if (grid_rows == 0 || n_chunks <= 0) return;
   const int64_t pool_tokens = (int64_t)a.num_blocks * a.block_size;
   if constexpr (sizeof(T) == 4) {
-    hipLaunchKernelGGL(fp32_naive_kernel, dim3((unsigned)grid_rows, n_chunks), dim3(FP), 0, a.stream,
-                       p, (const float*)a.q, (const float*)a.prefix_k, (const float*)a.prefix_v,
-                       (const float*)a.suffix_k_pool, (const float*)a.suffix_v_pool, a.block_table,
-                       a.suffix_lens, a.max_blocks, __builtin_ctz((unsigned)a.block_size),
-                       pool_tokens, a.sm_scale, (float*)(a.ws + p.off_naive_o),
-                       (float*)(a.ws + p.off_naive_lse), first_chunk);
+    launch_fp32_attention(p, a, 0, first_chunk, n_chunks, grid_rows);
   } else {
     hipLaunchKernelGGL(simple_naive_kernel<T>, dim3((unsigned)grid_rows, n_chunks), dim3(NT), 0,
                      a.stream, p, (const T*)a.q, (const T*)a.prefix_k, (const T*)a.prefix_v,
@@ -631,8 +682,8 @@ template <typename T>
 void simple_stage_qabs(const Plan& p, const DecodeArgs& a) {
   if (p.rows == 0 || p.n_lat <= 0) return;
   if constexpr (sizeof(T) == 4)
-    hipLaunchKernelGGL(fp32_qabs_kernel, dim3((unsigned)p.rows), dim3(FP), 0, a.stream, p.H,
-                       (const float*)a.q, (const float*)a.w_uk, (float*)(a.ws + p.off_qabs));
+    hipLaunchKernelGGL(fp32_qabs_kernel, dim3((p.B * p.Sq + FP_QUERIES - 1) / FP_QUERIES * p.H, 16),
+                       dim3(FP), 0, a.stream, p.H, p.B * p.Sq, (const float*)a.q, (const float*)a.w_uk, (float*)(a.ws + p.off_qabs));
   else
     hipLaunchKernelGGL(simple_qabs_kernel<T>, dim3((unsigned)p.rows), dim3(256), 0, a.stream, p.H,
                      (const T*)a.q, (const T*)a.w_uk, (T*)(a.ws + p.off_qabs));
@@ -641,11 +692,7 @@ template <typename T>
 void simple_stage_absorb(const Plan& p, const DecodeArgs& a) {
   if (p.rows == 0 || p.n_lat <= 0) return;
   if constexpr (sizeof(T) == 4)
-    hipLaunchKernelGGL(fp32_absorb_kernel, dim3((unsigned)p.rows, p.n_lat), dim3(FP), 0, a.stream, p,
-                       (const float*)(a.ws + p.off_qabs), (const float*)a.prefix_ckv,
-                       (const float*)a.prefix_krope, (const float*)a.suffix_pool, a.block_table,
-                       a.suffix_lens, a.max_blocks, __builtin_ctz((unsigned)a.block_size), a.sm_scale,
-                       (float*)(a.ws + p.off_lat_o), (float*)(a.ws + p.off_lat_lse));
+    launch_fp32_attention(p, a, p.n_lat, 0, 0, p.rows);
   else
     hipLaunchKernelGGL(simple_absorb_kernel<T>, dim3((unsigned)p.rows, p.n_lat), dim3(NT), 0,
                      a.stream, p, (const T*)(a.ws + p.off_qabs), (const T*)a.prefix_ckv,
@@ -657,7 +704,7 @@ template <typename T>
 void simple_stage_finalize(const Plan& p, const DecodeArgs& a) {
   if (p.rows == 0) return;
   if constexpr (sizeof(T) == 4)
-    hipLaunchKernelGGL(fp32_finalize_kernel, dim3((unsigned)p.rows), dim3(FP), 0, a.stream, p,
+    hipLaunchKernelGGL(fp32_finalize_kernel, dim3((unsigned)p.rows, 4), dim3(FP), 0, a.stream, p,
                        (const float*)(a.ws + p.off_naive_o), (const float*)(a.ws + p.off_naive_lse),
                        (const float*)(a.ws + p.off_lat_o), (const float*)(a.ws + p.off_lat_lse),
                        (const float*)a.w_uv, (float*)a.out, a.lse_out);

@@ -213,6 +213,20 @@ def test_streaming_projection_with_three_naive_partials(gpu_device, tune):
 
 
 @pytest.mark.parametrize("mode", ["mixed", "naive_only", "absorb_only"])
+@pytest.mark.parametrize("batch,prefix,suffix,q_len", [(1, 1, 1, 1), (1, 31, 15, 1), (1, 33, 17, 2), (3, 300, 130, 1),
+                                                       (5, 65, 33, 3), (9, 0, 100, 1), (2, 257, 0, 1)])
+def test_fp32_chunks_of_few_tokens(batch, prefix, suffix, q_len, mode, gpu_device):
+    """fp32, 16 to 240 rows: chunks down to 16 tokens, groups of 16 lanes without a token, numbers of
+    queries that are no multiple of four, one part empty; both passes in one launch."""
+    wl = W.make_workload(W.small_spec(dtype="fp32", batch=batch, heads=16, q_len=q_len, prefix_len=prefix,
+                                      suffix_min=min(q_len, suffix), suffix_max=suffix, seed=950 + prefix))
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64())
+    print(f"fp32 few tokens {mode} {batch} x {q_len} {prefix} + {suffix}", flush=True)
+    got, got_lse = Hh.run_library(wl, mode, gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "fp32", f"fp32_few/{mode}")
+
+
+@pytest.mark.parametrize("mode", ["mixed", "naive_only", "absorb_only"])
 @pytest.mark.parametrize("prefix,suffix,q_len", [(1, 64, 1), (63, 65, 2), (64, 1, 1), (65, 129, 3),
                                                  (200, 0, 1), (0, 130, 1)])
 def test_fp32_kernels_at_the_edges_of_their_tiles(prefix, suffix, q_len, mode, gpu_device):
