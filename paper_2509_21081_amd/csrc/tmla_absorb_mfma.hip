@@ -259,26 +259,8 @@ __global__ void __launch_bounds__(256, 1) absorb_attn_kernel(AbsorbArgs a) {
   }
 }
 
-// rank of every request by (suffix length descending, index ascending); order[rank] = request.
-// One wavefront per request: its lanes compare 64 other requests at a time and count
-// (a thread per request walking all lengths one by one is bound by the latency of each read:
-// 25 us for 512 requests).
-__global__ void __launch_bounds__(256) suffix_order_kernel(const int32_t* lens, int B,
-                                                           int32_t* order) {
-  const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (b >= B) return;   // wavefront-uniform
-  const int mine = lens[b];
-  // per-lane counts first (independent loads, several in flight), one reduction at the end
-  int rank = 0;
-#pragma unroll 8
-  for (int i = lane; i < B; i += 64) {
-    const int other = lens[i];
-    rank += (other > mine || (other == mine && i < b)) ? 1 : 0;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) rank += __shfl_xor(rank, off);
-  if (lane == 0) order[rank] = b;
+__global__ void __launch_bounds__(256) suffix_order_kernel(const int32_t* lens, int B, int32_t* order) {
+  rank_suffix(lens, B, order, blockIdx.x * 4 + (threadIdx.x >> 6));
 }
 
 // Workgroups are handed to the compute units in index order, each unit taking the next one when
@@ -287,13 +269,16 @@ __global__ void __launch_bounds__(256) suffix_order_kernel(const int32_t* lens, 
 // longest requests first evens that out.  Debug flags:
 // bit 14 orders whatever the grid size, bit 15 never orders.
 constexpr int ORDER_MAX_BATCH = 4096;   // the ranking is quadratic in the batch size
+static bool order_wanted(const Plan& p, long long wgs) {
+  if (p.as_chunks <= 0 || p.B < 2 || p.B > ORDER_MAX_BATCH || (debug_flags() & 0x8000)) return false;
+  return wgs > NUM_CU || (debug_flags() & 0x4000);
+}
 const int32_t* suffix_request_order(const Plan& p, const DecodeArgs& d, long long wgs) {
-  if (p.as_chunks <= 0 || !d.suffix_lens || p.B < 2 || p.B > ORDER_MAX_BATCH) return nullptr;
-  if (debug_flags() & 0x8000) return nullptr;
-  if (wgs <= NUM_CU && !(debug_flags() & 0x4000)) return nullptr;
+  if (!order_wanted(p, wgs)) return nullptr;
   int32_t* order = (int32_t*)(d.ws + p.off_order);
-  hipLaunchKernelGGL(suffix_order_kernel, dim3((p.B + 3) / 4), dim3(256), 0, d.stream,
-                     d.suffix_lens, p.B, order);
+  if (!d.ranked)
+    hipLaunchKernelGGL(suffix_order_kernel, dim3((p.B + 3) / 4), dim3(256), 0, d.stream, d.suffix_lens,
+                       p.B, order);
   return order;
 }
 
@@ -334,6 +319,37 @@ bool absorb_grid(const Plan& p, int what, int rows_per_wg, AbsorbGrid* g, long l
   return true;
 }
 
+// The kernels of a call's absorb passes.  Debug flags: bit 12 keeps the 64-row kernel, bit 13 takes the
+// 128-row kernel whatever the grid size.
+struct AbsorbKernels {
+  bool joint;              // prefix and suffixes in one launch of pre_rows rows a workgroup
+  int pre_rows, own_rows;  // 64 or 128; the suffixes' kernel: 16, 32, 64 or 128
+};
+static AbsorbKernels absorb_kernels(const Plan& p) {
+  const bool keep64 = debug_flags() & 0x1000, force128 = debug_flags() & 0x2000;
+  const int R = p.Sq * p.H;
+  AbsorbKernels k;
+  k.joint = p.abs_joint && !force128;
+  k.pre_rows = (p.ap_rows == 128 && !keep64) || force128 ? 128 : 64;
+  // 128 rows per workgroup when the request has whole blocks of them and the grid still covers
+  // the chip (measured against the 64-row kernel at L_n = 256 ... 4096: 4 to 25 % less time).
+  const bool rows128 = R % 128 == 0 && !keep64 &&
+                       (force128 || (long long)p.as_chunks * p.B * (R / 128) >= NUM_CU);
+  k.own_rows = R <= 16 ? 16 : rows128 ? 128 : R > 32 ? 64 : 32;
+  return k;
+}
+
+bool suffix_order_wanted(const Plan& p) {
+  if (p.n_lat <= 0 || p.rows == 0 || p.as_chunks <= 0) return false;
+  const AbsorbKernels k = absorb_kernels(p);
+  const int rows = k.joint ? k.pre_rows : k.own_rows;
+  if (rows <= 32) return order_wanted(p, (long long)p.as_chunks * p.B);
+  AbsorbGrid grid;
+  long long ids, wgs;
+  return absorb_grid(p, k.joint ? WITH_PREFIX | WITH_SUFFIX : WITH_SUFFIX, rows, &grid, &ids, &wgs) &&
+         order_wanted(p, wgs);
+}
+
 int mfma_absorb_attention(const Plan& p, const DecodeArgs& d) {
   if (p.n_lat <= 0 || p.rows == 0) return TMLA_OK;
   AbsorbArgs a;
@@ -352,25 +368,18 @@ int mfma_absorb_attention(const Plan& p, const DecodeArgs& d) {
   a.max_blocks = d.max_blocks; a.bs_shift = __builtin_ctz((unsigned)d.block_size);
   a.rows = p.rows;
   a.c = d.sm_scale * LOG2E;
-  // Debug flags: bit 12 keeps the 64-row kernel, bit 13 takes the 128-row kernel whatever the
-  // grid size.
-  const bool keep64 = debug_flags() & 0x1000, force128 = debug_flags() & 0x2000;
-  if (p.abs_joint && !force128)
-    return p.ap_rows == 128 && !keep64 ? mfma_absorb128_attention(p, d, a, WITH_PREFIX | WITH_SUFFIX)
-                                       : mfma_absorb64_attention(p, d, a, WITH_PREFIX | WITH_SUFFIX);
+  const AbsorbKernels k = absorb_kernels(p);
+  if (k.joint)
+    return k.pre_rows == 128 ? mfma_absorb128_attention(p, d, a, WITH_PREFIX | WITH_SUFFIX)
+                             : mfma_absorb64_attention(p, d, a, WITH_PREFIX | WITH_SUFFIX);
   if (p.ap_chunks > 0) {
-    const int rc = (p.ap_rows == 128 && !keep64) || force128
-                       ? mfma_absorb128_attention(p, d, a, WITH_PREFIX)
-                       : mfma_absorb64_attention(p, d, a, WITH_PREFIX);
+    const int rc = k.pre_rows == 128 ? mfma_absorb128_attention(p, d, a, WITH_PREFIX)
+                                     : mfma_absorb64_attention(p, d, a, WITH_PREFIX);
     if (rc != TMLA_OK || p.as_chunks == 0) return rc;
   }
-  if (a.R <= 16) return mfma_absorb16_attention(p, d, a);
-  // 128 rows per workgroup when the request has whole blocks of them and the grid still covers
-  // the chip (measured against the 64-row kernel at L_n = 256 ... 4096: 4 to 25 % less time).
-  if (a.R % 128 == 0 && !keep64 &&
-      (force128 || (long long)p.as_chunks * p.B * (a.R / 128) >= NUM_CU))
-    return mfma_absorb128_attention(p, d, a, WITH_SUFFIX);
-  if (a.R > 32) return mfma_absorb64_attention(p, d, a, WITH_SUFFIX);
+  if (k.own_rows == 16) return mfma_absorb16_attention(p, d, a);
+  if (k.own_rows == 128) return mfma_absorb128_attention(p, d, a, WITH_SUFFIX);
+  if (k.own_rows == 64) return mfma_absorb64_attention(p, d, a, WITH_SUFFIX);
   static LdsOptIn lds;
   auto kernel = absorb_attn_kernel;
   if (lds.ensure((const void*)kernel, AB_LDS_BYTES) != hipSuccess) return TMLA_ERR_HIP;

@@ -134,6 +134,8 @@ struct DecodeArgs {
   int num_blocks, block_size, max_blocks;
   float sm_scale;
   hipStream_t stream;
+  // set by the query absorption: its launch has ranked the requests for the absorb pass
+  mutable bool ranked = false;
 };
 
 // Scalar reference kernels (any dtype; the only path for fp32).
@@ -163,9 +165,11 @@ int mfma_prefix_nodes(PrefixKind kind, const Plan* plans, const DecodeArgs* args
 int mfma_naive_suffix_attention(const Plan& p, const DecodeArgs& a);
 int mfma_query_absorb(const Plan& p, const DecodeArgs& a);
 int mfma_absorb_attention(const Plan& p, const DecodeArgs& a);
-// Requests sorted by suffix length, longest first (written to the workspace by a small kernel
-// on the call's stream), for a pass that launches `wgs` workgroups; nullptr = keep the order
-// of the batch.
+// Whether the suffix pass of a call takes the requests by length, longest first.
+bool suffix_order_wanted(const Plan& p);
+// Requests sorted by suffix length, longest first (written to the workspace by the query absorption's
+// launch, or by a small kernel on the call's stream), for a pass that launches `wgs` workgroups;
+// nullptr = keep the order of the batch.
 const int32_t* suffix_request_order(const Plan& p, const DecodeArgs& a, long long wgs);
 int mfma_absorb16_attention(const Plan& p, const DecodeArgs& a);   // S_q * H <= 16
 int mfma_finalize(const Plan& p, const DecodeArgs& a);

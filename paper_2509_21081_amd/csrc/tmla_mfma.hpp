@@ -102,6 +102,25 @@ __device__ __forceinline__ float softmax_block(f32x16& s, float& m, float& l, fl
   return alpha;
 }
 
+// rank of request b by (suffix length descending, index ascending); order[rank] = request.  One
+// wavefront per request: its lanes compare 64 other requests at a time and count (a thread per
+// request walking all lengths one by one is bound by the latency of each read: 25 us for 512 requests).
+__device__ inline void rank_suffix(const int32_t* lens, int B, int32_t* order, int b) {
+  const int lane = threadIdx.x & 63;
+  if (b >= B) return;   // wavefront-uniform
+  const int mine = lens[b];
+  // per-lane counts first (independent loads, several in flight), one reduction at the end
+  int rank = 0;
+#pragma unroll 8
+  for (int i = lane; i < B; i += 64) {
+    const int other = lens[i];
+    rank += (other > mine || (other == mine && i < b)) ? 1 : 0;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) rank += __shfl_xor(rank, off);
+  if (lane == 0) order[rank] = b;
+}
+
 // Same contract as softmax_block, for blocks known to be full (no masking), with a shortcut for
 // the common case that the exponent reference is still good: the probabilities are formed
 // against the current reference straight away, and their per-lane sum doubles as the range

@@ -26,15 +26,28 @@ constexpr int QA_ROW_BYTES = 320;  // 256 + 64: 16 banks on per row, so the 4 ro
 // batches: the slice would otherwise be fetched again for every 128 queries).  The fragments of
 // the next block are requested right behind the MFMAs of the current one and arrive while its
 // rows are turned around and stored.
+// Rank: where the absorb pass behind it wants the requests by suffix length, the first `layers` of
+// the grid's z rank them, a wavefront each, beside the others (a launch of its own takes 4.8 us).
+struct RankArgs {
+  const int32_t* lens;
+  int32_t* order;
+  int B, layers;
+};
 template <int QBK>
 __global__ void __launch_bounds__(256) qabs_kernel(const __bf16* __restrict__ q,
                                                    const __bf16* __restrict__ w_uk,
-                                                   __bf16* __restrict__ qabs, int M, int H) {
+                                                   __bf16* __restrict__ qabs, int M, int H,
+                                                   RankArgs rank) {
   constexpr int ST_ROW = 272;   // row of the store staging: 256 + 16 B, rows stay 16-byte aligned
   __shared__ __attribute__((aligned(16))) char wt[128 * QA_ROW_BYTES];   // 40 KiB weight slice
   // store staging: its own region when the slice must survive for the next block, else the slice
   __shared__ __attribute__((aligned(16))) char st_own[QBK > 1 ? 4 * 32 * ST_ROW : 16];
-  const int h = blockIdx.x, lq = blockIdx.y, qs0 = blockIdx.z * QBK;
+  if ((int)blockIdx.z < rank.layers) {
+    const int wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    rank_suffix(rank.lens, rank.B, rank.order, wg * 4 + (threadIdx.x >> 6));
+    return;
+  }
+  const int h = blockIdx.x, lq = blockIdx.y, qs0 = (blockIdx.z - rank.layers) * QBK;
   const int nqs = (M + 127) / 128;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g = lane >> 5;
   // stage W_UK[h][0:128][lq*128 : lq*128+128]: 128 rows x 16 chunks of 16 B
@@ -130,12 +143,15 @@ int mfma_query_absorb(const Plan& p, const DecodeArgs& d) {
   // Four blocks of 128 queries per workgroup for large batches (measured: -13 % at 1024 queries
   // per head, nothing to gain at 256 and below), as long as the grid still covers the chip twice
   const int qbk = (nqs >= 8 && p.H * 4 * ((nqs + 3) / 4) >= 2 * NUM_CU) ? 4 : 1;
-  dim3 grid(p.H, 4, (nqs + qbk - 1) / qbk);
+  RankArgs rank = {d.suffix_lens, (int32_t*)(d.ws + p.off_order), p.B, 0};
+  d.ranked = suffix_order_wanted(p);
+  if (d.ranked) rank.layers = (p.B + 16 * p.H - 1) / (16 * p.H);
+  dim3 grid(p.H, 4, (nqs + qbk - 1) / qbk + rank.layers);
   const __bf16* q = (const __bf16*)d.q;
   const __bf16* w = (const __bf16*)d.w_uk;
   __bf16* out = (__bf16*)(d.ws + p.off_qabs);
-  if (qbk == 4) hipLaunchKernelGGL(qabs_kernel<4>, grid, dim3(256), 0, d.stream, q, w, out, M, p.H);
-  else hipLaunchKernelGGL(qabs_kernel<1>, grid, dim3(256), 0, d.stream, q, w, out, M, p.H);
+  auto kernel = qbk == 4 ? qabs_kernel<4> : qabs_kernel<1>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, d.stream, q, w, out, M, p.H, rank);
   return TMLA_OK;
 }
 
