@@ -85,7 +85,6 @@ struct Plan {
   bool abs_joint;      //   prefix and suffix in one launch, of ap_rows rows a workgroup
   int as_chunks;       // absorb over the paged suffix: chunks per request
   int as_chunk;        //   tokens per chunk (multiple of block_size)
-  bool lat_apart;      // up to four latent partials of a row are merged in fp32, not in bf16
   int n_naive;         // = np_split + ns_chunks   (128-wide partials per row)
   int n_lat;           // = ap_chunks + as_chunks  (512-wide latent partials per row)
   size_t off_qabs, off_naive_o, off_naive_lse, off_lat_o, off_lat_lse, off_order, total;

@@ -66,6 +66,17 @@ template <int OFF>
 __device__ inline void lds_write_b128(uint32_t addr, bf16x8 v) {
   asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFF) : "memory");
 }
+__device__ inline float lds_read_f32(uint32_t addr) {
+  float v;
+  asm volatile("ds_read_b32 %0, %1" : "=v"(v) : "v"(addr) : "memory");
+  return v;
+}
+// one float, waited for (with every LDS read in front of it)
+__device__ inline float lds_read_f32_now(uint32_t addr) {
+  float v;
+  asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
+  return v;
+}
 __device__ inline f32x4 lds_read_f32x4(uint32_t addr) {
   f32x4 v;
   asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");

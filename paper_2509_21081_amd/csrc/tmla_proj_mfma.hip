@@ -369,24 +369,22 @@ __global__ void __launch_bounds__(256) finalize_kernel(FinalizeArgs a) {
   finalize_tail(a, row, wave, g, l_a, oa);
 }
 
-// Same computation for a compile-time number NL <= 4 of latent partials (the common case: the
-// suffix is rarely split more).  Nothing depends on anything but the loads, so all of them --
-// partial LSEs, weight fragments, latent partials -- are issued back to back and the kernel pays
-// one memory round trip instead of one per k-step; the merge weights live in registers.
-// NN > 0: the number of naive partials is NN and they are loaded up front with everything else
-// (0: any number, loaded in the epilogue).
-// SPLIT: a workgroup takes one of the four value blocks -- small batches, where a workgroup per head
-// and query block leaves compute units idle while each of the others fetches 128 KiB of weights.
-// APART: the partials are projected one by one and merged in fp32.  Merged first, the latent row is
+// Same computation for a compile-time number NL <= 4 of latent partials and so few rows that a
+// workgroup takes one of the four value blocks: one per head and query block would leave compute
+// units idle while each of the others fetches 128 KiB of weights.  Nothing depends on anything but
+// the loads, so all of them -- partial LSEs, weight fragments, latent partials -- are issued back to
+// back and the kernel pays one memory round trip instead of one per k-step; the merge weights live
+// in registers.  NN > 0: the number of naive partials is NN and they are loaded up front with
+// everything else (0: any number, loaded in the epilogue).
+// The partials are projected one by one and merged in fp32.  Merged first, the latent row is
 // rounded to bf16 once more on top of its partials, which would make a suffix that is cut only to
 // fill the chip less precise than one left whole: 8 requests x 256 tokens x 16 heads, error of the
 // output against fp64 2.95e-3 in one chunk, 3.33e-3 in four merged first, 2.87e-3 in four apart.
-template <int NL, int NN, bool SPLIT, bool APART>
+template <int NL, int NN>
 __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
-  constexpr int MB = SPLIT ? 1 : 4;          // value blocks of 32 columns of this workgroup
-  __shared__ float red[4][MB][16][64];       // [wavefront][value block][acc register][lane]
+  __shared__ float red[4][16][64];           // [wavefront][acc register][lane]
   int h, qb, vb = 0;
-  if (!finalize_item<SPLIT>(a, h, qb, vb)) return;
+  if (!finalize_item<true>(a, h, qb, vb)) return;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int qi = qb * 32 + n;
   const bool valid = qi < a.M;
@@ -397,12 +395,9 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
   for (int i = 0; i < NL; i++) ll[i] = a.lat_lse[(size_t)i * a.rows + row];
   const __bf16* wp = a.w_uv + ((size_t)h * D_V + 32 * vb + n) * D_L + 8 * g + 128 * wave;
   const __bf16* lp = a.lat_o + row * D_L + 8 * g + 128 * wave;
-  bf16x8 wf[8][MB];
+  bf16x8 wf[8];
 #pragma unroll
-  for (int ks = 0; ks < 8; ks++)
-#pragma unroll
-    for (int mb = 0; mb < MB; mb++)
-      wf[ks][mb] = *(const bf16x8*)(wp + (size_t)(32 * mb) * D_L + 16 * ks);
+  for (int ks = 0; ks < 8; ks++) wf[ks] = *(const bf16x8*)(wp + 16 * ks);
   bf16x8 x[NL][8];
 #pragma unroll
   for (int i = 0; i < NL; i++)
@@ -410,10 +405,8 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
     for (int ks = 0; ks < 8; ks++)
       x[i][ks] = *(const bf16x8*)(lp + (size_t)i * a.rows * D_L + 16 * ks);
   NaivePrefetch<(NN > 0 ? NN : 1)> pre;
-  // the value block that this wavefront finishes (SPLIT: wavefront 0 the workgroup's only one)
-  const int own = SPLIT ? vb : wave;
   if constexpr (NN > 0) {
-    prefetch_naive(a, row, own, g, pre);
+    prefetch_naive(a, row, vb, g, pre);
 #pragma unroll
     for (int i = 0; i < NN; i++)
       asm volatile("" : "+v"(pre.lse[i]), "+v"(pre.o[i][0]), "+v"(pre.o[i][1]), "+v"(pre.o[i][2]),
@@ -424,8 +417,7 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
   // uses to save registers, and each k-step waits for its own round trip
 #pragma unroll
   for (int ks = 0; ks < 8; ks++) {
-#pragma unroll
-    for (int mb = 0; mb < MB; mb++) asm volatile("" : "+v"(wf[ks][mb]));
+    asm volatile("" : "+v"(wf[ks]));
 #pragma unroll
     for (int i = 0; i < NL; i++) asm volatile("" : "+v"(x[i][ks]));
   }
@@ -446,102 +438,73 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
 #pragma unroll
   for (int i = 0; i < NL; i++) w[i] *= inv;
 
-  f32x16 acc[MB];
+  f32x16 acc;
 #pragma unroll
-  for (int mb = 0; mb < MB; mb++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) acc[mb][v] = 0.f;
-  if constexpr (NL > 1 && APART) {
+  for (int v = 0; v < 16; v++) acc[v] = 0.f;
+  if constexpr (NL > 1) {
     // every partial projected as it is and weighted afterwards: a query is one column of the MFMA,
     // so its weight is one number per lane, and a partial that was never written spoils its own
     // column only
 #pragma unroll
     for (int i = 0; i < NL; i++) {
-      f32x16 part[MB];
+      f32x16 part;
 #pragma unroll
-      for (int mb = 0; mb < MB; mb++)
+      for (int v = 0; v < 16; v++) part[v] = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; v++) part[mb][v] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 8; ks++)
-#pragma unroll
-        for (int mb = 0; mb < MB; mb++) part[mb] = mfma32(wf[ks][mb], x[i][ks], part[mb]);
+      for (int ks = 0; ks < 8; ks++) part = mfma32(wf[ks], x[i][ks], part);
       const bool use = w[i] > 0.f;
 #pragma unroll
-      for (int mb = 0; mb < MB; mb++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) acc[mb][v] += use ? w[i] * part[mb][v] : 0.f;
-      // (four partials at once do not fit the registers beside the weights)
-      if constexpr (NL == 4) __builtin_amdgcn_sched_barrier(0);
+      for (int v = 0; v < 16; v++) acc[v] += use ? w[i] * part[v] : 0.f;
     }
   } else {
+    // a single partial is already the merged latent output (weight 1, or 0 if it saw nothing)
+    const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int ks = 0; ks < 8; ks++) {
-      bf16x8 bfrag;
-      if constexpr (NL == 1) {
-        // a single partial is already the merged latent output (weight 1, or 0 if it saw nothing)
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-        bfrag = w[0] > 0.f ? x[0][ks] : zero;
-      } else {
-        float m8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < NL; i++) {
-          const bool use = w[i] > 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; e++) m8[e] += use ? w[i] * (float)x[i][ks][e] : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; e++) bfrag[e] = (__bf16)m8[e];
-      }
-#pragma unroll
-      for (int mb = 0; mb < MB; mb++) acc[mb] = mfma32(wf[ks][mb], bfrag, acc[mb]);
-    }
+    for (int ks = 0; ks < 8; ks++) acc = mfma32(wf[ks], w[0] > 0.f ? x[0][ks] : zero, acc);
   }
 #pragma unroll
-  for (int mb = 0; mb < MB; mb++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) red[wave][mb][v][lane] = acc[mb][v];
+  for (int v = 0; v < 16; v++) red[wave][v][lane] = acc[v];
   __syncthreads();
-  if (SPLIT && wave > 0) return;
-  const int rb = SPLIT ? 0 : wave;
+  if (wave > 0 || !valid) return;
   float oa[16];
 #pragma unroll
-  for (int v = 0; v < 16; v++)
-    oa[v] = red[0][rb][v][lane] + red[1][rb][v][lane] + red[2][rb][v][lane] + red[3][rb][v][lane];
-  if (!valid) return;
-  if constexpr (NN > 0) finalize_tail_prefetched(a, row, own, g, l_a, oa, pre);
-  else finalize_tail(a, row, own, g, l_a, oa);
+  for (int v = 0; v < 16; v++) oa[v] = red[0][v][lane] + red[1][v][lane] + red[2][v][lane] + red[3][v][lane];
+  if constexpr (NN > 0) finalize_tail_prefetched(a, row, vb, g, l_a, oa, pre);
+  else finalize_tail(a, row, vb, g, l_a, oa);
 }
 
-// One latent partial (the suffix is in one chunk -- every large batch) and many queries per head:
-// a workgroup takes a run of consecutive blocks of 32 queries of its head with its share of
-// W_UV[h] resident in registers, and the partials of a block -- 32 latent rows of 1 KiB and the
-// 32 x 512 B of each naive partial -- stream through an LDS ring of whole blocks, one or two
-// blocks ahead of their use.  Wavefront w owns value columns [32 w, 32 w + 32) over the whole
-// contraction, so nothing is summed across wavefronts; the latent rows in LDS are shared by all
-// four.  A compute unit takes in data at a limited rate and every request here is a full
-// contiguous row (the per-lane fragment loads of the other kernels fetch 32 bytes per row and
-// instruction), which is what this kernel is about: it is bound by memory, not by its 32 MFMAs
-// per block and wavefront.
-//   LDS slot: latent row r at r * 1024, its 16-byte chunk c in place c ^ (r & 15) (the reads of
-//   a k-step take one chunk from each of 16 rows: the swizzle spreads them over the banks);
-//   behind it naive partial i, row r at r * 512, chunk c (of 32) in place c ^ (r & 15).
-// vmcnt bookkeeping: a block's transfers are the youngest memory operations but for the
-// transfers of the blocks behind it, so "at most TPW * (FS_NSLOT - 2) in flight" means it landed
-// (stores in between only make the wait stricter).
-constexpr int FS_X_BYTES = 32 * 1024;
-constexpr int FS_N_BYTES = 32 * 512;
-template <int NN>
-struct FsLayout {
-  static constexpr int NSLOT = NN == 1 ? 3 : 2;
-  static constexpr int SLOT = FS_X_BYTES + NN * FS_N_BYTES;
-  static constexpr int BYTES = NSLOT * SLOT;     // 144 KiB (one naive partial), 128 (two), 160 (three)
-  static constexpr int TPW = 8 + 4 * NN;         // transfers per wavefront and block
-};
+// One to four latent partials and more blocks of 32 queries than half the compute units: a workgroup
+// takes a run of consecutive blocks of its head, and everything comes through an LDS ring of 16 KiB
+// units, up to eight under way: first W_UV[h] (eight units, whose fragments then stay in registers),
+// then the partials of block after block, 32 rows x 512 B each -- half of a latent partial's columns
+// or all of a naive one's.  Wavefront w owns value columns [32 w, 32 w + 32) over the whole
+// contraction, so nothing is summed across wavefronts; the rows in LDS are shared by all four.
+// What bounds it is the data that a compute unit takes in, and a load that fetches 32 bytes from each
+// of 32 rows (MFMA fragments straight from memory) takes four times the cycles of one that fetches
+// two runs of 512: the kernel that loaded fragments took 24.0 us for 256 x 64 rows of three latent
+// partials (now 17.7 us), 13.0 for 111 x 64 rows of two latent and two naive ones (10.8), 13.7 for 64 x
+// 128 of them (12.4), 15.6 for 512 x 16 of one and eight (14.2).  With the weights as fragments: 20.2,
+// 12.8, 13.6, 18.2.  256 x 128 rows of one latent and two naive partials, where the partials were
+// streamed before: 22.0 then, 22.4 now, 92 MB.
+// Every latent partial is projected as it is and weighted afterwards: a query is one column of the
+// MFMA, so its weight is one number per lane, and a partial that was never written spoils its own
+// column only.  (Merged first, the row would be rounded to bf16 once more.)
+//   LDS slot: row r at r * 512, its 16-byte chunk c (of 32) in place c ^ (r & 15) (a read takes
+//   one chunk from each of 16 rows: the swizzle spreads them over the banks).
+//   Behind the ring: the final weight of every partial, [partial][query of the run].
+// vmcnt bookkeeping: a unit's four transfers are the youngest memory operations but for those of
+// the units behind it, so "at most 4 x (units behind it) in flight" means it landed (stores in
+// between only make the wait stricter).
+constexpr int FR_UNIT = 32 * 512;
+constexpr int FR_NSLOT = 9;
+constexpr int FR_MAX_QBK = 8;        // a thread per query of the run computes the weights
+constexpr int FR_MAX_WEIGHTS = 128;  // partials x blocks of a run
+constexpr int FR_BYTES = FR_NSLOT * FR_UNIT + FR_MAX_WEIGHTS * 32 * 4;
+static_assert(FR_BYTES <= 163840, "LDS of a compute unit");
+constexpr int FR_MAX_HEADS = 32768;  // rows of a block within 32-bit offsets
+constexpr int FR_LSE_AHEAD = 8;      // LSEs of a query held in registers (any others are read again)
 
-template <int NN>
-__global__ void __launch_bounds__(256, 1) finalize_stream_kernel(FinalizeArgs a, int qbk) {
-  using L = FsLayout<NN>;
+__global__ void __launch_bounds__(256, 1) finalize_ring_kernel(FinalizeArgs a, int qbk) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int nqb = (a.M + 31) / 32, ngrp = (nqb + qbk - 1) / qbk;
   const int id = blockIdx.x, sl = id >> 3;
@@ -550,143 +513,204 @@ __global__ void __launch_bounds__(256, 1) finalize_stream_kernel(FinalizeArgs a,
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb0 = qg * qbk, nblk = min(qbk, nqb - qb0);
+  const int nlat2 = 2 * a.n_lat, units = nlat2 + a.n_naive, total = 8 + nblk * units;
 
-  auto row_of = [&](int qb, int r) {
-    const int qi = qb * 32 + r;
-    return qi < a.M ? (size_t)qi * a.H + h : (size_t)h;
-  };
-  // the transfers of block qb into ring slot `slot` issued by this wavefront: latent rows
-  // wave, wave + 4, ...; pairs of naive rows 2 t, 2 t + 1 for t = wave, wave + 4, ...
-  auto issue_block = [&](int qb, int slot) __attribute__((always_inline)) {
-    char* dst = smem + slot * L::SLOT;
-#pragma unroll
-    for (int k = 0; k < 8; k++) {
-      const int r = wave + 4 * k;
-      const char* src = (const char*)(a.lat_o + row_of(qb, r) * D_L);
-      dma16(src + ((lane ^ (r & 15)) << 4), dst + r * 1024);
+  const uint32_t smem_base = lds_addr(smem), tab = smem_base + FR_NSLOT * FR_UNIT;
+
+  // ---- the LSEs of this thread's query, into the table of the weights
+  const int parts = a.n_lat + a.n_naive;
+  const bool mine = tid < nblk * 32 && qb0 * 32 + tid < a.M;
+  const size_t own_row = (size_t)(qb0 * 32 + tid) * a.H + h;
+  if (mine) {
+#pragma unroll 1
+    for (int i = 0; i < parts; i++) {
+      const float* src = i < a.n_lat ? a.lat_lse + i * (size_t)a.rows : a.naive_lse + (i - a.n_lat) * (size_t)a.rows;
+      __builtin_amdgcn_global_load_lds((glb_void_ptr)(src + own_row),
+                                       (lds_void_ptr)(lds_char_ptr)(smem + FR_NSLOT * FR_UNIT + (i * qbk * 32 + 64 * wave) * 4),
+                                       4, 0, 0);
     }
-#pragma unroll
-    for (int i = 0; i < NN; i++)
-#pragma unroll
-      for (int k = 0; k < 4; k++) {
-        const int t = wave + 4 * k, r = 2 * t + g;
-        const char* src = (const char*)(a.naive_o + ((size_t)i * a.rows + row_of(qb, r)) * D_V);
-        dma16(src + ((n ^ (r & 15)) << 4), dst + FS_X_BYTES + i * FS_N_BYTES + t * 1024);
-      }
-  };
-  struct Lse { float lat, naive[NN]; };
-  auto load_lse = [&](int qb, Lse& l) __attribute__((always_inline)) {
-    const size_t row = row_of(qb, n);
-    l.lat = a.lat_lse[row];
-#pragma unroll
-    for (int i = 0; i < NN; i++) l.naive[i] = a.naive_lse[(size_t)i * a.rows + row];
-  };
-
-  // W_UV[h][32 wave + n][16 ks + 8 g ..]: the A fragments of all 32 k-steps
-  bf16x8 wf[32];
-  {
-    const __bf16* wp = a.w_uv + ((size_t)h * D_V + 32 * wave + n) * D_L + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < 32; ks++) wf[ks] = *(const bf16x8*)(wp + 16 * ks);
   }
-  Lse lse_cur, lse_next;
-  load_lse(qb0, lse_cur);
-  lse_next = lse_cur;
-#pragma unroll
-  for (int j = 0; j < L::NSLOT - 1; j++)
-    if (j < nblk) issue_block(qb0 + j, j);
 
-  const uint32_t smem_base = lds_addr(smem);
-  const uint32_t x_lane = n * 1024 + ((g ^ (n & 15)) << 4);
-  const uint32_t n_lane = FS_X_BYTES + n * 512;
-  int slot = 0;
-  for (int it = 0; it < nblk; it++) {
-    const int qb = qb0 + it;
-    // block `it` has landed when only the transfers of the blocks behind it are in flight
-    if (L::NSLOT == 3 && it + 1 < nblk) vm_wait<L::TPW>();
-    else vm_wait<0>();
-    raw_barrier();   // everybody's part of the block is there; everybody is done with block it - 1
-    if (it + 1 < nblk) load_lse(qb + 1, lse_next);
-    if (it + L::NSLOT - 1 < nblk) {
-      int fill = slot - 1;
-      if (fill < 0) fill += L::NSLOT;
-      issue_block(qb + L::NSLOT - 1, fill);
+  // W_UV[h] is the ring's first eight units: all 128 rows x 128 B of each, rows 8 t ... 8 t + 7 for
+  // t = wave, wave + 4, ...; row r at r * 128, chunk c (of 8) in place c ^ ((r >> 1) & 7)
+#pragma unroll
+  for (int j = 0; j < 8; j++)
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const int r = 8 * (wave + 4 * k) + (lane >> 3);
+      dma16((const char*)(a.w_uv + ((size_t)h * D_V + r) * D_L) + j * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4),
+            smem + j * FR_UNIT + (wave + 4 * k) * 1024);
     }
-    const uint32_t sb = smem_base + slot * L::SLOT;
-    const bool valid = qb * 32 + n < a.M;
-    // a single partial is already the merged latent output (weight 1, or 0 if it saw nothing:
-    // then its row was never written and is replaced by zeros)
-    const bool any = lse_cur.lat > -INFINITY && valid;
-    const float l_a = any ? lse_cur.lat : -INFINITY;
 
-    // ---- up-projection: fragments through a ring of eight registers, eight reads ahead
-    uint32_t xa[8];
+  // the next unit into the next ring slot: rows 2 t, 2 t + 1 for t = wave, wave + 4, ...; the rows of
+  // the last block that are no query's are its last query's once more
+  int iss_qb = qb0, iss_j = 0;
+  uint32_t iss_at = 8 * FR_UNIT + wave * 1024, iss_row[4];
+  auto block_rows = [&]() __attribute__((always_inline)) {
+    const int last = a.M - 1 - iss_qb * 32;
 #pragma unroll
-    for (int j = 0; j < 8; j++) xa[j] = (sb + x_lane) ^ (j << 5);
-    bf16x8 fr[8];
-    static_for<8>([&](auto j_) {
-      constexpr int j = decltype(j_)::value;
-      fr[j] = lds_read_b128<0>(xa[j]);
-    });
+    for (int k = 0; k < 4; k++) iss_row[k] = (uint32_t)min(2 * wave + g + 8 * k, last) * (uint32_t)a.H;
+  };
+  block_rows();
+  const uint32_t chunk[2] = {(uint32_t)((n ^ (2 * wave + g)) << 4), (uint32_t)((n ^ (2 * wave + g + 8)) << 4)};
+  auto issue = [&]() __attribute__((always_inline)) {
+    const size_t row = (size_t)iss_qb * 32 * a.H + h;
+    const bool lat = iss_j < nlat2;
+    const char* src = lat ? (const char*)(a.lat_o + ((iss_j >> 1) * (size_t)a.rows + row) * D_L) + (iss_j & 1) * D_L
+                          : (const char*)(a.naive_o + ((iss_j - nlat2) * (size_t)a.rows + row) * D_V);
+    const int row_shift = lat ? 10 : 9;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+      dma16_scalar_base<false>((iss_row[k] << row_shift) + chunk[k & 1], src, smem_base, iss_at + k * 4096);
+    iss_at += FR_UNIT;
+    if (iss_at >= FR_NSLOT * FR_UNIT) iss_at -= FR_NSLOT * FR_UNIT;
+    if (++iss_j == units) {
+      iss_j = 0;
+      iss_qb++;
+      block_rows();
+    }
+  };
+
+  // waits for the next unit, requests the one eight behind it, returns where it is
+  int slot = 0, behind = total - 1;
+  auto next_unit = [&]() __attribute__((always_inline)) {
+    static_assert(FR_NSLOT == 9, "cases below");
+    if (behind >= 7) vm_wait<28>();
+    else switch (behind) {
+      case 0: vm_wait<0>(); break;
+      case 1: vm_wait<4>(); break;
+      case 2: vm_wait<8>(); break;
+      case 3: vm_wait<12>(); break;
+      case 4: vm_wait<16>(); break;
+      case 5: vm_wait<20>(); break;
+      default: vm_wait<24>();
+    }
+    raw_barrier();   // everybody's part of the unit is there; everybody is done with the one in front
+    if (behind >= 8) issue();
+    const uint32_t at = smem_base + slot * FR_UNIT;
+    if (++slot == FR_NSLOT) slot = 0;
+    behind--;
+    return at;
+  };
+  // the A fragments of all 32 k-steps: row 32 wave + n, k = 16 ks + 8 g ..
+  bf16x8 wf[32];
+  static_for<8>([&](auto j_) {
+    constexpr int j = decltype(j_)::value;
+    const uint32_t at = next_unit() + (32 * wave + n) * 128;
+#pragma unroll
+    for (int q = 0; q < 4; q++) wf[4 * j + q] = lds_read_b128<0>(at + (((2 * q + g) ^ ((n >> 1) & 7)) << 4));
+    lgkm_wait<0>(wf[4 * j], wf[4 * j + 1], wf[4 * j + 2], wf[4 * j + 3]);
+  });
+  // the weights of this thread's query in place of its LSEs: of a latent partial that was never written
+  // (LSE = -inf) 0, of a naive one -1
+  if (mine) {
+    const uint32_t own = tab + tid * 4, step = qbk * 128;
+    float l[FR_LSE_AHEAD], mx = -INFINITY, z = 0.f;
+#pragma unroll
+    for (int i = 0; i < FR_LSE_AHEAD; i++) l[i] = lds_read_f32(own + (i < parts ? i : 0) * step);
+    lgkm_wait<0>(l[0], l[1], l[2], l[3]);
+    lgkm_wait<0>(l[4], l[5], l[6], l[7]);
+#pragma unroll
+    for (int i = 0; i < 4; i++) mx = fmaxf(mx, i < a.n_lat ? l[i] : -INFINITY);
+#pragma unroll
+    for (int i = 0; i < 4; i++) z += i < a.n_lat && l[i] > -INFINITY ? __expf(l[i] - mx) : 0.f;
+    const float l_a = z > 0.f ? mx + __logf(z) : -INFINITY;
+    float m2 = l_a;
+#pragma unroll
+    for (int i = 1; i < FR_LSE_AHEAD; i++) m2 = fmaxf(m2, i >= a.n_lat && i < parts ? l[i] : -INFINITY);
+    for (int i = FR_LSE_AHEAD; i < parts; i++) m2 = fmaxf(m2, lds_read_f32_now(own + i * step));
+    const bool any = m2 > -INFINITY;
+    const float w_a = l_a > -INFINITY ? __expf(l_a - m2) : 0.f;
+    auto of = [&](float x) { return any && x != -INFINITY ? __expf(x - m2) : 0.f; };   // (NaN stays)
+    float z2 = w_a;
+#pragma unroll
+    for (int i = 1; i < FR_LSE_AHEAD; i++) z2 += i >= a.n_lat && i < parts ? of(l[i]) : 0.f;
+    for (int i = FR_LSE_AHEAD; i < parts; i++) z2 += of(lds_read_f32_now(own + i * step));
+    const float inv2 = any ? 1.f / z2 : 0.f, inv = z > 0.f ? w_a / z * inv2 : 0.f;
+    auto put_naive = [&](int i, float x) {
+      lds_write_b32(own + i * step, any && x != -INFINITY ? of(x) * inv2 : -1.f);
+    };
+#pragma unroll
+    for (int i = 0; i < FR_LSE_AHEAD; i++) {
+      if (i < a.n_lat) lds_write_b32(own + i * step, z > 0.f && l[i] > -INFINITY ? __expf(l[i] - mx) * inv : 0.f);
+      else if (i < parts) put_naive(i, l[i]);
+    }
+    for (int i = FR_LSE_AHEAD; i < parts; i++) put_naive(i, lds_read_f32_now(own + i * step));
+    lgkm_wait<0>();
+    if (a.lse_out) a.lse_out[own_row] = any ? m2 + __logf(z2) : -INFINITY;
+  }
+
+  const uint32_t x_lane = n * 512 + ((g ^ (n & 15)) << 4);
+#pragma unroll 1
+  for (int it = 0; it < nblk; it++) {
+    const uint32_t w_lane = tab + (it * 32 + n) * 4;
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; v++) acc[v] = 0.f;
-    static_for<32>([&](auto ks_) {
-      constexpr int ks = decltype(ks_)::value;
-      constexpr int later = 31 - ks < 7 ? 31 - ks : 7;
-      lgkm_wait<later>(fr[ks % 8]);
-      const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-      const bf16x8 bfrag = any ? fr[ks % 8] : zero;
-      acc = mfma32(wf[ks], bfrag, acc);
-      if constexpr (ks + 8 < 32) fr[ks % 8] = lds_read_b128<256 * ((ks + 8) >> 3)>(xa[ks % 8]);
-    });
-
-    // ---- the naive partials of this lane's value columns, then merge, normalise, store
-    NaivePrefetch<NN> pre;
+#pragma unroll 1
+    for (int i = 0; i < a.n_lat; i++) {
+      f32x16 part;
 #pragma unroll
-    for (int i = 0; i < NN; i++) {
-      pre.lse[i] = lse_cur.naive[i];
+      for (int v = 0; v < 16; v++) part[v] = 0.f;
+      static_for<2>([&](auto half_) {
+        constexpr int half = decltype(half_)::value;
+        const uint32_t sb = next_unit();
+        // fragments through a ring of eight registers, eight reads ahead
+        uint32_t xa[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) xa[j] = (sb + x_lane) ^ (j << 5);
+        bf16x8 fr[8];
+        static_for<8>([&](auto j_) {
+          constexpr int j = decltype(j_)::value;
+          fr[j] = lds_read_b128<0>(xa[j]);
+        });
+        static_for<16>([&](auto ks_) {
+          constexpr int ks = decltype(ks_)::value;
+          constexpr int later = 15 - ks < 7 ? 15 - ks : 7;
+          lgkm_wait<later>(fr[ks % 8]);
+          part = mfma32(wf[16 * half + ks], fr[ks % 8], part);
+          if constexpr (ks + 8 < 16) fr[ks % 8] = lds_read_b128<256>(xa[ks % 8]);
+        });
+      });
+      const float w = lds_read_f32_now(w_lane + i * qbk * 128);
+      const bool use = w > 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[v] += use ? w * part[v] : 0.f;
+    }
+#pragma unroll 1
+    for (int i = 0; i < a.n_naive; i++) {
+      const uint32_t sb = next_unit() + n * 512;
+      f32x4 x[4];
+#pragma unroll
+      for (int v4 = 0; v4 < 4; v4++) x[v4] = lds_read_f32x4(sb + (((8 * wave + 2 * v4 + g) ^ (n & 15)) << 4));
+      const float w = lds_read_f32_now(w_lane + (a.n_lat + i) * qbk * 128);
+      lgkm_wait<0>(x[0], x[1], x[2], x[3]);
+      const bool use = !(w < 0.f);
+#pragma unroll
+      for (int v4 = 0; v4 < 4; v4++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) acc[4 * v4 + e] += use ? w * x[v4][e] : 0.f;
+    }
+    const int qi = (qb0 + it) * 32 + n;
+    if (qi < a.M) {
+      __bf16* dst = a.out + ((size_t)qi * a.H + h) * D_V + 32 * wave + 4 * g;
 #pragma unroll
       for (int v4 = 0; v4 < 4; v4++) {
-        const int c = 8 * wave + 2 * v4 + g;
-        pre.o[i][v4] = lds_read_f32x4(sb + n_lane + i * FS_N_BYTES + ((c ^ (n & 15)) << 4));
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; e++) o[e] = (__bf16)acc[4 * v4 + e];
+        *(bf16x4*)(dst + 8 * v4) = o;
       }
     }
-    float oa[16];
-#pragma unroll
-    for (int v = 0; v < 16; v++) oa[v] = acc[v];
-#pragma unroll
-    for (int i = 0; i < NN; i++)
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(pre.o[i][0]), "+v"(pre.o[i][1]), "+v"(pre.o[i][2]), "+v"(pre.o[i][3])
-                   :: "memory");
-    if (valid) finalize_tail_prefetched(a, row_of(qb, n), wave, g, l_a, oa, pre);
-    lse_cur = lse_next;
-    slot = slot + 1 == L::NSLOT ? 0 : slot + 1;
   }
 }
 
-template <int NN>
-static int launch_finalize_stream(const FinalizeArgs& a, int heads8, int nqb, int qbk,
-                                  hipStream_t stream) {
-  static LdsOptIn lds;
-  if (lds.ensure((const void*)finalize_stream_kernel<NN>, FsLayout<NN>::BYTES) != hipSuccess)
-    return TMLA_ERR_HIP;
-  dim3 grid(heads8 * ((nqb + qbk - 1) / qbk));
-  hipLaunchKernelGGL(finalize_stream_kernel<NN>, grid, dim3(256), FsLayout<NN>::BYTES, stream, a,
-                     qbk);
-  return TMLA_OK;
-}
-
-template <int NL, bool SPLIT, bool APART>
+template <int NL>
 static void launch_finalize_few(const FinalizeArgs& a, dim3 grid, hipStream_t stream) {
-  // The prefetch costs 34 registers, which halves the wavefronts per SIMD: it pays only where a
-  // compute unit gets so few workgroups that latency, not occupancy, sets the time.
-  const bool few_wgs = SPLIT || grid.x <= 2 * NUM_CU;
-  switch (few_wgs ? a.n_naive : 0) {
-    case 1: hipLaunchKernelGGL((finalize_few_kernel<NL, 1, SPLIT, APART>), grid, dim3(256), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((finalize_few_kernel<NL, 2, SPLIT, APART>), grid, dim3(256), 0, stream, a); break;
-    default: hipLaunchKernelGGL((finalize_few_kernel<NL, 0, SPLIT, APART>), grid, dim3(256), 0, stream, a);
+  switch (a.n_naive) {
+    case 1: hipLaunchKernelGGL((finalize_few_kernel<NL, 1>), grid, dim3(256), 0, stream, a); break;
+    case 2: hipLaunchKernelGGL((finalize_few_kernel<NL, 2>), grid, dim3(256), 0, stream, a); break;
+    default: hipLaunchKernelGGL((finalize_few_kernel<NL, 0>), grid, dim3(256), 0, stream, a);
   }
 }
 
@@ -907,38 +931,27 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
                        (int64_t)p.rows);
     a.n_lat = 1;
   }
-  // one latent partial, one to three naive partials, and at least two blocks of 32 queries per
-  // compute unit: runs of up to eight blocks per workgroup, so that the grid still covers the chip
-  if (a.n_lat == 1 && p.n_naive >= 1 && p.n_naive <= 3) {
-    const int nqb = (a.M + 31) / 32;
-    const int heads8 = (p.H + 7) / 8 * 8;
-    const long long per_cu = (long long)heads8 * nqb / NUM_CU;
-    const int qbk = (int)(per_cu > 8 ? 8 : per_cu);
-    if (qbk >= 2)
-      return p.n_naive == 1   ? launch_finalize_stream<1>(a, heads8, nqb, qbk, d.stream)
-             : p.n_naive == 2 ? launch_finalize_stream<2>(a, heads8, nqb, qbk, d.stream)
-                              : launch_finalize_stream<3>(a, heads8, nqb, qbk, d.stream);
-  }
-  dim3 grid(8 * ((a.M + 31) / 32) * ((p.H + 7) / 8));
+  const int heads8 = (p.H + 7) / 8 * 8, nqb = (a.M + 31) / 32, parts = a.n_lat + a.n_naive;
+  const long long blocks = (long long)heads8 * nqb;
   // up to half a workgroup per compute unit the value blocks are dealt out; from 256 workgroups on that
   // costs 7 us, since every workgroup reads all latent partials
-  const bool split = grid.x <= NUM_CU / 2;
-  if (split && a.n_lat >= 1 && a.n_lat <= 4) grid.x *= 4;
-  switch (a.n_lat) {
-    // (SPLIT: always apart, the matrix cores idle there; else only where a whole suffix would not
-    // have been cut: batch 64 x 128 heads, two chunks of 256 tokens, 95.5 -> 98.1 us a step)
-#define TMLA_FEW(NL) \
-  if (split) launch_finalize_few<NL, true, true>(a, grid, d.stream); \
-  else if (p.lat_apart) launch_finalize_few<NL, false, true>(a, grid, d.stream); \
-  else launch_finalize_few<NL, false, false>(a, grid, d.stream)
-    case 1:
-      if (split) launch_finalize_few<1, true, false>(a, grid, d.stream);
-      else launch_finalize_few<1, false, false>(a, grid, d.stream);
-      break;
-    case 2: TMLA_FEW(2); break;
-    case 3: TMLA_FEW(3); break;
-    case 4: TMLA_FEW(4); break;
-#undef TMLA_FEW
+  const bool split = blocks <= NUM_CU / 2;
+  if (a.n_lat >= 1 && a.n_lat <= 4 && !split && parts <= FR_MAX_WEIGHTS && p.H <= FR_MAX_HEADS) {
+    // runs as short as one round of workgroups allows (every one takes in 128 KiB of weights)
+    const int per_head = std::max(1, NUM_CU / heads8);
+    const int qbk = std::min((nqb + per_head - 1) / per_head, std::min(FR_MAX_QBK, FR_MAX_WEIGHTS / parts));
+    static LdsOptIn lds;
+    if (lds.ensure((const void*)finalize_ring_kernel, FR_BYTES) != hipSuccess) return TMLA_ERR_HIP;
+    hipLaunchKernelGGL(finalize_ring_kernel, dim3(heads8 * ((nqb + qbk - 1) / qbk)), dim3(256), FR_BYTES, d.stream, a,
+                       qbk);
+    return TMLA_OK;
+  }
+  const dim3 grid((unsigned)blocks), grid4((unsigned)blocks * 4);
+  switch (split ? a.n_lat : 0) {
+    case 1: launch_finalize_few<1>(a, grid4, d.stream); break;
+    case 2: launch_finalize_few<2>(a, grid4, d.stream); break;
+    case 3: launch_finalize_few<3>(a, grid4, d.stream); break;
+    case 4: launch_finalize_few<4>(a, grid4, d.stream); break;
     default: hipLaunchKernelGGL(finalize_kernel, grid, dim3(256), 0, d.stream, a);
   }
   return TMLA_OK;

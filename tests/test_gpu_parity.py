@@ -212,6 +212,25 @@ def test_streaming_projection_with_three_naive_partials(gpu_device, tune):
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", "stream3")
 
 
+@pytest.mark.parametrize("heads,batch,chunks,splits", [(16, 257, 1, 0), (16, 290, 3, 9), (48, 100, 2, 16), (128, 33, 4, 1),
+                                                       (128, 70, 2, 3), (128, 515, 1, 1), (128, 300, 4, 30)])
+def test_projection_through_the_ring(heads, batch, chunks, splits, gpu_device, tune):
+    """Runs of one to eight blocks of 32 queries with a short last block, a last run shorter than the others, one to four
+    latent partials beside none to 30 naive ones (runs cut short by the weights' table), some requests without
+    a suffix and, without a prefix, with nothing to see at all."""
+    tune(T.TUNE_PREFIX_SPLITS, splits)
+    tune(T.TUNE_SUFFIX_CHUNK, 64)
+    spec = W.small_spec(name="ring", dtype="bf16", batch=batch, heads=heads, q_len=1, prefix_len=128 * splits,
+                        suffix_min=0, suffix_max=64 * chunks, seed=670 + splits)
+    wl = W.make_workload(spec)
+    last = (batch - 1) // 32 * 32
+    pairs = [(b, h) for b in sorted({0, 1, 31, 32, last - 1, last, batch - 1}) if b < batch for h in (0, 7, heads - 1)]
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64(), pairs=pairs)
+    print(f"projection through the ring {heads} x {batch}, {chunks} + {splits} partials", flush=True)
+    got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"ring/{heads}x{batch}/{chunks}+{splits}")
+
+
 @pytest.mark.parametrize("mode", ["mixed", "naive_only", "absorb_only"])
 @pytest.mark.parametrize("batch,prefix,suffix,q_len", [(1, 1, 1, 1), (1, 31, 15, 1), (1, 33, 17, 2), (3, 300, 130, 1),
                                                        (5, 65, 33, 3), (9, 0, 100, 1), (2, 257, 0, 1)])
