@@ -22,8 +22,14 @@ typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
 // in LDS and read through the transposing LDS load to form the A operand (rows = latent columns).
 constexpr int QA_ROW_BYTES = 320;  // 256 + 64: 16 banks on per row, so the 4 rows x 64 B of a transposing read (32 lanes) cover the 64 banks once
 
+// Queries arrive as whole rows of 256 bytes and become fragments through LDS: fetched as fragments,
+// 32 bytes from each of 32 rows an instruction, they took four times the cycles.  The RoPE parts
+// are dealt out to the four quarters and requested with everything else.  Before and after: 111
+// queries x 64 heads 7.7 -> 6.7 us, 256 x 64 10.8 -> 9.8, 512 x 16 7.8 -> 6.6, 256 x 128 16.8 -> 15.9.
+// SMALL: up to 32 queries, which the wavefronts share, each with a quarter of the slice's columns (one
+// wavefront with all of them is a longer chain): 1 x 128 6.8 -> 5.7 us, 8 x 16 4.8 -> 4.05.
 // QBK: blocks of 128 queries a workgroup takes in turn with its weight slice staged once (large
-// batches: the slice would otherwise be fetched again for every 128 queries).  The fragments of
+// batches: the slice would otherwise be fetched again for every 128 queries).  The rows of
 // the next block are requested right behind the MFMAs of the current one and arrive while its
 // rows are turned around and stored.
 // Rank: where the absorb pass behind it wants the requests by suffix length, the first `layers` of
@@ -33,15 +39,18 @@ struct RankArgs {
   int32_t* order;
   int B, layers;
 };
-template <int QBK>
-__global__ void __launch_bounds__(256) qabs_kernel(const __bf16* __restrict__ q,
+template <int QBK, bool SMALL>
+__global__ void __launch_bounds__(256, QBK > 1 ? 2 : 4) qabs_kernel(const __bf16* __restrict__ q,
                                                    const __bf16* __restrict__ w_uk,
                                                    __bf16* __restrict__ qabs, int M, int H,
                                                    RankArgs rank) {
-  constexpr int ST_ROW = 272;   // row of the store staging: 256 + 16 B, rows stay 16-byte aligned
-  __shared__ __attribute__((aligned(16))) char wt[128 * QA_ROW_BYTES];   // 40 KiB weight slice
-  // store staging: its own region when the slice must survive for the next block, else the slice
-  __shared__ __attribute__((aligned(16))) char st_own[QBK > 1 ? 4 * 32 * ST_ROW : 16];
+  constexpr int ST_ROW = 272;   // row of the query and store staging: 256 + 16 B, rows stay 16-byte aligned
+  constexpr int MB = SMALL ? 1 : 4;
+  static_assert(!SMALL || QBK == 1, "32 queries are one block");
+  // 40 KiB weight slice (four workgroups a compute unit, to the byte); query and store staging: behind it
+  // when the slice must survive for the next block, else the slice itself
+  constexpr int WT_BYTES = 128 * QA_ROW_BYTES;
+  __shared__ __attribute__((aligned(16))) char wt[WT_BYTES + (QBK > 1 ? 4 * 32 * ST_ROW : 0)];
   if ((int)blockIdx.z < rank.layers) {
     const int wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     rank_suffix(rank.lens, rank.B, rank.order, wg * 4 + (threadIdx.x >> 6));
@@ -50,43 +59,59 @@ __global__ void __launch_bounds__(256) qabs_kernel(const __bf16* __restrict__ q,
   const int h = blockIdx.x, lq = blockIdx.y, qs0 = (blockIdx.z - rank.layers) * QBK;
   const int nqs = (M + 127) / 128;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g = lane >> 5;
+  const int rr = lane >> 4, ch = lane & 15;
+  const int wq = SMALL ? 0 : wave;   // this wavefront's 32 of the 128 queries
+  // 32 queries as whole rows of 256 bytes (rows past the last one repeat it), and this workgroup's
+  // quarter of the block's RoPE parts
+  bf16x8 qr[8], rope;
+  auto load_q = [&](int qsb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      const int qq = min(qsb * 128 + wq * 32 + 4 * i + rr, M - 1);
+      qr[i] = *(const bf16x8*)(q + ((size_t)qq * H + h) * D_QK + ch * 8);
+    }
+    const int qq = min(qsb * 128 + lq * 32 + (tid >> 3), M - 1);
+    rope = *(const bf16x8*)(q + ((size_t)qq * H + h) * D_QK + D_N + (tid & 7) * 8);
+  };
+  char* mine = wt + (QBK > 1 ? WT_BYTES : 0) + wave * (32 * ST_ROW);
+  bf16x8 qf[8];
+  auto turn_q = [&]() __attribute__((always_inline)) {   // (each wavefront reads back what it wrote itself)
+#pragma unroll
+    for (int i = 0; i < 8; i++) *(bf16x8*)(mine + (4 * i + rr) * ST_ROW + ch * 16) = qr[i];
+#pragma unroll
+    for (int ks = 0; ks < 8; ks++) qf[ks] = *(const bf16x8*)(mine + n * ST_ROW + (16 * ks + 8 * g) * 2);
+  };
+  load_q(qs0);
   // stage W_UK[h][0:128][lq*128 : lq*128+128]: 128 rows x 16 chunks of 16 B
+  bf16x8 wr[8];
   {
     const __bf16* src = w_uk + ((size_t)h * D_N) * D_L + lq * 128;
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-      const int cidx = tid + 256 * i;
-      const int r = cidx >> 4, ch = cidx & 15;
-      *(bf16x8*)(wt + r * QA_ROW_BYTES + ch * 16) = *(const bf16x8*)(src + (size_t)r * D_L + ch * 8);
-    }
+    for (int i = 0; i < 8; i++) wr[i] = *(const bf16x8*)(src + (size_t)(16 * i + (tid >> 4)) * D_L + (tid & 15) * 8);
   }
-  bf16x8 qf[8];
-  auto load_q = [&](int qsb) __attribute__((always_inline)) {
-    const int qi = (qsb * 4 + wave) * 32 + n;
-    const size_t row = (size_t)(qi < M ? qi : 0) * H + h;
+  // everything is requested before anything is waited for
 #pragma unroll
-    for (int ks = 0; ks < 8; ks++) {
-      bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-      qf[ks] = qi < M ? *(const bf16x8*)(q + row * D_QK + 16 * ks + 8 * g) : z;
-    }
-  };
-  load_q(qs0);
+  for (int i = 0; i < 8; i++) asm volatile("" : "+v"(qr[i]), "+v"(wr[i]));
+  turn_q();
+  if (QBK == 1) __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 8; i++) *(bf16x8*)(wt + (16 * i + (tid >> 4)) * QA_ROW_BYTES + (tid & 15) * 16) = wr[i];
   __syncthreads();
   const int j16 = lane >> 4, r16 = lane & 15;
   // transposing read: contraction row 16*ks + 8*g + 4*half + r/4, latent 32*mb + 16*(j%2) + 4*(r%4)
-  const int a_off = (8 * g + (r16 >> 2)) * QA_ROW_BYTES + (16 * (j16 & 1) + 4 * (r16 & 3)) * 2;
+  const int a_off = (8 * g + (r16 >> 2)) * QA_ROW_BYTES + (16 * (j16 & 1) + 4 * (r16 & 3)) * 2 + (SMALL ? 64 * wave : 0);
   for (int it = 0; it < QBK; it++) {
     const int qsb = qs0 + it;
     if (qsb >= nqs) break;                    // workgroup-uniform
-    f32x16 acc[4];
+    f32x16 acc[MB];
 #pragma unroll
-    for (int mb = 0; mb < 4; mb++)
+    for (int mb = 0; mb < MB; mb++)
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[mb][v] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 8; ks++) {
 #pragma unroll
-      for (int mb = 0; mb < 4; mb++) {
+      for (int mb = 0; mb < MB; mb++) {
         const char* src = wt + a_off + (16 * ks) * QA_ROW_BYTES + 64 * mb;
         const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src));
         const short4v hi =
@@ -95,44 +120,37 @@ __global__ void __launch_bounds__(256) qabs_kernel(const __bf16* __restrict__ q,
         acc[mb] = mfma32(__builtin_bit_cast(bf16x8, both), qf[ks], acc[mb]);
       }
     }
-    if (QBK > 1 && it + 1 < QBK && qsb + 1 < nqs) load_q(qsb + 1);
+    {
+      const int qq = qsb * 128 + lq * 32 + (tid >> 3);   // RoPE part: verbatim copy
+      if (qq < M) *(bf16x8*)(qabs + ((size_t)qq * H + h) * D_ROW + D_L + (tid & 7) * 8) = rope;
+    }
+    const bool more = QBK > 1 && it + 1 < QBK && qsb + 1 < nqs;
+    if (more) load_q(qsb + 1);
     // Store through LDS: a lane holds 8-byte pieces of its query's row, 16 bytes apart from its
     // neighbour's; turned around in LDS, sixteen lanes write one query's 256 bytes of this latent
     // quarter in one piece.  With a single block the weight slice is free once everybody has
     // its fragments and serves as the staging buffer.
     if (QBK == 1) __syncthreads();
-    {
-      char* mine = (QBK > 1 ? st_own : wt) + wave * (32 * ST_ROW);
+    char* st = SMALL ? wt : mine;
 #pragma unroll
-      for (int mb = 0; mb < 4; mb++)
+    for (int mb = 0; mb < MB; mb++)
 #pragma unroll
-        for (int v4 = 0; v4 < 4; v4++) {
-          bf16x4 w;
+      for (int v4 = 0; v4 < 4; v4++) {
+        bf16x4 w;
 #pragma unroll
-          for (int e = 0; e < 4; e++) w[e] = (__bf16)acc[mb][4 * v4 + e];
-          *(bf16x4*)(mine + n * ST_ROW + (32 * mb + 8 * v4 + 4 * g) * 2) = w;
-        }
-      // (each wavefront reads back only what it wrote itself: no barrier)
-      const int rr = lane >> 4, ch = lane & 15;
-#pragma unroll
-      for (int i = 0; i < 8; i++) {
-        const int r = 4 * i + rr;
-        const bf16x8 w = *(const bf16x8*)(mine + r * ST_ROW + ch * 16);
-        const int qq = (qsb * 4 + wave) * 32 + r;
-        if (qq < M) *(bf16x8*)(qabs + ((size_t)qq * H + h) * D_ROW + lq * 128 + ch * 8) = w;
+        for (int e = 0; e < 4; e++) w[e] = (__bf16)acc[mb][4 * v4 + e];
+        *(bf16x4*)(st + n * ST_ROW + (32 * (SMALL ? wave : mb) + 8 * v4 + 4 * g) * 2) = w;
       }
-    }
-    if (lq == 0) {  // RoPE part: verbatim copy, 128 queries x 8 chunks
+    // (each wavefront reads back only what it wrote itself: no barrier, but for the shared 32 rows)
+    if (SMALL) __syncthreads();
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int cidx = tid + 256 * i;
-        const int qq = qsb * 128 + (cidx >> 3), ch = cidx & 7;
-        if (qq < M) {
-          const size_t rr = (size_t)qq * H + h;
-          *(bf16x8*)(qabs + rr * D_ROW + D_L + ch * 8) = *(const bf16x8*)(q + rr * D_QK + D_N + ch * 8);
-        }
-      }
+    for (int i = 0; i < (SMALL ? 2 : 8); i++) {
+      const int r = 4 * (SMALL ? 4 * i + wave : i) + rr;
+      const bf16x8 w = *(const bf16x8*)(st + r * ST_ROW + ch * 16);
+      const int qq = qsb * 128 + wq * 32 + r;
+      if (qq < M) *(bf16x8*)(qabs + ((size_t)qq * H + h) * D_ROW + lq * 128 + ch * 8) = w;
     }
+    if (more) turn_q();
   }
 }
 
@@ -150,7 +168,7 @@ int mfma_query_absorb(const Plan& p, const DecodeArgs& d) {
   const __bf16* q = (const __bf16*)d.q;
   const __bf16* w = (const __bf16*)d.w_uk;
   __bf16* out = (__bf16*)(d.ws + p.off_qabs);
-  auto kernel = qbk == 4 ? qabs_kernel<4> : qabs_kernel<1>;
+  auto kernel = M <= 32 ? qabs_kernel<1, true> : qbk == 4 ? qabs_kernel<4, false> : qabs_kernel<1, false>;
   hipLaunchKernelGGL(kernel, grid, dim3(256), 0, d.stream, q, w, out, M, p.H, rank);
   return TMLA_OK;
 }

@@ -212,6 +212,21 @@ def test_streaming_projection_with_three_naive_partials(gpu_device, tune):
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", "stream3")
 
 
+@pytest.mark.parametrize("batch,q_len", [(31, 1), (32, 1), (33, 1), (8, 4), (9, 4), (127, 1), (129, 1), (515, 2)])
+def test_query_absorption_of_partly_filled_blocks(batch, q_len, gpu_device):
+    """Queries per head around 32 (all wavefronts on the same 32), 128 (a wavefront each) and beyond 1024 (four
+    blocks a workgroup with 128 heads); the rows that fill a block up are nobody's."""
+    heads = 128 if batch > 500 else 16
+    spec = W.small_spec(name="absorption", dtype="bf16", batch=batch, heads=heads, q_len=q_len, prefix_len=40,
+                        suffix_min=q_len, suffix_max=30, seed=690 + batch)
+    wl = W.make_workload(spec)
+    pairs = [(b, h) for b in sorted({0, 7, batch // 2, batch - 1}) for h in (0, 7, heads - 1)]
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64(), pairs=pairs)
+    print(f"query absorption {heads} x {batch} x {q_len}", flush=True)
+    got, got_lse = Hh.run_library(wl, "absorb_only", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"absorption/{batch}x{q_len}")
+
+
 @pytest.mark.parametrize("heads,batch,chunks,splits", [(16, 257, 1, 0), (16, 290, 3, 9), (48, 100, 2, 16), (128, 33, 4, 1),
                                                        (128, 70, 2, 3), (128, 515, 1, 1), (128, 300, 4, 30)])
 def test_projection_through_the_ring(heads, batch, chunks, splits, gpu_device, tune):
