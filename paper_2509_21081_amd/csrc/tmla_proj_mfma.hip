@@ -491,7 +491,7 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
   else finalize_tail(a, row, vb, g, l_a, oa);
 }
 
-// One to four latent partials and more blocks of 32 queries than half the compute units: a workgroup
+// One to four latent partials and, as a rule, more blocks of 32 queries than half the compute units: a workgroup
 // takes a run of consecutive blocks of its head, and everything comes through an LDS ring of 16 KiB
 // units, up to eight under way: first W_UV[h] (eight units, whose fragments then stay in registers),
 // then the partials of block after block, 32 rows x 512 B each -- half of a latent partial's columns
@@ -951,13 +951,19 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
   }
   const int heads8 = (p.H + 7) / 8 * 8, nqb = (a.M + 31) / 32, parts = a.n_lat + a.n_naive;
   const long long blocks = (long long)heads8 * nqb;
-  // up to half a workgroup per compute unit the value blocks are dealt out; from 256 workgroups on that
-  // costs 7 us, since every workgroup reads all latent partials
-  const bool split = blocks <= NUM_CU / 2;
+  // Up to half a workgroup per compute unit the value blocks are dealt out, unless their rows make it more
+  // work to read all latent partials four times than the ring has with half of the units: 32 x 128 rows of
+  // four partials 14.7 us and 11.7 through the ring, 60 x 64 rows of three and more naive ones 13.4
+  // and 11.6; 32 x 64 rows 8.9 and 11.0, 12 x 128 rows 9.8 and 10.9, 250 x 16 rows of one and sixteen
+  // naive ones 13.1 and 15.8.
+  const bool many_rows = p.rows > 3072 && a.n_lat >= 2 && 2 * a.n_lat + a.n_naive <= 10;
+  const bool split = blocks <= NUM_CU / 2 && !many_rows;
   if (a.n_lat >= 1 && a.n_lat <= 4 && !split && parts <= FR_MAX_WEIGHTS && p.H <= FR_MAX_HEADS) {
-    // runs as short as one round of workgroups allows (every one takes in 128 KiB of weights)
-    const int per_head = std::max(1, NUM_CU / heads8);
-    const int qbk = std::min((nqb + per_head - 1) / per_head, std::min(FR_MAX_QBK, FR_MAX_WEIGHTS / parts));
+    // runs as short as one round of workgroups allows (every one takes in 128 KiB of weights); more
+    // rounds than one as even as can be (2100 queries x 64 heads, runs of eight and of six: 76.6, 69.6 us)
+    auto ceil_div = [](int x, int y) { return (x + y - 1) / y; };
+    const int per_head = std::max(1, NUM_CU / heads8), one_round = ceil_div(nqb, per_head);
+    const int rounds = ceil_div(one_round, std::min(FR_MAX_QBK, FR_MAX_WEIGHTS / parts)), qbk = ceil_div(one_round, rounds);
     static LdsOptIn lds;
     if (lds.ensure((const void*)finalize_ring_kernel, FR_BYTES) != hipSuccess) return TMLA_ERR_HIP;
     hipLaunchKernelGGL(finalize_ring_kernel, dim3(heads8 * ((nqb + qbk - 1) / qbk)), dim3(256), FR_BYTES, d.stream, a,

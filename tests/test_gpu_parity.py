@@ -228,7 +228,8 @@ def test_query_absorption_of_partly_filled_blocks(batch, q_len, gpu_device):
 
 
 @pytest.mark.parametrize("heads,batch,chunks,splits", [(16, 257, 1, 0), (16, 290, 3, 9), (48, 100, 2, 16), (128, 33, 4, 1),
-                                                       (128, 70, 2, 3), (128, 515, 1, 1), (128, 300, 4, 30)])
+                                                       (128, 70, 2, 3), (128, 515, 1, 1), (128, 300, 4, 30),
+                                                       (64, 56, 2, 4), (128, 25, 3, 4)])
 def test_projection_through_the_ring(heads, batch, chunks, splits, gpu_device, tune):
     """Runs of one to eight blocks of 32 queries with a short last block, a last run shorter than the others, one to four
     latent partials beside none to 30 naive ones (runs cut short by the weights' table), some requests without
