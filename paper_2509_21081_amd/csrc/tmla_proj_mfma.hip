@@ -2,8 +2,7 @@
 //   * query absorption  Q_abs = Q_nope W_UK  (paper Algorithm 1 step 5), plus the copy of the
 //     RoPE part, producing the 576-wide absorbed query rows the latent attention consumes;
 //   * up-projection O_A = O_lat W_UV^T (step 7) fused with the LSE combine (step 8): the latent
-//     split partials are merged on the fly while they are loaded as the MFMA operand, projected,
-//     then merged with the 128-wide naive partials and stored.
+//     split partials are projected and merged in fp32 with the 128-wide naive partials, and stored.
 // Both are per-head GEMMs with the queries on the MFMA column axis (transposed products, see
 // tmla_mfma.hpp), so all per-query softmax weights are per-lane scalars.
 #include "tmla_common.hpp"
