@@ -379,7 +379,9 @@ __device__ void fp32_attend(const float* q_row, int t0, int t1, float scale, K1 
       if (valid[i]) s[i] = d;
       m_new = fmaxf(m_new, s[i]);
     }
-    const float alpha = m == -INFINITY ? 0.f : expf(m - m_new);
+    // (a score of -inf has weight 0, also where the group has seen nothing else so far)
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = expf(m - m_use);
     l *= alpha;
 #pragma unroll
     for (int k = 0; k < NV; k++) {
@@ -388,7 +390,7 @@ __device__ void fp32_attend(const float* q_row, int t0, int t1, float scale, K1 
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       if (!valid[i]) continue;
-      const float p = expf(s[i] - m_new);
+      const float p = expf(s[i] - m_use);
       l += p;
 #pragma unroll
       for (int k = 0; k < NV; k++) fma4(acc[k], p, x[i][V0 + k]);
@@ -408,8 +410,12 @@ __device__ void fp32_attend(const float* q_row, int t0, int t1, float scale, K1 
 #pragma unroll
   for (int i = 0; i < FP_GROUPS; i++) {
     const float li = l_lds[i];
-    w[i] = li == 0.f ? 0.f : expf(m_lds[i] - mx);   // (0: a group without tokens; a NaN stays one)
+    w[i] = li == 0.f ? 0.f : expf(m_lds[i] - mx);   // (0: a group that saw nothing; a NaN stays one)
     lt += li * w[i];
+  }
+  if (lt == 0.f) {   // every score was -inf
+    if (tid == 0) *lse_out = -INFINITY;
+    return;
   }
   const float inv = 1.f / lt;
   for (int c = tid; c < 64 * NV; c += FP) {

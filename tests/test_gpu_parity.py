@@ -308,6 +308,43 @@ def test_fp32_shows_a_nan_beside_finite_partials(mode, gpu_device, tune):
         assert np.isnan(got).all() and np.isnan(got_lse).all()
 
 
+# tokens that are masked: one of the first, a middle and the last tile, a run longer than a tile, all
+MASKED = {"first": [0], "middle": [77], "last": [149], "two": [5, 21], "run": list(range(3, 73)),
+          "all": list(range(150))}
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("part", ["prefix", "suffix", "both"])
+@pytest.mark.parametrize("masked", list(MASKED))
+def test_fp32_drops_keys_that_score_minus_infinity(masked, part, mode, gpu_device):
+    """fp32: a key masked through its RoPE part (a score of -inf) drops out like a token that is not
+    there, also where it is all that a group of 16 lanes, a chunk or a row has to see.  One request
+    (chunks of 16 and 32 tokens) and twenty (chunks of several tiles)."""
+    for batch in (1, 20):
+        spec = W.small_spec(name="masked", dtype="fp32", batch=batch, heads=16, q_len=1, prefix_len=150,
+                            suffix_min=150, suffix_max=150, seed=960 + batch)
+        wl = W.make_workload(spec)
+        wl.q[..., 128] = 1.0
+        a = wl.as_float64()
+        gone = MASKED[masked]
+        keep = [t for t in range(150) if t not in gone]
+        if part != "suffix":
+            wl.prefix_krope[gone, 0] = -float("inf")
+            a["prefix_ckv"], a["prefix_krope"] = a["prefix_ckv"][keep], a["prefix_krope"][keep]
+        if part != "prefix":
+            bs, whole = spec.block_size, a["pool"].copy()
+            for table in a["block_table"]:
+                for t in gone:
+                    wl.pool[table[t // bs], t % bs, 512] = -float("inf")
+                for i, t in enumerate(keep):
+                    a["pool"][table[i // bs], i % bs] = whole[table[t // bs], t % bs]
+            a["suffix_lens"] = np.full(batch, len(keep))
+        ref, ref_lse = O.mla_decode_definition(**a, pairs=[(b, h) for b in range(0, batch, 7) for h in (0, 9, 15)])
+        print(f"fp32 masked keys {masked} {part} {mode} batch={batch}", flush=True)
+        got, got_lse = Hh.run_library(wl, mode, gpu_device)
+        Hh.assert_parity(got, got_lse, ref, ref_lse, "fp32", f"fp32_masked/{masked}/{part}/{mode}/{batch}")
+
+
 @pytest.mark.parametrize("flags", [0, 0x400], ids=["pipelined", "8-wave"])
 @pytest.mark.parametrize("prefix_len", [31, 32, 40, 288, 1024, 1100])
 def test_pipelined_prefix_kernel_long_runs(prefix_len, flags, gpu_device, tune):
