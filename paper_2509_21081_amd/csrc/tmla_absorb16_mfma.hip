@@ -288,11 +288,11 @@ __global__ void __launch_bounds__(256, 1) absorb16_kernel(AbsorbArgs a) {
   for (int w = 0; w < 4; w++) {
     mw[w] = ml[(w * 2 + 0) * 16 + n];
     lw[w] = ml[(w * 2 + 1) * 16 + n];
-    if (lw[w] > 0.f) ms = fmaxf(ms, mw[w]);   // (else: no token of that share is visible)
+    if (lw[w] != 0.f) ms = fmaxf(ms, mw[w]);   // (0: no token of that share is visible)
   }
 #pragma unroll
-  for (int w = 0; w < 4; w++) ls += lw[w] > 0.f ? lw[w] * fast_exp2(mw[w] - ms) : 0.f;
-  const bool use = lt > 0.f;
+  for (int w = 0; w < 4; w++) ls += lw[w] != 0.f ? lw[w] * fast_exp2(mw[w] - ms) : 0.f;
+  const bool use = lt != 0.f;   // (a share that scored NaN takes the whole chunk with it: ls > 0 fails)
   const float f = use ? fast_exp2(m - ms) / ls : 0.f;
   {
     char* dst = slot + n * A16_OUT_ROW + 16 * q4;

@@ -484,6 +484,33 @@ def test_prefix_kernels_with_values_that_are_not_finite(prefix_len, kernel, gpu_
         Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"nan_key_{kernel}")
 
 
+@pytest.mark.parametrize("heads", [16, 32, 64])
+@pytest.mark.parametrize("token", [5, 40, 90, 127, 150])
+def test_a_nan_takes_its_whole_chunk_of_a_suffix(token, heads, gpu_device, tune):
+    """Kernels for up to 16, 32 and 64 rows a request, chunks of 128 and 72 tokens: a key that scores NaN
+    takes the whole chunk with it and not the part of a wavefront (up to 16 rows each of the four has
+    32 of the 128 tokens), and no other chunk or request."""
+    tune(T.TUNE_SUFFIX_CHUNK, 128)
+    spec = W.small_spec(name="nan_chunk", dtype="bf16", batch=3, heads=heads, q_len=1, prefix_len=64,
+                        suffix_min=200, suffix_max=200, seed=970)
+    wl = W.make_workload(spec)
+    clean, clean_lse = Hh.run_library(wl, "mixed", gpu_device)
+    assert np.isfinite(clean).all() and np.isfinite(clean_lse).all()
+    a = wl.as_float64()
+    table = a["block_table"][1]
+    wl.pool[table[token // 64], token % 64, 570] = float("nan")
+    if token < 128:     # the second chunk is left, its 72 tokens in front
+        whole = a["pool"].copy()
+        for i in range(72):
+            a["pool"][table[i // 64], i % 64] = whole[table[(128 + i) // 64], (128 + i) % 64]
+    a["suffix_lens"] = np.array([200, 72 if token < 128 else 128, 200])
+    ref, ref_lse = O.mla_decode_definition(**a, pairs=[(1, h) for h in range(0, heads, 5)])
+    print(f"NaN at suffix token {token}, {heads} heads", flush=True)
+    got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"nan_chunk/{heads}/{token}")
+    assert np.array_equal(got[[0, 2]], clean[[0, 2]]) and np.array_equal(got_lse[[0, 2]], clean_lse[[0, 2]])
+
+
 @pytest.mark.parametrize("gain", [256.0, 16.0, 1.0 / 64.0])
 def test_suffix_scores_far_from_the_first_step(gain, gpu_device, tune):
     """The same for the absorb pass over the suffix with more than 32 query rows per request: the
