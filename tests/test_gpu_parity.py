@@ -160,6 +160,21 @@ def test_latent_rows_of_partly_filled_groups(heads, q_len, gpu_device):
         Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"groups/{heads}x{q_len}/{mode}")
 
 
+@pytest.mark.parametrize("lo,hi", [(0, 3), (30, 34), (60, 68), (92, 100), (124, 132)])
+def test_chunks_of_one_and_of_several_wavefronts(lo, hi, gpu_device, tune):
+    """Up to 16 rows a request: chunks of up to 64 tokens are one wavefront's, longer ones are shared by two to
+    four and merged; lengths around one to four tiles, whole and as the rest behind a chunk of 128."""
+    for add in (0, 128):
+        tune(T.TUNE_SUFFIX_CHUNK, 128 if add else 256)
+        spec = W.small_spec(name="alone", dtype="bf16", batch=24, heads=16, q_len=1, prefix_len=0,
+                            suffix_min=add + lo, suffix_max=add + hi, seed=650 + hi)
+        wl = W.make_workload(spec)
+        ref, ref_lse = O.mla_decode_absorb_all_heads(**wl.as_float64())
+        print(f"16-row chunks of {add} + {lo} to {hi} tokens", flush=True)
+        got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
+        Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"alone/{add}+{lo}")
+
+
 @pytest.mark.parametrize("batch", [1, 33])
 @pytest.mark.parametrize("chunks", [4, 5, 16, 17, 32, 33, 64, 70])
 def test_latent_partials_of_every_merge_size(chunks, batch, gpu_device, tune):
