@@ -133,8 +133,8 @@ __device__ inline void dma16_stream(const void* src, void* dst) {
 #endif
 // The same (streaming) transfer with the address split into a wave-uniform base (in scalar registers) and a
 // 32-bit per-lane offset: no 64-bit vector additions per transfer.  `lds` + `lds2` = wave-uniform
-// LDS byte address (two terms so that the sum lands in M0 directly).  The statement sets M0 behind the compiler's back, which is safe only in kernels that
-// issue every global-to-LDS transfer through it and use nothing else that reads M0.
+// LDS byte address (two terms so that the sum lands in M0 directly).  M0 is an output of the statement, so
+// that the compiler sets it again for a transfer of its own behind it.
 template <bool STREAM = true>
 __device__ inline void dma16_scalar_base(uint32_t lane_off, const void* base, uint32_t lds,
                                          uint32_t lds2 = 0) {
@@ -145,12 +145,13 @@ __device__ inline void dma16_scalar_base(uint32_t lane_off, const void* base, ui
   base = (const void*)(((uint64_t)hi << 32) | lo);
   lds = __builtin_amdgcn_readfirstlane(lds);
   lds2 = __builtin_amdgcn_readfirstlane(lds2);
+  uint32_t m0;
   if constexpr (STREAM)
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" TMLA_STREAM_POLICY
-                 ::"v"(lane_off), "s"(base), "s"(lds), "s"(lds2) : "memory", "scc");
+    asm volatile("s_add_u32 %0, %3, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" TMLA_STREAM_POLICY
+                 : "=&{m0}"(m0) : "v"(lane_off), "s"(base), "s"(lds), "s"(lds2) : "memory", "scc");
   else
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 ::"v"(lane_off), "s"(base), "s"(lds), "s"(lds2) : "memory", "scc");
+    asm volatile("s_add_u32 %0, %3, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 : "=&{m0}"(m0) : "v"(lane_off), "s"(base), "s"(lds), "s"(lds2) : "memory", "scc");
 }
 
 // Scalar (SMEM) load of one int from a wave-uniform address.  A vector load here would have to be

@@ -439,15 +439,17 @@ __device__ inline void pl_mfma_o_dma(f32x16& d, const bf16x8& a, const bf16x8& b
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
   base = (const void*)(((uint64_t)hi << 32) | lo);
   lds = __builtin_amdgcn_readfirstlane(lds);
+  uint32_t m0;   // (an output, as in dma16_scalar_base)
 #define PL_MFMA_DMA_W(POLICY)                                                                   \
-  asm volatile("s_mov_b32 m0, %5\n\ts_waitcnt lgkmcnt(%6)\n\t"                                  \
-               "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0\n\tglobal_load_lds_dwordx4 %3, %4" POLICY \
-               : "+a"(d) : "v"(a), "v"(b), "v"(lane_off), "s"(base), "s"(lds), "n"(PL_WAIT)      \
-               : "memory")
+  asm volatile("s_mov_b32 %1, %6\n\ts_waitcnt lgkmcnt(%7)\n\t"                                  \
+               "v_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\tglobal_load_lds_dwordx4 %4, %5" POLICY \
+               : "+a"(d), "=&{m0}"(m0)                                                          \
+               : "v"(a), "v"(b), "v"(lane_off), "s"(base), "s"(lds), "n"(PL_WAIT) : "memory")
 #define PL_MFMA_DMA(POLICY)                                                                     \
-  asm volatile("s_mov_b32 m0, %5\n\t"                                                           \
-               "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0\n\tglobal_load_lds_dwordx4 %3, %4" POLICY \
-               : "+a"(d) : "v"(a), "v"(b), "v"(lane_off), "s"(base), "s"(lds) : "memory")
+  asm volatile("s_mov_b32 %1, %6\n\t"                                                           \
+               "v_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\tglobal_load_lds_dwordx4 %4, %5" POLICY \
+               : "+a"(d), "=&{m0}"(m0)                                                          \
+               : "v"(a), "v"(b), "v"(lane_off), "s"(base), "s"(lds) : "memory")
   if constexpr (WAIT && STREAM) PL_MFMA_DMA_W(TMLA_STREAM_POLICY);
   else if constexpr (WAIT) PL_MFMA_DMA_W("");
   else if constexpr (STREAM) PL_MFMA_DMA(TMLA_STREAM_POLICY);
