@@ -212,19 +212,19 @@ def test_merge_and_projection_in_one_launch(splits, heads, batch, chunks, gpu_de
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"one_launch/{heads}x{batch}/{chunks}+{splits}")
 
 
-def test_streaming_projection_with_three_naive_partials(gpu_device, tune):
-    """200 requests x 128 heads in three prefix splits: the streaming up-projection with three naive
-    partials per row (LDS full to the byte), runs of 3, 3 and 1 blocks, a ragged last block and
-    requests without a suffix."""
+def test_projection_runs_of_four_and_three_blocks(gpu_device, tune):
+    """200 requests x 128 heads in three prefix splits: the projection through the ring with one latent and
+    three naive partials per row, runs of four and of three blocks of 32 queries (one round of
+    workgroups), a ragged last block and requests without a suffix."""
     tune(T.TUNE_PREFIX_SPLITS, 3)
-    spec = W.small_spec(name="stream3", dtype="bf16", batch=200, heads=128, q_len=1, prefix_len=300,
+    spec = W.small_spec(name="runs_4_3", dtype="bf16", batch=200, heads=128, q_len=1, prefix_len=300,
                         suffix_min=0, suffix_max=20, seed=333)
     wl = W.make_workload(spec)
     pairs = [(b, h) for b in (0, 31, 32, 95, 96, 191, 192, 199) for h in (0, 63, 127)]
     ref, ref_lse = O.mla_decode_definition(**wl.as_float64(), pairs=pairs)
-    print("streaming projection, three naive partials", flush=True)
+    print("projection, runs of four and three blocks", flush=True)
     got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
-    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", "stream3")
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", "runs_4_3")
 
 
 @pytest.mark.parametrize("batch,q_len", [(31, 1), (32, 1), (33, 1), (8, 4), (9, 4), (127, 1), (129, 1), (515, 2)])
@@ -242,13 +242,18 @@ def test_query_absorption_of_partly_filled_blocks(batch, q_len, gpu_device):
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"absorption/{batch}x{q_len}")
 
 
-@pytest.mark.parametrize("heads,batch,chunks,splits", [(16, 257, 1, 0), (16, 290, 3, 9), (48, 100, 2, 16), (128, 33, 4, 1),
-                                                       (128, 70, 2, 3), (128, 515, 1, 1), (128, 300, 4, 30),
-                                                       (64, 56, 2, 4), (128, 25, 3, 4)])
-def test_projection_through_the_ring(heads, batch, chunks, splits, gpu_device, tune):
-    """Runs of one to eight blocks of 32 queries with a short last block, a last run shorter than the others, one to four
-    latent partials beside none to 30 naive ones (runs cut short by the weights' table), some requests without
-    a suffix and, without a prefix, with nothing to see at all."""
+@pytest.mark.parametrize("heads,batch,chunks,splits,run",
+                         [(16, 257, 1, 0, 1), (16, 290, 3, 9, 1), (48, 100, 2, 16, 1), (128, 33, 4, 1, 1),
+                          (128, 70, 2, 3, 2), (128, 515, 1, 1, 5), (128, 300, 4, 30, 3), (64, 56, 2, 4, 1),
+                          (128, 25, 3, 4, 1), (128, 509, 1, 1, 8), (128, 509, 1, 15, 8)])
+def test_projection_through_the_ring(heads, batch, chunks, splits, run, gpu_device, tune):
+    """Runs of one to eight blocks of 32 queries (eight: every thread has a query's weights to compute) with
+    a short last block, a last run shorter than the others, one to four latent partials beside none to 30
+    naive ones (runs cut short by the weights' table; 16 partials x 8 blocks fill it, and the LDS, to the
+    byte), some requests without a suffix and, without a prefix, with nothing to see at all."""
+    blocks, parts = -(-batch // 32), chunks + splits
+    one_round = -(-blocks // max(1, 256 // heads))
+    assert run == -(-one_round // -(-one_round // min(8, 128 // parts)))   # (as the host cuts them)
     tune(T.TUNE_PREFIX_SPLITS, splits)
     tune(T.TUNE_SUFFIX_CHUNK, 64)
     spec = W.small_spec(name="ring", dtype="bf16", batch=batch, heads=heads, q_len=1, prefix_len=128 * splits,
@@ -823,10 +828,9 @@ def test_combine_lse_matches_definition(n, rows, width, out_dtype, gpu_device):
 @pytest.mark.parametrize("mode", ["mixed", "absorb_only"])
 def test_large_batch_projection_kernels(mode, gpu_device):
     """More than 1024 queries per head at 64 heads: the query absorption stages a weight slice once
-    for four blocks of 128 queries, and the up-projection streams runs of eight blocks of 32
-    through its LDS ring (three slots, one naive partial) -- both with a ragged last group
-    (1100 = 8 x 128 + 76 = 34 x 32 + 12 queries: runs of 8, 8, 8, 8 and 3 blocks).  Every row
-    against the tensor-form absorb checker, a sample against the definition."""
+    for four blocks of 128 queries, with a ragged last group (1100 = 8 x 128 + 76 = 34 x 32 + 12
+    queries), and the projection takes seven runs of five blocks of 32 a head, in two rounds of
+    workgroups.  Every row against the tensor-form absorb checker, a sample against the definition."""
     spec = W.small_spec(name="large_batch_h64", dtype="bf16", batch=1100, heads=64, q_len=1,
                         prefix_len=64, suffix_min=0, suffix_max=24, seed=55)
     wl = W.make_workload(spec)
@@ -840,10 +844,10 @@ def test_large_batch_projection_kernels(mode, gpu_device):
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"large_batch/{mode}/definition")
 
 
-def test_streaming_upprojection_two_naive_partials(gpu_device):
+def test_projection_with_two_naive_partials(gpu_device):
     """200 requests x 128 heads: the prefix pass splits its tokens in two (two naive partials per
-    row), and the up-projection takes runs of 3, 3 and 1 blocks of 32 queries through its
-    two-slot ring, the last block with 8 valid rows.  Some requests have no suffix at all (their
+    row), and the projection takes runs of 4 and 3 blocks of 32 queries through its ring, the last
+    block with 8 valid rows.  Some requests have no suffix at all (their
     latent partial is never written and must count as zeros)."""
     spec = W.small_spec(name="two_naive_partials_h128", dtype="bf16", batch=200, heads=128, q_len=1,
                         prefix_len=160, suffix_min=0, suffix_max=20, seed=77)
@@ -852,7 +856,7 @@ def test_streaming_upprojection_two_naive_partials(gpu_device):
     ref2, ref2_lse = Hh.oracle_absorb_all_heads_parallel(O, a)
     pairs = [(b, h) for b in (0, 95, 96, 191, 192, 199) for h in (0, 64, 127)]
     ref, ref_lse = O.mla_decode_definition(**a, pairs=pairs)
-    print("streaming up-projection, two naive partials", flush=True)
+    print("projection, two naive partials", flush=True)
     got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
     Hh.assert_parity(got, got_lse, ref2, ref2_lse, "bf16", "two_naive/absorb-form")
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", "two_naive/definition")
