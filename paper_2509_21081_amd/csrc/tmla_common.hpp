@@ -76,15 +76,15 @@ struct Plan {
   int B, Sq, H, Ls, max_suffix, mode, dtype;
   int64_t rows;        // B*Sq*H output rows, row = (b*Sq + s)*H + h
   int np_split;        // naive prefix: number of token splits (0: no naive prefix pass)
-  int p_chunk;         //   tokens per split (multiple of 32)
+  int p_chunk;         //   tokens per split (multiple of 32; fp32: of 16)
   int ns_chunks;       // naive suffix (naive_only): chunks per request
   int ns_chunk;        //   tokens per chunk (multiple of block_size)
   int ap_chunks;       // absorb over the latent prefix (absorb_only): chunks of it, for all requests
-  int ap_chunk;        //   tokens per chunk (multiple of 32)
+  int ap_chunk;        //   tokens per chunk (multiple of 32; fp32: of 16)
   int ap_rows;         //   query rows a workgroup takes (64 or 128), cut from all requests' rows
   bool abs_joint;      //   prefix and suffix in one launch, of ap_rows rows a workgroup
   int as_chunks;       // absorb over the paged suffix: chunks per request
-  int as_chunk;        //   tokens per chunk (multiple of block_size)
+  int as_chunk;        //   tokens per chunk (multiple of block_size; fp32: of 16)
   int n_naive;         // = np_split + ns_chunks   (128-wide partials per row)
   int n_lat;           // = ap_chunks + as_chunks  (512-wide latent partials per row)
   size_t off_qabs, off_naive_o, off_naive_lse, off_lat_o, off_lat_lse, off_order, total;
@@ -133,8 +133,7 @@ struct DecodeArgs {
   int num_blocks, block_size, max_blocks;
   float sm_scale;
   hipStream_t stream;
-  // set by the query absorption: its launch has ranked the requests for the absorb pass
-  mutable bool ranked = false;
+  bool ranked = false;   // the query absorption's launch has ranked the requests for the absorb pass
 };
 
 // Scalar reference kernels (any dtype; the only path for fp32).
@@ -162,7 +161,8 @@ PrefixKind prefix_kind(int H, int M, int Ls);
 constexpr int PREFIX_NODES_MAX = 8;
 int mfma_prefix_nodes(PrefixKind kind, const Plan* plans, const DecodeArgs* args, int n);
 int mfma_naive_suffix_attention(const Plan& p, const DecodeArgs& a);
-int mfma_query_absorb(const Plan& p, const DecodeArgs& a);
+// `ranked`: whether its launch has ranked the requests as well
+int mfma_query_absorb(const Plan& p, const DecodeArgs& a, bool* ranked);
 int mfma_absorb_attention(const Plan& p, const DecodeArgs& a);
 // Whether the suffix pass of a call takes the requests by length, longest first.
 bool suffix_order_wanted(const Plan& p);

@@ -153,7 +153,8 @@ __global__ void __launch_bounds__(256, QBK > 1 ? 2 : 4) qabs_kernel(const __bf16
   }
 }
 
-int mfma_query_absorb(const Plan& p, const DecodeArgs& d) {
+int mfma_query_absorb(const Plan& p, const DecodeArgs& d, bool* ranked) {
+  *ranked = false;
   if (p.n_lat <= 0 || p.rows == 0) return TMLA_OK;
   const int M = p.B * p.Sq;
   const int nqs = (M + 127) / 128;
@@ -161,8 +162,8 @@ int mfma_query_absorb(const Plan& p, const DecodeArgs& d) {
   // per head, nothing to gain at 256 and below), as long as the grid still covers the chip twice
   const int qbk = (nqs >= 8 && p.H * 4 * ((nqs + 3) / 4) >= 2 * NUM_CU) ? 4 : 1;
   RankArgs rank = {d.suffix_lens, (int32_t*)(d.ws + p.off_order), p.B, 0};
-  d.ranked = suffix_order_wanted(p);
-  if (d.ranked) rank.layers = (p.B + 16 * p.H - 1) / (16 * p.H);
+  *ranked = suffix_order_wanted(p);
+  if (*ranked) rank.layers = (p.B + 16 * p.H - 1) / (16 * p.H);
   dim3 grid(p.H, 4, (nqs + qbk - 1) / qbk + rank.layers);
   const __bf16* q = (const __bf16*)d.q;
   const __bf16* w = (const __bf16*)d.w_uk;
