@@ -952,11 +952,12 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
   const int heads8 = (p.H + 7) / 8 * 8, nqb = (a.M + 31) / 32, parts = a.n_lat + a.n_naive;
   const long long blocks = (long long)heads8 * nqb;
   // Up to half a workgroup per compute unit the value blocks are dealt out, unless their rows make it more
-  // work to read all latent partials four times than the ring has with half of the units: 32 x 128 rows of
-  // four partials 14.7 us and 11.7 through the ring, 60 x 64 rows of three and more naive ones 13.4
-  // and 11.6; 32 x 64 rows 8.9 and 11.0, 12 x 128 rows 9.8 and 10.9, 250 x 16 rows of one and sixteen
-  // naive ones 13.1 and 15.8.
-  const bool many_rows = p.rows > 3072 && a.n_lat >= 2 && 2 * a.n_lat + a.n_naive <= 10;
+  // work to read all latent partials four times than the ring has with half of the units.  Steps with the
+  // ring less those without, 10 to 256 queries x 16 to 128 heads, two / three / four latent partials and up
+  // to six naive ones: 4096 rows -2.2 ... +0.1, -3.6 ... -0.9, -4.6 ... -2.9 us, 3200 rows -2.0 ... +0.6, -3.4
+  // ... -0.2, -4.7 ... -1.4; 2048 rows (128 heads x 16) +0.3 ... +1.2, 0.0 ... +1.0, -0.5 ... +0.2; one: -1.2 ... +1.6
+  // anywhere.  Eight to twelve naive ones and 3200 rows or more: -0.8 ... +1.7, -1.8 ... +1.0, -2.9 ... -0.7.
+  const bool many_rows = p.rows > 3072 && a.n_lat >= 2 && (a.n_naive <= 6 || a.n_lat == 4);
   const bool split = blocks <= NUM_CU / 2 && !many_rows;
   if (a.n_lat >= 1 && a.n_lat <= 4 && !split && parts <= FR_MAX_WEIGHTS && p.H <= FR_MAX_HEADS) {
     // runs as short as one round of workgroups allows (every one takes in 128 KiB of weights); more

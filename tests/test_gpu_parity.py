@@ -245,7 +245,7 @@ def test_query_absorption_of_partly_filled_blocks(batch, q_len, gpu_device):
 @pytest.mark.parametrize("heads,batch,chunks,splits,run",
                          [(16, 257, 1, 0, 1), (16, 290, 3, 9, 1), (48, 100, 2, 16, 1), (128, 33, 4, 1, 1),
                           (128, 70, 2, 3, 2), (128, 515, 1, 1, 5), (128, 300, 4, 30, 3), (64, 56, 2, 4, 1),
-                          (128, 25, 3, 4, 1), (128, 509, 1, 1, 8), (128, 509, 1, 15, 8)])
+                          (128, 25, 3, 4, 1), (64, 50, 4, 12, 1), (128, 509, 1, 1, 8), (128, 509, 1, 15, 8)])
 def test_projection_through_the_ring(heads, batch, chunks, splits, run, gpu_device, tune):
     """Runs of one to eight blocks of 32 queries (eight: every thread has a query's weights to compute) with
     a short last block, a last run shorter than the others, one to four latent partials beside none to 30
