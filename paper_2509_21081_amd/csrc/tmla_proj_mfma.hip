@@ -914,12 +914,19 @@ __global__ void __launch_bounds__(256) merge_project_kernel(FinalizeArgs a) {
     if (a.lse_out && half == 0 && tid == 0) a.lse_out[row] = any ? m2 + __logf(z2) : -INFINITY;
   }
 }
-// Steps with the merge pass and the projection / with this kernel, absorb form, 4096 + 300 tokens: 16
-// rows 20.6 / 18.8 us, 128 rows 27.4 / 24.8, 384 30.0 / 28.8, 512 30.6 / 30.3, 768 36.4 / 36.7, 1024
-// 37.8 / 39.8.  Fewer partials, which the projection by itself would merge: four latent and two naive
-// ones, 128 rows 74.5 / 70.9, 512 rows 75.7 / 73.7; two and two, 128 rows 43.2 / 42.7, 512 44.4 / 45.0.
-static bool merge_project_pays(int64_t rows, int n_lat) {
-  return n_lat >= 1 && rows <= (n_lat >= 3 ? 512 : 256);
+// Where it pays: its time goes up with the rows, that of the others with the latent partials, with a third
+// naive one (no longer requested up front there) and with a second round of workgroups (blocks > 64).
+// Steps with this kernel less those without, 16 to 64 heads / 128, none to two naive partials:
+//   one latent partial, 128 rows 0.0 ... +0.6 / -1.4 ... -0.5 us, 256 +0.5 ... +1.3 / -0.7 ... +0.3
+//   two, 128 rows -0.5 ... 0.0 / -1.8 ... -1.5, 256 -0.2 ... +0.8 / -1.2 ... -0.6, 384 +0.3 ... +1.0 / -0.4 ... +0.2
+//   three, 256 rows -1.1 ... +0.4 / -1.9 ... -1.2, 384 -0.8 ... +0.1 / -1.4 ... -0.5, 512 -0.7 ... +1.8 / -0.4 ... +0.2
+//   four, 384 rows -1.7 ... -0.8 / -2.2 ... -1.5, 512 -1.8 ... +1.1 / -1.2 ... -0.7
+// and with four to sixteen naive ones: one, 256 rows -2.1 ... -0.3, 384 -1.4 ... +0.2; two, 384 -2.1 ... -0.6.
+// More than four need the merge pass without it: 16 rows 20.6 / 18.8 us a step, 128 rows 27.4 / 24.8, 384 30.0
+// / 28.8, 512 30.6 / 30.3, 768 36.4 / 36.7.
+static bool merge_project_pays(const FinalizeArgs& a, long long blocks) {
+  const int n = a.n_lat + (a.n_naive > 2 ? 2 : 0) + (blocks > NUM_CU / 4 ? 1 : 0);
+  return a.n_lat >= 1 && a.rows <= 128 * std::min(n - 1, 4);
 }
 
 int mfma_finalize(const Plan& p, const DecodeArgs& d) {
@@ -935,7 +942,9 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
   a.out = (__bf16*)d.out;
   a.lse_out = d.lse_out;
   a.M = p.B * p.Sq; a.H = p.H; a.n_naive = p.n_naive; a.n_lat = p.n_lat; a.rows = p.rows;
-  if (!merge_inside && merge_project_pays(p.rows, a.n_lat)) {
+  const int heads8 = (p.H + 7) / 8 * 8, nqb = (a.M + 31) / 32;
+  const long long blocks = (long long)heads8 * nqb;   // of 32 queries
+  if (!merge_inside && merge_project_pays(a, blocks)) {
     auto merge = a.n_lat <= 4 ? merge_project_kernel<1> : a.n_lat <= 16 ? merge_project_kernel<4> : a.n_lat <= 32 ? merge_project_kernel<8>
                  : a.n_lat <= 64 ? merge_project_kernel<16> : merge_project_kernel<32>;
     hipLaunchKernelGGL(merge, dim3((unsigned)(2 * p.rows)), dim3(256), 0, d.stream, a);
@@ -949,8 +958,7 @@ int mfma_finalize(const Plan& p, const DecodeArgs& d) {
                        (int64_t)p.rows);
     a.n_lat = 1;
   }
-  const int heads8 = (p.H + 7) / 8 * 8, nqb = (a.M + 31) / 32, parts = a.n_lat + a.n_naive;
-  const long long blocks = (long long)heads8 * nqb;
+  const int parts = a.n_lat + a.n_naive;
   // Up to half a workgroup per compute unit the value blocks are dealt out, unless their rows make it more
   // work to read all latent partials four times than the ring has with half of the units.  Steps with the
   // ring less those without, 10 to 256 queries x 16 to 128 heads, two / three / four latent partials and up
