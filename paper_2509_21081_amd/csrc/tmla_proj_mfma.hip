@@ -925,8 +925,9 @@ __global__ void __launch_bounds__(256) merge_project_kernel(FinalizeArgs a) {
 // More than four need the merge pass without it: 16 rows 20.6 / 18.8 us a step, 128 rows 27.4 / 24.8, 384 30.0
 // / 28.8, 512 30.6 / 30.3, 768 36.4 / 36.7.
 static bool merge_project_pays(const FinalizeArgs& a, long long blocks) {
-  const int n = a.n_lat + (a.n_naive > 2 ? 2 : 0) + (blocks > NUM_CU / 4 ? 1 : 0);
-  return a.n_lat >= 1 && a.rows <= 128 * std::min(n - 1, 4);
+  const int ahead = 2 * a.n_lat + (a.n_naive > 2 ? 4 : 0) +
+                    (blocks > NUM_CU / 4 ? 3 + (a.n_naive == 2 ? 1 : 0) : 0);
+  return a.n_lat >= 1 && a.rows <= 64 * std::min(ahead - 2, 8);
 }
 
 int mfma_finalize(const Plan& p, const DecodeArgs& d) {
