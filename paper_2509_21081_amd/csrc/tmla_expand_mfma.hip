@@ -19,7 +19,7 @@
 // Measured on MI355X against a tile of 256 tokens x 256 outputs per workgroup with the whole
 // contraction streamed through LDS and an epilogue of its own: 32768 tokens x 128 heads 1573 ->
 // 930 to 975 us (1.13 to 1.18 PFLOP/s with 2.8 TB/s of stores; 800 us without the stores, 690 us
-// without any transfer), 4096 x 128 194 -> 126 us, 1003 x 16 20.0 -> 9.4 us.  Stores without the
+// without any transfer), 4096 x 128 194 -> 122 us, 1003 x 16 20.0 -> 8.4 us.  Stores without the
 // non-temporal hint: 1240 us.
 #include <algorithm>
 #include <type_traits>
@@ -112,7 +112,7 @@ __device__ __forceinline__ void expand_walk(const ExpandArgs& a, char* smem, int
   // through LDS in pieces of 32 rows x 128 columns, three of a wavefront's eight under way at a time
   // in the ring's other slots: row r of a piece at r * 256, its 16-byte chunk c in place c ^ (r & 15).
   // (32 whole rows at a time, each half waited for by itself and the first tiles behind them, they
-  // held up 1003 tokens x 16 heads by 1.3 us, 10.3 against 9.0; read straight into the registers, 32
+  // held up 1003 tokens x 16 heads, K and V in one workgroup, by 1.3 us; read straight into the registers, 32
   // bytes of 32 rows per load, by another 4 us.)
   bf16x8 w[NI][EX_NKS];
   {
@@ -344,8 +344,9 @@ static int expand_splits(int H, int64_t ntb) {
 // K and V of a head by workgroups of their own: half of the weights to fetch, twice the blocks, and each
 // of them bound by LDS (a fragment feeds one MFMA) rather than by the matrix cores.  Where all ranges run at
 // once, a workgroup takes 6.0 us + 1.75 per block with both and 5.2 + 1.0 with one of them (16 to
-// 64 heads, one to eight blocks, within 4 %): 200 tokens x 16 heads 7.4 / 6.3 us, 600 x 32 11.1 / 10.2,
-// 1003 x 16 9.9 / 9.4, 1003 x 32 13.0 / 13.2, 434 x 128 20.1 / 22.4.
+// 64 heads, one to eight blocks, within 4 %, launch included): back to back, 200 tokens x 16 heads 6.7 /
+// 5.5 us, 600 x 32 10.3 / 9.2, 1003 x 16 8.4 / 8.0, 1003 x 32 11.4 / 11.4, 434 x 64 10.5 / 10.0, 700 x 64 14.0 /
+// 15.0, 434 x 128 18.0 / 20.0.
 static bool expand_in_halves(int H, int64_t ntb, int splits) {
   if (2 * H > NUM_CU || H * splits > NUM_CU) return false;
   const int64_t s = std::min<int64_t>(ntb, NUM_CU / (2 * H));

@@ -502,8 +502,9 @@ __global__ void __launch_bounds__(256) finalize_few_kernel(FinalizeArgs a) {
 // two runs of 512: the kernel that loaded fragments took 24.0 us for 256 x 64 rows of three latent
 // partials (now 17.7 us), 13.0 for 111 x 64 rows of two latent and two naive ones (10.8), 13.7 for 64 x
 // 128 of them (12.4), 15.6 for 512 x 16 of one and eight (14.2).  With the weights as fragments: 20.2,
-// 12.8, 13.6, 18.2.  256 x 128 rows of one latent and two naive partials, where the partials were
-// streamed before: 22.0 then, 22.4 now, 92 MB.
+// 12.8, 13.6, 18.2.  One latent partial, where the partials were streamed before, then and now: 256 x 128
+// rows and two naive ones (92 MB) 20.8 and 21.4, 192 x 128 16.7 and 16.9, 400 x 64 24.8 and 16.8; one naive one,
+// 320 x 128 20.4 and 20.3, 512 x 128 28.7 and 27.6, 700 x 128 52.0 and 44.1.
 // Every latent partial is projected as it is and weighted afterwards: a query is one column of the
 // MFMA, so its weight is one number per lane, and a partial that was never written spoils its own
 // column only.  (Merged first, the row would be rounded to bf16 once more.)

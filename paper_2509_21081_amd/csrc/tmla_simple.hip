@@ -309,7 +309,8 @@ simple_finalize_kernel(Plan p, const float* __restrict__ naive_o,
 // neighbouring lanes continue; a tile's keys and values are requested at once and read once; chunks go
 // down to 16 tokens; weights are dealt out by columns; the naive and the absorb pass, which do not
 // depend on each other, share a launch.  4 requests x 16 heads over 256 + 64 tokens, the step: 81.5 us
-// with a thread per token, 30.0 with coalesced accesses and a launch per stage, 16.8 now.
+// with a thread per token, 30.0 with coalesced accesses and a launch per stage, 16.8 now (replayed
+// from a graph 23.9 and 14.2).
 constexpr int FP = 256;         // threads
 constexpr int FP_GROUPS = FP / 16;
 constexpr int FP_TILE = 4 * FP_GROUPS;   // tokens per tile, four per group of 16 lanes
