@@ -431,7 +431,9 @@ __global__ void __launch_bounds__(256, 1) absorb128_kernel(Absorb128Args args) {
     // ---- denominators: the score owners publish theirs, everybody reads all four blocks
     raw_barrier();   // everyone is past its last read of the probabilities
     {
-      const float lt = sum_halves(l);
+      // (where every score of step 0 was -inf there was no reference for the tokens behind it)
+      const bool none = !exact && m == -INFINITY && vis_q > t0 + 64;
+      const float lt = none ? INFINITY : sum_halves(l);
       if (g == 0) lbuf[qb * 32 + n] = lt;
     }
     __syncthreads();

@@ -414,7 +414,9 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
     // ---- denominators: sum the two token halves of either query block through LDS
     raw_barrier();   // everyone is past its last read of the maxima buffer
     {
-      const float lh = sum_halves(l);
+      // (where every score of step 0 was -inf there was no reference for the tokens behind it)
+      const bool none = fixed && (qb ? m[1] : m[0]) == -INFINITY && vis_q > t0 + 64;
+      const float lh = none ? INFINITY : sum_halves(l);
       if (g == 0) lds_write_b32(mx_wr, lh);
     }
     lgkm_wait<0>();

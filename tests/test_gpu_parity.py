@@ -504,6 +504,40 @@ def test_prefix_kernels_with_values_that_are_not_finite(prefix_len, kernel, gpu_
         Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"nan_key_{kernel}")
 
 
+@pytest.mark.parametrize("heads,flags", [(16, 0), (32, 0), (64, 0), (128, 0), (128, 0x2000)])
+@pytest.mark.parametrize("masked", ["first", "run", "head", "all"])
+def test_absorb_kernels_drop_keys_that_score_minus_infinity(masked, heads, flags, gpu_device, tune):
+    """Kernels for up to 16, 32, 64 and 128 rows (debug flag bit 13), latent prefix and suffix in one chunk
+    each: keys masked through their RoPE part drop out, also where they are all that the first 64-token step
+    has, whose maxima the 64- and 128-row kernels take as references for the steps behind it."""
+    gone = list(range(70)) if masked == "head" else MASKED[masked]
+    keep = [t for t in range(150) if t not in gone]
+    tune(T.TUNE_SUFFIX_CHUNK, 256)
+    tune(T.TUNE_ABSORB_PREFIX_CHUNK, 256)
+    for part in ("prefix", "suffix"):
+        spec = W.small_spec(name="masked", dtype="bf16", batch=3, heads=heads, q_len=1, prefix_len=150,
+                            suffix_min=150, suffix_max=150, seed=961)
+        wl = W.make_workload(spec)
+        wl.q[..., 128] = 1.0
+        a = wl.as_float64()
+        if part == "prefix":
+            wl.prefix_krope[gone, 0] = -float("inf")
+            a["prefix_ckv"], a["prefix_krope"] = a["prefix_ckv"][keep], a["prefix_krope"][keep]
+        else:
+            whole = a["pool"].copy()
+            for table in a["block_table"]:
+                for t in gone:
+                    wl.pool[table[t // 64], t % 64, 512] = -float("inf")
+                for i, t in enumerate(keep):
+                    a["pool"][table[i // 64], i % 64] = whole[table[t // 64], t % 64]
+            a["suffix_lens"] = np.full(3, len(keep))
+        ref, ref_lse = O.mla_decode_definition(**a, pairs=[(b, h) for b in (0, 2) for h in (0, 9, 15)])
+        for mode in ("absorb_only", "mixed"):
+            print(f"masked keys {masked} of the {part}, {heads} heads, flags {flags:#x}, {mode}", flush=True)
+            got, got_lse = Hh.run_library(wl, mode, gpu_device, flags=flags)
+            Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"masked/{masked}/{part}/{heads}/{mode}")
+
+
 @pytest.mark.parametrize("heads", [16, 32, 64])
 @pytest.mark.parametrize("token", [5, 40, 90, 127, 150])
 def test_a_nan_takes_its_whole_chunk_of_a_suffix(token, heads, gpu_device, tune):
