@@ -200,7 +200,8 @@ def test_latent_partials_of_every_merge_size(chunks, batch, gpu_device, tune):
 @pytest.mark.parametrize("splits", [0, 1, 4, 19])
 def test_merge_and_projection_in_one_launch(splits, heads, batch, chunks, gpu_device, tune):
     """16 to 528 rows, 1 to 6 latent partials beside none to 19 naive ones (16 are requested up front), on
-    either side of the line from which merge and projection share a launch; some requests without a suffix and, without a prefix, with nothing to see at all."""
+    either side of the line from which merge and projection share a launch; some requests without a
+    suffix and, without a prefix, with nothing to see at all."""
     tune(T.TUNE_PREFIX_SPLITS, splits)
     tune(T.TUNE_SUFFIX_CHUNK, 64)
     spec = W.small_spec(name="one_launch", dtype="bf16", batch=batch, heads=heads, q_len=1,
