@@ -277,9 +277,9 @@ int typhoon_mla_combine_lse(int32_t num_partials, int64_t rows, int32_t width,
  *   bit 9 (0x200): scalar kernel for the naive suffix attention of naive_only mode.
  *   bit 10 (0x400): naive prefix attention with more than 128 queries per head runs on the
  *     8-wavefront kernel (moving exponent references) instead of the software-pipelined one.
- *   bit 11 (0x800): the absorb attention kernel for more than 32 query rows per request walks
- *     every chunk with moving exponent references (otherwise only chunks in which its first walk,
- *     with references fixed at the chunk's first tokens, overflowed).
+ *   bit 11 (0x800): the absorb attention kernels that give a workgroup 64 query rows walk every
+ *     chunk with moving or exact exponent references (otherwise only chunks in which the first
+ *     walk, with references fixed at the chunk's first tokens, overflowed).
  *   bit 12 (0x1000): the absorb passes keep the kernel that gives a workgroup 64 query rows;
  *     bit 13 (0x2000): the latent prefix, and the suffixes of requests with a multiple of 128
  *     rows, take the 128-row kernel whatever the grid size (by default a cost model decides for

@@ -1,7 +1,7 @@
 // Absorb-formulation flash-decode over latent cache rows (paper Algorithm 1 step 6), 64 query rows
-// per workgroup, 64 tokens per step: the suffixes of requests with more than 32 query rows
-// (S_q * H > 32), the latent prefix for groups of 64 rows cut from all requests, and on small
-// grids both in one launch, whatever the rows per request.
+// per workgroup, 64 tokens per step: launches of the 64-row kernels that cover the chip with workgroups
+// that share no tiles, or with suffixes and latent prefix together (keeps_steps() in
+// tmla_absorb64_pipelined_mfma.hip, which has the kernel for all others).
 //
 // The two matrix products of a step want different work splits, so the four wavefronts change
 // roles inside a step and hand the probabilities over through LDS:
@@ -471,7 +471,7 @@ __global__ void __launch_bounds__(256, 1) absorb64_kernel(Absorb64Args args) {
   }
 }
 
-int mfma_absorb64_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what) {
+int mfma_absorb64_steps_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what) {
   Absorb64Args args;
   args.a = a;
   args.moving_only = (debug_flags() & 0x800) != 0;

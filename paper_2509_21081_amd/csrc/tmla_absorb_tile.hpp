@@ -217,6 +217,7 @@ enum { WITH_PREFIX = 1, WITH_SUFFIX = 2 };
 bool absorb_grid(const Plan& p, int what, int rows_per_wg, AbsorbGrid* grid, long long* ids,
                  long long* wgs);
 int mfma_absorb64_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what);
+int mfma_absorb64_steps_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what);
 int mfma_absorb128_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what);
 int mfma_absorb16_attention(const Plan& p, const DecodeArgs& d, AbsorbArgs a);   // S_q * H <= 16, suffixes
 

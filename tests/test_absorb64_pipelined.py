@@ -1,0 +1,70 @@
+"""The software-pipelined absorb kernel with 64 query rows per workgroup: chunks of one to six tiles of 32 tokens with every
+remainder that its ring of four treats differently, partial row groups, the causal edge, and the wait states
+around its assembly MFMAs."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from oracle import mla_oracle as O
+from paper_2509_21081_amd import binding as T
+from paper_2509_21081_amd import build as B
+from paper_2509_21081_amd import workloads as W
+from tests import helpers as Hh
+from tests import test_isa_hazards as hz
+
+# (tokens, heads, q_len): one tile and parts of it, the first with a prefetched tile, the last partial; 48 and
+# 96 rows leave row blocks that are partly or wholly no request's
+SHAPES = [(1, 48, 1), (31, 48, 1), (32, 64, 1), (33, 48, 2), (64, 64, 2), (65, 48, 1), (96, 64, 1), (97, 48, 3),
+          (127, 64, 1), (128, 48, 4), (129, 80, 1), (160, 64, 1), (161, 96, 1), (192, 64, 4)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tokens,heads,q_len", SHAPES)
+def test_tiles_and_their_remainders(tokens, heads, q_len, gpu_device, tune):
+    tune(T.TUNE_SUFFIX_CHUNK, 256)   # one chunk a request
+    tune(T.TUNE_ABSORB_PREFIX_CHUNK, 64)
+    wl = W.make_workload(W.small_spec(name="tiles", dtype="bf16", batch=3, heads=heads, q_len=q_len, prefix_len=97,
+                                      suffix_min=max(tokens, q_len), suffix_max=max(tokens, q_len), seed=tokens))
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64())
+    for mode in ["mixed", "absorb_only"]:
+        for flags in [0x1000, 0x1800]:   # the 64-row kernel; its exact walk
+            print(f"64-row pipelined kernel {tokens} x {heads} x {q_len} {mode} {flags:#x}", flush=True)
+            got, got_lse = Hh.run_library(wl, mode, gpu_device, flags=flags)
+            Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"tiles/{tokens}/{heads}/{q_len}/{mode}/{flags:#x}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,prefix", [(255, 64), (256, 64), (256, 0)])
+def test_both_sides_of_the_line_to_the_kernel_of_64_token_steps(batch, prefix, gpu_device, tune):
+    tune(T.TUNE_SUFFIX_CHUNK, 128)
+    wl = W.make_workload(W.small_spec(name="line", dtype="bf16", batch=batch, heads=64, q_len=1, prefix_len=prefix,
+                                      suffix_min=1, suffix_max=110, seed=batch + prefix))
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64())
+    print(f"64-row kernels batch={batch} prefix={prefix}", flush=True)
+    got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"line/{batch}/{prefix}")
+
+
+@pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="hipcc not available")
+def test_wait_states_of_the_assembly_mfmas(tmp_path):
+    out = tmp_path / "k.s"
+    subprocess.run([B.HIPCC, *B.FLAGS, "-S", "--cuda-device-only", "-o", str(out),
+                    os.path.join(B.CSRC, "tmla_absorb64_pipelined_mfma.hip")], check=True, capture_output=True)
+    text = out.read_text()
+    kernel = "absorb64_pipelined_kernel"
+    starts = [m.start() for m in re.finditer(r"\n_ZN4tmla%d%sI[^:\s]*:" % (len(kernel), kernel), text)]
+    assert len(starts) == 2
+    for start in starts:
+        instrs, labels = [], {}
+        for raw in text[start:text.index("\n.Lfunc_end", start)].split("\n"):
+            t = raw.split(";")[0].strip()
+            if t.endswith(":"):
+                labels[t[:-1]] = len(instrs)
+            elif t and not t.startswith("."):
+                instrs.append(t)
+        for where, seq in hz._sequences(instrs, labels):
+            hz._check_valu_to_mfma(seq, where)
+            hz._check_mfma_result(seq, where)
+        assert sum(i.startswith("v_mfma") for i in instrs) > 100
