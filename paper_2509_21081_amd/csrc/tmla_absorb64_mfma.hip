@@ -1,6 +1,6 @@
 // Absorb-formulation flash-decode over latent cache rows (paper Algorithm 1 step 6), 64 query rows
-// per workgroup, 64 tokens per step: launches of the 64-row kernels that cover the chip with workgroups
-// that share no tiles, or with suffixes and latent prefix together (keeps_steps() in
+// per workgroup, 64 tokens per step: launches of the 64-row kernels in chunks of up to 128 tokens, and those that
+// cover the chip with workgroups that share no tiles, or with suffixes and latent prefix together (keeps_steps() in
 // tmla_absorb64_pipelined_mfma.hip, which has the kernel for all others).
 //
 // The two matrix products of a step want different work splits, so the four wavefronts change

@@ -655,7 +655,11 @@ __global__ void __launch_bounds__(256, 1) absorb64_pipelined_kernel(Absorb64Pipe
   }
 }
 
-// Launches that cover the chip and keep the kernel that walks 64 tokens a step:
+// Launches that keep the kernel that walks 64 tokens a step.  Chunks of up to 128 tokens: this kernel's code is
+// the longer one, and inside a step, where other kernels run in between, its first pass over it costs what
+// one or two steps' worth of tiles gain (pass by itself / step, that kernel and this one: 2 x 64 heads over 2048 +
+// 603 tokens in chunks of 64 9.75, 9.66 / 19.5, 20.0 us; 8 x 16 over 4096 + 1200 in chunks of 128 10.4, 10.4 / 20.1, 20.7; of
+// 192 11.9, 11.1 / 21.7, 21.2).  And launches that cover the chip:
 //   * suffixes of up to 64 rows a request, whose workgroups stream rows that no other reads, beside another
 //     pass of the call.  HBM sets the pace there and the chip's power that of the step; the faster pass draws
 //     more of it.  256 requests x 64 heads absorb_only, 4096 + 512 tokens: the pass 34.5 us with that kernel and
@@ -666,6 +670,8 @@ __global__ void __launch_bounds__(256, 1) absorb64_pipelined_kernel(Absorb64Pipe
 //     tokens 60.9 and 55.4 us), but the cross-over table of auto mode, whose entries other callers hold fixed, says
 //     mixed from there on (61 us).
 static bool keeps_steps(const Plan& p, int what, long long wgs) {
+  const int longest = std::max((what & WITH_PREFIX) ? p.ap_chunk : 0, (what & WITH_SUFFIX) ? p.as_chunk : 0);
+  if (longest <= 128) return true;
   if (wgs < NUM_CU) return false;
   if (what == WITH_SUFFIX) return p.Sq * p.H <= 64 && p.n_naive + p.ap_chunks > 0;
   return what == (WITH_PREFIX | WITH_SUFFIX);

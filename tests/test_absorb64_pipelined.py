@@ -6,6 +6,7 @@ import re
 import subprocess
 
 import pytest
+import torch
 
 from oracle import mla_oracle as O
 from paper_2509_21081_amd import binding as T
@@ -23,10 +24,13 @@ SHAPES = [(1, 48, 1), (31, 48, 1), (32, 64, 1), (33, 48, 2), (64, 64, 2), (65, 4
 @pytest.mark.gpu
 @pytest.mark.parametrize("tokens,heads,q_len", SHAPES)
 def test_tiles_and_their_remainders(tokens, heads, q_len, gpu_device, tune):
-    tune(T.TUNE_SUFFIX_CHUNK, 256)   # one chunk a request
-    tune(T.TUNE_ABSORB_PREFIX_CHUNK, 64)
-    wl = W.make_workload(W.small_spec(name="tiles", dtype="bf16", batch=3, heads=heads, q_len=q_len, prefix_len=97,
-                                      suffix_min=max(tokens, q_len), suffix_max=max(tokens, q_len), seed=tokens))
+    # one chunk of 192 tokens a request, of which it has `tokens` (chunks of up to 128 are another kernel's); the
+    # prefix in one such chunk and one of 33 tokens
+    tune(T.TUNE_SUFFIX_CHUNK, 192)
+    tune(T.TUNE_ABSORB_PREFIX_CHUNK, 192)
+    wl = W.make_workload(W.small_spec(name="tiles", dtype="bf16", batch=3, heads=heads, q_len=q_len, prefix_len=225,
+                                      suffix_min=192, suffix_max=192, seed=tokens))
+    wl.suffix_lens.fill_(max(tokens, q_len))
     ref, ref_lse = O.mla_decode_definition(**wl.as_float64())
     for mode in ["mixed", "absorb_only"]:
         for flags in [0x1000, 0x1800]:   # the 64-row kernel; its exact walk
@@ -38,9 +42,12 @@ def test_tiles_and_their_remainders(tokens, heads, q_len, gpu_device, tune):
 @pytest.mark.gpu
 @pytest.mark.parametrize("batch,prefix", [(255, 64), (256, 64), (256, 0)])
 def test_both_sides_of_the_line_to_the_kernel_of_64_token_steps(batch, prefix, gpu_device, tune):
-    tune(T.TUNE_SUFFIX_CHUNK, 128)
+    tune(T.TUNE_SUFFIX_CHUNK, 192)
     wl = W.make_workload(W.small_spec(name="line", dtype="bf16", batch=batch, heads=64, q_len=1, prefix_len=prefix,
                                       suffix_min=1, suffix_max=110, seed=batch + prefix))
+    # (chunks of 192 tokens: up to 128 the other kernel takes any grid)
+    wl.block_table = torch.nn.functional.pad(wl.block_table, (0, 1))
+    wl.max_suffix_len = 192
     ref, ref_lse = O.mla_decode_definition(**wl.as_float64())
     print(f"64-row kernels batch={batch} prefix={prefix}", flush=True)
     got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
