@@ -190,7 +190,9 @@ inline bool prefix_paired(int H, int M, int Ls) {
   return M > PAIRED_MIN_M && M <= PIPELINED_MIN_M && !(debug_flags() & 0x400) &&
          ((debug_flags() & 0x20000) || (int64_t)Ls * H >= (int64_t)PAIRED_MIN_TOKENS * NUM_CU);
 }
-constexpr int MAX_CHUNKS = 64;  // per-request chunk bound for each of the latent prefix / suffix
+// Chunk bound for each of a request's latent prefix and suffix (one or two groups of rows behind a long prefix
+// take more: many_chunks_pay() in tmla_api.hip).
+constexpr int MAX_CHUNKS = 64;
 void launch_combine_lse(int num_partials, int64_t rows, int width, const float* po,
                         const float* pl, void* out, int out_dtype, float* lse_out,
                         hipStream_t stream);
