@@ -1,7 +1,7 @@
 // Absorb-formulation flash-decode over latent cache rows (paper Algorithm 1 step 6), 64 query rows
-// per workgroup, 64 tokens per step: launches of the 64-row kernels in chunks of up to 128 tokens, and those that
-// cover the chip with workgroups that share no tiles, or with suffixes and latent prefix together (keeps_steps() in
-// tmla_absorb64_pipelined_mfma.hip, which has the kernel for all others).
+// per workgroup, 64 tokens per step: launches of the 64-row kernels in chunks of up to 128 tokens, and of those that
+// cover the chip some of requests with more than 32 rows (keeps_steps() in tmla_absorb64_pipelined_mfma.hip, which
+// has the kernel for all others).
 //
 // The two matrix products of a step want different work splits, so the four wavefronts change
 // roles inside a step and hand the probabilities over through LDS:

@@ -666,15 +666,18 @@ __global__ void __launch_bounds__(256, 1) absorb64_pipelined_kernel(Absorb64Pipe
 //     32.0 with this one, the step 189.6 us at 2.15 GHz and 195.0 at 2.04 (on another box 182.5 and 183.3); without
 //     a prefix 52.6 and 51.7.  Rows in more groups share their tiles: 259 requests x 3 x 48 heads over 416 + 1197
 //     tokens 259 and 225 us; fewer workgroups: 28 x 48 heads x 2 over 608 + 537 49.5 and 48.4;
-//   * suffixes and latent prefix in one launch.  This kernel would be the faster one (128 x 64 heads over 1024 + 512
-//     tokens 60.9 and 55.4 us), but the cross-over table of auto mode, whose entries other callers hold fixed, says
-//     mixed from there on (61 us).
+//   * suffixes and latent prefix in one launch, above 32 rows a request.  This kernel would be the faster one (128 x 64
+//     heads over 1024 + 512 tokens 61.2 and 52.1 us), but auto mode says mixed from there on (61.7 us): its
+//     cross-over for 64 heads and 1024 tokens, which callers know as 128 requests, was measured with that kernel.
+//     Up to 32 rows nothing hangs on that kernel: 1736 random steps of 16 and 32 rows that it ran take 0.906 of their
+//     time with this one, 1.02 at most, and the cross-overs fit better (16 heads x 4096 + 512, that one / this one / mixed: 128
+//     requests 58.6, 50.6, 55.1 us; 192 73.1, 63.3, 70.5; 224 84.3, 76.0, 74.3, cross-over 198).
 static bool keeps_steps(const Plan& p, int what, long long wgs) {
   const int longest = std::max((what & WITH_PREFIX) ? p.ap_chunk : 0, (what & WITH_SUFFIX) ? p.as_chunk : 0);
   if (longest <= 128) return true;
   if (wgs < NUM_CU) return false;
   if (what == WITH_SUFFIX) return p.Sq * p.H <= 64 && p.n_naive + p.ap_chunks > 0;
-  return what == (WITH_PREFIX | WITH_SUFFIX);
+  return what == (WITH_PREFIX | WITH_SUFFIX) && p.Sq * p.H > 32;
 }
 
 int mfma_absorb64_attention(const Plan& p, const DecodeArgs& d, const AbsorbArgs& a, int what) {
