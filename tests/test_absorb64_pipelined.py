@@ -55,6 +55,46 @@ def test_both_sides_of_the_line_to_the_kernel_of_64_token_steps(batch, prefix, g
     Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"line/{batch}/{prefix}")
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("token", [5, 40, 100, 150, 191, 200])
+def test_a_nan_takes_its_whole_chunk(token, gpu_device, tune):
+    """Chunks of 192 and 108 tokens: a key that scores NaN takes the whole chunk with it, in whichever tile it is, and no
+    other chunk or request."""
+    tune(T.TUNE_SUFFIX_CHUNK, 192)
+    wl = W.make_workload(W.small_spec(name="nan_tiles", dtype="bf16", batch=3, heads=64, q_len=1, prefix_len=64,
+                                      suffix_min=300, suffix_max=300, seed=971))
+    clean, clean_lse = Hh.run_library(wl, "mixed", gpu_device)
+    assert np.isfinite(clean).all() and np.isfinite(clean_lse).all()
+    a = wl.as_float64()
+    table = a["block_table"][1]
+    wl.pool[table[token // 64], token % 64, 570] = float("nan")
+    if token < 192:     # the second chunk is left, its 108 tokens in front
+        whole = a["pool"].copy()
+        for i in range(108):
+            a["pool"][table[i // 64], i % 64] = whole[table[(192 + i) // 64], (192 + i) % 64]
+    a["suffix_lens"] = np.array([300, 108 if token < 192 else 192, 300])
+    ref, ref_lse = O.mla_decode_definition(**a, pairs=[(1, h) for h in range(0, 64, 5)])
+    print(f"NaN at suffix token {token}", flush=True)
+    got, got_lse = Hh.run_library(wl, "mixed", gpu_device)
+    Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"nan_tiles/{token}")
+    assert np.array_equal(got[[0, 2]], clean[[0, 2]]) and np.array_equal(got_lse[[0, 2]], clean_lse[[0, 2]])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("suffix", [4097, 4300])
+def test_a_chunk_of_more_blocks_than_lanes(suffix, gpu_device, tune):
+    """One chunk of 65 and of 68 cache blocks: a lane holds each of the first 64 entries of the block table, the others are
+    loaded one by one."""
+    tune(T.TUNE_SUFFIX_CHUNK, 4352)
+    wl = W.make_workload(W.small_spec(name="blocks", dtype="bf16", batch=2, heads=64, q_len=1, prefix_len=0,
+                                      suffix_min=suffix, suffix_max=suffix, seed=suffix))
+    ref, ref_lse = O.mla_decode_definition(**wl.as_float64(), pairs=[(b, h) for b in (0, 1) for h in (0, 21, 63)])
+    for flags in [0, 0x800]:
+        print(f"one chunk of {suffix} tokens, flags {flags:#x}", flush=True)
+        got, got_lse = Hh.run_library(wl, "mixed", gpu_device, flags=flags)
+        Hh.assert_parity(got, got_lse, ref, ref_lse, "bf16", f"blocks/{suffix}/{flags:#x}")
+
+
 def decode_absorb(heads, batch, prefix, suffix, device):
     """absorb_only step of the first `batch` of the same 256 requests"""
     wl = W.make_workload(W.small_spec(name="dispatch", dtype="bf16", batch=256, heads=heads, q_len=1, prefix_len=prefix,

@@ -509,8 +509,8 @@ def test_prefix_kernels_with_values_that_are_not_finite(prefix_len, kernel, gpu_
 @pytest.mark.parametrize("masked", ["first", "run", "head", "all"])
 def test_absorb_kernels_drop_keys_that_score_minus_infinity(masked, heads, flags, gpu_device, tune):
     """Kernels for up to 16, 32, 64 and 128 rows (debug flag bit 13), latent prefix and suffix in one chunk
-    each: keys masked through their RoPE part drop out, also where they are all that the first 64-token step
-    has, whose maxima the 64- and 128-row kernels take as references for the steps behind it."""
+    each: keys masked through their RoPE part drop out, also where they are all that the first tokens of the chunk
+    have, whose maxima the 64- and 128-row kernels (32 and 64 of them) take as references for those behind."""
     gone = list(range(70)) if masked == "head" else MASKED[masked]
     keep = [t for t in range(150) if t not in gone]
     tune(T.TUNE_SUFFIX_CHUNK, 256)
@@ -569,11 +569,12 @@ def test_a_nan_takes_its_whole_chunk_of_a_suffix(token, heads, gpu_device, tune)
 @pytest.mark.parametrize("gain", [256.0, 16.0, 1.0 / 64.0])
 def test_suffix_scores_far_from_the_first_step(gain, gpu_device, tune):
     """The same for the absorb pass over the suffix with more than 32 query rows per request: the
-    64-row kernel first walks a chunk with exponent references fixed at its first 64 tokens and
-    walks it again with moving references if its denominators overflowed.  The RoPE part of every
+    pipelined 64-row kernel first walks a chunk with exponent references fixed at its first 32 tokens
+    and walks it again with exact ones if its denominators overflowed (the kernel of 64-token steps, which
+    has shorter chunks: test_absorb64_steps.py).  The RoPE part of every
     cached suffix row behind the first block is scaled (stored as given, so exact for the
     oracle); one chunk per request (forced), so with gain 256 every workgroup overflows and the
-    result is bit-identical to the walk with moving references alone (debug flag 0x800)."""
+    result is bit-identical to the walk with exact references alone (debug flag 0x800)."""
     tune(T.TUNE_SUFFIX_CHUNK, 4096)
     spec = W.small_spec(name="suffix_growth", dtype="bf16", batch=6, heads=128, q_len=1,
                         prefix_len=40, suffix_min=200, suffix_max=700, seed=91)
