@@ -26,11 +26,12 @@ namespace tmla {
 
 // private tile layout: latent rows at r * 1056 with the 16-byte chunk c in slot
 // c ^ ((r >> 3) & 1), then 32 x 128 B of rope with chunk c of row r in slot c ^ ((r >> 1) & 7).
-// The LDS has 64 four-byte banks; a 16-byte read is served 16 lanes at a time, an 8-byte
-// transposing read 32 lanes at a time.  The row stride is 8 banks mod 64: the transposing reads
-// of the output product (8 rows x 32 B per 32 lanes) cover the banks exactly, and the score
-// product's 16 rows x 16 B per 16 lanes do so because rows r and r + 8 sit in different halves
-// of a 32-byte pair.  Rope rows of equal parity share 32 banks; the swizzle separates the eight
+// The LDS has 64 four-byte banks; a 16-byte read is served 16 lanes at a time (of each half 0 .. 3, 12 .. 15 and
+// 20 .. 27, then the others), an 8-byte transposing read 32 lanes at a time.  The row stride is 8 banks mod
+// 64: the transposing reads of the output product (8 rows x 32 B per 32 lanes) cover the banks exactly.
+// The score product's reads take two turns a group: rows r and r + 8 sit in different halves of a 32-byte
+// pair, but a group has rows 0 .. 3 and 12 .. 15 of one chunk with 4 .. 11 of the next, which fall
+// on the same banks (8.2 cycles a read, 4.3 without conflicts).  Rope rows of equal parity share 32 banks; the swizzle separates the eight
 // of them that a 16-lane group reads.
 constexpr int A16_ROW_BYTES = 1056;
 constexpr int A16_MAIN_BYTES = 32 * A16_ROW_BYTES;

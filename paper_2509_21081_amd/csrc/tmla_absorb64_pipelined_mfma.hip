@@ -171,8 +171,8 @@ __global__ void __launch_bounds__(256, 1) absorb64_pipelined_kernel(Absorb64Pipe
 
   // ---- tile streaming: global -> LDS (see tmla_absorb_tile.hpp)
   // Rows in slots c ^ f((row >> 2) & 3) with f = 0, 3, 2, 1: a 16-byte read is served sixteen lanes at a time, 0 .. 3, 12 ..
-  // 15, 20 .. 27 first, i.e. rows 0 .. 3 and 12 .. 15 of one chunk and 4 .. 11 of the next (8.0 cycles a read with f = 0, 1,
-  // 2, 3, 4.1 with this one).
+  // 15, 20 .. 27 first, i.e. rows 0 .. 3 and 12 .. 15 of one chunk and 4 .. 11 of the next (8.2 cycles a read with f = 0, 1,
+  // 2, 3, 4.4 with this one).
   DmaLane dl = dma_lane(wave, lane);
   dl.off[1] = (lane ^ 3) << 4;
   dl.off[3] = (lane ^ 1) << 4;
