@@ -2,14 +2,14 @@
 MFMAs in assembly, so nothing inserts the wait states the hardware needs around them.  The
 kernels are arranged so that no dependent pair is ever close; this test compiles them to
 assembly and checks it by counting wait states between producer and consumer: an ordinary
-instruction counts 1, `s_nop N` counts N + 1, an MFMA in between counts its 8 passes (the matrix
-pipe takes the next one only when the previous one has gone through them).
+instruction counts 1, `s_nop N` counts N + 1, and an MFMA is issued only when the one before it has gone through
+its passes (8 of a 32x32x16, 4 of a 16x16x32).
 
   * a vector-ALU write of a register (copies placed by the register allocator included) must
     lie at least VALU_TO_MFMA wait states in front of an assembly MFMA that reads it;
-  * the result of a v_mfma_f32_32x32x16_bf16 (8 passes) may be read -- by the vector ALU, by a
+  * the result of an MFMA may be read -- by the vector ALU, by a
     store, by an LDS write, or as the A/B operand of a later MFMA -- or overwritten only
-    MFMA_RESULT wait states behind it (passes + 3, one more on gfx950).  An MFMA that
+    passes + 3, one more on gfx950, wait states behind it (MFMA_RESULT behind a 32x32x16).  An MFMA that
     accumulates into the registers of the one before it is the chained case the hardware
     handles itself and is not checked.
 
@@ -29,7 +29,7 @@ KERNELS = [("tmla_prefix_mfma.hip", "prefix_attn_pipelined_kernel"),
            ("tmla_expand_mfma.hip", "expand_gemm_kernel")]
 VALU_TO_MFMA = 4      # wait states between a vector-ALU write and an assembly MFMA reading it
 MFMA_RESULT = 12      # wait states between an 8-pass MFMA and any other use of its result
-MFMA_PASSES = 8
+MFMA_PASSES = {"32x32x16": 8, "16x16x32": 4}
 WINDOW = 48           # instructions looked at on either side of a loop's back edge
 
 
@@ -50,13 +50,25 @@ def _operands(line):
     return [t.strip().split()[0] if t.strip() else "" for t in body.split(",")]
 
 
-def _wait_states(ins):
-    op = ins.split()[0]
-    if op == "s_nop":
-        return int(ins.split()[1], 0) + 1
-    if op.startswith("v_mfma"):
-        return MFMA_PASSES
-    return 1
+def _passes(ins):
+    return MFMA_PASSES[re.match(r"v_mfma_f32_(\w+?)_", ins).group(1)]
+
+
+def _result_wait(ins):
+    return _passes(ins) + MFMA_RESULT - MFMA_PASSES["32x32x16"]
+
+
+def _wait_states(seq, p, i):
+    """Wait states between the issue of seq[p] and that of seq[i], at least."""
+    at, free = 0, 0          # issue of the instruction, and when the matrix pipe takes the next MFMA
+    for k in range(p, i + 1):
+        if seq[k].startswith("v_mfma"):
+            at = max(at, free)
+            free = at + _passes(seq[k])
+        if k < i:
+            op = seq[k].split()
+            at += int(op[1], 0) + 1 if op[0] == "s_nop" else 1
+    return at - 1
 
 
 def _overlap(a, b):
@@ -113,8 +125,8 @@ def _check_valu_to_mfma(seq, where):
             continue
         n_mfma += 1
         reads = [_regs(t) for t in _operands(ins)[1:]]     # A, B, C
-        waited = 0
-        for prev in reversed(seq[max(0, i - 4 * VALU_TO_MFMA):i]):
+        for j in range(i - 1, max(0, i - 4 * VALU_TO_MFMA) - 1, -1):
+            prev, waited = seq[j], _wait_states(seq, j, i)
             if waited >= VALU_TO_MFMA:
                 break
             op = prev.split()[0]
@@ -124,7 +136,6 @@ def _check_valu_to_mfma(seq, where):
                     assert not _overlap(r, dst), (
                         f"{where}: '{prev}' writes an operand of '{ins}' only {waited} wait "
                         f"states in front of it")
-            waited += _wait_states(prev)
     return n_mfma
 
 
@@ -138,17 +149,16 @@ def _check_mfma_result(seq, where):
             touched = ops[1:3]            # A and B; C / D in the same registers is the chained case
         else:
             touched = ops                 # sources, and the destination (write after write)
-        waited = 0
-        for prev in reversed(seq[max(0, i - MFMA_RESULT):i]):
+        for j in range(i - 1, max(0, i - MFMA_RESULT - 1) - 1, -1):
+            prev, waited = seq[j], _wait_states(seq, j, i)
             if waited >= MFMA_RESULT:
                 break
-            if prev.startswith("v_mfma"):
+            if prev.startswith("v_mfma") and waited < _result_wait(prev):
                 dst = _regs(_operands(prev)[0])
                 for r in touched:
                     assert not _overlap(r, dst), (
                         f"{where}: '{ins}' touches the result of '{prev}' only {waited} wait "
                         f"states behind it")
-            waited += _wait_states(prev)
 
 
 @pytest.mark.parametrize("source,kernel", KERNELS)
@@ -189,3 +199,19 @@ def test_the_checker_itself_sees_a_planted_hazard():
     with pytest.raises(AssertionError):
         _check_valu_to_mfma(bad, "planted")
     _check_valu_to_mfma(["v_mov_b32 v20, 0", "s_nop 3", ok[0]], "planted")
+
+
+def test_the_checker_counts_passes_by_shape():
+    big = "v_mfma_f32_32x32x16_bf16 v[0:15], v[20:23], a[0:3], v[0:15]"
+    small = "v_mfma_f32_16x16x32_bf16 v[16:19], v[20:23], a[0:3], v[16:19]"
+    other = "v_mfma_f32_16x16x32_bf16 v[24:27], v[20:23], a[0:3], v[24:27]"
+    read_big, read_small = "v_add_f32 v40, v0, v1", "v_add_f32 v40, v16, v17"
+    # an MFMA in between is issued behind the passes of the one before it, whatever its own
+    assert _wait_states([big, other, read_big], 0, 2) == 8
+    assert _wait_states([small, big, read_small], 0, 2) == 4
+    _check_mfma_result([small, "s_nop 7", read_small], "planted")
+    _check_mfma_result([small, other, other, read_small], "planted")
+    for seq in ([small, "s_nop 6", read_small], [small, other, "s_nop 2", read_small], [small, big, "s_nop 2", read_small],
+                [big, "s_nop 7", "s_nop 2", read_big], [big, other, "s_nop 2", read_big]):
+        with pytest.raises(AssertionError):
+            _check_mfma_result(seq, "planted")
