@@ -119,6 +119,36 @@ def test_joint_launches_of_few_rows_stay_with_the_pipelined_kernel(heads, gpu_de
     assert np.array_equal(small, large[:few]) and np.array_equal(small_lse, large_lse[:few])
 
 
+def decode_mixed(batch, prefix, suffix, device):
+    """mixed step of the first `batch` of the same 257 requests x 64 heads"""
+    wl = W.make_workload(W.small_spec(name="lines", dtype="bf16", batch=257, heads=64, q_len=1, prefix_len=prefix,
+                                      suffix_min=suffix, suffix_max=suffix, seed=7))
+    wl.q, wl.block_table, wl.suffix_lens = wl.q[:batch], wl.block_table[:batch], wl.suffix_lens[:batch]
+    wl.block_table = torch.nn.functional.pad(wl.block_table, (0, 4 - wl.block_table.shape[1]))
+    wl.max_suffix_len = 256
+    print(f"line {batch} x 64 over {prefix} + {suffix}", flush=True)
+    return Hh.run_library(wl, "mixed", device)
+
+
+@pytest.mark.gpu
+def test_which_kernel_a_launch_takes(gpu_device, tune):
+    """By equal and different bits, as above: 64 rows a request beside a prefix pass go back to the kernel of 64-token steps
+    from 256 workgroups on, without a prefix they do not, and chunks of up to 128 tokens always do."""
+    def same(x, y):
+        n = min(len(x[0]), len(y[0]))
+        return np.array_equal(x[0][:n], y[0][:n]) and np.array_equal(x[1][:n], y[1][:n])
+    tune(T.TUNE_SUFFIX_CHUNK, 256)
+    a, b, c = (decode_mixed(n, 64, 160, gpu_device) for n in (254, 255, 256))
+    assert same(a, b) and not same(b, c)
+    assert same(decode_mixed(255, 0, 160, gpu_device), decode_mixed(256, 0, 160, gpu_device))
+    # 100 tokens, one chunk of 256, 192 and 128
+    runs = []
+    for chunk in (256, 192, 128):
+        tune(T.TUNE_SUFFIX_CHUNK, chunk)
+        runs.append(decode_mixed(40, 0, 100, gpu_device))
+    assert same(runs[0], runs[1]) and not same(runs[0], runs[2])
+
+
 @pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="hipcc not available")
 def test_wait_states_of_the_assembly_mfmas(tmp_path):
     out = tmp_path / "k.s"
