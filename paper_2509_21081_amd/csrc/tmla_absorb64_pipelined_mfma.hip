@@ -12,9 +12,12 @@
 //   outputs  O^T += C_N^T P^T: wavefront w takes latent columns [128 w, 128 w + 128) for all 64
 //            queries, so each transposed cache fragment feeds two MFMAs (one per query block): 16 of them.
 // One barrier a period: period t runs the scores of tile t + 1 and the outputs of tile t, with the exponentials
-// of tile t + 1 between the latter's MFMAs, while tiles t + 2 and t + 3 are on their way (four tiles fill the
-// LDS).  A lone wavefront issues one instruction in about five cycles whatever its kind, so LDS reads,
-// transfers, exponentials and address arithmetic are dealt out between the MFMAs; the probes behind this order
+// of tile t + 1 among the latter's MFMAs, while tiles t + 2 and t + 3 are on their way (four tiles fill the
+// LDS).  A lone wavefront issues one instruction in about five cycles whatever its kind, so LDS reads and
+// transfers are dealt out between the MFMAs, and so are the exponentials as far as the compiler follows: in the
+// period that requests a tile, the branches around that tile's address end a basic block behind the third pair of
+// output MFMAs, and the first four exponentials with their arithmetic, some twenty vector instructions, run behind
+// them without an MFMA; in the last periods of a walk they are dealt out as written.  The probes behind this order
 // (cycles a period without / with barrier): reads of a pair in front of its MFMAs 1473 / 1646, between them
 // 1353 / 1494.  In the kernel a period takes about 1850 cycles for 1088 of matrix time (0.81 us); the kernel that
 // walked 64 tokens a step, products and exponentials one behind the other with three barriers, took 1.04 us
@@ -536,7 +539,8 @@ __global__ void __launch_bounds__(256, 1) absorb64_pipelined_kernel(Absorb64Pipe
         constexpr int requested = 12 + 2 * p < 20 ? 12 + 2 * p : 20;
         mfma_v0(p_, std::integral_constant<int, requested - 1 - need(p)>{});
         if constexpr (p < 4) rd_o(std::integral_constant<int, 12 + 2 * p>{}, va, vb, pa);
-        // one exponential behind each MFMA from the second pair on
+        // one exponential behind each MFMA from the second pair on (where prefetch_src() follows, the compiler
+        // moves the first four of them behind its branches)
         if constexpr (p > 0) {
           if constexpr (p < 5) prob_at(std::integral_constant<int, 2 * (p - 1)>{});
           A64P_SB();
@@ -611,12 +615,8 @@ __global__ void __launch_bounds__(256, 1) absorb64_pipelined_kernel(Absorb64Pipe
     if (__builtin_amdgcn_ballot_w64(bad) == 0) break;
     raw_barrier();   // everyone has read the denominators
   }
-  // ---- outputs, turned around in LDS (slots 2 and 3, which nobody reads any more): a lane holds
-  // 8-byte pieces of its row, and stored like that the 128 store instructions of a workgroup, 32
-  // rows each, keep the memory pipeline busy for 4.3 us (cycle stamps: end of the walk to the
-  // last store done, 132 workgroups on the chip; 5.8 with 256); with a whole row of 1 KiB per
-  // instruction 2.0 (2.2).  Steps: 8 x 16 heads absorb_only over 4096 + 1200 25.3 -> 23.2 us, 64 x 128
-  // heads mixed over 4096 + 512 95.7 -> 92.9.
+  // ---- outputs, turned around in LDS (slots 2 and 3, which nobody reads any more) and stored as whole rows of
+  // 1 KiB, as in the kernel of 64-token steps, whose comment has the times of both ways.
   constexpr int ST_ROW = D_L * 2 + 16;   // conflict-free for the 8-byte writes of 16 rows x 2 halves
   char* st = smem + 2 * AB_TILE_BYTES;
   static_assert(2 * AB_TILE_BYTES + 64 * ST_ROW <= A64P_LDS_BYTES, "the outputs fit the idle slots");
@@ -661,11 +661,13 @@ __global__ void __launch_bounds__(256, 1) absorb64_pipelined_kernel(Absorb64Pipe
 // 603 tokens in chunks of 64 9.75, 9.66 / 19.5, 20.0 us; 8 x 16 over 4096 + 1200 in chunks of 128 10.4, 10.4 / 20.1, 20.7; of
 // 192 11.9, 11.1 / 21.7, 21.2).  And launches that cover the chip:
 //   * suffixes of up to 64 rows a request, whose workgroups stream rows that no other reads, beside another
-//     pass of the call.  HBM sets the pace there and the chip's power that of the step; the faster pass draws
-//     more of it.  256 requests x 64 heads absorb_only, 4096 + 512 tokens: the pass 34.5 us with that kernel and
-//     32.0 with this one, the step 189.6 us at 2.15 GHz and 195.0 at 2.04 (on another box 182.5 and 183.3); without
-//     a prefix 52.6 and 51.7.  Rows in more groups share their tiles: 259 requests x 3 x 48 heads over 416 + 1197
-//     tokens 259 and 225 us; fewer workgroups: 28 x 48 heads x 2 over 608 + 537 49.5 and 48.4;
+//     pass of the call.  Behind a latent prefix the chip's power sets the pace of the step, and the faster pass
+//     draws more of it: 256 requests x 64 heads absorb_only, 4096 + 512 tokens, the pass 34.5 us with that kernel and
+//     32.0 with this one, the step 189.6 us at 2.15 GHz and 195.0 at 2.04 (on another box 182.5 and 183.3); 339 random
+//     absorb_only steps of 33 to 64 rows take 0.98 of their time with this one on average and 1.04 at most.  Behind a
+//     naive prefix the line is too wide: 1250 random mixed steps would take 0.96 with this one, 1.00 at most.
+//     Without a prefix 256 x 64 heads take 52.6 and 51.7.  Rows in more groups share their tiles: 259 requests x 3 x
+//     48 heads over 416 + 1197 tokens 259 and 225 us; fewer workgroups: 28 x 48 heads x 2 over 608 + 537 49.5 and 48.4;
 //   * suffixes and latent prefix in one launch, above 32 rows a request.  This kernel would be the faster one (128 x 64
 //     heads over 1024 + 512 tokens 61.2 and 52.1 us), but auto mode says mixed from there on (61.7 us): its
 //     cross-over for 64 heads and 1024 tokens, which callers know as 128 requests, was measured with that kernel.
